@@ -8,13 +8,9 @@
 //      a table in global memory). Best = max connection, ties -> smallest
 //      label; the capacity check W[L] + c(v) <= U is evaluated on the best
 //      label first and only rescans the table when that label is full.
-//   2. compact the movers in ascending vertex id (stable scan),
-//   3. stable LSD radix sort of (target, vertex) by target, so each target's
-//      proposers stay in ascending id,
-//   4. inclusive prefix sum of c over the sorted movers; a mover is admitted
-//      iff W[t] + (its prefix within the target's segment) <= U,
-//   5. apply: write labels, then update W with integer atomics (exact,
-//      order independent), count moves, update the device stop flag.
+//   2. admit (admit.hpp): the proposers to a target in ascending vertex id
+//      while W[t] + (their weight so far) <= U; labels, W and the move count
+//      are updated and the device stop flag set.
 // No host synchronisation happens between rounds; after the stop flag is set
 // every later kernel of the call returns immediately.
 #include <algorithm>
@@ -23,18 +19,13 @@
 #include <cstring>
 #include <string>
 
+#include "admit.hpp"
 #include "lp.hpp"
 #include "prims.hpp"
 
 namespace gp {
 
 namespace {
-
-// per-group round bookkeeping: gs[q] = {moves this round, previous moves, done, rounds_run, rounds seen}
-struct GroupState {
-    int32_t moves, prev, done, rounds_run, seen;
-    int64_t total;
-};
 
 struct LPArgs {
     const int32_t *xadj, *adjncy, *adjwgt, *vwgt;
@@ -77,10 +68,6 @@ __device__ __forceinline__ int32_t cur_dirmode(const LPArgs &a) {
 
 __device__ __forceinline__ bool dir_ok(int32_t L, int32_t own, int32_t dirmode) {
     return dirmode == 0 || (dirmode == 1 ? (L < own) : (L > own));
-}
-
-__device__ __forceinline__ int64_t vweight(const int32_t *vwgt, int32_t v) {
-    return vwgt ? (int64_t)vwgt[v] : (int64_t)1;
 }
 
 template <typename AccT>
@@ -1568,9 +1555,11 @@ __global__ __launch_bounds__(kPropBlock) void k_dense_rows(LPArgs a, int32_t nla
 }
 
 // After the admission: the admitted movers' edges change the rows of their
-// table neighbours. 16 lanes per mover; a mover above kRowSplit neighbours is
-// queued instead as chunks of kRowChunk entries (vertex, first entry, old
-// block, new block), which k_rows_update_big spreads over whole workgroups.
+// table neighbours. `parts` workgroups per tile of the movers (on skewed graphs
+// the movers with many neighbours share a few tiles: with one workgroup each,
+// rmat24 took 87 us a round here instead of 39), 16 lanes per mover; a mover above kRowSplit neighbours is queued instead as chunks of kRowChunk
+// entries (vertex, first entry, old block, new block), which
+// k_rows_update_big spreads over whole workgroups.
 constexpr int kRowSplit = 256;
 constexpr int kRowChunk = 4096;
 template <typename AccT>
@@ -1581,23 +1570,26 @@ __device__ __forceinline__ void row_move(AccT *rows, int KT, int32_t r, int32_t 
 }
 
 template <int KT, typename AccT>
-__global__ __launch_bounds__(256) void k_rows_update(const uint32_t *mk, const int32_t *mv, const int32_t *oldlab,
-                                                     const int32_t *nmov, const int32_t *__restrict__ xadj,
+__global__ __launch_bounds__(256) void k_rows_update(AdmitCtx c, const int32_t *__restrict__ xadj,
                                                      const int32_t *__restrict__ adjncy,
                                                      const int32_t *__restrict__ adjwgt,
                                                      const int32_t *__restrict__ rowidx, AccT *rows, int4 *big,
-                                                     int32_t *nbig, unsigned long long *pushed_total) {
+                                                     int32_t *nbig, int64_t *pushed, int32_t parts) {
     constexpr int GL = 16;
-    const int32_t n = *nmov;
+    __shared__ int64_t t64[256 / kWave + 1];
+    if (c.dev->done) return;
+    const int32_t tile = blockIdx.x / parts, part = blockIdx.x % parts;
+    const int32_t n = c.tcnt[tile];
+    if (part * (256 / GL) >= n) return;  // uniform
+    const int32_t *mv = c.mv + (int64_t)tile * c.tile, *old = c.old + (int64_t)tile * c.tile;
     const int gl = threadIdx.x % GL;
-    const int64_t step = (int64_t)gridDim.x * blockDim.x / GL;
-    long long pushed = 0;  // the movers' edges, counted once per mover
-    for (int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / GL; p < n; p += step) {
-        const int32_t from = oldlab[p];
+    int64_t sum = 0;  // the movers' edges, counted once per mover
+    for (int32_t p = part * (256 / GL) + threadIdx.x / GL; p < n; p += parts * (256 / GL)) {
+        const int32_t from = old[p];
         if (from < 0) continue;  // refused by the admission
-        const int32_t u = mv[p], to = (int32_t)mk[p];
+        const int32_t u = mv[p], to = c.labels[u];
         const int32_t e0 = xadj[u], e1 = xadj[u + 1];
-        if (gl == 0) pushed += e1 - e0;
+        if (gl == 0) sum += e1 - e0;
         if (e1 - e0 > kRowSplit) {
             if (gl == 0) {
                 const int32_t nc = (e1 - e0 + kRowChunk - 1) / kRowChunk;
@@ -1611,8 +1603,8 @@ __global__ __launch_bounds__(256) void k_rows_update(const uint32_t *mk, const i
             if (r >= 0) row_move<AccT>(rows, KT, r, from, to, adjwgt ? (AccT)adjwgt[e] : (AccT)1);
         }
     }
-    pushed = wave_sum(pushed);
-    if (lane_id() == 0 && pushed) atomicAdd(pushed_total, (unsigned long long)pushed);
+    sum = block_sum<256>(sum, t64);
+    if (threadIdx.x == 0) pushed[blockIdx.x] += sum;
 }
 
 template <int KT, typename AccT>
@@ -1650,7 +1642,8 @@ struct RowTables {
     int32_t nt = 0;
     int32_t nsmall = 0;  // rows filled per vertex; the rest (chunked big vertices) by chunks
     int64_t entries = 0;  // edges of the table vertices
-    unsigned long long *pushed = nullptr;  // edges of the admitted movers pushed into rows
+    int32_t parts = 8;          // workgroups of the update per tile of movers
+    int64_t *pushed = nullptr;  // [tiles * parts] edges of the admitted movers pushed into rows
     double sel_bytes = 0;
 };
 
@@ -1678,11 +1671,10 @@ int rows_select(const LPArgs &a, int32_t nlabels, TierList tl, const RowTables &
 }
 
 template <int KT, typename AccT>
-int rows_update(const RowTables &rt, const uint32_t *mk, const int32_t *mv, const int32_t *oldlab,
-                const int32_t *nmov, const int32_t *xadj, const int32_t *adjncy, const int32_t *adjwgt, int64_t n,
-                int64_t nnz, hipStream_t s) {
-    hipLaunchKernelGGL((k_rows_update<KT, AccT>), dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, mk, mv, oldlab, nmov,
-                       xadj, adjncy, adjwgt, rt.rowidx, (AccT *)rt.rows, rt.big, rt.nbig, rt.pushed);
+int rows_update(const RowTables &rt, const AdmitCtx &ac, const int32_t *xadj, const int32_t *adjncy,
+                const int32_t *adjwgt, int64_t nnz, hipStream_t s) {
+    hipLaunchKernelGGL((k_rows_update<KT, AccT>), dim3(ac.ntiles * rt.parts), dim3(256), 0, s, ac, xadj, adjncy,
+                       adjwgt, rt.rowidx, (AccT *)rt.rows, rt.big, rt.nbig, rt.pushed, rt.parts);
     hipLaunchKernelGGL((k_rows_update_big<KT, AccT>), dim3(grid_for(nnz / kRowChunk + 1, 1, 4096)), dim3(256), 0, s,
                        rt.big, rt.nbig, xadj, adjncy, adjwgt, rt.rowidx, (AccT *)rt.rows);
     GP_LAUNCH_CHECK();
@@ -1801,109 +1793,14 @@ __global__ void k_hub_caps(const int32_t *xadj, const int32_t *hubs, int32_t nh,
     }
 }
 
-// ---------------------------------------------------------------- admission / apply
-
-struct MoverFlag {
-    const int32_t *prop;
-    const int32_t *done;
-    __device__ bool operator()(int64_t i) const { return !*done && prop[i] >= 0; }
-};
-struct MoverEmit {
-    const int32_t *prop;
-    uint32_t *mk;
-    int32_t *mv;
-    __device__ void operator()(int64_t i, int32_t pos) const {
-        mk[pos] = (uint32_t)prop[i];
-        mv[pos] = (int32_t)i;
-    }
-};
-
-struct MoverWeight {
-    const int32_t *mv;
-    const int32_t *vwgt;
-    __device__ int64_t operator()(int64_t p) const { return vweight(vwgt, mv[p]); }
-};
-struct StoreIncl {
-    int64_t *S;
-    __device__ void operator()(int64_t p, int64_t ex, int64_t v) const { S[p] = ex + v; }
-};
-
-
-__global__ void k_heads(const uint32_t *mk, const int32_t *nmov, int32_t *headpos) {
-    const int32_t n = *nmov;
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n;
-         p += (int64_t)gridDim.x * blockDim.x)
-        if (p == 0 || mk[p] != mk[p - 1]) headpos[mk[p]] = (int32_t)p;
-}
-
-__global__ void k_admit(const uint32_t *mk, const int32_t *mv, const int32_t *nmov, const int32_t *headpos,
-                        const int64_t *S, const int64_t *W, int64_t U, const int64_t *capv, int32_t *labels,
-                        uint8_t *lab8, int32_t *oldlab, LPDev *dev, const int32_t *group, GroupState *gs,
-                        uint8_t *act) {
-    const int32_t n = *nmov;
-    const int lane = lane_id();
-    int32_t cnt = 0;
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p - lane < n;
-         p += (int64_t)gridDim.x * blockDim.x) {
-        bool moved = false;
-        int32_t gq = 0;
-        if (p < n) {
-            const int32_t t = (int32_t)mk[p];
-            const int32_t h = headpos[t];
-            const int64_t pre = S[p] - (h > 0 ? S[h - 1] : 0);
-            if (W[t] + pre <= (capv ? capv[t] : U)) {
-                const int32_t v = mv[p];
-                oldlab[p] = labels[v];
-                labels[v] = t;
-                if (lab8) lab8[v] = (uint8_t)t;
-                cnt++;
-                moved = true;
-                if (group) gq = group[v];
-            } else {
-                oldlab[p] = -1;
-                if (act && act[mv[p]] == 0) act[mv[p]] = 1;  // refused by capacity: evaluated again
-            }
-        }
-        // movers sorted by target lie mostly in one graph: one count per wave
-        const uint64_t mm = group ? __ballot(moved) : 0ull;
-        if (mm) {
-            const int32_t g0 = __shfl(gq, __ffsll((unsigned long long)mm) - 1, kWave);
-            if (__ballot(moved && gq != g0) == 0) {
-                if (lane == 0) atomicAdd(&gs[g0].moves, (int32_t)__popcll(mm));
-            } else if (moved) {
-                atomicAdd(&gs[gq].moves, 1);
-            }
-        }
-    }
-    cnt = wave_sum(cnt);
-    if (lane_id() == 0 && cnt) atomicAdd(&dev->round_moves, cnt);
-}
-__global__ void k_apply_w(const uint32_t *mk, const int32_t *mv, const int32_t *nmov, const int32_t *oldlab,
-                          const int32_t *vwgt, const int32_t *headpos, const int64_t *S, int64_t *W) {
-    const int32_t n = *nmov;
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n;
-         p += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t old = oldlab[p];
-        if (old < 0) continue;
-        const unsigned long long c = (unsigned long long)vweight(vwgt, mv[p]);
-        atomicAdd((unsigned long long *)&W[old], (unsigned long long)(-(long long)c));
-        const uint32_t t = mk[p];
-        const bool tail = (p + 1 == n) || mk[p + 1] != t || oldlab[p + 1] < 0;
-        if (tail) {
-            const int32_t h = headpos[t];
-            const int64_t in = S[p] - (h > 0 ? S[h - 1] : 0);
-            atomicAdd((unsigned long long *)&W[t], (unsigned long long)in);
-        }
-    }
-}
+// ---------------------------------------------------------------- small rounds
 
 // Everything of a round after the proposals, in one workgroup, for graphs of
 // at most kFuseMax vertices (single graphs without active sets): compaction
 // of the movers in ascending vertex order, the stable sort by target, the
 // segmented prefix of mover weights per target, admission against the
 // weights of the round start, the label and weight updates and the round
-// bookkeeping — the work of compact, radix_sort, k_heads, the prefix scan,
-// k_admit, k_apply_w and k_round_end. A mover is packed as
+// bookkeeping. A mover is packed as
 // (target << vbits) | vertex in LDS. Position p of a sequence belongs to wave
 // p / kFuseWaveSpan, row (p % kFuseWaveSpan) / kWave, lane p % kWave, so the
 // (wave, row, lane) order is the position order.
@@ -2134,28 +2031,6 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(const int32_t *prop,
     }
 }
 
-// Few labels: net weight change per label aggregated in LDS first.
-__global__ __launch_bounds__(256) void k_apply_w_small(const uint32_t *mk, const int32_t *mv, const int32_t *nmov,
-                                                       const int32_t *oldlab, const int32_t *vwgt, int32_t nl,
-                                                       int64_t *W) {
-    __shared__ unsigned long long h[kSmallLabels];
-    const int32_t n = *nmov;
-    if ((int64_t)blockIdx.x * blockDim.x >= n) return;
-    for (int i = threadIdx.x; i < nl; i += blockDim.x) h[i] = 0;
-    __syncthreads();
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n;
-         p += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t old = oldlab[p];
-        if (old < 0) continue;
-        const unsigned long long c = (unsigned long long)vweight(vwgt, mv[p]);
-        atomicAdd(&h[mk[p]], c);
-        atomicAdd(&h[old], (unsigned long long)(-(long long)c));
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < nl; i += blockDim.x)
-        if (h[i]) atomicAdd((unsigned long long *)&W[i], h[i]);
-}
-
 // ---------------------------------------------------------------- active-set rounds
 // act[v] = evaluations v still owes (see k_act_step, k_admit, k_act_mark).
 
@@ -2187,20 +2062,20 @@ __global__ __launch_bounds__(256) void k_act_step(const int32_t *xadj, int32_t n
 }
 
 // After the admission: every neighbour of an admitted mover owes `renew`
-// evaluations. 16 lanes per mover; a mover above kMarkSplit neighbours is
+// evaluations. One workgroup per tile of the movers, 16 lanes per mover; a mover above kMarkSplit neighbours is
 // queued instead as chunks of kMarkChunk entries (list `big`, count `nbig`),
 // which k_act_mark_big spreads over whole workgroups.
 constexpr int kMarkSplit = 256;
 constexpr int kMarkChunk = 4096;
-__global__ __launch_bounds__(256) void k_act_mark(const int32_t *mv, const int32_t *oldlab, const int32_t *nmov,
-                                                  const int32_t *xadj, const int32_t *adjncy, uint8_t *act,
+__global__ __launch_bounds__(256) void k_act_mark(AdmitCtx c, const int32_t *xadj, const int32_t *adjncy,
                                                   uint8_t renew, int2 *big, int32_t *nbig) {
     constexpr int GL = 16;
-    const int32_t n = *nmov;
+    if (c.dev->done) return;
+    const int32_t n = c.tcnt[blockIdx.x];
+    const int32_t *mv = c.mv + (int64_t)blockIdx.x * c.tile, *old = c.old + (int64_t)blockIdx.x * c.tile;
     const int gl = threadIdx.x % GL;
-    const int64_t step = (int64_t)gridDim.x * blockDim.x / GL;
-    for (int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / GL; p < n; p += step) {
-        if (oldlab[p] < 0) continue;
+    for (int32_t p = threadIdx.x / GL; p < n; p += 256 / GL) {
+        if (old[p] < 0) continue;
         const int32_t v = mv[p];
         const int32_t e0 = xadj[v], e1 = xadj[v + 1];
         if (e1 - e0 > kMarkSplit) {
@@ -2211,7 +2086,7 @@ __global__ __launch_bounds__(256) void k_act_mark(const int32_t *mv, const int32
             }
             continue;
         }
-        for (int32_t e = e0 + gl; e < e1; e += GL) act[adjncy[e]] = renew;
+        for (int32_t e = e0 + gl; e < e1; e += GL) c.act[adjncy[e]] = renew;
     }
 }
 
@@ -2284,18 +2159,6 @@ __global__ void k_round_end_groups(GroupState *gs, int32_t ng) {
         st.moves = 0;
         gs[q] = st;
     }
-}
-
-__global__ void k_round_end(LPDev *dev) {
-    const int32_t r = dev->round;
-    dev->round = r + 1;
-    if (dev->done) return;
-    const int32_t m = dev->round_moves;
-    dev->rounds_run = r + 1;
-    dev->total_moves += m;
-    if (r >= 1 && m == 0 && dev->prev_moves == 0) dev->done = 1;
-    dev->prev_moves = m;
-    dev->round_moves = 0;
 }
 
 __global__ void k_label_weights(const int32_t *labels, const int32_t *vwgt, int32_t n, int64_t *W) {
@@ -2532,7 +2395,9 @@ size_t lp_scratch_bound(int64_t n, int64_t nnz, int64_t nlabels, bool active) {
             b += 2 * R(4 * nbig) + R(4) + R(8 * nbig) + R(16 * dchunks) + R(nbig * KT * (wide ? 8.0 : 4.0));
             b += R(n);  // byte labels
         }
-        b += 6 * R(4.0 * n) + R(4) + R(4.0 * nlabels) + R(8.0 * n) + R(sizeof(LPDev));  // per-round buffers
+        // per-round buffers: 36 bytes a vertex, more than they take now (callers size
+        // workspaces by this bound, and it decides what the static scratch accepts)
+        b += 6 * R(4.0 * n) + R(4) + R(4.0 * nlabels) + R(8.0 * n) + R(sizeof(LPDev));
         if (active) b += R(n) + R(8.0 * ((double)nnz / kMarkChunk + (double)nnz / kMarkSplit + 1)) + R(4);
         worst = std::max(worst, b);
     }
@@ -2792,22 +2657,12 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     }
 
     // ---- per-round buffers
-    int32_t *prop = nullptr, *mv = nullptr, *mv2 = nullptr, *nmov = nullptr, *headpos = nullptr,
-            *oldlab = nullptr;
-    uint32_t *mk = nullptr, *mk2 = nullptr;
-    int64_t *S = nullptr;
+    int32_t *prop = nullptr;
     LPDev *dev = nullptr;
-    GP_TRY(sc.alloc(&prop, n));
-    GP_TRY(sc.alloc(&mk, n));
-    GP_TRY(sc.alloc(&mk2, n));
-    GP_TRY(sc.alloc(&mv, n));
-    GP_TRY(sc.alloc(&mv2, n));
-    GP_TRY(sc.alloc(&nmov, 1));
-    GP_TRY(sc.alloc(&headpos, nlabels));
-    GP_TRY(sc.alloc(&oldlab, n));
-    GP_TRY(sc.alloc(&S, n));
+    const size_t npad = ((size_t)n + kDadmChunk - 1) / kDadmChunk * kDadmChunk;
+    GP_TRY(sc.alloc(&prop, npad));
     GP_TRY(sc.alloc(&dev, 1));
-    GP_HIP(hipMemsetAsync(prop, 0xFF, sizeof(int32_t) * (size_t)n, s));
+    GP_HIP(hipMemsetAsync(prop, 0xFF, sizeof(int32_t) * npad, s));
     GP_HIP(hipMemsetAsync(dev, 0, sizeof(LPDev), s));
     GroupState *gstate = nullptr;
     if (group && ngroups > 0) {
@@ -2819,6 +2674,54 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     const int key_bits = bits_for(nlabels > 0 ? nlabels - 1 : 0);
     const int vbits = bits_for(n > 0 ? n - 1 : 0);
     const bool fuse_rest = !group && !active && n <= kFuseMax && vbits + key_bits <= 32;
+    AdmitCtx ac{};
+    if (!fuse_rest) {
+        ac.n = n;
+        ac.nlabels = nlabels;
+        ac.prop = prop;
+        ac.vwgt = g.vwgt;
+        ac.W = W;
+        ac.U = U;
+        ac.capv = capv;
+        ac.labels = labels;
+        ac.lab8 = lab8;
+        ac.dev = dev;
+        ac.group = group;
+        ac.gs = gstate;
+        ac.vbits = vbits;
+        if (dense) {
+            const int64_t chunks = (int64_t)(npad / kDadmChunk);
+            ac.tile = (int32_t)((chunks + kDadmMaxTiles - 1) / kDadmMaxTiles) * kDadmChunk;
+            ac.ntiles = (int32_t)(((int64_t)n + ac.tile - 1) / ac.tile);
+            ac.ncol = nlabels + ac.ntiles;
+        } else {
+            ac.tile = kSadmTile;
+            ac.ntiles = (int32_t)(((int64_t)n + kSadmTile - 1) / kSadmTile);
+            ac.ncol = ac.ntiles;
+        }
+        GP_TRY(sc.alloc(&ac.mv, n));
+        GP_TRY(sc.alloc(&ac.old, n));
+        GP_TRY(sc.alloc(&ac.tcnt, ac.ntiles));
+        GP_TRY(sc.alloc(&ac.tmoves, ac.ncol));
+        if (dense) {
+            GP_TRY(sc.alloc(&ac.part, (size_t)nlabels * ac.ntiles));
+            GP_TRY(sc.alloc(&ac.cut, nlabels));
+            GP_TRY(sc.alloc(&ac.cutroom, nlabels));
+        } else {
+            // the tier sort's three other buffers are free by now
+            ac.cpos = tval2;
+            ac.segv = reinterpret_cast<int32_t *>(tkey);
+            ac.segp = reinterpret_cast<int32_t *>(tkey2);
+            GP_TRY(sc.alloc(&ac.ccnt, nlabels));
+            GP_TRY(sc.alloc(&ac.coff, nlabels));
+            // a contested target has at least two proposers (each alone fits)
+            GP_TRY(sc.alloc(&ac.ct, n / 2));
+            GP_TRY(sc.alloc(&ac.ctW, n / 2));
+            GP_TRY(sc.alloc(&ac.nct, 2));
+            GP_HIP(hipMemsetAsync(ac.ccnt, 0, sizeof(int32_t) * (size_t)nlabels, s));
+            GP_HIP(hipMemsetAsync(ac.nct, 0, sizeof(int32_t) * 2, s));
+        }
+    }
     // active-set rounds: every vertex starts owing one evaluation per direction
     const uint8_t renew = dir_alternate ? 2 : 1;
     uint8_t *act = nullptr;
@@ -2830,6 +2733,7 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         // nnz / kMarkChunk + nnz / kMarkSplit of them
         GP_TRY(sc.alloc(&mbig, (size_t)g.nnz / kMarkChunk + (size_t)g.nnz / kMarkSplit + 1));
         GP_TRY(sc.alloc(&nmbig, 1));
+        ac.act = act;
         GP_HIP(hipMemsetAsync(nmbig, 0, sizeof(int32_t), s));
         hipLaunchKernelGGL(k_act_fill, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, act, n, renew);
         GP_LAUNCH_CHECK();
@@ -2859,8 +2763,9 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
             GP_TRY(sc.alloc(&rt.rowidx, n));
             GP_TRY(sc.alloc(&rt.big, (size_t)g.nnz / kRowChunk + (size_t)g.nnz / kRowSplit + 1));
             GP_TRY(sc.alloc(&rt.nbig, 1));
-            GP_TRY(sc.alloc(&rt.pushed, 1));
-            GP_HIP(hipMemsetAsync(rt.pushed, 0, sizeof(unsigned long long), s));
+            const size_t np = (size_t)ac.ntiles * rt.parts + 1;
+            GP_TRY(sc.alloc(&rt.pushed, np));
+            GP_HIP(hipMemsetAsync(rt.pushed, 0, sizeof(int64_t) * np, s));
             GP_HIP(hipMemsetAsync(rt.rows, 0, (size_t)rb, s));
             GP_HIP(hipMemsetAsync(rt.rowidx, 0xFF, sizeof(int32_t) * (size_t)n, s));
             GP_HIP(hipMemsetAsync(rt.nbig, 0, sizeof(int32_t), s));
@@ -2959,43 +2864,37 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
             GP_LAUNCH_CHECK();
             return GP_OK;
         }
-        // compaction of movers (ascending vertex id)
-        RT_TRY(compact(MoverFlag{prop, &dev->done}, MoverEmit{prop, mk, mv}, n, nullptr, nmov, sc));
-        uint32_t *k1 = mk, *k2 = mk2;
-        int32_t *v1 = mv, *v2 = mv2;
-        RT_TRY((radix_sort<uint32_t, int32_t>(&k1, &v1, &k2, &v2, n, nmov, key_bits, sc)));
-        const unsigned gb = grid_for(n, 256, 8192);
-        hipLaunchKernelGGL(k_heads, dim3(gb), dim3(256), 0, s, k1, nmov, headpos);
-        GP_LAUNCH_CHECK();
-        RT_TRY((scan<int64_t>(MoverWeight{v1, g.vwgt}, StoreIncl{S}, n, nmov, (int64_t *)nullptr, sc)));
-        hipLaunchKernelGGL(k_admit, dim3(gb), dim3(256), 0, s, k1, v1, nmov, headpos, S, W, U, capv, labels, lab8, oldlab,
-                           dev, group, gstate, act);
+        if (dense) {
+            hipLaunchKernelGGL(k_dadm_tally, dim3(ac.ntiles), dim3(kDadmBlock), 0, s, ac);
+            hipLaunchKernelGGL(k_dadm_cut, dim3(nlabels), dim3(256), 0, s, ac);
+            hipLaunchKernelGGL(k_dadm_apply, dim3(ac.ncol), dim3(kDadmBlock), 0, s, ac);
+        } else {
+            hipLaunchKernelGGL(k_sadm_tally, dim3(ac.ntiles), dim3(kSadmBlock), 0, s, ac);
+            hipLaunchKernelGGL(k_sadm_apply, dim3(ac.ntiles), dim3(kSadmBlock), 0, s, ac);
+            hipLaunchKernelGGL(k_sadm_offsets, dim3(grid_for(nlabels, 256, 64)), dim3(256), 0, s, ac);
+            hipLaunchKernelGGL(k_sadm_scatter, dim3(ac.ntiles), dim3(kSadmBlock), 0, s, ac);
+            hipLaunchKernelGGL(k_sadm_select, dim3(grid_for(n, 256, 512)), dim3(kSelBlock), 0, s, ac);
+        }
         GP_LAUNCH_CHECK();
         if (act) {
-            hipLaunchKernelGGL(k_act_mark, dim3(gb), dim3(256), 0, s, v1, oldlab, nmov, g.xadj, g.adjncy, act, renew,
-                               mbig, nmbig);
+            hipLaunchKernelGGL(k_act_mark, dim3(ac.ntiles), dim3(256), 0, s, ac, g.xadj, g.adjncy, renew, mbig, nmbig);
             hipLaunchKernelGGL(k_act_mark_big, dim3(grid_for(g.nnz / kMarkChunk + 1, 1, 4096)), dim3(256), 0, s, mbig,
                                nmbig, g.xadj, g.adjncy, act, renew);
             GP_LAUNCH_CHECK();
         }
-        if (nlabels <= kSmallLabels)
-            hipLaunchKernelGGL(k_apply_w_small, dim3(grid_for(n, 256, 1024)), dim3(256), 0, s, k1, v1, nmov, oldlab,
-                               g.vwgt, nlabels, W);
-        else
-            hipLaunchKernelGGL(k_apply_w, dim3(gb), dim3(256), 0, s, k1, v1, nmov, oldlab, g.vwgt, headpos, S, W);
-        GP_LAUNCH_CHECK();
         if (rt.rows) {
             if (wide)
-                RT_TRY((KTd == 16 ? rows_update<16, int64_t>(rt, k1, v1, oldlab, nmov, g.xadj, g.adjncy, g.adjwgt, n, g.nnz, s)
-                       : KTd == 64 ? rows_update<64, int64_t>(rt, k1, v1, oldlab, nmov, g.xadj, g.adjncy, g.adjwgt, n, g.nnz, s)
-                                   : rows_update<256, int64_t>(rt, k1, v1, oldlab, nmov, g.xadj, g.adjncy, g.adjwgt, n, g.nnz, s)));
+                RT_TRY((KTd == 16 ? rows_update<16, int64_t>(rt, ac, g.xadj, g.adjncy, g.adjwgt, g.nnz, s)
+                       : KTd == 64 ? rows_update<64, int64_t>(rt, ac, g.xadj, g.adjncy, g.adjwgt, g.nnz, s)
+                                   : rows_update<256, int64_t>(rt, ac, g.xadj, g.adjncy, g.adjwgt, g.nnz, s)));
             else
-                RT_TRY((KTd == 16 ? rows_update<16, int32_t>(rt, k1, v1, oldlab, nmov, g.xadj, g.adjncy, g.adjwgt, n, g.nnz, s)
-                       : KTd == 64 ? rows_update<64, int32_t>(rt, k1, v1, oldlab, nmov, g.xadj, g.adjncy, g.adjwgt, n, g.nnz, s)
-                                   : rows_update<256, int32_t>(rt, k1, v1, oldlab, nmov, g.xadj, g.adjncy, g.adjwgt, n, g.nnz, s)));
+                RT_TRY((KTd == 16 ? rows_update<16, int32_t>(rt, ac, g.xadj, g.adjncy, g.adjwgt, g.nnz, s)
+                       : KTd == 64 ? rows_update<64, int32_t>(rt, ac, g.xadj, g.adjncy, g.adjwgt, g.nnz, s)
+                                   : rows_update<256, int32_t>(rt, ac, g.xadj, g.adjncy, g.adjwgt, g.nnz, s)));
         }
         if (group) hipLaunchKernelGGL(k_round_end_groups, dim3(grid_for(ngroups, 256, 1024)), dim3(256), 0, s, gstate, ngroups);
-        hipLaunchKernelGGL(k_round_end, dim3(1), dim3(1), 0, s, dev);
+        if (dense) hipLaunchKernelGGL(k_dadm_end, dim3(nlabels), dim3(256), 0, s, ac);
+        else hipLaunchKernelGGL(k_sadm_end, dim3(1), dim3(256), 0, s, ac);
         GP_LAUNCH_CHECK();
     #undef RT_TRY
         return GP_OK;
@@ -3032,9 +2931,13 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     }
     if (out || prof_on()) {
         LPDev h;
-        unsigned long long pushed = 0;
+        int64_t pushed = 0;
+        if (rt.rows)
+            GP_TRY((reduce<int64_t>(LoadIn<int64_t>{rt.pushed}, ac.ntiles * rt.parts, nullptr,
+                                   rt.pushed + ac.ntiles * rt.parts, sc)));
         GP_HIP(hipMemcpyAsync(&h, dev, sizeof(LPDev), hipMemcpyDeviceToHost, s));
-        if (rt.rows) GP_HIP(hipMemcpyAsync(&pushed, rt.pushed, sizeof(pushed), hipMemcpyDeviceToHost, s));
+        if (rt.rows)
+            GP_HIP(hipMemcpyAsync(&pushed, rt.pushed + ac.ntiles * rt.parts, sizeof(pushed), hipMemcpyDeviceToHost, s));
         GP_HIP(hipStreamSynchronize(s));
         prof_flush();
         if (!out) return GP_OK;
@@ -3045,7 +2948,7 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         out->row_entries = rt.rows ? rt.entries : 0;
         out->row_width = rt.rows ? KTd : 0;
         out->row_sum_bytes = rt.rows ? (wide ? 8 : 4) : 0;
-        out->row_updates = rt.rows ? (int64_t)pushed : 0;
+        out->row_updates = rt.rows ? pushed : 0;
         out->group_rounds.clear();
         out->group_moves.clear();
         if (group) {
