@@ -2479,7 +2479,8 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         }
         for (int t = 1; t < kTiers - 1; t++) tk.bound[t] = std::max(tk.bound[t], tk.bound[t - 1]);
     }
-    hipLaunchKernelGGL(k_tier_keys, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, tk, n, tkey, tval, tcnt, tedge);
+    // few workgroups: each adds its counts to one cache line
+    hipLaunchKernelGGL(k_tier_keys, dim3(grid_for(n, 256 * 8, 1024)), dim3(256), 0, s, tk, n, tkey, tval, tcnt, tedge);
     GP_LAUNCH_CHECK();
     GP_TRY((radix_sort<uint32_t, int32_t>(&tkey, &tval, &tkey2, &tval2, n, nullptr, 4, sc)));
     int32_t hcnt[kTiers];
