@@ -69,6 +69,7 @@ struct AdmitCtx {
     const int32_t *group;
     GroupState *gs;
     uint8_t *act;  // active-set rounds: a refused vertex owes at least one evaluation
+    uint8_t *todo;  // set by the movers' marks (refinement), null: none
     // the round's movers: tile i owns entries [i * tile, i * tile + tcnt[i])
     int32_t tile, ntiles;
     int32_t *mv;      // vertex

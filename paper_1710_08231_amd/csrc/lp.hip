@@ -39,16 +39,91 @@ struct LPArgs {
     const int64_t *capv;   // optional per-label capacity (batched graphs); null: every label has U
     const uint8_t *lab8;   // dense mode (<= 256 labels): byte copy of labels for the neighbour gathers
     const uint8_t *act;    // active-set rounds: evaluations each vertex still owes (0: no proposal); null: all
+    uint8_t *todo;         // bit of the round's direction clear: the vertex is settled in it; null: none is
     const int32_t *group;  // batched graphs: group of each vertex; null: one graph
     const GroupState *gs;  // batched graphs: per-group state
 };
+
+// A vertex none of whose labels in the round's direction has a larger
+// connection than its own label is settled in that direction: whatever the
+// label weights do, it proposes nothing there until a neighbour or it itself
+// moves (its connections and the direction rule depend on their labels only).
+// Its todo bit of the direction is then clear and it is not evaluated again;
+// an admitted mover sets both bits of itself and its neighbours. Refinement
+// leaves most vertices settled (on a weighted 96^3 grid, k = 64, 10% of the
+// vertices have to be evaluated per round, on R-MAT-19 31%).
+__device__ __forceinline__ uint8_t round_bit(const LPArgs &a) {
+    return a.dir_alternate ? (uint8_t)(1 << ((*a.round) & 1)) : (uint8_t)1;
+}
+constexpr uint8_t kTodoBoth = 3;
+constexpr int kPropBlock = 256;
 
 // An inactive vertex makes no proposal: its edge range is taken as empty.
 // A group that stopped (two idle rounds) stays idle: its state is a fixed
 // point of the rounds, and its labels and weights are its own, so evaluating
 // its vertices again could only yield proposals refused as before.
-__device__ __forceinline__ bool inactive(const LPArgs &a, int32_t v) {
-    return (a.act && a.act[v] == 0) || (a.group && a.gs[a.group[v]].done);
+__device__ __forceinline__ bool inactive(const LPArgs &a, int32_t v, uint8_t bit) {
+    return (a.act && a.act[v] == 0) || (a.todo && !(a.todo[v] & bit)) || (a.group && a.gs[a.group[v]].done);
+}
+
+// Some vertex of the lists may be inactive (not in plain clustering rounds).
+inline bool may_skip(const LPArgs &a) { return a.act || a.todo || a.group; }
+
+// One lane per vertex, after its evaluation: `over` says that some label in
+// the round's direction beat the own one.
+__device__ __forceinline__ void settle(const LPArgs &a, int32_t v, uint8_t bit, bool over) {
+    if (a.todo && !over) a.todo[v] &= (uint8_t)~bit;
+}
+
+// The vertices to evaluate among list entries [j0, min(j0 + span, count)) of
+// verts, into lv (and their entry's offset into lj), by one wave; returns how
+// many. Skipping happens here, before lanes are dealt to vertices: a wave looks
+// at up to 256 entries at once and its lane groups then only see live ones.
+constexpr int kSpanMax = 256;
+__device__ __forceinline__ int32_t wave_live(const LPArgs &a, const int32_t *verts, int64_t j0, int32_t span,
+                                             int64_t count, uint8_t bit, int32_t *lv, uint8_t *lj = nullptr) {
+    constexpr int Q = kSpanMax / kWave;
+    const int lane = lane_id();
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
+    int32_t v[Q];
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+        const int32_t o = q * kWave + lane;
+        v[q] = o < span && j0 + o < count ? verts[j0 + o] : -1;
+    }
+    int32_t n = 0;
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+        if (q * kWave >= span) break;
+        const bool live = v[q] >= 0 && !inactive(a, v[q], bit);
+        const uint64_t m = __ballot(live);
+        if (live) {
+            const int32_t at = n + (int32_t)__popcll(m & lt);
+            lv[at] = v[q];
+            if (lj) lj[at] = (uint8_t)(q * kWave + lane);
+        }
+        n += (int32_t)__popcll(m);
+    }
+    wave_sync();
+    return n;
+}
+
+// List entries a wave takes together (a multiple of its `groups` lane groups).
+// With vertices to skip: enough waves first (a short list is spread over the
+// chip), longer spans for long lists. With none to skip the waves interleave as
+// finely as they can: neighbouring rows share cache lines.
+inline int32_t span_for(const LPArgs &a, int64_t count, int groups) {
+    if (!may_skip(a)) return groups;
+    int32_t s = groups;
+    while (s < kSpanMax && count / s > 16384) s *= 2;
+    return s;
+}
+
+// lanes of this lane's group of GL
+template <int GL>
+__device__ __forceinline__ uint64_t group_mask() {
+    const int lane = lane_id();
+    return GL == kWave ? ~0ull : (((1ull << (GL & 63)) - 1ull) << (lane / GL * GL));
 }
 
 // Vertices of the degree tiers: tier t is verts[ts[t] .. ts[t+1]), both on the
@@ -163,13 +238,14 @@ __device__ __forceinline__ void block_best(AccT &bc, int32_t &bl, AccT *tc, int3
     __syncthreads();
 }
 
-constexpr int kPropBlock = 256;
 constexpr int kSmallLabels = 4096;  // label counts handled with per-block LDS totals
 constexpr int kDenseLabels = 256;   // label counts handled with dense per-vertex tables
 
 // GL lanes per vertex (GL <= 64), TBL table slots per vertex.
-template <int GL, int TBL, typename AccT>
-__global__ __launch_bounds__(kPropBlock) void k_propose_group(LPArgs a, TierList lists, int tier) {
+// SKIP: some vertices of the list may be inactive (without it the lanes read the
+// list itself: 42 VGPRs and eight waves a SIMD instead of 60 and seven).
+template <int GL, int TBL, typename AccT, bool SKIP>
+__global__ __launch_bounds__(kPropBlock) void k_propose_group(LPArgs a, TierList lists, int tier, int32_t span) {
     if (*a.done) return;
     const int64_t t0 = lists.ts[tier];
     const int32_t count = (int32_t)(lists.ts[tier + 1] - t0);
@@ -189,14 +265,19 @@ __global__ __launch_bounds__(kPropBlock) void k_propose_group(LPArgs a, TierList
         val[i] = 0;
     }
     wave_sync();
+    __shared__ int32_t slive[SKIP ? NW : 1][SKIP ? kSpanMax : 1];
+    const uint8_t bit = SKIP ? round_bit(a) : 0;
+    if (!SKIP) span = GPW;
     const unsigned b = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t stride = (int64_t)gridDim.x * NW * GPW;
-    for (int64_t wb = ((int64_t)b * NW + w) * GPW; wb < count; wb += stride) {
-        const int64_t idx = wb + grp;
-        const bool valid = idx < count;
-        const int32_t v = valid ? verts[idx] : 0;
+    const int64_t stride = (int64_t)gridDim.x * NW * span;
+    for (int64_t wb = ((int64_t)b * NW + w) * span; wb < count; wb += stride) {
+    int32_t nlive = GPW;
+    if constexpr (SKIP) nlive = wave_live(a, verts, wb, span, count, bit, slive[w]);
+    for (int32_t i0 = 0; i0 < nlive; i0 += GPW) {
+        const bool valid = SKIP ? i0 + grp < nlive : wb + grp < count;
+        const int32_t v = !valid ? 0 : (SKIP ? slive[w][i0 + grp] : verts[wb + grp]);
         const int32_t beg = valid ? a.xadj[v] : 0;
-        const int32_t end = (valid && !inactive(a, v)) ? a.xadj[v + 1] : beg;
+        const int32_t end = valid ? a.xadj[v + 1] : beg;
         const int32_t own = valid ? a.labels[v] : -1;
         AccT oc = 0;
         const int nch = (end - beg + GL - 1) / GL;
@@ -250,13 +331,18 @@ __global__ __launch_bounds__(kPropBlock) void k_propose_group(LPArgs a, TierList
             group_best<GL, AccT>(bc2, bl2);
             if (need2 && bl2 != INT_MAX && bc2 > oc) target = bl2;
         }
-        if (valid && gl == 0) a.prop[v] = target;
+        if (valid && gl == 0) {
+            a.prop[v] = target;
+            if (SKIP) settle(a, v, bit, bl != INT_MAX && bc > oc);
+        }
         wave_sync();
         for (int i = gl; i < TBL; i += GL) {
             key[i] = -1;
             val[i] = 0;
         }
         wave_sync();
+    }
+    wave_sync();
     }
 }
 
@@ -350,8 +436,8 @@ __device__ __forceinline__ unsigned long long group_max_u64(unsigned long long x
 }
 
 // GL lanes per vertex, TBL packed slots per vertex (degrees up to TBL / 2).
-template <int GL, int TBL>
-__global__ __launch_bounds__(kPropBlock) void k_pgroup(LPArgs a, TierList lists, int tier) {
+template <int GL, int TBL, bool SKIP>
+__global__ __launch_bounds__(kPropBlock) void k_pgroup(LPArgs a, TierList lists, int tier, int32_t span) {
     if (*a.done) return;
     const int64_t t0 = lists.ts[tier];
     const int32_t count = (int32_t)(lists.ts[tier + 1] - t0);
@@ -367,14 +453,19 @@ __global__ __launch_bounds__(kPropBlock) void k_pgroup(LPArgs a, TierList lists,
     unsigned long long *tbl = stbl + (w * GPW + grp) * TBL;
     for (int i = gl; i < TBL; i += GL) tbl[i] = kSlotEmpty;
     wave_sync();
+    __shared__ int32_t slive[SKIP ? NW : 1][SKIP ? kSpanMax : 1];
+    const uint8_t bit = SKIP ? round_bit(a) : 0;
+    if (!SKIP) span = GPW;
     const unsigned b = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t stride = (int64_t)gridDim.x * NW * GPW;
-    for (int64_t wb = ((int64_t)b * NW + w) * GPW; wb < count; wb += stride) {
-        const int64_t idx = wb + grp;
-        const bool valid = idx < count;
-        const int32_t v = valid ? verts[idx] : 0;
+    const int64_t stride = (int64_t)gridDim.x * NW * span;
+    for (int64_t wb = ((int64_t)b * NW + w) * span; wb < count; wb += stride) {
+    int32_t nlive = GPW;
+    if constexpr (SKIP) nlive = wave_live(a, verts, wb, span, count, bit, slive[w]);
+    for (int32_t i0 = 0; i0 < nlive; i0 += GPW) {
+        const bool valid = SKIP ? i0 + grp < nlive : wb + grp < count;
+        const int32_t v = !valid ? 0 : (SKIP ? slive[w][i0 + grp] : verts[wb + grp]);
         const int32_t beg = valid ? a.xadj[v] : 0;
-        const int32_t end = (valid && !inactive(a, v)) ? a.xadj[v + 1] : beg;
+        const int32_t end = valid ? a.xadj[v + 1] : beg;
         const int32_t own = valid ? a.labels[v] : -1;
         int32_t oc = 0;
         unsigned long long mybest = 0;
@@ -437,12 +528,17 @@ __global__ __launch_bounds__(kPropBlock) void k_pgroup(LPArgs a, TierList lists,
             group_best<GL, int32_t>(bc2, bl2);
             if (need2 && bl2 != INT_MAX && bc2 > oc) target = bl2;
         }
-        if (valid && gl == 0) a.prop[v] = target;
+        if (valid && gl == 0) {
+            a.prop[v] = target;
+            if (SKIP) settle(a, v, bit, bl != INT_MAX && bc > oc);
+        }
         wave_sync();
 #pragma unroll
         for (int i = 0; i < MAXE; i++)
             if (touched[i] != ~0u) tbl[touched[i]] = kSlotEmpty;
         wave_sync();
+    }
+    wave_sync();
     }
 }
 
@@ -455,74 +551,101 @@ __global__ __launch_bounds__(kPropBlock) void k_pgroup(LPArgs a, TierList lists,
 // row and entry are loaded while the current one is selected. (With 16 lanes
 // the shuffles cost more than the table: the tier of up to 16 neighbours keeps
 // k_pgroup.)
-template <int GL, int E>
-__global__ __launch_bounds__(kPropBlock) void k_plane(LPArgs a, TierList lists, int tier) {
+template <int GL, int E, bool SKIP>
+__global__ __launch_bounds__(kPropBlock) void k_plane(LPArgs a, TierList lists, int tier, int32_t span) {
     static_assert(E <= GL, "one entry per lane");
     if (*a.done) return;
     const int64_t t0 = lists.ts[tier];
     const int32_t count = (int32_t)(lists.ts[tier + 1] - t0);
     const int32_t *__restrict__ verts = lists.verts + t0;
     const int32_t dmode = cur_dirmode(a);
+    const uint8_t bit = SKIP ? round_bit(a) : 0;
+    if (!SKIP) span = kWave / GL;
     constexpr int GPW = kWave / GL;
     constexpr int NW = kPropBlock / kWave;
+    __shared__ int32_t slive[SKIP ? NW : 1][SKIP ? kSpanMax : 1];
     const int lane = lane_id(), w = threadIdx.x / kWave;
     const int gl = lane % GL, grp = lane / GL;
     const unsigned b = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t stride = (int64_t)gridDim.x * NW * GPW;
-    int64_t wb = ((int64_t)b * NW + w) * GPW;
-    bool valid = wb + grp < count;
-    int32_t v = valid ? verts[wb + grp] : 0;
-    int32_t beg = valid ? a.xadj[v] : 0;
-    int32_t end = (valid && !inactive(a, v)) ? a.xadj[v + 1] : beg;
-    int32_t own = valid ? a.labels[v] : -1;
-    int32_t u = beg + gl < end ? a.adjncy[beg + gl] : -1;
-    int32_t wt = (u >= 0 && a.adjwgt) ? a.adjwgt[beg + gl] : 1;
-    int32_t L = u >= 0 ? a.labels[u] : -1;
-    for (; wb < count; wb += stride) {
-        // the next vertex's row, label and entry
-        const int64_t nwb = wb + stride;
-        const bool nvalid = nwb + grp < count;
-        const int32_t nv = nvalid ? verts[nwb + grp] : 0;
-        const int32_t nbeg = nvalid ? a.xadj[nv] : 0;
-        const int32_t nend = (nvalid && !inactive(a, nv)) ? a.xadj[nv + 1] : nbeg;
-        const int32_t nown = nvalid ? a.labels[nv] : -1;
-        const int32_t nu = nbeg + gl < nend ? a.adjncy[nbeg + gl] : -1;
-        const int32_t nwt = (nu >= 0 && a.adjwgt) ? a.adjwgt[nbeg + gl] : 1;
-        int32_t c = 0;
-#pragma unroll
-        for (int d = 0; d < E; d++) {
-            const int32_t Ld = __shfl(L, d, GL);
-            const int32_t wd = __shfl(wt, d, GL);
-            if (Ld == L) c += wd;
+    const int64_t stride = (int64_t)gridDim.x * NW * span;
+    for (int64_t wb = ((int64_t)b * NW + w) * span; wb < count; wb += stride) {
+        // without SKIP all of the wave's entries in one go, one group of them
+        // per stride, so that the loads below run ahead across strides
+        int32_t nlive = 0;
+        if constexpr (SKIP) {
+            nlive = wave_live(a, verts, wb, span, count, bit, slive[w]);
+            if (nlive == 0) continue;
+        } else {
+            nlive = (int32_t)((count - wb + stride - 1) / stride) * GPW;
         }
-        const int32_t oc = group_sum<GL>((L >= 0 && L == own) ? wt : 0);
-        const bool cand = L >= 0 && L != own && dir_ok(L, own, dmode);
-        const unsigned long long best = group_max_u64<GL>(cand ? pack_best((uint32_t)c, L) : 0ull);
-        const int32_t bc = (int32_t)(best >> 32);
-        const int32_t bl = best ? (int32_t)~(uint32_t)best : INT_MAX;
-        const int64_t cv = valid ? vweight(a.vwgt, v) : 0;
-        int32_t target = -1;
-        bool need2 = false;
-        if (valid && bl != INT_MAX && bc > oc) {
-            if (a.W[bl] + cv <= capof(a, bl)) target = bl;
-            else need2 = true;
-        }
-        if (__ballot(need2)) {
-            int32_t bc2 = 0, bl2 = INT_MAX;
-            if (need2 && cand && a.W[L] + cv <= capof(a, L)) {
-                bc2 = c;
-                bl2 = L;
+        int32_t li = grp;          // the next vertex: place in the list of live ones,
+        int64_t lj = wb + grp;     // or list entry
+        const auto next = [&]() -> int32_t {
+            int32_t x = -1;
+            if constexpr (SKIP) {
+                if (li < nlive) x = slive[w][li];
+                li += GPW;
+            } else {
+                if (lj < count) x = verts[lj];
+                lj += stride;
             }
-            group_best<GL, int32_t>(bc2, bl2);
-            if (need2 && bl2 != INT_MAX && bc2 > oc) target = bl2;
+            return x;
+        };
+        int32_t v = next();
+        int32_t beg = v >= 0 ? a.xadj[v] : 0;
+        int32_t end = v >= 0 ? a.xadj[v + 1] : 0;
+        int32_t own = v >= 0 ? a.labels[v] : -1;
+        int32_t u = beg + gl < end ? a.adjncy[beg + gl] : -1;
+        int32_t wt = (u >= 0 && a.adjwgt) ? a.adjwgt[beg + gl] : 1;
+        int32_t L = u >= 0 ? a.labels[u] : -1;
+        for (int32_t i0 = 0; i0 < nlive; i0 += GPW) {
+            // the next vertex's row, label and entry
+            const int32_t nv = next();
+            const int32_t nbeg = nv >= 0 ? a.xadj[nv] : 0;
+            const int32_t nend = nv >= 0 ? a.xadj[nv + 1] : 0;
+            const int32_t nown = nv >= 0 ? a.labels[nv] : -1;
+            const int32_t nu = nbeg + gl < nend ? a.adjncy[nbeg + gl] : -1;
+            const int32_t nwt = (nu >= 0 && a.adjwgt) ? a.adjwgt[nbeg + gl] : 1;
+            int32_t c = 0;
+#pragma unroll
+            for (int d = 0; d < E; d++) {
+                const int32_t Ld = __shfl(L, d, GL);
+                const int32_t wd = __shfl(wt, d, GL);
+                if (Ld == L) c += wd;
+            }
+            const int32_t oc = group_sum<GL>((L >= 0 && L == own) ? wt : 0);
+            const bool cand = L >= 0 && L != own && dir_ok(L, own, dmode);
+            const unsigned long long best = group_max_u64<GL>(cand ? pack_best((uint32_t)c, L) : 0ull);
+            const int32_t bc = (int32_t)(best >> 32);
+            const int32_t bl = best ? (int32_t)~(uint32_t)best : INT_MAX;
+            const int64_t cv = v >= 0 ? vweight(a.vwgt, v) : 0;
+            int32_t target = -1;
+            bool need2 = false;
+            if (v >= 0 && bl != INT_MAX && bc > oc) {
+                if (a.W[bl] + cv <= capof(a, bl)) target = bl;
+                else need2 = true;
+            }
+            if (__ballot(need2)) {
+                int32_t bc2 = 0, bl2 = INT_MAX;
+                if (need2 && cand && a.W[L] + cv <= capof(a, L)) {
+                    bc2 = c;
+                    bl2 = L;
+                }
+                group_best<GL, int32_t>(bc2, bl2);
+                if (need2 && bl2 != INT_MAX && bc2 > oc) target = bl2;
+            }
+            if (v >= 0 && gl == 0) {
+                a.prop[v] = target;
+                if (SKIP) settle(a, v, bit, bl != INT_MAX && bc > oc);
+            }
+            v = nv;
+            own = nown;
+            u = nu;
+            wt = nwt;
+            L = nu >= 0 ? a.labels[nu] : -1;
         }
-        if (valid && gl == 0) a.prop[v] = target;
-        valid = nvalid;
-        v = nv;
-        own = nown;
-        u = nu;
-        wt = nwt;
-        L = nu >= 0 ? a.labels[nu] : -1;
+        if (!SKIP) break;
+        wave_sync();
     }
 }
 
@@ -539,6 +662,7 @@ __global__ __launch_bounds__(BLOCK) void k_pblock(LPArgs a, TierList lists, int 
     const int32_t count = (int32_t)(lists.ts[tier + 1] - t0);
     const int32_t *__restrict__ verts = lists.verts + t0;
     const int32_t dmode = cur_dirmode(a);
+    const uint8_t bit = round_bit(a);
     constexpr int NW = BLOCK / kWave;
     constexpr int MAXE = 4 * ((TBL / 2 + 4 * BLOCK - 1) / (4 * BLOCK));  // entries per thread
     __shared__ unsigned long long tbl[TBL];
@@ -552,7 +676,7 @@ __global__ __launch_bounds__(BLOCK) void k_pblock(LPArgs a, TierList lists, int 
     int32_t v = idx < count ? verts[idx] : 0;
     int32_t beg = idx < count ? a.xadj[v] : 0, end = idx < count ? a.xadj[v + 1] : 0;
     int32_t own = idx < count ? a.labels[v] : -1;
-    if (idx < count && inactive(a, v)) end = beg;
+    if (idx < count && inactive(a, v, bit)) end = beg;
     // entry it of this thread is beg + threadIdx.x + it * BLOCK
     int32_t L[MAXE], wv[MAXE];
     {
@@ -591,7 +715,7 @@ __global__ __launch_bounds__(BLOCK) void k_pblock(LPArgs a, TierList lists, int 
         const int32_t nbeg = nidx < count ? a.xadj[nv] : 0;
         int32_t nend = nidx < count ? a.xadj[nv + 1] : 0;
         const int32_t nown = nidx < count ? a.labels[nv] : -1;
-        if (nidx < count && inactive(a, nv)) nend = nbeg;
+        if (nidx < count && inactive(a, nv, bit)) nend = nbeg;
         int32_t nu[MAXE];
 #pragma unroll
         for (int it = 0; it < MAXE; it++) {
@@ -621,7 +745,10 @@ __global__ __launch_bounds__(BLOCK) void k_pblock(LPArgs a, TierList lists, int 
                 if (bl2 != INT_MAX && bc2 > oc) target = bl2;
             }
         }
-        if (threadIdx.x == 0) a.prop[v] = target;
+        if (threadIdx.x == 0) {
+            a.prop[v] = target;
+            settle(a, v, bit, bl != INT_MAX && bc > oc);
+        }
         __syncthreads();  // every lane has read the table and wbest
 #pragma unroll
         for (int i = 0; i < MAXE; i++)
@@ -643,6 +770,7 @@ __global__ __launch_bounds__(BLOCK) void k_propose_block(LPArgs a, TierList list
     const int32_t count = (int32_t)(lists.ts[tier + 1] - t0);
     const int32_t *__restrict__ verts = lists.verts + t0;
     const int32_t dmode = cur_dirmode(a);
+    const uint8_t bit = round_bit(a);
     constexpr int NW = BLOCK / kWave;
     constexpr int U4 = 4;
     __shared__ int32_t key[TBL];
@@ -664,7 +792,7 @@ __global__ __launch_bounds__(BLOCK) void k_propose_block(LPArgs a, TierList list
     for (; idx < count; idx += gridDim.x) {
         const int64_t nidx = idx + gridDim.x;
         const int32_t nv = nidx < count ? verts[nidx] : 0;
-        if (inactive(a, v)) end = beg;
+        if (inactive(a, v, bit)) end = beg;
         int lg = 6;
         while ((1 << lg) < 2 * (end - beg) && (1 << lg) < TBL) lg++;
         const uint32_t cap = 1u << lg;
@@ -720,7 +848,10 @@ __global__ __launch_bounds__(BLOCK) void k_propose_block(LPArgs a, TierList list
                 if (bl2 != INT_MAX && bc2 > oc) target = bl2;
             }
         }
-        if (threadIdx.x == 0) a.prop[v] = target;
+        if (threadIdx.x == 0) {
+            a.prop[v] = target;
+            settle(a, v, bit, bl != INT_MAX && bc > oc);
+        }
         for (uint32_t i = threadIdx.x; i < cap; i += BLOCK) {
             key[i] = -1;
             val[i] = 0;
@@ -741,12 +872,13 @@ __global__ __launch_bounds__(BLOCK) void k_propose_hub(LPArgs a, const int32_t *
                                                        const int32_t *hlog, int32_t *gkey, AccT *gval) {
     if (*a.done) return;
     const int32_t dmode = cur_dirmode(a);
+    const uint8_t bit = round_bit(a);
     constexpr int NW = BLOCK / kWave;
     __shared__ AccT tc[NW + 1];
     __shared__ int32_t tl[NW + 1];
     for (int64_t idx = blockIdx.x; idx < count; idx += gridDim.x) {
         const int32_t v = verts[idx];
-        if (inactive(a, v)) {  // uniform per workgroup: its table stays empty
+        if (inactive(a, v, bit)) {  // uniform per workgroup: its table stays empty
             if (threadIdx.x == 0) a.prop[v] = -1;
             continue;
         }
@@ -798,7 +930,10 @@ __global__ __launch_bounds__(BLOCK) void k_propose_hub(LPArgs a, const int32_t *
                 if (bl2 != INT_MAX && bc2 > oc) target = bl2;
             }
         }
-        if (threadIdx.x == 0) a.prop[v] = target;
+        if (threadIdx.x == 0) {
+            a.prop[v] = target;
+            settle(a, v, bit, bl != INT_MAX && bc > oc);
+        }
         for (uint32_t i = threadIdx.x; i < cap; i += BLOCK) {
             key[i] = -1;
             val[i] = 0;
@@ -882,7 +1017,7 @@ __global__ __launch_bounds__(kHubBlock) void k_hub_insert(LPArgs a, HubPlan hp) 
     __shared__ int32_t tmp[kHubBlock / kWave + 1];
     const int32_t h = hp.chunk_hub[blockIdx.x];
     const int32_t v = hp.hubs[h];
-    if (inactive(a, v)) return;  // uniform: nothing goes into the hub's buckets
+    if (inactive(a, v, round_bit(a))) return;  // uniform: nothing goes into the hub's buckets
     const int32_t nb = hp.nbk[h];
     const int32_t beg = a.xadj[v] + (blockIdx.x - hp.chunk_first[h]) * kHubChunk;
     const int32_t end = min(a.xadj[v + 1], beg + kHubChunk);
@@ -1075,101 +1210,111 @@ __global__ void k_hub_expand(const int32_t *first, const int32_t *num, int32_t n
 // while the current vertex is selected, so each vertex's chain of dependent
 // loads overlaps the previous vertex's reductions.
 template <int GL, int KT, typename AccT>
-__global__ __launch_bounds__(kPropBlock) void k_dense_group(LPArgs a, int32_t nlabels, TierList lists, int tier) {
+__global__ __launch_bounds__(kPropBlock) void k_dense_group(LPArgs a, int32_t nlabels, TierList lists, int tier,
+                                                            int32_t span) {
     if (*a.done) return;
     const int64_t t0 = lists.ts[tier];
     const int32_t count = (int32_t)(lists.ts[tier + 1] - t0);
     const int32_t *__restrict__ verts = lists.verts + t0;
     const int32_t dmode = cur_dirmode(a);
+    const uint8_t bit = round_bit(a);
     constexpr int GPW = kWave / GL;
     constexpr int NW = kPropBlock / kWave;
     // one table per lane group, KT + 1 apart so that the same block id of two
     // groups falls in different LDS banks
     __shared__ AccT sval[NW * GPW * (KT + 1)];
     __shared__ int64_t sW[KT];
+    __shared__ int32_t slive[NW][kSpanMax];
     const int lane = lane_id(), w = threadIdx.x / kWave;
     const int gl = lane % GL, grp = lane / GL;
+    const uint64_t gm = group_mask<GL>();
     AccT *val = sval + (w * GPW + grp) * (KT + 1);
     // slack of each label at the round start: W - capacity (> 0 never eligible)
     for (int i = threadIdx.x; i < KT; i += kPropBlock) sW[i] = i < nlabels ? a.W[i] - capof(a, i) : (int64_t(1) << 62);
     for (int i = gl; i < KT; i += GL) val[i] = 0;
     __syncthreads();
     const unsigned b = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t stride = (int64_t)gridDim.x * NW * GPW;
-    int64_t wb = ((int64_t)b * NW + w) * GPW;
-    // the group's vertex and its first two chunks, loaded one iteration ahead
-    bool valid = wb + grp < count;
-    int32_t v = valid ? verts[wb + grp] : 0;
-    int32_t beg = valid ? a.xadj[v] : 0;
-    int32_t end = (valid && !inactive(a, v)) ? a.xadj[v + 1] : beg;
-    int32_t own = valid ? a.labels[v] : -1;
-    int32_t u0 = beg + gl < end ? a.adjncy[beg + gl] : -1, u1 = beg + gl + GL < end ? a.adjncy[beg + gl + GL] : -1;
-    AccT w0 = (u0 >= 0 && a.adjwgt) ? (AccT)a.adjwgt[beg + gl] : (AccT)1;
-    AccT w1 = (u1 >= 0 && a.adjwgt) ? (AccT)a.adjwgt[beg + gl + GL] : (AccT)1;
-    int32_t L0 = u0 >= 0 ? (int32_t)a.lab8[u0] : -1, L1 = u1 >= 0 ? (int32_t)a.lab8[u1] : -1;
-    for (; wb < count; wb += stride) {
-        const int64_t nwb = wb + stride;
-        const bool nvalid = nwb + grp < count;
-        const int32_t nv = nvalid ? verts[nwb + grp] : 0;
-        AccT oc = 0;
-        const int nch = (end - beg + GL - 1) / GL;
-        const int maxch = wave_max(nch);
-        // chunks 0 and 1 from the registers, the rest as they come
-        if (u0 >= 0) {
-            if (L0 == own) oc += w0;
-            else if (dir_ok(L0, own, dmode)) lds_add<AccT>(&val[L0], w0);
-        }
-        if (u1 >= 0) {
-            if (L1 == own) oc += w1;
-            else if (dir_ok(L1, own, dmode)) lds_add<AccT>(&val[L1], w1);
-        }
-        for (int ch = 2; ch < maxch; ch += 2) {
-            const int32_t e0 = beg + ch * GL + gl, e1 = e0 + GL;
-            const int32_t x0 = e0 < end ? a.adjncy[e0] : -1, x1 = e1 < end ? a.adjncy[e1] : -1;
-            const AccT y0 = (e0 < end && a.adjwgt) ? (AccT)a.adjwgt[e0] : (AccT)1;
-            const AccT y1 = (e1 < end && a.adjwgt) ? (AccT)a.adjwgt[e1] : (AccT)1;
-            const int32_t M0 = x0 >= 0 ? (int32_t)a.lab8[x0] : -1, M1 = x1 >= 0 ? (int32_t)a.lab8[x1] : -1;
-            if (x0 >= 0) {
-                if (M0 == own) oc += y0;
-                else if (dir_ok(M0, own, dmode)) lds_add<AccT>(&val[M0], y0);
+    const int64_t stride = (int64_t)gridDim.x * NW * span;
+    for (int64_t wb = ((int64_t)b * NW + w) * span; wb < count; wb += stride) {
+        const int32_t nlive = wave_live(a, verts, wb, span, count, bit, slive[w]);
+        if (nlive == 0) continue;
+        // the group's vertex and its first two chunks, loaded one iteration ahead
+        int32_t v = grp < nlive ? slive[w][grp] : -1;
+        int32_t beg = v >= 0 ? a.xadj[v] : 0;
+        int32_t end = v >= 0 ? a.xadj[v + 1] : 0;
+        int32_t own = v >= 0 ? a.labels[v] : -1;
+        int32_t u0 = beg + gl < end ? a.adjncy[beg + gl] : -1, u1 = beg + gl + GL < end ? a.adjncy[beg + gl + GL] : -1;
+        AccT w0 = (u0 >= 0 && a.adjwgt) ? (AccT)a.adjwgt[beg + gl] : (AccT)1;
+        AccT w1 = (u1 >= 0 && a.adjwgt) ? (AccT)a.adjwgt[beg + gl + GL] : (AccT)1;
+        int32_t L0 = u0 >= 0 ? (int32_t)a.lab8[u0] : -1, L1 = u1 >= 0 ? (int32_t)a.lab8[u1] : -1;
+        for (int32_t i0 = 0; i0 < nlive; i0 += GPW) {
+            const int32_t ni = i0 + GPW + grp;
+            const int32_t nv = ni < nlive ? slive[w][ni] : -1;
+            AccT oc = 0;
+            const int nch = (end - beg + GL - 1) / GL;
+            const int maxch = wave_max(nch);
+            // chunks 0 and 1 from the registers, the rest as they come
+            if (u0 >= 0) {
+                if (L0 == own) oc += w0;
+                else if (dir_ok(L0, own, dmode)) lds_add<AccT>(&val[L0], w0);
             }
-            if (x1 >= 0) {
-                if (M1 == own) oc += y1;
-                else if (dir_ok(M1, own, dmode)) lds_add<AccT>(&val[M1], y1);
+            if (u1 >= 0) {
+                if (L1 == own) oc += w1;
+                else if (dir_ok(L1, own, dmode)) lds_add<AccT>(&val[L1], w1);
             }
-        }
-        // the next vertex's row, label and first two chunks
-        const int32_t nbeg = nvalid ? a.xadj[nv] : 0;
-        const int32_t nend = (nvalid && !inactive(a, nv)) ? a.xadj[nv + 1] : nbeg;
-        const int32_t nown = nvalid ? a.labels[nv] : -1;
-        u0 = nbeg + gl < nend ? a.adjncy[nbeg + gl] : -1;
-        u1 = nbeg + gl + GL < nend ? a.adjncy[nbeg + gl + GL] : -1;
-        w0 = (u0 >= 0 && a.adjwgt) ? (AccT)a.adjwgt[nbeg + gl] : (AccT)1;
-        w1 = (u1 >= 0 && a.adjwgt) ? (AccT)a.adjwgt[nbeg + gl + GL] : (AccT)1;
-        wave_sync();
-        oc = group_sum<GL>(oc);
-        L0 = u0 >= 0 ? (int32_t)a.lab8[u0] : -1;
-        L1 = u1 >= 0 ? (int32_t)a.lab8[u1] : -1;
-        const int64_t cv = valid ? vweight(a.vwgt, v) : 0;
-        AccT bc = 0;
-        int32_t bl = INT_MAX;
-        for (int i = gl; i < KT; i += GL) {
-            const AccT c = val[i];
-            if (c > 0 && sW[i] + cv <= 0 && better(c, i, bc, bl)) {
-                bc = c;
-                bl = i;
+            for (int ch = 2; ch < maxch; ch += 2) {
+                const int32_t e0 = beg + ch * GL + gl, e1 = e0 + GL;
+                const int32_t x0 = e0 < end ? a.adjncy[e0] : -1, x1 = e1 < end ? a.adjncy[e1] : -1;
+                const AccT y0 = (e0 < end && a.adjwgt) ? (AccT)a.adjwgt[e0] : (AccT)1;
+                const AccT y1 = (e1 < end && a.adjwgt) ? (AccT)a.adjwgt[e1] : (AccT)1;
+                const int32_t M0 = x0 >= 0 ? (int32_t)a.lab8[x0] : -1, M1 = x1 >= 0 ? (int32_t)a.lab8[x1] : -1;
+                if (x0 >= 0) {
+                    if (M0 == own) oc += y0;
+                    else if (dir_ok(M0, own, dmode)) lds_add<AccT>(&val[M0], y0);
+                }
+                if (x1 >= 0) {
+                    if (M1 == own) oc += y1;
+                    else if (dir_ok(M1, own, dmode)) lds_add<AccT>(&val[M1], y1);
+                }
             }
+            // the next vertex's row, label and first two chunks
+            const int32_t nbeg = nv >= 0 ? a.xadj[nv] : 0;
+            const int32_t nend = nv >= 0 ? a.xadj[nv + 1] : 0;
+            const int32_t nown = nv >= 0 ? a.labels[nv] : -1;
+            u0 = nbeg + gl < nend ? a.adjncy[nbeg + gl] : -1;
+            u1 = nbeg + gl + GL < nend ? a.adjncy[nbeg + gl + GL] : -1;
+            w0 = (u0 >= 0 && a.adjwgt) ? (AccT)a.adjwgt[nbeg + gl] : (AccT)1;
+            w1 = (u1 >= 0 && a.adjwgt) ? (AccT)a.adjwgt[nbeg + gl + GL] : (AccT)1;
+            wave_sync();
+            oc = group_sum<GL>(oc);
+            L0 = u0 >= 0 ? (int32_t)a.lab8[u0] : -1;
+            L1 = u1 >= 0 ? (int32_t)a.lab8[u1] : -1;
+            const int64_t cv = v >= 0 ? vweight(a.vwgt, v) : 0;
+            AccT bc = 0;
+            int32_t bl = INT_MAX;
+            bool over = false;
+            for (int i = gl; i < KT; i += GL) {
+                const AccT c = val[i];
+                over |= c > oc;
+                if (c > 0 && sW[i] + cv <= 0 && better(c, i, bc, bl)) {
+                    bc = c;
+                    bl = i;
+                }
+            }
+            const uint64_t om = __ballot(over);
+            group_best<GL, AccT>(bc, bl);
+            if (v >= 0 && gl == 0) {
+                a.prop[v] = (bl != INT_MAX && bc > oc) ? bl : -1;
+                settle(a, v, bit, (om & gm) != 0);
+            }
+            wave_sync();
+            for (int i = gl; i < KT; i += GL) val[i] = 0;
+            wave_sync();
+            v = nv;
+            beg = nbeg;
+            end = nend;
+            own = nown;
         }
-        group_best<GL, AccT>(bc, bl);
-        if (valid && gl == 0) a.prop[v] = (bl != INT_MAX && bc > oc) ? bl : -1;
-        wave_sync();
-        for (int i = gl; i < KT; i += GL) val[i] = 0;
-        wave_sync();
-        valid = nvalid;
-        v = nv;
-        beg = nbeg;
-        end = nend;
-        own = nown;
     }
 }
 
@@ -1178,63 +1323,73 @@ __global__ __launch_bounds__(kPropBlock) void k_dense_group(LPArgs a, int32_t nl
 // the group's first E lanes by shuffles, the k label weights of the round
 // start in LDS, the rule of k_dense_group.
 template <int GL, int E, int KT, typename AccT>
-__global__ __launch_bounds__(kPropBlock) void k_dense_lanes(LPArgs a, int32_t nlabels, TierList lists, int tier) {
+__global__ __launch_bounds__(kPropBlock) void k_dense_lanes(LPArgs a, int32_t nlabels, TierList lists, int tier,
+                                                            int32_t span) {
     static_assert(E <= GL, "one entry per lane");
     if (*a.done) return;
     const int64_t t0 = lists.ts[tier];
     const int32_t count = (int32_t)(lists.ts[tier + 1] - t0);
     const int32_t *__restrict__ verts = lists.verts + t0;
     const int32_t dmode = cur_dirmode(a);
+    const uint8_t bit = round_bit(a);
     constexpr int GPW = kWave / GL;
     constexpr int NW = kPropBlock / kWave;
     __shared__ int64_t sW[KT];
+    __shared__ int32_t slive[NW][kSpanMax];
     for (int i = threadIdx.x; i < KT; i += kPropBlock) sW[i] = i < nlabels ? a.W[i] - capof(a, i) : (int64_t(1) << 62);
     __syncthreads();
     const int lane = lane_id(), w = threadIdx.x / kWave;
     const int gl = lane % GL, grp = lane / GL;
+    const uint64_t gm = group_mask<GL>();
     const unsigned b = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t stride = (int64_t)gridDim.x * NW * GPW;
-    int64_t wb = ((int64_t)b * NW + w) * GPW;
-    bool valid = wb + grp < count;
-    int32_t v = valid ? verts[wb + grp] : 0;
-    int32_t beg = valid ? a.xadj[v] : 0;
-    int32_t end = (valid && !inactive(a, v)) ? a.xadj[v + 1] : beg;
-    int32_t own = valid ? a.labels[v] : -1;
-    int32_t u = beg + gl < end ? a.adjncy[beg + gl] : -1;
-    AccT wt = (u >= 0 && a.adjwgt) ? (AccT)a.adjwgt[beg + gl] : (AccT)1;
-    int32_t L = u >= 0 ? (int32_t)a.lab8[u] : -1;
-    for (; wb < count; wb += stride) {
-        const int64_t nwb = wb + stride;
-        const bool nvalid = nwb + grp < count;
-        const int32_t nv = nvalid ? verts[nwb + grp] : 0;
-        const int32_t nbeg = nvalid ? a.xadj[nv] : 0;
-        const int32_t nend = (nvalid && !inactive(a, nv)) ? a.xadj[nv + 1] : nbeg;
-        const int32_t nown = nvalid ? a.labels[nv] : -1;
-        const int32_t nu = nbeg + gl < nend ? a.adjncy[nbeg + gl] : -1;
-        const AccT nwt = (nu >= 0 && a.adjwgt) ? (AccT)a.adjwgt[nbeg + gl] : (AccT)1;
-        AccT c = 0;
+    const int64_t stride = (int64_t)gridDim.x * NW * span;
+    for (int64_t wb = ((int64_t)b * NW + w) * span; wb < count; wb += stride) {
+        const int32_t nlive = wave_live(a, verts, wb, span, count, bit, slive[w]);
+        if (nlive == 0) continue;
+        int32_t v = grp < nlive ? slive[w][grp] : -1;
+        int32_t beg = v >= 0 ? a.xadj[v] : 0;
+        int32_t end = v >= 0 ? a.xadj[v + 1] : 0;
+        int32_t own = v >= 0 ? a.labels[v] : -1;
+        int32_t u = beg + gl < end ? a.adjncy[beg + gl] : -1;
+        AccT wt = (u >= 0 && a.adjwgt) ? (AccT)a.adjwgt[beg + gl] : (AccT)1;
+        int32_t L = u >= 0 ? (int32_t)a.lab8[u] : -1;
+        for (int32_t i0 = 0; i0 < nlive; i0 += GPW) {
+            const int32_t ni = i0 + GPW + grp;
+            const int32_t nv = ni < nlive ? slive[w][ni] : -1;
+            const int32_t nbeg = nv >= 0 ? a.xadj[nv] : 0;
+            const int32_t nend = nv >= 0 ? a.xadj[nv + 1] : 0;
+            const int32_t nown = nv >= 0 ? a.labels[nv] : -1;
+            const int32_t nu = nbeg + gl < nend ? a.adjncy[nbeg + gl] : -1;
+            const AccT nwt = (nu >= 0 && a.adjwgt) ? (AccT)a.adjwgt[nbeg + gl] : (AccT)1;
+            AccT c = 0;
 #pragma unroll
-        for (int d = 0; d < E; d++) {
-            const int32_t Ld = __shfl(L, d, GL);
-            const AccT wd = __shfl(wt, d, GL);
-            if (Ld == L) c += wd;
+            for (int d = 0; d < E; d++) {
+                const int32_t Ld = __shfl(L, d, GL);
+                const AccT wd = __shfl(wt, d, GL);
+                if (Ld == L) c += wd;
+            }
+            const AccT oc = group_sum<GL>((L >= 0 && L == own) ? wt : (AccT)0);
+            const int64_t cv = v >= 0 ? vweight(a.vwgt, v) : 0;
+            AccT bc = 0;
+            int32_t bl = INT_MAX;
+            const bool cand = L >= 0 && L != own && c > 0 && dir_ok(L, own, dmode);
+            if (cand && sW[L] + cv <= 0) {
+                bc = c;
+                bl = L;
+            }
+            const uint64_t om = __ballot(cand && c > oc);
+            group_best<GL, AccT>(bc, bl);
+            if (v >= 0 && gl == 0) {
+                a.prop[v] = (bl != INT_MAX && bc > oc) ? bl : -1;
+                settle(a, v, bit, (om & gm) != 0);
+            }
+            v = nv;
+            own = nown;
+            u = nu;
+            wt = nwt;
+            L = nu >= 0 ? (int32_t)a.lab8[nu] : -1;
         }
-        const AccT oc = group_sum<GL>((L >= 0 && L == own) ? wt : (AccT)0);
-        const int64_t cv = valid ? vweight(a.vwgt, v) : 0;
-        AccT bc = 0;
-        int32_t bl = INT_MAX;
-        if (L >= 0 && L != own && c > 0 && dir_ok(L, own, dmode) && sW[L] + cv <= 0) {
-            bc = c;
-            bl = L;
-        }
-        group_best<GL, AccT>(bc, bl);
-        if (valid && gl == 0) a.prop[v] = (bl != INT_MAX && bc > oc) ? bl : -1;
-        valid = nvalid;
-        v = nv;
-        own = nown;
-        u = nu;
-        wt = nwt;
-        L = nu >= 0 ? (int32_t)a.lab8[nu] : -1;
+        wave_sync();
     }
 }
 
@@ -1280,7 +1435,7 @@ __global__ __launch_bounds__(256) void k_dense_chunk(LPArgs a, DenseBig db) {
     // call), so the edge loads wait on one load, not on three dependent ones
     const int4 d = db.desc[blockIdx.x];
     const int32_t v = d.x, beg = d.y, b = d.w;
-    if (inactive(a, v)) return;  // uniform: the vertex's row stays zero
+    if (inactive(a, v, round_bit(a))) return;  // uniform: the vertex's row stays zero
     const int32_t end = d.z;
     const int32_t own = a.labels[v];
     AccT oc = 0;
@@ -1329,18 +1484,22 @@ __global__ __launch_bounds__(256) void k_dense_finish(LPArgs a, DenseBig db, int
     const int64_t oc = (int64_t)db.own[b];
     AccT bc = 0;
     int32_t bl = INT_MAX;
+    bool over = false;
     for (int i = lane; i < nlabels; i += kWave) {
         const AccT c = row[i];
+        over |= (int64_t)c > oc;
         if (c > 0 && a.W[i] + cv <= capof(a, i) && better(c, i, bc, bl)) {
             bc = c;
             bl = i;
         }
         row[i] = 0;
     }
+    over = __ballot(over) != 0;
     group_best<kWave, AccT>(bc, bl);
     if (lane == 0) {
         a.prop[v] = (bl != INT_MAX && (int64_t)bc > oc) ? bl : -1;
         db.own[b] = 0;
+        settle(a, v, round_bit(a), over);
     }
 }
 
@@ -1354,23 +1513,28 @@ int launch_dense(const LPArgs &a, int32_t nlabels, const int64_t *tstart, TierLi
     constexpr int NW = kPropBlock / kWave;
     constexpr int G1 = KT >= 256 ? 16 : 4;
     constexpr int G2 = KT >= 256 ? 16 : 8;
-    auto blocks_for = [&](int32_t c, int per_block) { return grid_for(c, per_block, 16384); };
+    // `groups` vertices of a wave at a time
+    int32_t span = 0;
+    auto blocks_for = [&](int32_t c, int groups) {
+        span = span_for(a, c, groups);
+        return grid_for(c, NW * span, 16384);
+    };
     int32_t c;
     if ((c = cnt(1)) > 0)
-        GP_PROF_LAUNCH((std::string("k_dense_lanes<") + std::to_string(G1) + sfx).c_str(), tb[1], s, hipLaunchKernelGGL((k_dense_lanes<G1, 4, KT, AccT>), dim3(blocks_for(c, NW * (kWave / G1))), dim3(kPropBlock), 0,
-                           s, a, nlabels, tl, 1));
+        GP_PROF_LAUNCH((std::string("k_dense_lanes<") + std::to_string(G1) + sfx).c_str(), tb[1], s, hipLaunchKernelGGL((k_dense_lanes<G1, 4, KT, AccT>), dim3(blocks_for(c, kWave / G1)), dim3(kPropBlock), 0,
+                           s, a, nlabels, tl, 1, span));
     if ((c = cnt(2)) > 0)
-        GP_PROF_LAUNCH((std::string("k_dense_lanes<") + std::to_string(G2) + sfx).c_str(), tb[2], s, hipLaunchKernelGGL((k_dense_lanes<G2, 8, KT, AccT>), dim3(blocks_for(c, NW * (kWave / G2))), dim3(kPropBlock), 0,
-                           s, a, nlabels, tl, 2));
+        GP_PROF_LAUNCH((std::string("k_dense_lanes<") + std::to_string(G2) + sfx).c_str(), tb[2], s, hipLaunchKernelGGL((k_dense_lanes<G2, 8, KT, AccT>), dim3(blocks_for(c, kWave / G2)), dim3(kPropBlock), 0,
+                           s, a, nlabels, tl, 2, span));
     if ((c = cnt(3)) > 0)
-        GP_PROF_LAUNCH((std::string("k_dense_group<16") + sfx).c_str(), tb[3], s, hipLaunchKernelGGL((k_dense_group<16, KT, AccT>), dim3(blocks_for(c, NW * 4)), dim3(kPropBlock), 0, s, a,
-                           nlabels, tl, 3));
+        GP_PROF_LAUNCH((std::string("k_dense_group<16") + sfx).c_str(), tb[3], s, hipLaunchKernelGGL((k_dense_group<16, KT, AccT>), dim3(blocks_for(c, 4)), dim3(kPropBlock), 0, s, a,
+                           nlabels, tl, 3, span));
     if ((c = cnt(4)) > 0)
-        GP_PROF_LAUNCH((std::string("k_dense_group<32") + sfx).c_str(), tb[4], s, hipLaunchKernelGGL((k_dense_group<32, KT, AccT>), dim3(blocks_for(c, NW * 2)), dim3(kPropBlock), 0, s, a,
-                           nlabels, tl, 4));
+        GP_PROF_LAUNCH((std::string("k_dense_group<32") + sfx).c_str(), tb[4], s, hipLaunchKernelGGL((k_dense_group<32, KT, AccT>), dim3(blocks_for(c, 2)), dim3(kPropBlock), 0, s, a,
+                           nlabels, tl, 4, span));
     if ((c = cnt(5)) > 0)
-        GP_PROF_LAUNCH((std::string("k_dense_group<64") + sfx).c_str(), tb[5], s, hipLaunchKernelGGL((k_dense_group<64, KT, AccT>), dim3(blocks_for(c, NW)), dim3(kPropBlock), 0, s, a, nlabels,
-                           tl, 5));
+        GP_PROF_LAUNCH((std::string("k_dense_group<64") + sfx).c_str(), tb[5], s, hipLaunchKernelGGL((k_dense_group<64, KT, AccT>), dim3(blocks_for(c, 1)), dim3(kPropBlock), 0, s, a, nlabels,
+                           tl, 5, span));
     if (db && db->nbig > 0) {
         GP_PROF_LAUNCH((std::string("k_dense_chunk<") + std::to_string(KT) + sfx.substr(std::to_string(KT).size() + 2)).c_str(), tb[6] + tb[7] + tb[8] + tb[9] + tb[10], s, hipLaunchKernelGGL((k_dense_chunk<KT, AccT>), dim3(nchunks), dim3(256), 0, s, a, *db));
         hipLaunchKernelGGL((k_dense_finish<KT, AccT>), dim3((db->nbig + 3) / 4), dim3(256), 0, s, a, *db, nlabels);
@@ -1497,7 +1661,8 @@ __device__ __forceinline__ void load4<int64_t>(const int64_t *p, int64_t (&c)[4]
 template <int KT, typename AccT>
 __global__ __launch_bounds__(kPropBlock) void k_dense_rows(LPArgs a, int32_t nlabels, TierList lists, int tfirst,
                                                            int tend, const AccT *__restrict__ rows,
-                                                           const int32_t *__restrict__ rowidx, int32_t *nbig) {
+                                                           const int32_t *__restrict__ rowidx, int32_t *nbig,
+                                                           int32_t span) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *nbig = 0;
     if (*a.done) return;
     constexpr int GL = KT / 4;
@@ -1505,52 +1670,64 @@ __global__ __launch_bounds__(kPropBlock) void k_dense_rows(LPArgs a, int32_t nla
     constexpr int NW = kPropBlock / kWave;
     constexpr int UV = 4;
     __shared__ int64_t sW[KT];
+    __shared__ int32_t slive[NW][kSpanMax];
+    __shared__ uint8_t soff[NW][kSpanMax];
     for (int i = threadIdx.x; i < KT; i += kPropBlock) sW[i] = i < nlabels ? a.W[i] - capof(a, i) : (int64_t(1) << 62);
     __syncthreads();
     const int64_t t0 = lists.ts[tfirst];
     const int64_t count = lists.ts[tend] - t0;
     const int32_t dmode = cur_dirmode(a);
+    const uint8_t bit = round_bit(a);
     const int lane = lane_id(), gl = lane % GL, grp = lane / GL, w = threadIdx.x / kWave;
-    const int64_t stride = (int64_t)gridDim.x * NW * GPW;
-    for (int64_t base = ((int64_t)xcd_block(blockIdx.x, gridDim.x) * NW + w) * GPW + grp; base - grp < count;
-         base += UV * stride) {
-        int32_t v[UV], own[UV];
-        bool valid[UV], live[UV];
-        AccT c[UV][4];
+    const uint64_t gm = group_mask<GL>();
+    const int64_t stride = (int64_t)gridDim.x * NW * span;
+    for (int64_t wb = ((int64_t)xcd_block(blockIdx.x, gridDim.x) * NW + w) * span; wb < count; wb += stride) {
+        const int32_t nlive = wave_live(a, lists.verts + t0, wb, span, count, bit, slive[w], soff[w]);
+        for (int32_t i0 = 0; i0 < nlive; i0 += UV * GPW) {
+            int32_t v[UV], own[UV];
+            AccT c[UV][4];
 #pragma unroll
-        for (int u = 0; u < UV; u++) {
-            const int64_t j = base + u * stride;
-            valid[u] = j < count;
-            v[u] = valid[u] ? lists.verts[t0 + j] : 0;
-            if (!rowidx && valid[u]) load4<AccT>(rows + j * KT + 4 * gl, c[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < UV; u++) {
-            live[u] = valid[u] && !inactive(a, v[u]);
-            own[u] = live[u] ? a.labels[v[u]] : -1;
-            if (rowidx && valid[u]) load4<AccT>(rows + (int64_t)rowidx[v[u]] * KT + 4 * gl, c[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < UV; u++) {
-            const int64_t cv = live[u] ? vweight(a.vwgt, v[u]) : 0;
-            AccT oc = 0, bc = 0;
-            int32_t bl = INT_MAX;
-            if (live[u]) {
-#pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    const int32_t i = 4 * gl + q;
-                    const AccT x = c[u][q];
-                    if (i == own[u]) oc = x;
-                    else if (x > 0 && dir_ok(i, own[u], dmode) && sW[i] + cv <= 0 && better(x, i, bc, bl)) {
-                        bc = x;
-                        bl = i;
-                    }
+            for (int u = 0; u < UV; u++) {
+                const int32_t i = i0 + u * GPW + grp;
+                v[u] = i < nlive ? slive[w][i] : -1;
+                if (v[u] >= 0) {
+                    const int64_t row = rowidx ? (int64_t)rowidx[v[u]] : wb + soff[w][i];
+                    load4<AccT>(rows + row * KT + 4 * gl, c[u]);
                 }
             }
-            oc = group_sum<GL>(oc);
-            group_best<GL, AccT>(bc, bl);
-            if (valid[u] && gl == 0) a.prop[v[u]] = (bl != INT_MAX && bc > oc) ? bl : -1;
+#pragma unroll
+            for (int u = 0; u < UV; u++) own[u] = v[u] >= 0 ? a.labels[v[u]] : -1;
+#pragma unroll
+            for (int u = 0; u < UV; u++) {
+                if (i0 + u * GPW >= nlive) break;  // wave-uniform
+                const int64_t cv = v[u] >= 0 ? vweight(a.vwgt, v[u]) : 0;
+                AccT oc = 0, bc = 0, uc = 0;  // uc: largest sum in the round's direction, room or not
+                int32_t bl = INT_MAX;
+                if (v[u] >= 0) {
+#pragma unroll
+                    for (int q = 0; q < 4; q++) {
+                        const int32_t i = 4 * gl + q;
+                        const AccT x = c[u][q];
+                        if (i == own[u]) oc = x;
+                        else if (x > 0 && dir_ok(i, own[u], dmode)) {
+                            uc = x > uc ? x : uc;
+                            if (sW[i] + cv <= 0 && better(x, i, bc, bl)) {
+                                bc = x;
+                                bl = i;
+                            }
+                        }
+                    }
+                }
+                oc = group_sum<GL>(oc);
+                const uint64_t om = __ballot(uc > oc);
+                group_best<GL, AccT>(bc, bl);
+                if (v[u] >= 0 && gl == 0) {
+                    a.prop[v[u]] = (bl != INT_MAX && bc > oc) ? bl : -1;
+                    settle(a, v[u], bit, (om & gm) != 0);
+                }
+            }
         }
+        wave_sync();
     }
 }
 
@@ -1589,7 +1766,10 @@ __global__ __launch_bounds__(256) void k_rows_update(AdmitCtx c, const int32_t *
         if (from < 0) continue;  // refused by the admission
         const int32_t u = mv[p], to = c.labels[u];
         const int32_t e0 = xadj[u], e1 = xadj[u + 1];
-        if (gl == 0) sum += e1 - e0;
+        if (gl == 0) {
+            sum += e1 - e0;
+            if (c.todo) c.todo[u] = kTodoBoth;
+        }
         if (e1 - e0 > kRowSplit) {
             if (gl == 0) {
                 const int32_t nc = (e1 - e0 + kRowChunk - 1) / kRowChunk;
@@ -1599,7 +1779,8 @@ __global__ __launch_bounds__(256) void k_rows_update(AdmitCtx c, const int32_t *
             continue;
         }
         for (int32_t e = e0 + gl; e < e1; e += GL) {
-            const int32_t r = rowidx[adjncy[e]];
+            const int32_t x = adjncy[e], r = rowidx[x];
+            if (c.todo) c.todo[x] = kTodoBoth;
             if (r >= 0) row_move<AccT>(rows, KT, r, from, to, adjwgt ? (AccT)adjwgt[e] : (AccT)1);
         }
     }
@@ -1612,13 +1793,15 @@ __global__ __launch_bounds__(256) void k_rows_update_big(const int4 *big, const 
                                                          const int32_t *__restrict__ xadj,
                                                          const int32_t *__restrict__ adjncy,
                                                          const int32_t *__restrict__ adjwgt,
-                                                         const int32_t *__restrict__ rowidx, AccT *rows) {
+                                                         const int32_t *__restrict__ rowidx, AccT *rows,
+                                                         uint8_t *todo) {
     const int32_t nb = *nbig;
     for (int64_t i = blockIdx.x; i < nb; i += gridDim.x) {
         const int4 c = big[i];
         const int32_t e1 = min(xadj[c.x + 1], c.y + kRowChunk);
         for (int32_t e = c.y + threadIdx.x; e < e1; e += 256) {
-            const int32_t r = rowidx[adjncy[e]];
+            const int32_t x = adjncy[e], r = rowidx[x];
+            if (todo) todo[x] = kTodoBoth;
             if (r >= 0) row_move<AccT>(rows, KT, r, c.z, c.w, adjwgt ? (AccT)adjwgt[e] : (AccT)1);
         }
     }
@@ -1663,9 +1846,9 @@ int rows_fill(const RowTables &rt, const int32_t *xadj, const int32_t *adjncy, c
 template <int KT, typename AccT>
 int rows_select(const LPArgs &a, int32_t nlabels, TierList tl, const RowTables &rt, int tend, bool active,
                 hipStream_t s) {
-    constexpr int per_block = (kPropBlock / kWave) * (kWave / (KT / 4)) * 4;
+    const int32_t span = span_for(a, rt.nt, (kWave / (KT / 4)) * 4);
     const std::string name = std::string("k_dense_rows<") + std::to_string(KT) + (sizeof(AccT) == 4 ? ", int>" : ", long>");
-    GP_PROF_LAUNCH(name.c_str(), rt.sel_bytes, s, hipLaunchKernelGGL((k_dense_rows<KT, AccT>), dim3(grid_for(rt.nt, per_block, 16384)), dim3(kPropBlock), 0, s, a, nlabels, tl, rt.tfirst, tend, (const AccT *)rt.rows, active ? rt.rowidx : nullptr, rt.nbig));
+    GP_PROF_LAUNCH(name.c_str(), rt.sel_bytes, s, hipLaunchKernelGGL((k_dense_rows<KT, AccT>), dim3(grid_for(rt.nt, (kPropBlock / kWave) * span, 16384)), dim3(kPropBlock), 0, s, a, nlabels, tl, rt.tfirst, tend, (const AccT *)rt.rows, active ? rt.rowidx : nullptr, rt.nbig, span));
     GP_LAUNCH_CHECK();
     return GP_OK;
 }
@@ -1676,7 +1859,7 @@ int rows_update(const RowTables &rt, const AdmitCtx &ac, const int32_t *xadj, co
     hipLaunchKernelGGL((k_rows_update<KT, AccT>), dim3(ac.ntiles * rt.parts), dim3(256), 0, s, ac, xadj, adjncy,
                        adjwgt, rt.rowidx, (AccT *)rt.rows, rt.big, rt.nbig, rt.pushed, rt.parts);
     hipLaunchKernelGGL((k_rows_update_big<KT, AccT>), dim3(grid_for(nnz / kRowChunk + 1, 1, 4096)), dim3(256), 0, s,
-                       rt.big, rt.nbig, xadj, adjncy, adjwgt, rt.rowidx, (AccT *)rt.rows);
+                       rt.big, rt.nbig, xadj, adjncy, adjwgt, rt.rowidx, (AccT *)rt.rows, ac.todo);
     GP_LAUNCH_CHECK();
     return GP_OK;
 }
@@ -2090,6 +2273,39 @@ __global__ __launch_bounds__(256) void k_act_mark(AdmitCtx c, const int32_t *xad
     }
 }
 
+// The neighbours of an admitted mover, and the mover, are not settled any
+// more. kMarkParts workgroups share a tile's movers: each takes every
+// kMarkParts-th one, 16 lanes per mover, and its share of the entries of the
+// movers above kMarkSplit neighbours.
+constexpr int kMarkParts = 4;
+__global__ __launch_bounds__(256) void k_todo_mark(AdmitCtx c, const int32_t *xadj, const int32_t *adjncy) {
+    constexpr int GL = 16, NG = 256 / GL;
+    __shared__ int32_t beg[256], end[256];
+    if (c.dev->done) return;
+    const int32_t tile = blockIdx.x / kMarkParts, part = blockIdx.x % kMarkParts;
+    const int32_t n = c.tcnt[tile];
+    const int32_t *mv = c.mv + (int64_t)tile * c.tile, *old = c.old + (int64_t)tile * c.tile;
+    const int gl = threadIdx.x % GL, grp = threadIdx.x / GL;
+    for (int32_t p0 = 0; p0 < n; p0 += 256) {
+        const int32_t p = p0 + threadIdx.x;
+        const int32_t v = p < n && old[p] >= 0 ? mv[p] : -1;
+        const int32_t b = v >= 0 ? xadj[v] : 0, e = v >= 0 ? xadj[v + 1] : 0;
+        beg[threadIdx.x] = b;
+        end[threadIdx.x] = e;
+        if (v >= 0 && part == 0) c.todo[v] = kTodoBoth;
+        const bool anybig = __syncthreads_or(e - b > kMarkSplit);
+        for (int32_t i = part + kMarkParts * grp; i < 256; i += kMarkParts * NG)
+            if (end[i] - beg[i] <= kMarkSplit)
+                for (int32_t x = beg[i] + gl; x < end[i]; x += GL) c.todo[adjncy[x]] = kTodoBoth;
+        if (anybig)
+            for (int32_t i = 0; i < 256; i++)
+                if (end[i] - beg[i] > kMarkSplit)
+                    for (int32_t x = beg[i] + part * 256 + threadIdx.x; x < end[i]; x += kMarkParts * 256)
+                        c.todo[adjncy[x]] = kTodoBoth;
+        __syncthreads();
+    }
+}
+
 __global__ __launch_bounds__(256) void k_act_mark_big(const int2 *big, const int32_t *nbig, const int32_t *xadj,
                                                       const int32_t *adjncy, uint8_t *act, uint8_t renew) {
     const int32_t nb = *nbig;
@@ -2257,33 +2473,36 @@ int launch_proposals(const LPArgs &a, const int32_t *verts, const int64_t *tstar
     auto lst = [&](int t) { return verts + tstart[t]; };
     constexpr int NW = kPropBlock / kWave;
     // blocks: enough waves to cover the tier, capped so each block loops a few times
-    auto blocks_for = [&](int32_t c, int per_block) { return grid_for(c, per_block, 16384); };
+    // (`groups` vertices of a wave at a time)
+    int32_t span = 0;
+    auto blocks_for = [&](int32_t c, int groups) {
+        span = span_for(a, c, groups);
+        return grid_for(c, NW * span, 16384);
+    };
     int32_t c;
-    if ((c = cnt(1)) > 0) {
-        if constexpr (sizeof(AccT) == 4) GP_PROF_LAUNCH("k_plane<4, int>", tb[1], s, hipLaunchKernelGGL((k_plane<4, 4>), dim3(blocks_for(c, NW * 16)), dim3(kPropBlock), 0, s,
-                           a, tl, 1)); else GP_PROF_LAUNCH((std::string("k_propose_group<4, 8, ") + acc + ">").c_str(), tb[1], s, hipLaunchKernelGGL((k_propose_group<4, 8, AccT>), dim3(blocks_for(c, NW * 16)), dim3(kPropBlock), 0, s,
-                           a, tl, 1));
+    // tier t: GL lanes per vertex, a table of TBL slots (the lowest two tiers sum by shuffles with 32-bit sums)
+#define GP_LANES(t, GL, TBL, NARROW, NAME)                                                                              \
+    if ((c = cnt(t)) > 0) {                                                                                             \
+        const dim3 grid(blocks_for(c, kWave / GL)), block(kPropBlock);                                                  \
+        const std::string wname = "k_propose_group<" #GL ", " #TBL ", " + std::string(acc) + ">";                       \
+        const char *name = sizeof(AccT) == 4 ? NAME : wname.c_str();                                                    \
+        if constexpr (sizeof(AccT) == 4) {                                                                              \
+            if (skip) GP_PROF_LAUNCH(name, tb[t], s, hipLaunchKernelGGL((NARROW, true>), grid, block, 0, s, a, tl, t, span));  \
+            else GP_PROF_LAUNCH(name, tb[t], s, hipLaunchKernelGGL((NARROW, false>), grid, block, 0, s, a, tl, t, span));      \
+        } else {                                                                                                        \
+            if (skip) GP_PROF_LAUNCH(name, tb[t], s, hipLaunchKernelGGL((k_propose_group<GL, TBL, AccT, true>), grid, block, 0, s, a, tl, t, span));  \
+            else GP_PROF_LAUNCH(name, tb[t], s, hipLaunchKernelGGL((k_propose_group<GL, TBL, AccT, false>), grid, block, 0, s, a, tl, t, span));      \
+        }                                                                                                               \
     }
-    if ((c = cnt(2)) > 0) {
-        if constexpr (sizeof(AccT) == 4) GP_PROF_LAUNCH("k_plane<8, int>", tb[2], s, hipLaunchKernelGGL((k_plane<8, 8>), dim3(blocks_for(c, NW * 8)), dim3(kPropBlock), 0, s,
-                           a, tl, 2)); else GP_PROF_LAUNCH((std::string("k_propose_group<8, 16, ") + acc + ">").c_str(), tb[2], s, hipLaunchKernelGGL((k_propose_group<8, 16, AccT>), dim3(blocks_for(c, NW * 8)), dim3(kPropBlock), 0, s,
-                           a, tl, 2));
-    }
-    if ((c = cnt(3)) > 0) {
-        if constexpr (sizeof(AccT) == 4) GP_PROF_LAUNCH((std::string("k_pgroup<16, 32, ") + acc + ">").c_str(), tb[3], s, hipLaunchKernelGGL((k_pgroup<16, 32>), dim3(blocks_for(c, NW * 4)), dim3(kPropBlock), 0,
-                           s, a, tl, 3)); else GP_PROF_LAUNCH((std::string("k_propose_group<16, 32, ") + acc + ">").c_str(), tb[3], s, hipLaunchKernelGGL((k_propose_group<16, 32, AccT>), dim3(blocks_for(c, NW * 4)), dim3(kPropBlock), 0,
-                           s, a, tl, 3));
-    }
-    if ((c = cnt(4)) > 0) {
-        if constexpr (sizeof(AccT) == 4) GP_PROF_LAUNCH((std::string("k_pgroup<32, 128, ") + acc + ">").c_str(), tb[4], s, hipLaunchKernelGGL((k_pgroup<32, 128>), dim3(blocks_for(c, NW * 2)), dim3(kPropBlock), 0,
-                           s, a, tl, 4)); else GP_PROF_LAUNCH((std::string("k_propose_group<32, 128, ") + acc + ">").c_str(), tb[4], s, hipLaunchKernelGGL((k_propose_group<32, 128, AccT>), dim3(blocks_for(c, NW * 2)), dim3(kPropBlock), 0,
-                           s, a, tl, 4));
-    }
-    if ((c = cnt(5)) > 0) {
-        if constexpr (sizeof(AccT) == 4) GP_PROF_LAUNCH((std::string("k_pgroup<64, 512, ") + acc + ">").c_str(), tb[5], s, hipLaunchKernelGGL((k_pgroup<64, 512>), dim3(blocks_for(c, NW)), dim3(kPropBlock), 0, s,
-                           a, tl, 5)); else GP_PROF_LAUNCH((std::string("k_propose_group<64, 512, ") + acc + ">").c_str(), tb[5], s, hipLaunchKernelGGL((k_propose_group<64, 512, AccT>), dim3(blocks_for(c, NW)), dim3(kPropBlock), 0, s,
-                           a, tl, 5));
-    }
+    const bool skip = may_skip(a);
+#define GP_C ,
+    GP_LANES(1, 4, 8, k_plane<4 GP_C 4, "k_plane<4, int>")
+    GP_LANES(2, 8, 16, k_plane<8 GP_C 8, "k_plane<8, int>")
+    GP_LANES(3, 16, 32, k_pgroup<16 GP_C 32, "k_pgroup<16, 32, int>")
+    GP_LANES(4, 32, 128, k_pgroup<32 GP_C 128, "k_pgroup<32, 128, int>")
+    GP_LANES(5, 64, 512, k_pgroup<64 GP_C 512, "k_pgroup<64, 512, int>")
+#undef GP_C
+#undef GP_LANES
     if ((c = cnt(6)) > 0) {
         if constexpr (sizeof(AccT) == 4) GP_PROF_LAUNCH((std::string("k_pblock<128, 2048, ") + acc + ">").c_str(), tb[6], s, hipLaunchKernelGGL((k_pblock<128, 2048>), dim3(grid_for(c, 1, 16384)), dim3(128), 0, s, a,
                            tl, 6)); else GP_PROF_LAUNCH((std::string("k_propose_block<128, 2048, ") + acc + ">").c_str(), tb[6], s, hipLaunchKernelGGL((k_propose_block<128, 2048, AccT>), dim3(grid_for(c, 1, 16384)), dim3(128), 0, s, a,
@@ -2740,6 +2959,14 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         GP_LAUNCH_CHECK();
     }
 
+    // settled vertices are skipped in refinement (labels are blocks of at least
+    // four vertices on average) where the round tail leaves lists of the movers;
+    // in clustering most vertices neighbour a mover in every round
+    if (!fuse_rest && !act && (int64_t)nlabels * 4 <= n) {
+        GP_TRY(sc.alloc(&ac.todo, n));
+        GP_HIP(hipMemsetAsync(ac.todo, kTodoBoth, (size_t)n, s));
+    }
+
     // ---- dense mode: connection rows of the vertices above KT/8 neighbours
     // (the plain rounds keep gathering for the others). Not for the levels
     // whose round tail runs in one workgroup, nor in a caller's workspace or
@@ -2816,6 +3043,7 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         a.capv = capv;
         a.lab8 = lab8;
         a.act = act;
+        a.todo = ac.todo;
         a.group = group;
         a.gs = gstate;
         if (act && afirst < n) {
@@ -2881,6 +3109,10 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
             hipLaunchKernelGGL(k_act_mark, dim3(ac.ntiles), dim3(256), 0, s, ac, g.xadj, g.adjncy, renew, mbig, nmbig);
             hipLaunchKernelGGL(k_act_mark_big, dim3(grid_for(g.nnz / kMarkChunk + 1, 1, 4096)), dim3(256), 0, s, mbig,
                                nmbig, g.xadj, g.adjncy, act, renew);
+            GP_LAUNCH_CHECK();
+        }
+        if (ac.todo && !rt.rows) {  // (the rows' update marks what it visits)
+            hipLaunchKernelGGL(k_todo_mark, dim3(ac.ntiles * kMarkParts), dim3(256), 0, s, ac, g.xadj, g.adjncy);
             GP_LAUNCH_CHECK();
         }
         if (rt.rows) {

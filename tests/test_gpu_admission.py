@@ -79,3 +79,28 @@ def test_refine_admission(n, k, weighted):
             got, st = call(gp.to_device(g), torch.from_numpy(part).cuda(), k, lm, 8)
             assert np.array_equal(got.cpu().numpy(), want)
             assert (st["rounds_run"], st["moves"]) == (ost["rounds_run"], ost["moves"])
+
+
+@pytest.mark.parametrize("k", [5, 64, 300])
+@pytest.mark.parametrize("alternate", [1, 0])
+def test_settled_vertices_on_hub_graphs(k, alternate):
+    # vertices without a better block are not evaluated again until a neighbour moves; here hubs far
+    # above 256 neighbours move too (tight and loose bounds, with connection rows and without)
+    import torch
+    import paper_1710_08231_amd as gp
+    g = graphgen.rmat(15, 8)
+    n = len(g["xadj"]) - 1
+    rng = np.random.default_rng(k)
+    part = rng.integers(0, k, n).astype(np.int32)
+    B = np.bincount(part, minlength=k).astype(np.int64)
+    for lm in (int(B.max()), 2 * n):
+        P, W, moves, idle, r = part.copy(), B.copy(), 0, 0, 0
+        while r < 25 and idle < 2:
+            P, W, m, _ = oracle.lp_round(g, P, W, lm, r, alternate)
+            idle = idle + 1 if m == 0 else 0
+            moves += m
+            r += 1
+        for call in (gp.lp_refine, gp.lp_refine_static):
+            got, st = call(gp.to_device(g), torch.from_numpy(part).cuda(), k, lm, 25, dir_alternate=alternate)
+            assert np.array_equal(got.cpu().numpy(), P)
+            assert (st["rounds_run"], st["moves"]) == (r, moves)
