@@ -18,7 +18,9 @@
 //   h_l   = ReLU(b_l + Ws_l h_{l-1}[v] + Wn_l m_l[v]),  m_l[v] = (sum_u w(v,u) h_{l-1}[u]) / d(v)
 //   z[v]  = bh + Wh h_3[v];  block(v) = argmax z[v] (ties -> lowest)
 // d(v) is the weighted degree; a vertex without neighbours keeps y and gets m = 0.
+#include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <utility>
 
 #include "mpnn.hpp"
@@ -54,105 +56,261 @@ __global__ void k_bf16(const float *__restrict__ in, float *__restrict__ out, in
     }
 }
 
-// 1/d(v) (binary64 reciprocal rounded once) and the maxima of c and deg.
-__global__ void k_vstats(int32_t n, const int32_t *__restrict__ xadj, const int32_t *__restrict__ adjwgt,
-                         const int32_t *__restrict__ vwgt, bool active_only, float *__restrict__ rinv,
-                         int32_t *__restrict__ mx) {
+// Aggregation over neighbours, acc <- fma(w(v,u), X[u][c], acc) over the CSR
+// row in order: one chain per (row, column), so a row's time is bound by its
+// degree times the latency of a fused multiply-add, as long as its operands are
+// there. Rows up to kWideRow entries: a lane per column (16, 32 or 64 lanes per
+// row) that gets the neighbours' ids from its row's lanes, loaded together, and
+// requests 16 neighbours' values at once. Wider rows: a workgroup per row and
+// slice of kSlice columns; four waves fetch the next kStage neighbours' slices
+// and stage them in LDS while kSlice lanes of the fifth run their chains over
+// those staged before. At 50,000 vertices and 3M entries (the widest row has
+// 12,600) a walk step took 1.29 ms with a thread per (row, column) that loaded
+// id and value one after the other and staging without overlap, and takes 0.09
+// ms so, 17 cycles per step of the widest row. Rows of 97 to 192 entries cost
+// less in lanes (a walk step 96 -> 91 us, a 64-column layer 335 -> 258 us),
+// wider ones less staged (122 us with lanes up to 512).
+constexpr int kWideRow = 192;
+constexpr int kSlice = 16;
+constexpr int kStage = 256;
+constexpr int kGatherBlock = kWave + kStage;  // one wave for the chains, the others fetch and stage
+constexpr int kStagePitch = kStage + 4;  // a lane's four values lie in banks of their own
+
+struct WideFlag {
+    const int32_t *xadj;
+    __device__ bool operator()(int64_t v) const { return xadj[v + 1] - xadj[v] > kWideRow; }
+};
+struct WideEmit {
+    int32_t *wide;
+    __device__ void operator()(int64_t v, int32_t pos) const { wide[pos] = (int32_t)v; }
+};
+
+// 1/d(v) (binary64 reciprocal rounded once) and the maxima of c and deg. A
+// workgroup per wide row (the first `wblocks` of them), 16 lanes per other row:
+// a lane per row walked a hub's weights alone (1.34 ms at 50,000 vertices and
+// 3.3M entries). Bound: one read of the weights.
+__global__ __launch_bounds__(kMB) void k_vstats(int32_t n, const int32_t *__restrict__ wide,
+                                                const int32_t *__restrict__ nwide, int32_t wblocks,
+                                                const int32_t *__restrict__ xadj,
+                                                const int32_t *__restrict__ adjwgt, const int32_t *__restrict__ vwgt,
+                                                bool active_only, float *__restrict__ rinv, int32_t *__restrict__ mx) {
+    __shared__ int32_t tmp[kMB / kWave + 1];
+    __shared__ int64_t t64[kMB / kWave + 1];
+    constexpr int GL = 16;
     int32_t cm = 0, dm = 0;
-    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
-        const int32_t b = xadj[v], e = xadj[v + 1];
-        int64_t s = e - b;
-        if (adjwgt) {
-            s = 0;
-            for (int32_t i = b; i < e; i++) s += adjwgt[i];
-        }
-        rinv[v] = s > 0 ? (float)(1.0 / (double)s) : 0.0f;
-        if (!active_only || e > b) {
+    if ((int32_t)blockIdx.x < wblocks) {
+        const int32_t m = *nwide;
+        for (int32_t r = blockIdx.x; r < m; r += wblocks) {
+            const int32_t v = wide[r], b = xadj[v], e = xadj[v + 1];
+            int64_t s = 0;
+            if (adjwgt) {
+                for (int32_t i0 = b + threadIdx.x; i0 < e; i0 += 4 * kMB) {
+                    int32_t x[4];
+#pragma unroll
+                    for (int j = 0; j < 4; j++) x[j] = i0 + j * kMB < e ? adjwgt[i0 + j * kMB] : 0;
+                    s += (int64_t)x[0] + x[1] + x[2] + x[3];
+                }
+                s = block_sum<kMB>(s, t64);
+            } else {
+                s = e - b;
+            }
+            if (threadIdx.x == 0) rinv[v] = (float)(1.0 / (double)s);
             cm = max(cm, vwgt ? vwgt[v] : 1);
             dm = max(dm, e - b);
         }
-    }
-    cm = wave_max(cm);
-    dm = wave_max(dm);
-    if (lane_id() == 0) {
-        atomicMax(&mx[0], cm);
-        atomicMax(&mx[1], dm);
-    }
-}
-
-// acc <- fma(w(v,u), X[u][c], acc) over the CSR row [b, e) in order. The
-// loads of kUnroll neighbours are issued before their (sequential) FMAs, so a
-// high-degree row waits on memory once per group instead of once per edge.
-constexpr int kUnroll = 16;
-__device__ __forceinline__ float row_fma(int32_t b, int32_t e, const int32_t *__restrict__ adjncy,
-                                         const int32_t *__restrict__ adjwgt, const float *__restrict__ X,
-                                         int32_t stride, int32_t c, float acc) {
-    int32_t q = b;
-    for (; q + kUnroll <= e; q += kUnroll) {
-        float wv[kUnroll], xv[kUnroll];
+    } else {
+        const int gl = threadIdx.x % GL;
+        for (int32_t v0 = (blockIdx.x - wblocks) * (kMB / GL); v0 < n; v0 += (gridDim.x - wblocks) * (kMB / GL)) {
+            const int32_t v = v0 + threadIdx.x / GL;
+            const int32_t b = v < n ? xadj[v] : 0, e = v < n ? xadj[v + 1] : 0;
+            if (v >= n || e - b > kWideRow) continue;
+            const int32_t s = e - b;
+            if (adjwgt) {  // each weight fits 31 bits, their sum may not
+                int64_t t = 0;
+                for (int32_t i = b + gl; i < e; i += GL) t += adjwgt[i];
 #pragma unroll
-        for (int j = 0; j < kUnroll; j++) {
-            wv[j] = adjwgt ? (float)adjwgt[q + j] : 1.0f;
-            xv[j] = X[(int64_t)adjncy[q + j] * stride + c];
+                for (int d = GL / 2; d > 0; d >>= 1) t += __shfl_xor(t, d, GL);
+                if (gl == 0) rinv[v] = t > 0 ? (float)(1.0 / (double)t) : 0.0f;
+            } else if (gl == 0) {
+                rinv[v] = s > 0 ? (float)(1.0 / (double)s) : 0.0f;
+            }
+            if (!active_only || e > b) {
+                cm = max(cm, vwgt ? vwgt[v] : 1);
+                dm = max(dm, e - b);
+            }
         }
-#pragma unroll
-        for (int j = 0; j < kUnroll; j++) acc = __builtin_fmaf(wv[j], xv[j], acc);
     }
-    for (; q < e; q++) acc = __builtin_fmaf(adjwgt ? (float)adjwgt[q] : 1.0f, X[(int64_t)adjncy[q] * stride + c], acc);
-    return acc;
+    cm = block_max<kMB>(cm, tmp);
+    dm = block_max<kMB>(dm, tmp);
+    if (threadIdx.x == 0) {
+        if (cm > __hip_atomic_load(&mx[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&mx[0], cm);
+        if (dm > __hip_atomic_load(&mx[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&mx[1], dm);
+    }
 }
 
-// Rows above kBigRow entries: one workgroup per row. The workgroup stages a
-// chunk of neighbours' values in LDS and the first `cols` threads run the same
-// sequential FMA chains as row_fma, fed from LDS, chunk after chunk; a
-// lane-per-output thread would otherwise wait on memory for the whole row.
-constexpr int kBigRow = 2048;
-constexpr int kBigStage = 16384;  // staged floats per chunk (64 KB)
-
-struct BigFlag {
-    const int32_t *xadj;
-    __device__ bool operator()(int64_t v) const { return xadj[v + 1] - xadj[v] > kBigRow; }
-};
-struct BigEmit {
-    int32_t *big;
-    __device__ void operator()(int64_t v, int32_t pos) const { big[pos] = (int32_t)v; }
-};
-
-// WALK: out[v][c] = (X[v][c] + acc * rinv[v]) / 2, else out[v][c] = acc * rinv[v]
-template <bool WALK>
-__global__ __launch_bounds__(256) void k_rows_big(const int32_t *__restrict__ big, const int32_t *__restrict__ nbig,
-                                                  int32_t cols, const int32_t *__restrict__ xadj,
-                                                  const int32_t *__restrict__ adjncy,
-                                                  const int32_t *__restrict__ adjwgt, const float *__restrict__ rinv,
-                                                  const float *__restrict__ X, float *__restrict__ out) {
-    __shared__ float sx[kBigStage];
-    __shared__ float sw[kBigStage / 16];
-    __shared__ int32_t su[kBigStage / 16];
-    const int32_t chunk = kBigStage / cols;  // cols <= 64: at least 256 neighbours per chunk
-    const int32_t nb = *nbig;
-    for (int32_t r = blockIdx.x; r < nb; r += gridDim.x) {
-        const int32_t v = big[r];
-        const int32_t b = xadj[v], e = xadj[v + 1];
+// The first `wblocks` workgroups take the wide rows, the others the rest.
+// WALK: out[v][c] = (X[v][c] + acc * rinv[v]) / 2 (X[v][c] without neighbours),
+// else out[v][c] = acc * rinv[v] (0 without neighbours).
+template <int COLS, bool WALK>
+__global__ __launch_bounds__(kGatherBlock) void k_gather(int32_t n, const int32_t *__restrict__ wide,
+                                                         const int32_t *__restrict__ nwide, int32_t wblocks,
+                                                         const int32_t *__restrict__ xadj,
+                                                         const int32_t *__restrict__ adjncy,
+                                                         const int32_t *__restrict__ adjwgt,
+                                                         const float *__restrict__ rinv, const float *__restrict__ X,
+                                                         float *__restrict__ out) {
+    __shared__ __align__(16) float sx[2][kSlice * kStagePitch + 16];  // + 16: the chains read ahead
+    __shared__ __align__(16) float sw[2][kStage + 16];
+    if ((int32_t)blockIdx.x < wblocks) {
+        constexpr int SL = (COLS + kSlice - 1) / kSlice;
+        const int32_t items = *nwide * SL;
+        const bool chain = threadIdx.x < kWave;      // the first wave
+        const int32_t t = (int32_t)threadIdx.x - kWave;  // the others: neighbour t of each chunk
+        for (int32_t it = blockIdx.x; it < items; it += wblocks) {
+            const int32_t v = wide[it / SL], c0 = it % SL * kSlice;
+            const int32_t cols = min(kSlice, COLS - c0);
+            const int32_t b = xadj[v], e = xadj[v + 1], nch = (e - b + kStage - 1) / kStage;
+            float acc = 0.0f, wv = 0.0f, x[kSlice];
+            int32_t nu = 0, nw = 1;
+            // ids and weights are requested two chunks before their values are staged
+            const auto fetch_id = [&](int32_t q) {
+                nu = q < e ? adjncy[q] : 0;
+                nw = q < e && adjwgt ? adjwgt[q] : 1;
+            };
+            const auto fetch = [&]() {
+                wv = (float)nw;
+                const float *r = X + (int64_t)nu * COLS + c0;
+                if constexpr (COLS % 4 == 0) {
+#pragma unroll
+                    for (int j = 0; j < kSlice / 4; j++) {
+                        const float4 f = reinterpret_cast<const float4 *>(r)[j];
+                        x[4 * j] = f.x;
+                        x[4 * j + 1] = f.y;
+                        x[4 * j + 2] = f.z;
+                        x[4 * j + 3] = f.w;
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < kSlice; j++) x[j] = r[j < cols ? j : 0];
+                }
+            };
+            const auto stage = [&](int buf) {
+                sw[buf][t] = wv;
+#pragma unroll
+                for (int j = 0; j < kSlice; j++) sx[buf][j * kStagePitch + t] = x[j];
+            };
+            if (!chain) {
+                fetch_id(b + t);
+                fetch();
+                fetch_id(b + kStage + t);
+                stage(0);
+                if (nch > 1) {
+                    fetch();
+                    fetch_id(b + 2 * kStage + t);
+                }
+            }
+            __syncthreads();
+            for (int32_t ch = 0; ch < nch; ch++) {
+                if (!chain) {
+                    if (ch + 1 < nch) {
+                        stage((ch + 1) & 1);
+                        if (ch + 2 < nch) {
+                            fetch();
+                            fetch_id(b + (ch + 3) * kStage + t);
+                        }
+                    }
+                } else if (threadIdx.x < kSlice) {
+                    const float *xc = sx[ch & 1] + threadIdx.x * kStagePitch, *wc = sw[ch & 1];
+                    const float4 *xs = reinterpret_cast<const float4 *>(xc);
+                    const float4 *ws = reinterpret_cast<const float4 *>(wc);
+                    const int32_t len = min(kStage, e - b - ch * kStage);
+                    // 32 steps at a time; each half's operands are read while the other half runs
+                    float4 xa[4], wa[4], xb[4], wb[4];
+                    const auto load = [&](float4 (&xr)[4], float4 (&wr)[4], int32_t g) {
+#pragma unroll
+                        for (int j = 0; j < 4; j++) {
+                            xr[j] = xs[4 * g + j];
+                            wr[j] = ws[4 * g + j];
+                        }
+                    };
+                    const auto steps = [&](const float4 (&xr)[4], const float4 (&wr)[4]) {
+#pragma unroll
+                        for (int j = 0; j < 4; j++) {
+                            acc = __builtin_fmaf(wr[j].x, xr[j].x, acc);
+                            acc = __builtin_fmaf(wr[j].y, xr[j].y, acc);
+                            acc = __builtin_fmaf(wr[j].z, xr[j].z, acc);
+                            acc = __builtin_fmaf(wr[j].w, xr[j].w, acc);
+                        }
+                    };
+                    const int32_t pairs = len / 32;
+                    load(xa, wa, 0);
+                    for (int32_t p = 0; p < pairs; p++) {
+                        load(xb, wb, 2 * p + 1);
+                        __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the steps
+                        steps(xa, wa);
+                        __builtin_amdgcn_sched_barrier(0);
+                        load(xa, wa, 2 * p + 2);  // past the chunk after its last pair: not used
+                        __builtin_amdgcn_sched_barrier(0);
+                        steps(xb, wb);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    for (int32_t q = pairs * 32; q < len; q++) acc = __builtin_fmaf(wc[q], xc[q], acc);
+                }
+                __syncthreads();
+            }
+            if ((int32_t)threadIdx.x < cols) {
+                const int64_t i = (int64_t)v * COLS + c0 + threadIdx.x;
+                out[i] = WALK ? (X[i] + acc * rinv[v]) * 0.5f : acc * rinv[v];
+            }
+        }
+        return;
+    }
+    // ---- rows of at most kWideRow entries
+    constexpr int GL = COLS <= 16 ? 16 : (COLS <= 32 ? 32 : 64), NG = kGatherBlock / GL;
+    constexpr int UB = 16;
+    const int32_t c = threadIdx.x % GL, grp = threadIdx.x / GL;
+    const int32_t cc = c < COLS ? c : 0;
+    for (int32_t v0 = (blockIdx.x - wblocks) * NG; v0 < n; v0 += (gridDim.x - wblocks) * NG) {
+        const int32_t v = v0 + grp;
+        const int32_t b = v < n ? xadj[v] : 0;
+        int32_t e = v < n ? xadj[v + 1] : 0;
+        const bool mine = v < n && e - b <= kWideRow;
+        if (!mine) e = b;
         float acc = 0.0f;
-        for (int32_t q0 = b; q0 < e; q0 += chunk) {
-            const int32_t len = min(chunk, e - q0);
-            for (int32_t q = threadIdx.x; q < len; q += 256) {
-                su[q] = adjncy[q0 + q];
-                sw[q] = adjwgt ? (float)adjwgt[q0 + q] : 1.0f;
+        const int32_t chunks = wave_max((e - b + GL - 1) / GL);
+        int32_t u = b + c < e ? adjncy[b + c] : 0;
+        float w = b + c < e && adjwgt ? (float)adjwgt[b + c] : 1.0f;
+        for (int32_t ch = 0; ch < chunks; ch++) {
+            const int32_t nq = b + (ch + 1) * GL + c;
+            const int32_t nu = nq < e ? adjncy[nq] : 0;
+            const float nw = nq < e && adjwgt ? (float)adjwgt[nq] : 1.0f;
+#pragma unroll
+            for (int s0 = 0; s0 < GL; s0 += UB) {
+                const int32_t left = e - (b + ch * GL + s0);  // entries of the row from here on
+                if (__ballot(left > 0) == 0) break;
+                float xv[UB], ws[UB];
+#pragma unroll
+                for (int j = 0; j < UB; j++) {
+                    xv[j] = X[(int64_t)__shfl(u, s0 + j, GL) * COLS + cc];
+                    ws[j] = __shfl(w, s0 + j, GL);
+                }
+#pragma unroll
+                for (int j = 0; j < UB; j++) {
+                    const float f = __builtin_fmaf(ws[j], xv[j], acc);
+                    acc = j < left ? f : acc;
+                }
             }
-            __syncthreads();
-            for (int32_t i = threadIdx.x; i < len * cols; i += 256) {
-                const int32_t q = i / cols, c = i - q * cols;
-                sx[i] = X[(int64_t)su[q] * cols + c];
-            }
-            __syncthreads();
-            if (threadIdx.x < cols)
-                for (int32_t q = 0; q < len; q++) acc = __builtin_fmaf(sw[q], sx[q * cols + threadIdx.x], acc);
-            __syncthreads();
+            u = nu;
+            w = nw;
         }
-        if (threadIdx.x < cols) {
-            const int64_t i = (int64_t)v * cols + threadIdx.x;
-            out[i] = WALK ? (X[i] + acc * rinv[v]) * 0.5f : acc * rinv[v];
+        if (mine && c < COLS) {
+            const int64_t i = (int64_t)v * COLS + c;
+            if (WALK) {
+                const float self = X[i];
+                out[i] = e > b ? (self + acc * rinv[v]) * 0.5f : self;
+            } else {
+                out[i] = e > b ? acc * rinv[v] : 0.0f;
+            }
         }
     }
 }
@@ -177,21 +335,6 @@ __global__ void k_probes(int32_t n, uint64_t seed, const int32_t *__restrict__ r
     }
 }
 
-// one lazy random-walk step of every probe
-__global__ void k_walk(int32_t n, const int32_t *__restrict__ xadj, const int32_t *__restrict__ adjncy,
-                       const int32_t *__restrict__ adjwgt, const float *__restrict__ rinv,
-                       const float *__restrict__ Yin, float *__restrict__ Yout) {
-    const int64_t N = (int64_t)n * kMpProbe;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t v = (int32_t)(i / kMpProbe), j = (int32_t)(i % kMpProbe);
-        const int32_t b = xadj[v], e = xadj[v + 1];
-        if (e - b > kBigRow) continue;  // k_rows_big
-        const float acc = row_fma(b, e, adjncy, adjwgt, Yin, kMpProbe, j, 0.0f);
-        const float self = Yin[i];
-        Yout[i] = e > b ? (self + acc * rinv[v]) * 0.5f : self;
-    }
-}
-
 __global__ void k_features(int32_t n, const int32_t *__restrict__ xadj, const int32_t *__restrict__ vwgt,
                            const int32_t *__restrict__ mx, const float *__restrict__ Y, float *__restrict__ X) {
     const double cmax = (double)mx[0];
@@ -207,34 +350,64 @@ __global__ void k_features(int32_t n, const int32_t *__restrict__ xadj, const in
     }
 }
 
-// M[v][c] = (sum_u w(v,u) H[u][c]) / d(v): threads walk (v, c) pairs, so a
-// wavefront reads whole contiguous rows H[u][*] of each neighbour.
-__global__ void k_aggregate(int32_t n, int32_t din, const int32_t *__restrict__ xadj,
-                            const int32_t *__restrict__ adjncy, const int32_t *__restrict__ adjwgt,
-                            const float *__restrict__ rinv, const float *__restrict__ H, float *__restrict__ M) {
-    const int64_t N = (int64_t)n * din;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t v = (int32_t)(i / din), c = (int32_t)(i % din);
-        const int32_t b = xadj[v], e = xadj[v + 1];
-        if (e - b > kBigRow) continue;  // k_rows_big
-        const float acc = row_fma(b, e, adjncy, adjwgt, H, din, c, 0.0f);
-        M[i] = e > b ? acc * rinv[v] : 0.0f;
+// Hidden layers: O[v][o] = ReLU(b[o] + sum_i Ws[o][i] H[v][i] + sum_i Wn[o][i] M[v][i]),
+// lane o of a wave is output o, weights transposed in LDS. A wave takes VB
+// vertices at a time, so a weight read from LDS serves VB chains, and their
+// inputs (the same for all lanes) come through scalar loads. Bound: the LDS
+// reads; 71 us a layer at 50,000 vertices with one vertex per wave, 22 us so.
+template <int DIN>
+__global__ __launch_bounds__(kMB) void k_hidden(int32_t n, const float *__restrict__ H, const float *__restrict__ M,
+                                                const float *__restrict__ Ws, const float *__restrict__ Wn,
+                                                const float *__restrict__ bias, float *__restrict__ O) {
+    constexpr int VB = 4, NW = kMB / kWave;
+    __shared__ float sWs[DIN * kMpHid], sWn[DIN * kMpHid];
+    for (int32_t t = threadIdx.x; t < DIN * kMpHid; t += kMB) {
+        const int32_t o = t / DIN, i = t % DIN;
+        sWs[i * kMpHid + o] = Ws[t];
+        sWn[i * kMpHid + o] = Wn[t];
+    }
+    __syncthreads();
+    const int lane = lane_id();
+    const float bo = bias[lane];
+    const int32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * NW + threadIdx.x / kWave);
+    for (int32_t v0 = wave * VB; v0 < n; v0 += gridDim.x * NW * VB) {
+        float acc[VB];
+        const float *h[VB], *m[VB];
+#pragma unroll
+        for (int j = 0; j < VB; j++) {
+            const int64_t v = min(v0 + j, n - 1);
+            acc[j] = bo;
+            h[j] = H + v * DIN;
+            m[j] = M + v * DIN;
+        }
+#pragma unroll 8
+        for (int i = 0; i < DIN; i++) {
+            const float w = sWs[i * kMpHid + lane];
+#pragma unroll
+            for (int j = 0; j < VB; j++) acc[j] = __builtin_fmaf(w, h[j][i], acc[j]);
+        }
+#pragma unroll 8
+        for (int i = 0; i < DIN; i++) {
+            const float w = sWn[i * kMpHid + lane];
+#pragma unroll
+            for (int j = 0; j < VB; j++) acc[j] = __builtin_fmaf(w, m[j][i], acc[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < VB; j++)
+            if (v0 + j < n) O[(int64_t)(v0 + j) * kMpHid + lane] = acc[j] > 0.0f ? acc[j] : 0.0f;
     }
 }
 
-// O[v][o] = act(b[o] + sum_i Ws[o][i] H[v][i] + sum_i Wn[o][i] M[v][i]) with
-// the weights staged transposed in LDS (lane o reads consecutive words).
-// `dp` lanes (a power of two >= dout) serve one vertex.
-template <bool NEIGH, bool RELU>
-__global__ __launch_bounds__(kMB) void k_dense(int32_t n, int32_t din, int32_t dout, int32_t dp,
-                                               const float *__restrict__ H, const float *__restrict__ M,
-                                               const float *__restrict__ Ws, const float *__restrict__ Wn,
-                                               const float *__restrict__ bias, float *__restrict__ O) {
-    __shared__ float sWs[kMpHid * kMpHid], sWn[NEIGH ? kMpHid * kMpHid : 1], sb[kMpHid];
+// The head: Z[v][o] = b[o] + sum_i W[o][i] H[v][i] with the weights staged
+// transposed in LDS (lane o reads consecutive words). `dp` lanes (a power of
+// two >= dout) serve one vertex.
+__global__ __launch_bounds__(kMB) void k_head(int32_t n, int32_t din, int32_t dout, int32_t dp,
+                                              const float *__restrict__ H, const float *__restrict__ W,
+                                              const float *__restrict__ bias, float *__restrict__ O) {
+    __shared__ float sW[kMpHid * kMpHid], sb[kMpHid];
     for (int32_t t = threadIdx.x; t < din * dout; t += kMB) {
         const int32_t o = t / din, i = t % din;
-        sWs[i * dout + o] = Ws[t];
-        if (NEIGH) sWn[i * dout + o] = Wn[t];
+        sW[i * dout + o] = W[t];
     }
     for (int32_t t = threadIdx.x; t < dout; t += kMB) sb[t] = bias[t];
     __syncthreads();
@@ -243,12 +416,8 @@ __global__ __launch_bounds__(kMB) void k_dense(int32_t n, int32_t din, int32_t d
     for (int64_t v = (int64_t)blockIdx.x * vpb + threadIdx.x / dp; v < n; v += (int64_t)gridDim.x * vpb) {
         const float *h = H + v * din;
         float acc = sb[o];
-        for (int32_t i = 0; i < din; i++) acc = __builtin_fmaf(sWs[i * dout + o], h[i], acc);
-        if (NEIGH) {
-            const float *m = M + v * din;
-            for (int32_t i = 0; i < din; i++) acc = __builtin_fmaf(sWn[i * dout + o], m[i], acc);
-        }
-        O[v * dout + o] = RELU ? (acc > 0.0f ? acc : 0.0f) : acc;
+        for (int32_t i = 0; i < din; i++) acc = __builtin_fmaf(sW[i * dout + o], h[i], acc);
+        O[v * dout + o] = acc;
     }
 }
 
@@ -351,15 +520,18 @@ __global__ __launch_bounds__(kLeftBlock) void k_decode_leftover(int32_t n, int32
 
 // ------------------------------------------------------------------ training
 
-__global__ void k_softmax(int32_t n, int32_t k, const float *__restrict__ Z, float *__restrict__ S) {
-    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
-        const float *z = Z + (int64_t)v * k;
-        float m = z[0];
-        for (int32_t c = 1; c < k; c++) m = fmaxf(m, z[c]);
-        float s = 0.0f;
-        for (int32_t c = 0; c < k; c++) s += __expf(z[c] - m);
-        const float inv = 1.0f / s;
-        for (int32_t c = 0; c < k; c++) S[(int64_t)v * k + c] = __expf(z[c] - m) * inv;
+// S = softmax(Z): `kp` lanes (a power of two >= k) per vertex.
+__global__ __launch_bounds__(kMB) void k_softmax(int32_t n, int32_t k, int32_t kp, const float *__restrict__ Z,
+                                                 float *__restrict__ S) {
+    const int32_t c = threadIdx.x % kp, vpb = kMB / kp;
+    for (int64_t v = (int64_t)blockIdx.x * vpb + threadIdx.x / kp; v < n; v += (int64_t)gridDim.x * vpb) {
+        const float z = c < k ? Z[v * k + c] : -INFINITY;
+        float m = z;
+        for (int32_t d = kp / 2; d > 0; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, kp));
+        const float x = c < k ? __expf(z - m) : 0.0f;
+        float s = x;
+        for (int32_t d = kp / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, kp);
+        if (c < k) S[v * k + c] = x * (1.0f / s);
     }
 }
 
@@ -368,19 +540,26 @@ constexpr float kPClip = 1e-6f;
 // Edge term of the loss: for every directed edge (v,u), p = <S_v, S_u> and
 // BCE against [t_v == t_u], weighted by w(v,u)/Omega. gS[v] collects the
 // gradient w.r.t. S_v from both directions of each edge (2 * dl/dp * S_u).
-// `kp` lanes (a power of two >= k) serve one vertex.
+// One workgroup per vertex, `kp` lanes (a power of two >= k) per edge, so a row
+// takes kMB / kp edges at a time: with kp lanes per vertex the widest row set
+// the time (277 us at 835 vertices and 28,000 entries, 24 us so).
 __global__ __launch_bounds__(kMB) void k_edge_loss(int32_t n, int32_t k, int32_t kp, const int32_t *__restrict__ xadj,
                                                    const int32_t *__restrict__ adjncy,
                                                    const int32_t *__restrict__ adjwgt,
                                                    const int32_t *__restrict__ target, const float *__restrict__ S,
-                                                   float inv_omega, float *__restrict__ gS, double *__restrict__ loss) {
-    const int32_t c = threadIdx.x % kp, vpb = kMB / kp;
+                                                   const int64_t *__restrict__ omega, float *__restrict__ gS,
+                                                   double *__restrict__ loss) {
+    __shared__ float sg[kMB];
+    __shared__ double sl[kMB / kWave + 1];
+    const float inv_omega = *omega > 0 ? (float)(1.0 / (double)*omega) : 0.0f;
+    const int32_t c = threadIdx.x % kp, grp = threadIdx.x / kp, ng = kMB / kp;
     double lsum = 0.0;
-    for (int64_t v = (int64_t)blockIdx.x * vpb + threadIdx.x / kp; v < n; v += (int64_t)gridDim.x * vpb) {
+    for (int64_t v = blockIdx.x; v < n; v += gridDim.x) {
         const float sv = c < k ? S[v * k + c] : 0.0f;
         const int32_t tv = target[v];
+        const int32_t b = xadj[v], e = xadj[v + 1];
         float g = 0.0f, l = 0.0f;
-        for (int32_t q = xadj[v]; q < xadj[v + 1]; q++) {
+        for (int32_t q = b + grp; q < e; q += ng) {
             const int32_t u = adjncy[q];
             const float su = c < k ? S[(int64_t)u * k + c] : 0.0f;
             float p = sv * su;
@@ -393,11 +572,18 @@ __global__ __launch_bounds__(kMB) void k_edge_loss(int32_t n, int32_t k, int32_t
             const float dldp = inside ? (y ? -1.0f / pc : 1.0f / (1.0f - pc)) : 0.0f;
             g += 2.0f * w * dldp * su;
         }
-        if (c < k) gS[v * k + c] = g;
         if (c == 0) lsum += l;
+        sg[threadIdx.x] = g;
+        __syncthreads();
+        for (int32_t h = ng / 2; h > 0; h >>= 1) {  // ng is a power of two
+            if (grp < h) sg[threadIdx.x] += sg[threadIdx.x + h * kp];
+            __syncthreads();
+        }
+        if ((int32_t)threadIdx.x < k) gS[v * k + threadIdx.x] = sg[threadIdx.x];
+        __syncthreads();
     }
-    lsum = wave_sum(lsum);
-    if (lane_id() == 0 && lsum != 0.0) atomicAdd(loss, lsum);
+    lsum = block_sum<kMB>(lsum, sl);
+    if (threadIdx.x == 0 && lsum != 0.0) atomicAdd(loss, lsum);
 }
 
 // Q[c] = sum_v c(v) S[v][c] (binary64 accumulation)
@@ -415,84 +601,95 @@ __global__ __launch_bounds__(kMB) void k_colsum(int32_t n, int32_t k, const floa
     for (int32_t t = threadIdx.x; t < k; t += kMB) atomicAdd(&Q[t], (double)part[t]);
 }
 
-// dZ = S * (g - <S, g>) with g = gS + balance term 2 lam k (Q_c/C - 1/k) c(v)/C
-__global__ void k_softmax_back(int32_t n, int32_t k, const float *__restrict__ S, const float *__restrict__ gS,
-                               const double *__restrict__ Q, double invC, float lam, const int32_t *__restrict__ vwgt,
-                               float *__restrict__ dZ) {
-    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
+// dZ = S * (g - <S, g>) with g = gS + balance term 2 lam k (Q_c/C - 1/k) c(v)/C;
+// `kp` lanes (a power of two >= k) per vertex.
+__global__ __launch_bounds__(kMB) void k_softmax_back(int32_t n, int32_t k, int32_t kp, const float *__restrict__ S,
+                                                      const float *__restrict__ gS, const double *__restrict__ Q,
+                                                      const int64_t *__restrict__ C, float lam,
+                                                      const int32_t *__restrict__ vwgt, float *__restrict__ dZ) {
+    const int32_t c = threadIdx.x % kp, vpb = kMB / kp;
+    const double invC = 1.0 / (double)*C;
+    const float bal = c < k ? (float)(2.0 * lam * k * (Q[c] * invC - 1.0 / k)) : 0.0f;
+    for (int64_t v = (int64_t)blockIdx.x * vpb + threadIdx.x / kp; v < n; v += (int64_t)gridDim.x * vpb) {
         const float cv = (float)((vwgt ? (double)vwgt[v] : 1.0) * invC);
-        float dot = 0.0f;
-        for (int32_t c = 0; c < k; c++) {
-            const float bal = (float)(2.0 * lam * k * (Q[c] * invC - 1.0 / k));
-            const float g = gS[(int64_t)v * k + c] + bal * cv;
-            dot += S[(int64_t)v * k + c] * g;
-        }
-        for (int32_t c = 0; c < k; c++) {
-            const float bal = (float)(2.0 * lam * k * (Q[c] * invC - 1.0 / k));
-            const float g = gS[(int64_t)v * k + c] + bal * cv;
-            dZ[(int64_t)v * k + c] = S[(int64_t)v * k + c] * (g - dot);
-        }
+        const float s = c < k ? S[v * k + c] : 0.0f;
+        const float g = c < k ? gS[v * k + c] + bal * cv : 0.0f;
+        float dot = s * g;
+        for (int32_t d = kp / 2; d > 0; d >>= 1) dot += __shfl_xor(dot, d, kp);
+        if (c < k) dZ[v * k + c] = s * (g - dot);
     }
 }
 
-// dH = dH * [Hout > 0]
-__global__ void k_relu_mask(int64_t count, float *__restrict__ dH, const float *__restrict__ Hout) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
-        if (!(Hout[i] > 0.0f)) dH[i] = 0.0f;
+// C = total vertex weight (whole numbers: any order)
+__global__ __launch_bounds__(kMB) void k_vsum(int32_t n, const int32_t *__restrict__ vwgt, int64_t *__restrict__ C) {
+    __shared__ int64_t tmp[kMB / kWave + 1];
+    int64_t s = 0;
+    for (int64_t v = (int64_t)blockIdx.x * kMB + threadIdx.x; v < n; v += (int64_t)gridDim.x * kMB)
+        s += vwgt ? vwgt[v] : 1;
+    s = block_sum<kMB>(s, tmp);
+    if (threadIdx.x == 0) atomicAdd((unsigned long long *)C, (unsigned long long)s);
 }
 
-constexpr int kWgChunk = 32;
-constexpr int kWgMaxE = (kMpHid * (kMpHid + 1) + kMB - 1) / kMB;
+constexpr int kWgChunk = 16;
+constexpr int kWgTile = 4;                             // outputs x inputs of one thread
+constexpr int kWgPitch = kMpHid + kWgTile;
+static_assert(kMpMaxK <= kMpHid, "a chunk's rows of A fit kWgPitch");
 
-// gW[o][i] += sum_v A[v][o] B[v][i]; gb[o] += sum_v A[v][o] (when gb != null).
-// A block stages kWgChunk rows of A and B in LDS and keeps its share of the
-// dout x (din+1) sums in registers; one atomic per entry per block at the end.
+// gW[o][i] += sum_v A[v][o] B[v][i]; gb[o] += sum_v A[v][o] (when gb != null),
+// for one or two matrices B (blockIdx.y) with the same A. A workgroup stages
+// kWgChunk rows of A and B in LDS; a thread keeps a 4 x 4 tile of the sums in
+// registers (eight LDS words per sixteen products), one atomic per entry and
+// workgroup at the end. A workgroup takes kWgRows rows at a time: the fewer
+// workgroups, the fewer binary32 sums meet in the gradient (with one chunk per
+// workgroup its relative error against binary64 was 1.2e-7 instead of 0.9e-7
+// at 835 vertices).
+constexpr int kWgPer = 4, kWgRows = kWgPer * kWgChunk;
+struct WGrad {
+    const float *B;
+    float *gW, *gb;
+};
 __global__ __launch_bounds__(kMB) void k_wgrad(int32_t n, int32_t dout, int32_t din, const float *__restrict__ A,
-                                               const float *__restrict__ B, float *__restrict__ gW,
-                                               float *__restrict__ gb) {
-    __shared__ float sA[kWgChunk * kMpMaxK], sB[kWgChunk * (kMpHid + 1)];
-    const int32_t dc = din + 1, E = dout * dc;
-    float acc[kWgMaxE];
-#pragma unroll
-    for (int r = 0; r < kWgMaxE; r++) acc[r] = 0.0f;
-    for (int64_t base = (int64_t)blockIdx.x * kWgChunk; base < n; base += (int64_t)gridDim.x * kWgChunk) {
+                                               WGrad first, WGrad second) {
+    __shared__ __align__(16) float sA[kWgChunk * kWgPitch], sB[kWgChunk * kWgPitch];
+    const WGrad w = blockIdx.y == 0 ? first : second;
+    const int32_t o0 = threadIdx.x / (kMpHid / kWgTile) * kWgTile, i0 = threadIdx.x % (kMpHid / kWgTile) * kWgTile;
+    float acc[kWgTile][kWgTile] = {}, bsum = 0.0f;
+    for (int64_t i = 0, base = (int64_t)blockIdx.x * kWgRows; base < n;
+         i++, base = ((int64_t)blockIdx.x + i / kWgPer * gridDim.x) * kWgRows + i % kWgPer * kWgChunk) {
         const int32_t rows = (int32_t)min<int64_t>(kWgChunk, n - base);
         __syncthreads();
-        for (int32_t t = threadIdx.x; t < kWgChunk * dout; t += kMB) {
-            const int32_t r = t / dout;
-            sA[t] = r < rows ? A[(base + r) * dout + t % dout] : 0.0f;
-        }
-        for (int32_t t = threadIdx.x; t < kWgChunk * dc; t += kMB) {
-            const int32_t r = t / dc, i = t % dc;
-            sB[t] = r < rows ? (i < din ? B[(base + r) * din + i] : 1.0f) : 0.0f;
+        for (int32_t t = threadIdx.x; t < kWgChunk * kMpHid; t += kMB) {
+            const int32_t r = t / kMpHid, x = t % kMpHid;
+            sA[r * kWgPitch + x] = r < rows && x < dout ? A[(base + r) * dout + x] : 0.0f;
+            sB[r * kWgPitch + x] = r < rows && x < din ? w.B[(base + r) * din + x] : 0.0f;
         }
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < kWgMaxE; r++) {
-            const int32_t e = threadIdx.x + r * kMB;
-            if (e < E) {
-                const int32_t o = e / dc, i = e % dc;
-                float s = acc[r];
-                for (int32_t q = 0; q < kWgChunk; q++) s += sA[q * dout + o] * sB[q * dc + i];
-                acc[r] = s;
-            }
+        for (int q = 0; q < kWgChunk; q++) {
+            const float4 x = *reinterpret_cast<const float4 *>(sA + q * kWgPitch + o0);
+            const float4 y = *reinterpret_cast<const float4 *>(sB + q * kWgPitch + i0);
+            const float xa[4] = {x.x, x.y, x.z, x.w}, ya[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+            for (int o = 0; o < kWgTile; o++)
+#pragma unroll
+                for (int i = 0; i < kWgTile; i++) acc[o][i] = __builtin_fmaf(xa[o], ya[i], acc[o][i]);
+            if (threadIdx.x < kMpHid) bsum += sA[q * kWgPitch + threadIdx.x];
         }
     }
 #pragma unroll
-    for (int r = 0; r < kWgMaxE; r++) {
-        const int32_t e = threadIdx.x + r * kMB;
-        if (e < E) {
-            const int32_t o = e / dc, i = e % dc;
-            if (i < din) atomicAdd(&gW[o * din + i], acc[r]);
-            else if (gb) atomicAdd(&gb[o], acc[r]);
-        }
-    }
+    for (int o = 0; o < kWgTile; o++)
+#pragma unroll
+        for (int i = 0; i < kWgTile; i++)
+            if (o0 + o < dout && i0 + i < din) atomicAdd(&w.gW[(o0 + o) * din + i0 + i], acc[o][i]);
+    if (w.gb && (int32_t)threadIdx.x < dout) atomicAdd(&w.gb[threadIdx.x], bsum);
 }
 
 // out1[v][i] = sum_o W1[o][i] D[v][o]; out2 likewise with W2 (when given).
+// mask (when given): out1[v][i] = 0 where !(mask[v][i] > 0) (the ReLU below).
 __global__ __launch_bounds__(kMB) void k_dense_t(int32_t n, int32_t dout, int32_t din, const float *__restrict__ D,
                                                  const float *__restrict__ W1, const float *__restrict__ W2,
-                                                 float *__restrict__ out1, float *__restrict__ out2) {
+                                                 const float *__restrict__ mask, float *__restrict__ out1,
+                                                 float *__restrict__ out2) {
     __shared__ float s1[kMpHid * kMpMaxK], s2[kMpHid * kMpMaxK];
     for (int32_t t = threadIdx.x; t < din * dout; t += kMB) {
         s1[t] = W1[t];
@@ -509,24 +706,49 @@ __global__ __launch_bounds__(kMB) void k_dense_t(int32_t n, int32_t dout, int32_
             a += s1[o * din + i] * d[o];
             if (W2) b += s2[o * din + i] * d[o];
         }
-        out1[t] = a;
+        out1[t] = mask && !(mask[t] > 0.0f) ? 0.0f : a;
         if (W2) out2[t] = b;
     }
 }
 
-// out[u][i] += sum_{v in N(u)} w(u,v) dM[v][i] / d(v)   (transpose of the aggregation)
-__global__ void k_aggregate_t(int32_t n, int32_t din, const int32_t *__restrict__ xadj,
-                              const int32_t *__restrict__ adjncy, const int32_t *__restrict__ adjwgt,
-                              const float *__restrict__ rinv, const float *__restrict__ dM, float *__restrict__ out) {
-    const int64_t N = (int64_t)n * din;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t u = (int32_t)(i / din), c = (int32_t)(i % din);
+// out[u][i] = (out[u][i] + sum_{v in N(u)} w(u,v) dM[v][i] / d(v)) [mask[u][i] > 0]:
+// the transpose of the aggregation, then the ReLU of the layer below. One
+// workgroup per row, a lane per column, the row's entries dealt to the waves 16
+// at a time (88 us with a lane per output at 835 vertices, 9 us so).
+__global__ __launch_bounds__(kMB) void k_aggregate_t(int32_t n, const int32_t *__restrict__ xadj,
+                                                     const int32_t *__restrict__ adjncy,
+                                                     const int32_t *__restrict__ adjwgt,
+                                                     const float *__restrict__ rinv, const float *__restrict__ dM,
+                                                     const float *__restrict__ mask, float *__restrict__ out) {
+    constexpr int NW = kMB / kWave, UB = 16;
+    __shared__ float part[NW][kMpHid];
+    const int lane = lane_id(), w = threadIdx.x / kWave;
+    for (int32_t u = blockIdx.x; u < n; u += gridDim.x) {
+        const int32_t b = xadj[u], e = xadj[u + 1];
         float acc = 0.0f;
-        for (int32_t q = xadj[u]; q < xadj[u + 1]; q++) {
-            const int32_t v = adjncy[q];
-            acc += (adjwgt ? (float)adjwgt[q] : 1.0f) * rinv[v] * dM[(int64_t)v * din + c];
+        for (int32_t q0 = b + w * UB; q0 < e; q0 += NW * UB) {
+            const int32_t q = q0 + (lane & (UB - 1));
+            const int32_t v = q < e ? adjncy[q] : 0;
+            const float f = q < e ? (adjwgt ? (float)adjwgt[q] : 1.0f) * rinv[v] : 0.0f;
+            float x[UB];
+#pragma unroll
+            for (int j = 0; j < UB; j++) x[j] = dM[(int64_t)__shfl(v, j, kWave) * kMpHid + lane];
+#pragma unroll
+            for (int j = 0; j < UB; j++) {
+                const float t = __builtin_fmaf(__shfl(f, j, kWave), x[j], acc);
+                acc = q0 + j < e ? t : acc;
+            }
         }
-        out[i] += acc;
+        part[w][lane] = acc;
+        __syncthreads();
+        if (w == 0) {
+            const int64_t i = (int64_t)u * kMpHid + lane;
+            float t = out[i];
+#pragma unroll
+            for (int j = 0; j < NW; j++) t += part[j][lane];
+            out[i] = mask[i] > 0.0f ? t : 0.0f;
+        }
+        __syncthreads();
     }
 }
 
@@ -568,12 +790,64 @@ struct Net {  // offsets of the parameter blocks
     }
 };
 
-// the rows above kBigRow entries (device list and count)
-int big_rows(const DevGraph &g, int32_t **big, int32_t **nbig, Scratch &sc) {
-    GP_TRY(sc.alloc(big, g.n));
-    GP_TRY(sc.alloc(nbig, 1));
-    GP_HIP(hipMemsetAsync(*nbig, 0, sizeof(int32_t), sc.stream()));
-    return compact(BigFlag{g.xadj}, BigEmit{*big}, g.n, nullptr, *nbig, sc);
+// the rows above kWideRow entries (device list and count)
+struct WideRows {
+    int32_t *list = nullptr, *count = nullptr;
+};
+int wide_rows(const DevGraph &g, WideRows &w, Scratch &sc) {
+    GP_TRY(sc.alloc(&w.list, g.n));
+    GP_TRY(sc.alloc(&w.count, 1));
+    GP_HIP(hipMemsetAsync(w.count, 0, sizeof(int32_t), sc.stream()));
+    return compact(WideFlag{g.xadj}, WideEmit{w.list}, g.n, nullptr, w.count, sc);
+}
+
+// at most this many: each has more than kWideRow of the entries
+int64_t wide_most(const DevGraph &g) { return std::min<int64_t>(g.n, (int64_t)g.nnz / (kWideRow + 1)); }
+
+template <int COLS, bool WALK>
+int gather(const DevGraph &g, const WideRows &w, const float *rinv, const float *X, float *out, hipStream_t s) {
+    constexpr int GL = COLS <= 16 ? 16 : (COLS <= 32 ? 32 : 64);
+    const int64_t most = wide_most(g) * ((COLS + kSlice - 1) / kSlice);
+    const unsigned wb = most > 0 ? grid_for(most, 1, 4096) : 0;
+    hipLaunchKernelGGL((k_gather<COLS, WALK>), dim3(wb + grid_for(g.n, kGatherBlock / GL, 1 << 15)), dim3(kGatherBlock), 0, s, g.n,
+                       w.list, w.count, (int32_t)wb, g.xadj, g.adjncy, g.adjwgt, rinv, X, out);
+    GP_LAUNCH_CHECK();
+    return GP_OK;
+}
+
+// X: [n][18] features; rinv (may be null): receives 1/d(v)
+int features(const DevGraph &g, uint64_t seed, bool active_only, float *X, float *rinv, const WideRows &wide,
+             Scratch &sc) {
+    hipStream_t s = sc.stream();
+    const int32_t n = g.n;
+    float *r = rinv, *Ya = nullptr, *Yb = nullptr;
+    int32_t *mx = nullptr, *rank = nullptr, *cnt = nullptr;
+    if (!r) GP_TRY(sc.alloc(&r, n));
+    GP_TRY(sc.alloc(&Ya, (size_t)n * kMpProbe));
+    GP_TRY(sc.alloc(&Yb, (size_t)n * kMpProbe));
+    GP_TRY(sc.alloc(&mx, 2));
+    GP_HIP(hipMemsetAsync(mx, 0, sizeof(int32_t) * 2, s));
+    const unsigned wb = wide_most(g) > 0 ? grid_for(wide_most(g), 1, 512) : 0;
+    hipLaunchKernelGGL(k_vstats, dim3(wb + grid_for(n, kMB / 16, 1024)), dim3(kMB), 0, s, n, wide.list, wide.count,
+                       (int32_t)wb, g.xadj, g.adjwgt, g.vwgt, active_only, r, mx);
+    GP_LAUNCH_CHECK();
+    if (active_only) {
+        GP_TRY(sc.alloc(&rank, n));
+        GP_TRY(sc.alloc(&cnt, 1));
+        GP_HIP(hipMemsetAsync(rank, 0, sizeof(int32_t) * (size_t)n, s));
+        GP_TRY(compact(ActiveFlag{g.xadj}, RankEmit{rank}, n, nullptr, cnt, sc));
+    }
+    hipLaunchKernelGGL(k_probes, dim3(grid_for((int64_t)n * kMpProbe, 256, 1 << 16)), dim3(256), 0, s, n, seed, rank,
+                       Ya);
+    GP_LAUNCH_CHECK();
+    for (int t = 0; t < kMpWalk; t++) {
+        GP_TRY((gather<kMpProbe, true>(g, wide, r, Ya, Yb, s)));
+        std::swap(Ya, Yb);
+    }
+    hipLaunchKernelGGL(k_features, dim3(grid_for((int64_t)n * kMpFeat, 256, 1 << 16)), dim3(256), 0, s, n, g.xadj,
+                       g.vwgt, mx, Ya, X);
+    GP_LAUNCH_CHECK();
+    return GP_OK;
 }
 
 struct Acts {  // forward activations kept for the backward pass
@@ -594,26 +868,27 @@ int run_forward(const DevGraph &g, int32_t k, const float *params, uint64_t seed
     GP_TRY(sc.alloc(&a.Z, (size_t)n * k));
     hipLaunchKernelGGL(k_bf16, dim3(grid_for(P, 256, 256)), dim3(256), 0, s, params, a.Wt, P);
     GP_LAUNCH_CHECK();
-    GP_TRY(mpnn_features(g, seed, active_only, a.X, a.rinv, sc));
+    WideRows wide;
+    GP_TRY(wide_rows(g, wide, sc));
+    GP_TRY(features(g, seed, active_only, a.X, a.rinv, wide, sc));
     const Net net(k);
     const float *in = a.X;
-    int32_t *big = nullptr, *nbig = nullptr;
-    GP_TRY(big_rows(g, &big, &nbig, sc));
+    const unsigned gh = grid_for(n, 4 * (kMB / kWave), 2048);
     for (int l = 0; l < 3; l++) {
-        const int32_t din = l == 0 ? kMpFeat : kMpHid;
-        hipLaunchKernelGGL(k_aggregate, dim3(grid_for((int64_t)n * din, 256, 1 << 16)), dim3(256), 0, s, n, din,
-                           g.xadj, g.adjncy, g.adjwgt, a.rinv, in, a.M[l]);
-        hipLaunchKernelGGL(k_rows_big<false>, dim3(grid_for(n, 1, 1024)), dim3(256), 0, s, big, nbig, din, g.xadj,
-                           g.adjncy, g.adjwgt, a.rinv, in, a.M[l]);
-        GP_LAUNCH_CHECK();
-        hipLaunchKernelGGL((k_dense<true, true>), dim3(grid_for(n, kMB / kMpHid, 2048)), dim3(kMB), 0, s, n, din,
-                           kMpHid, kMpHid, in, a.M[l], a.Wt + net.ws[l], a.Wt + net.wn[l], a.Wt + net.b[l], a.H[l]);
+        const float *ws = a.Wt + net.ws[l], *wn = a.Wt + net.wn[l], *bl = a.Wt + net.b[l];
+        if (l == 0) {
+            GP_TRY((gather<kMpFeat, false>(g, wide, a.rinv, in, a.M[l], s)));
+            hipLaunchKernelGGL(k_hidden<kMpFeat>, dim3(gh), dim3(kMB), 0, s, n, in, a.M[l], ws, wn, bl, a.H[l]);
+        } else {
+            GP_TRY((gather<kMpHid, false>(g, wide, a.rinv, in, a.M[l], s)));
+            hipLaunchKernelGGL(k_hidden<kMpHid>, dim3(gh), dim3(kMB), 0, s, n, in, a.M[l], ws, wn, bl, a.H[l]);
+        }
         GP_LAUNCH_CHECK();
         in = a.H[l];
     }
     const int32_t kp = pow2_at_least(k);
-    hipLaunchKernelGGL((k_dense<false, false>), dim3(grid_for(n, kMB / kp, 2048)), dim3(kMB), 0, s, n, kMpHid, k, kp,
-                       in, nullptr, a.Wt + net.wh, nullptr, a.Wt + net.bh, a.Z);
+    hipLaunchKernelGGL(k_head, dim3(grid_for(n, kMB / kp, 2048)), dim3(kMB), 0, s, n, kMpHid, k, kp, in,
+                       a.Wt + net.wh, a.Wt + net.bh, a.Z);
     GP_LAUNCH_CHECK();
     return GP_OK;
 }
@@ -621,41 +896,10 @@ int run_forward(const DevGraph &g, int32_t k, const float *params, uint64_t seed
 }  // namespace
 
 int mpnn_features(const DevGraph &g, uint64_t seed, bool active_only, float *X, float *rinv, Scratch &sc) {
-    hipStream_t s = sc.stream();
-    const int32_t n = g.n;
-    if (n == 0) return GP_OK;
-    float *r = rinv, *Ya = nullptr, *Yb = nullptr;
-    int32_t *mx = nullptr, *rank = nullptr, *cnt = nullptr;
-    if (!r) GP_TRY(sc.alloc(&r, n));
-    GP_TRY(sc.alloc(&Ya, (size_t)n * kMpProbe));
-    GP_TRY(sc.alloc(&Yb, (size_t)n * kMpProbe));
-    GP_TRY(sc.alloc(&mx, 2));
-    GP_HIP(hipMemsetAsync(mx, 0, sizeof(int32_t) * 2, s));
-    hipLaunchKernelGGL(k_vstats, dim3(grid_for(n, 256, 2048)), dim3(256), 0, s, n, g.xadj, g.adjwgt, g.vwgt,
-                       active_only, r, mx);
-    GP_LAUNCH_CHECK();
-    if (active_only) {
-        GP_TRY(sc.alloc(&rank, n));
-        GP_TRY(sc.alloc(&cnt, 1));
-        GP_HIP(hipMemsetAsync(rank, 0, sizeof(int32_t) * (size_t)n, s));
-        GP_TRY(compact(ActiveFlag{g.xadj}, RankEmit{rank}, n, nullptr, cnt, sc));
-    }
-    int32_t *big = nullptr, *nbig = nullptr;
-    GP_TRY(big_rows(g, &big, &nbig, sc));
-    const unsigned gp16 = grid_for((int64_t)n * kMpProbe, 256, 1 << 16);
-    hipLaunchKernelGGL(k_probes, dim3(gp16), dim3(256), 0, s, n, seed, rank, Ya);
-    GP_LAUNCH_CHECK();
-    for (int t = 0; t < kMpWalk; t++) {
-        hipLaunchKernelGGL(k_walk, dim3(gp16), dim3(256), 0, s, n, g.xadj, g.adjncy, g.adjwgt, r, Ya, Yb);
-        hipLaunchKernelGGL(k_rows_big<true>, dim3(grid_for(n, 1, 1024)), dim3(256), 0, s, big, nbig, kMpProbe,
-                           g.xadj, g.adjncy, g.adjwgt, r, Ya, Yb);
-        GP_LAUNCH_CHECK();
-        std::swap(Ya, Yb);
-    }
-    hipLaunchKernelGGL(k_features, dim3(grid_for((int64_t)n * kMpFeat, 256, 1 << 16)), dim3(256), 0, s, n, g.xadj,
-                       g.vwgt, mx, Ya, X);
-    GP_LAUNCH_CHECK();
-    return GP_OK;
+    if (g.n == 0) return GP_OK;
+    WideRows wide;
+    GP_TRY(wide_rows(g, wide, sc));
+    return features(g, seed, active_only, X, rinv, wide, sc);
 }
 
 int mpnn_forward(const DevGraph &g, int32_t k, const float *params, uint64_t seed, bool active_only, float *Z,
@@ -706,74 +950,64 @@ int mpnn_backward(const DevGraph &g, int32_t k, const float *params, uint64_t se
     }
     Acts a;
     GP_TRY(run_forward(g, k, params, seed, false, a, sc));
-    // Omega (sum of all directed edge weights) and C (total vertex weight)
-    int64_t omega = 0;
-    GP_TRY(total_edge_weight(g, &omega, sc));
     const int32_t kp = pow2_at_least(k);
     float *S = nullptr, *gS = nullptr, *dZ = nullptr, *dA = nullptr, *dB = nullptr, *dM = nullptr;
-    double *acc = nullptr;  // [0] edge loss, [1..k] Q, [k+1] C
+    double *acc = nullptr;  // [0] edge loss, [1..k] Q
+    int64_t *tot = nullptr;  // Omega (sum of all directed edge weights), C (total vertex weight)
     GP_TRY(sc.alloc(&S, (size_t)n * k));
     GP_TRY(sc.alloc(&gS, (size_t)n * k));
     GP_TRY(sc.alloc(&dZ, (size_t)n * k));
     GP_TRY(sc.alloc(&dA, (size_t)n * kMpHid));
     GP_TRY(sc.alloc(&dB, (size_t)n * kMpHid));
     GP_TRY(sc.alloc(&dM, (size_t)n * kMpHid));
-    GP_TRY(sc.alloc(&acc, (size_t)k + 2));
-    GP_HIP(hipMemsetAsync(acc, 0, sizeof(double) * ((size_t)k + 2), s));
-    hipLaunchKernelGGL(k_softmax, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, n, k, a.Z, S);
+    GP_TRY(sc.alloc(&acc, (size_t)k + 4));
+    tot = reinterpret_cast<int64_t *>(acc + k + 2);
+    GP_HIP(hipMemsetAsync(acc, 0, sizeof(double) * ((size_t)k + 4), s));
+    if (g.nnz > 0)
+        hipLaunchKernelGGL(k_vsum, dim3(grid_for(g.nnz, kMB * 16, 256)), dim3(kMB), 0, s, g.nnz, g.adjwgt, tot);
+    hipLaunchKernelGGL(k_vsum, dim3(grid_for(n, kMB * 16, 256)), dim3(kMB), 0, s, n, g.vwgt, tot + 1);
+    const unsigned gk = grid_for(n, kMB / kp, 4096);
+    hipLaunchKernelGGL(k_softmax, dim3(gk), dim3(kMB), 0, s, n, k, kp, a.Z, S);
     GP_LAUNCH_CHECK();
-    const float inv_omega = omega > 0 ? (float)(1.0 / (double)omega) : 0.0f;
-    hipLaunchKernelGGL(k_edge_loss, dim3(grid_for(n, kMB / kp, 4096)), dim3(kMB), 0, s, n, k, kp, g.xadj, g.adjncy,
-                       g.adjwgt, target, S, inv_omega, gS, acc);
+    hipLaunchKernelGGL(k_edge_loss, dim3(grid_for(n, 1, 1024)), dim3(kMB), 0, s, n, k, kp, g.xadj, g.adjncy,
+                       g.adjwgt, target, S, tot, gS, acc);
     GP_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_colsum, dim3(grid_for((int64_t)n * k, 256, 1024)), dim3(kMB), 0, s, n, k, S, g.vwgt,
                        acc + 1);
     GP_LAUNCH_CHECK();
-    // total vertex weight on the host (a single small copy)
-    double C = (double)n;
-    if (g.vwgt) {
-        std::vector<int32_t> hv(n);
-        GP_HIP(hipMemcpyAsync(hv.data(), g.vwgt, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost, s));
-        GP_HIP(hipStreamSynchronize(s));
-        C = 0.0;
-        for (int32_t x : hv) C += x;
-    }
-    hipLaunchKernelGGL(k_softmax_back, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, n, k, S, gS, acc + 1, 1.0 / C,
-                       lam, g.vwgt, dZ);
+    hipLaunchKernelGGL(k_softmax_back, dim3(gk), dim3(kMB), 0, s, n, k, kp, S, gS, acc + 1, tot + 1, lam, g.vwgt, dZ);
     GP_LAUNCH_CHECK();
     const Net net(k);
-    const unsigned gw = grid_for(n, kWgChunk, 512);
+    const unsigned gw = grid_for(n, kWgRows, 512);
     // head
-    hipLaunchKernelGGL(k_wgrad, dim3(gw), dim3(kMB), 0, s, n, k, kMpHid, dZ, a.H[2], grad + net.wh, grad + net.bh);
+    hipLaunchKernelGGL(k_wgrad, dim3(gw), dim3(kMB), 0, s, n, k, kMpHid, dZ,
+                       WGrad{a.H[2], grad + net.wh, grad + net.bh}, WGrad{});
     GP_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_dense_t, dim3(grid_for((int64_t)n * kMpHid, 256, 4096)), dim3(kMB), 0, s, n, k, kMpHid, dZ,
-                       a.Wt + net.wh, nullptr, dA, nullptr);
+                       a.Wt + net.wh, (const float *)nullptr, a.H[2], dA, (float *)nullptr);
     GP_LAUNCH_CHECK();
     for (int l = 2; l >= 0; l--) {
         const int32_t din = l == 0 ? kMpFeat : kMpHid;
         const float *Hin = l == 0 ? a.X : a.H[l - 1];
-        hipLaunchKernelGGL(k_relu_mask, dim3(grid_for((int64_t)n * kMpHid, 256, 8192)), dim3(256), 0, s,
-                           (int64_t)n * kMpHid, dA, a.H[l]);
-        GP_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_wgrad, dim3(gw), dim3(kMB), 0, s, n, kMpHid, din, dA, Hin, grad + net.ws[l],
-                           grad + net.b[l]);
-        GP_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_wgrad, dim3(gw), dim3(kMB), 0, s, n, kMpHid, din, dA, a.M[l], grad + net.wn[l],
-                           nullptr);
+        hipLaunchKernelGGL(k_wgrad, dim3(gw, 2), dim3(kMB), 0, s, n, kMpHid, din, dA,
+                           WGrad{Hin, grad + net.ws[l], grad + net.b[l]}, WGrad{a.M[l], grad + net.wn[l], nullptr});
         GP_LAUNCH_CHECK();
         if (l == 0) break;
         hipLaunchKernelGGL(k_dense_t, dim3(grid_for((int64_t)n * din, 256, 4096)), dim3(kMB), 0, s, n, kMpHid, din,
-                           dA, a.Wt + net.ws[l], a.Wt + net.wn[l], dB, dM);
+                           dA, a.Wt + net.ws[l], a.Wt + net.wn[l], (const float *)nullptr, dB, dM);
         GP_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_aggregate_t, dim3(grid_for((int64_t)n * din, 256, 1 << 16)), dim3(256), 0, s, n, din,
-                           g.xadj, g.adjncy, g.adjwgt, a.rinv, dM, dB);
+        hipLaunchKernelGGL(k_aggregate_t, dim3(grid_for(n, 1, 8192)), dim3(kMB), 0, s, n, g.xadj, g.adjncy, g.adjwgt,
+                           a.rinv, dM, a.H[l - 1], dB);
         GP_LAUNCH_CHECK();
         std::swap(dA, dB);
     }
     if (loss_host) {
-        std::vector<double> h((size_t)k + 1);
-        GP_HIP(hipMemcpyAsync(h.data(), acc, sizeof(double) * ((size_t)k + 1), hipMemcpyDeviceToHost, s));
+        std::vector<double> h((size_t)k + 4);
+        GP_HIP(hipMemcpyAsync(h.data(), acc, sizeof(double) * ((size_t)k + 4), hipMemcpyDeviceToHost, s));
         GP_HIP(hipStreamSynchronize(s));
+        int64_t total;
+        std::memcpy(&total, &h[k + 3], sizeof(total));
+        const double C = (double)total;
         double bal = 0.0;
         for (int32_t c = 0; c < k; c++) {
             const double d = h[1 + c] / C - 1.0 / k;
