@@ -83,8 +83,8 @@ struct AdmitCtx {
     int64_t *cutroom;    // [nlabels] room left before that tile
     // more labels
     int32_t *cpos, *segv, *segp;  // [n] position among the target's proposers; their vertices and list entries
-    int32_t *ccnt, *coff;         // [nlabels] proposers of a contested target (0 between rounds), their first slot
-    int32_t *ct;                  // contested targets
+    int32_t *ccnt;                // [nlabels] proposers of a contested target, then their first slot; 0 between rounds
+    int32_t *ct, *ctS;            // contested targets, their proposers
     int64_t *ctW;                 // W of a contested target with everything proposed
     int32_t *nct;                 // [2] contested targets, slots given out
     int vbits;
@@ -450,12 +450,15 @@ __global__ __launch_bounds__(256) void k_sadm_offsets(AdmitCtx c) {
     const int32_t m = c.nct[0];
     for (int32_t i0 = blockIdx.x * 256; i0 < m; i0 += gridDim.x * 256) {
         const int32_t i = i0 + threadIdx.x;
-        const int32_t t = i < m ? c.ct[i] : -1;
+        const int32_t t = i < m ? c.ct[i] : -1, s = t >= 0 ? c.ccnt[t] : 0;
         int32_t tot;
-        const int32_t ex = block_excl_scan<256>(t >= 0 ? c.ccnt[t] : 0, t32, &tot);
+        const int32_t ex = block_excl_scan<256>(s, t32, &tot);
         if (threadIdx.x == 0) sbase = atomicAdd(&c.nct[1], tot);
         __syncthreads();
-        if (t >= 0) c.coff[t] = sbase + ex;
+        if (t >= 0) {
+            c.ctS[i] = s;
+            c.ccnt[t] = sbase + ex;
+        }
         __syncthreads();
     }
 }
@@ -479,7 +482,7 @@ __global__ __launch_bounds__(kSadmBlock) void k_sadm_scatter(AdmitCtx c) {
         if (from >= 0) {
             atomicAdd(&val[adm_slot(key, from)], (unsigned long long)vweight(c.vwgt, v));
         } else {
-            const int32_t s = c.coff[c.prop[v]] + c.cpos[p];
+            const int32_t s = c.ccnt[c.prop[v]] + c.cpos[p];
             c.segv[s] = v;
             c.segp[s] = p;
         }
@@ -511,9 +514,9 @@ __global__ __launch_bounds__(kSelBlock) void k_sadm_select(AdmitCtx c) {
     int32_t moves = 0;
     // ---- more than 64 proposers: one workgroup per target
     for (int32_t i = blockIdx.x; i < m; i += gridDim.x) {
-        const int32_t t = c.ct[i], s = c.ccnt[t];
+        const int32_t t = c.ct[i], s = c.ctS[i];
         if (s <= kWave) continue;  // uniform
-        const int32_t *sv = c.segv + c.coff[t], *sp = c.segp + c.coff[t];
+        const int32_t *sv = c.segv + c.ccnt[t], *sp = c.segp + c.ccnt[t];
         int64_t room = 0;    // for the proposers with the digits found so far
         int32_t prefix = 0;  // those digits
         const int top = ((c.vbits + kSelBits - 1) / kSelBits - 1) * kSelBits;
@@ -583,10 +586,10 @@ __global__ __launch_bounds__(kSelBlock) void k_sadm_select(AdmitCtx c) {
     }
     // ---- at most 64 proposers: one wave per target
     for (int32_t i = blockIdx.x * NW + wid; i < m; i += gridDim.x * NW) {
-        const int32_t t = c.ct[i], s = c.ccnt[t];
-        if (s == 0 || s > kWave) continue;  // done above, or taken there
+        const int32_t t = c.ct[i], s = c.ctS[i];
+        if (s > kWave) continue;  // taken above
         const bool valid = lane < s;
-        const int32_t j = c.coff[t] + lane;
+        const int32_t j = c.ccnt[t] + lane;
         const int32_t v = valid ? c.segv[j] : INT_MAX;
         const int64_t w = valid ? vweight(c.vwgt, v) : 0;
         const int64_t room = cap_of(c, t) - c.ctW[i] + wave_sum(w);

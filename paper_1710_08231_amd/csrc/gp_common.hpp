@@ -386,22 +386,92 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <typename T>
-__device__ __forceinline__ T wave_incl_scan(T x) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        T y = __shfl_up(x, d, kWave);
-        if (lane >= d) x += y;
+// ---- cross-lane moves inside the register file (DPP, and gfx950's row and half
+// swaps): a few cycles each, where a shuffle goes through the LDS unit with its
+// latency. Every lane of the wave has to be active.
+template <int CTRL, int ROWS = 0xf, typename T>
+__device__ __forceinline__ T dpp_move(T x) {  // lanes without a source (or outside ROWS) get 0
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two registers");
+    if constexpr (sizeof(T) == 4) {
+        const int y = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, ROWS, 0xf, false);
+        return __builtin_bit_cast(T, y);
+    } else {
+        const int2 v = __builtin_bit_cast(int2, x);
+        int2 r;
+        r.x = __builtin_amdgcn_update_dpp(0, v.x, CTRL, ROWS, 0xf, false);
+        r.y = __builtin_amdgcn_update_dpp(0, v.y, CTRL, ROWS, 0xf, false);
+        return __builtin_bit_cast(T, r);
+    }
+}
+
+// The two halves' values of x for every lane, halves of 2 * D lanes (D = 16 or
+// 32): `lo` from the lanes without bit D, `hi` from those with it.
+template <int D>
+__device__ __forceinline__ void swap32(uint32_t x, uint32_t &lo, uint32_t &hi) {
+    if constexpr (D == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        lo = r[0];
+        hi = r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        lo = r[0];
+        hi = r[1];
+    }
+}
+template <int D, typename T>
+__device__ __forceinline__ void swap_halves(T x, T &lo, T &hi) {
+    if constexpr (sizeof(T) == 4) {
+        uint32_t l, h;
+        swap32<D>(__builtin_bit_cast(uint32_t, x), l, h);
+        lo = __builtin_bit_cast(T, l);
+        hi = __builtin_bit_cast(T, h);
+    } else {
+        const uint2 v = __builtin_bit_cast(uint2, x);
+        uint2 l, h;
+        swap32<D>(v.x, l.x, h.x);
+        swap32<D>(v.y, l.y, h.y);
+        lo = __builtin_bit_cast(T, l);
+        hi = __builtin_bit_cast(T, h);
+    }
+}
+
+// x reduced over aligned groups of GL lanes with a commutative op; every lane
+// gets the result. Each step joins the two halves of a twice as wide group, whose
+// lanes already agree: neighbours and pairs in a quad, the mirrored quad, the
+// mirrored half row, then the row and half swaps.
+template <int GL, typename T, typename Op>
+__device__ __forceinline__ T group_reduce(T x, Op op) {
+    if constexpr (GL >= 2) x = op(x, dpp_move<0xB1>(x));   // quad_perm [1, 0, 3, 2]
+    if constexpr (GL >= 4) x = op(x, dpp_move<0x4E>(x));   // quad_perm [2, 3, 0, 1]
+    if constexpr (GL >= 8) x = op(x, dpp_move<0x141>(x));  // row_half_mirror
+    if constexpr (GL >= 16) x = op(x, dpp_move<0x140>(x)); // row_mirror
+    if constexpr (GL >= 32) {
+        T lo, hi;
+        swap_halves<16>(x, lo, hi);
+        x = op(lo, hi);
+    }
+    if constexpr (GL >= 64) {
+        T lo, hi;
+        swap_halves<32>(x, lo, hi);
+        x = op(lo, hi);
     }
     return x;
 }
 
 template <typename T>
-__device__ __forceinline__ T wave_sum(T x) {
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d, kWave);
+__device__ __forceinline__ T wave_incl_scan(T x) {
+    x += dpp_move<0x111>(x);       // row_shr by 1, 2, 4, 8
+    x += dpp_move<0x112>(x);
+    x += dpp_move<0x114>(x);
+    x += dpp_move<0x118>(x);
+    x += dpp_move<0x142, 0xa>(x);  // row_bcast15: the last lane of rows 0 and 2 into rows 1 and 3
+    x += dpp_move<0x143, 0xc>(x);  // row_bcast31: lane 31 into the upper half
     return x;
+}
+
+template <typename T>
+__device__ __forceinline__ T wave_sum(T x) {
+    return group_reduce<kWave>(x, [](T a, T b) { return a + b; });
 }
 
 // a[key] += x over the lanes with `valid`: one atomic for the wave when all of
@@ -413,9 +483,7 @@ __device__ __forceinline__ void wave_add_keyed(T *a, int32_t key, T x, bool vali
     if (!vm) return;
     const int32_t k0 = __shfl(key, __ffsll((unsigned long long)vm) - 1, kWave);
     if (__ballot(valid && key != k0) == 0) {
-        T v = valid ? x : T(0);
-#pragma unroll
-        for (int d = kWave / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
+        const T v = wave_sum(valid ? x : T(0));
         if (lane_id() == 0) atomicAdd(&a[k0], v);
     } else if (valid) {
         atomicAdd(&a[key], x);
@@ -424,22 +492,12 @@ __device__ __forceinline__ void wave_add_keyed(T *a, int32_t key, T x, bool vali
 
 template <typename T>
 __device__ __forceinline__ T wave_max(T x) {
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) {
-        T y = __shfl_xor(x, d, kWave);
-        x = y > x ? y : x;
-    }
-    return x;
+    return group_reduce<kWave>(x, [](T a, T b) { return b > a ? b : a; });
 }
 
 template <typename T>
 __device__ __forceinline__ T wave_min(T x) {
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) {
-        T y = __shfl_xor(x, d, kWave);
-        x = y < x ? y : x;
-    }
-    return x;
+    return group_reduce<kWave>(x, [](T a, T b) { return b < a ? b : a; });
 }
 
 // Workgroup-wide exclusive scan; `tmp` must hold BLOCK/64 + 1 elements.

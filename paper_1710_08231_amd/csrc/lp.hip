@@ -198,24 +198,26 @@ __device__ __forceinline__ bool better(AccT c, int32_t L, AccT bc, int32_t bl) {
     return c > bc || (c == bc && L < bl);
 }
 
+// The best (conn, label) of each group of GL lanes, to all of them.
 template <int GL, typename AccT>
 __device__ __forceinline__ void group_best(AccT &bc, int32_t &bl) {
-#pragma unroll
-    for (int d = GL / 2; d > 0; d >>= 1) {
-        AccT oc = __shfl_xor(bc, d, GL);
-        int32_t ol = __shfl_xor(bl, d, GL);
-        if (better(oc, ol, bc, bl)) {
-            bc = oc;
-            bl = ol;
-        }
+    if constexpr (sizeof(AccT) == 4) {
+        // conn >= 0 and label in one word: larger conn, then smaller label
+        const unsigned long long x = ((unsigned long long)(uint32_t)bc << 32) | (uint32_t)~(uint32_t)bl;
+        const unsigned long long y =
+            group_reduce<GL>(x, [](unsigned long long p, unsigned long long q) { return q > p ? q : p; });
+        bc = (AccT)(y >> 32);
+        bl = (int32_t)~(uint32_t)y;
+    } else {
+        const AccT c = group_reduce<GL>(bc, [](AccT p, AccT q) { return q > p ? q : p; });
+        bl = group_reduce<GL>(bc == c ? bl : INT_MAX, [](int32_t p, int32_t q) { return q < p ? q : p; });
+        bc = c;
     }
 }
 
 template <int GL, typename T>
 __device__ __forceinline__ T group_sum(T x) {
-#pragma unroll
-    for (int d = GL / 2; d > 0; d >>= 1) x += __shfl_xor(x, d, GL);
-    return x;
+    return group_reduce<GL>(x, [](T p, T q) { return p + q; });
 }
 
 template <int BLOCK, typename AccT>
@@ -427,12 +429,7 @@ __device__ __forceinline__ void best_with_room(const LPArgs &a, const unsigned l
 
 template <int GL>
 __device__ __forceinline__ unsigned long long group_max_u64(unsigned long long x) {
-#pragma unroll
-    for (int d = GL / 2; d > 0; d >>= 1) {
-        const unsigned long long y = __shfl_xor(x, d, GL);
-        x = y > x ? y : x;
-    }
-    return x;
+    return group_reduce<GL>(x, [](unsigned long long p, unsigned long long q) { return q > p ? q : p; });
 }
 
 // GL lanes per vertex, TBL packed slots per vertex (degrees up to TBL / 2).
@@ -1979,18 +1976,19 @@ __global__ void k_hub_caps(const int32_t *xadj, const int32_t *hubs, int32_t nh,
 // ---------------------------------------------------------------- small rounds
 
 // Everything of a round after the proposals, in one workgroup, for graphs of
-// at most kFuseMax vertices (single graphs without active sets): compaction
-// of the movers in ascending vertex order, the stable sort by target, the
-// segmented prefix of mover weights per target, admission against the
-// weights of the round start, the label and weight updates and the round
-// bookkeeping. A mover is packed as
-// (target << vbits) | vertex in LDS. Position p of a sequence belongs to wave
-// p / kFuseWaveSpan, row (p % kFuseWaveSpan) / kWave, lane p % kWave, so the
-// (wave, row, lane) order is the position order.
+// at most kFuseMax vertices (single graphs without active sets): the weight
+// proposed to each target is summed in LDS, and the proposers of targets that
+// stay within their bound move. Only the proposers of the others go on:
+// compaction in ascending vertex order, the stable sort by target, the segmented
+// prefix of their weights per target and admission against the weights of the
+// round start; then the label and weight updates, the todo marks and the round
+// bookkeeping. A contested mover is packed as
+// (target << vbits) | vertex in LDS. Bound: one workgroup's latency
+// chain (loads, LDS sums, barriers); with all movers in the sort it took 10 to
+// 24 us a round.
 constexpr int kFuseBlock = 1024;
 constexpr int kFuseWaves = kFuseBlock / kWave;
 constexpr int kFuseRows = 16;
-constexpr int kFuseWaveSpan = kFuseRows * kWave;
 constexpr int kFuseMax = kFuseBlock * kFuseRows;
 constexpr int kFuseLdsLabels = 1024;  // label weights held in LDS for the whole round
 
@@ -2014,21 +2012,24 @@ __device__ __forceinline__ T fuse_excl_scan(T x, T *tmp, T *total) {
     return before + inc - x;
 }
 
-__global__ __launch_bounds__(kFuseBlock) void k_round_small(const int32_t *prop, int32_t n, int vbits,
+__global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32_t n, int vbits,
                                                             int key_bits, const int32_t *vwgt, int64_t *W,
                                                             int64_t U, const int64_t *capv, int32_t nlabels,
-                                                            int32_t *labels, uint8_t *lab8, LPDev *dev) {
+                                                            int32_t *labels, uint8_t *lab8, LPDev *dev,
+                                                            uint8_t *todo, const int32_t *xadj,
+                                                            const int32_t *adjncy) {
     constexpr int NW = kFuseWaves;
-    __shared__ uint32_t bufA[kFuseMax], bufB[kFuseMax];
+    __shared__ __align__(16) uint32_t buf[2 * kFuseMax];
+    uint32_t *const bufA = buf, *const bufB = buf + kFuseMax;
     __shared__ uint32_t wc[NW * 256];  // per (wave, digit) counters, then placement offsets
     __shared__ long long Wl[kFuseLdsLabels];
     __shared__ int32_t tmpi[NW];
     __shared__ uint32_t tmpu[NW];
     __shared__ int32_t wf[NW];
     __shared__ long long wv[NW];
+    __shared__ int32_t nlist;
     const int lane = lane_id(), w = threadIdx.x / kWave;
     const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (kWave - lane));
-    const int32_t wbase = w * kFuseWaveSpan;
     const bool wlds = nlabels <= kFuseLdsLabels;
     // everything the round reads from its start state is requested at once
     const int32_t done = dev->done;
@@ -2036,35 +2037,83 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(const int32_t *prop,
     if (threadIdx.x == 0) {
         round = dev->round;
         prev_moves = dev->prev_moves;
+        nlist = 0;
     }
+    // vertex r * kFuseBlock + thread: a small level occupies the first rows only
+    const int vrows = (n + kFuseBlock - 1) / kFuseBlock;
     int32_t t_of[kFuseRows];
+    bool mine = false;
 #pragma unroll
     for (int r = 0; r < kFuseRows; r++) {
-        const int32_t v = wbase + r * kWave + lane;
-        t_of[r] = v < n ? prop[v] : -1;
+        const int32_t v = r * kFuseBlock + (int32_t)threadIdx.x;
+        t_of[r] = v < n && !done ? prop[v] : -1;
+        mine |= t_of[r] >= 0;
     }
     if (wlds)
         for (int i = threadIdx.x; i < nlabels; i += kFuseBlock) Wl[i] = W[i];
-    // ---- compaction: movers in ascending vertex order
+    // ---- weight proposed to each target; nlabels <= kFuseMax 64-bit sums fill the two buffers
+    unsigned long long *const inflow = reinterpret_cast<unsigned long long *>(buf);
+    for (int i = threadIdx.x; i < nlabels; i += kFuseBlock) inflow[i] = 0;
+    const bool any = __syncthreads_or(mine);
+    uint32_t go = 0;  // bit r: row r's vertex moves (its target stays within its bound)
+    int32_t moves = 0;
+    int32_t m = 0;  // contested movers
     uint32_t item[kFuseRows];
     int32_t rank[kFuseRows];
-    int32_t cnt = 0;
+    if (any) {
 #pragma unroll
-    for (int r = 0; r < kFuseRows; r++) {
-        const int32_t v = wbase + r * kWave + lane;
-        const int32_t t = done ? -1 : t_of[r];
-        const uint64_t mb = __ballot(t >= 0);
-        item[r] = ((uint32_t)t << vbits) | (uint32_t)v;
-        rank[r] = (t >= 0) ? cnt + (int32_t)__popcll(mb & lt) : -1;
-        cnt += (int32_t)__popcll(mb);
+        for (int r = 0; r < kFuseRows; r++) {
+            if (r >= vrows) break;
+            const int32_t v = r * kFuseBlock + (int32_t)threadIdx.x;
+            if (t_of[r] < 0) continue;
+            prop[v] = -1;  // a settled vertex writes none next time
+            atomicAdd(&inflow[t_of[r]], (unsigned long long)vweight(vwgt, v));
+        }
+        __syncthreads();
+        long long room[kFuseRows];
+#pragma unroll
+        for (int r = 0; r < kFuseRows; r++) {
+            room[r] = 0;
+            if (r >= vrows) break;
+            const int32_t t = t_of[r];
+            if (t >= 0) room[r] = (capv ? capv[t] : U) - (wlds ? Wl[t] : W[t]);
+        }
+        bool con = false;
+#pragma unroll
+        for (int r = 0; r < kFuseRows; r++) {
+            if (r >= vrows) break;
+            if (t_of[r] < 0) continue;
+            if ((long long)inflow[t_of[r]] <= room[r]) go |= 1u << r;
+            else con = true;
+        }
+        const bool contested = __syncthreads_or(con);
+        if (contested) {
+            // ---- compaction: contested movers in ascending vertex order, counts per (row, wave)
+#pragma unroll
+            for (int r = 0; r < kFuseRows; r++) {
+                const bool x = t_of[r] >= 0 && !((go >> r) & 1);
+                const uint64_t mb = __ballot(x);
+                item[r] = ((uint32_t)t_of[r] << vbits) | (uint32_t)(r * kFuseBlock + (int32_t)threadIdx.x);
+                rank[r] = x ? (int32_t)__popcll(mb & lt) : -1;
+                if (lane == 0) wc[r * NW + w] = (uint32_t)__popcll(mb);
+            }
+            __syncthreads();
+            uint32_t tot = 0;
+            const uint32_t c0 = threadIdx.x < kFuseRows * NW ? wc[threadIdx.x] : 0u;
+            const uint32_t ex = fuse_excl_scan<uint32_t>(c0, tmpu, &tot);
+            if (threadIdx.x < kFuseRows * NW) wc[threadIdx.x] = ex;
+            __syncthreads();
+            m = (int32_t)tot;
+#pragma unroll
+            for (int r = 0; r < kFuseRows; r++)
+                if (rank[r] >= 0) bufA[wc[r * NW + w] + (uint32_t)rank[r]] = item[r];
+            __syncthreads();
+        }
     }
-    int32_t m = 0;
-    const int32_t woff = fuse_excl_scan<int32_t>(lane == 0 ? cnt : 0, tmpi, &m);
-    const int32_t wstart = __shfl(woff, 0, kWave);
-#pragma unroll
-    for (int r = 0; r < kFuseRows; r++)
-        if (rank[r] >= 0) bufA[wstart + rank[r]] = item[r];
-    __syncthreads();
+    // position p of the contested movers belongs to wave p / (rows * kWave), row
+    // (p / kWave) % rows, lane p % kWave: few movers take one row of many waves
+    const int rows = (m + kFuseBlock - 1) / kFuseBlock;
+    const int32_t wbase = w * rows * kWave;
     // ---- stable LSD sort by target, 8 bits a pass
     uint32_t *cur = bufA, *oth = bufB;
     for (int shift = 0; m > 0 && shift < key_bits; shift += 8) {
@@ -2078,7 +2127,7 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(const int32_t *prop,
             const int32_t p = wbase + r * kWave + lane;
             rank[r] = -1;
             dg[r] = 0;
-            if (wbase + r * kWave >= m) continue;  // wave-uniform
+            if (r >= rows || wbase + r * kWave >= m) continue;  // wave-uniform
             const bool valid = p < m;
             item[r] = valid ? cur[p] : 0u;
             const uint32_t dig = (item[r] >> (vbits + shift)) & mask;
@@ -2133,7 +2182,7 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(const int32_t *prop,
         const int32_t p = wbase + r * kWave + lane;
         pre[r] = 0;
         seen[r] = false;
-        if (wbase + r * kWave >= m) continue;  // wave-uniform
+        if (r >= rows || wbase + r * kWave >= m) continue;  // wave-uniform
         const bool valid = p < m;
         const uint32_t it = valid ? cur[p] : 0u;
         item[r] = it;
@@ -2169,40 +2218,70 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(const int32_t *prop,
 #pragma unroll
     for (int r = 0; r < kFuseRows; r++) {
         const int32_t p = wbase + r * kWave + lane;
-        if (p >= m) continue;
+        if (r >= rows || p >= m) continue;
         if (!seen[r]) pre[r] += carry;
         const uint32_t t = item[r] >> vbits;
         const long long wt = wlds ? Wl[t] : W[t];
         adm[p] = (wt + pre[r] <= (capv ? capv[t] : U)) ? 1 : 0;
     }
     __syncthreads();
-    // ---- labels and weights
-    int32_t moves = 0;
+    // ---- labels and weights (every decision read the weights of the round start before the barrier)
+    const auto weight = [&](int32_t t) { return (unsigned long long *)(wlds ? &Wl[t] : (long long *)&W[t]); };
+    uint32_t went = 0;  // bit r: the contested mover of row r is admitted
+    int32_t old[kFuseRows];
+#pragma unroll
+    for (int r = 0; r < kFuseRows; r++) {
+        old[r] = 0;
+        if (r >= vrows) break;
+        if ((go >> r) & 1) old[r] = labels[r * kFuseBlock + (int32_t)threadIdx.x];
+    }
+#pragma unroll
+    for (int r = 0; r < kFuseRows; r++) {
+        if (r >= vrows) break;
+        if (!((go >> r) & 1)) continue;
+        const int32_t v = r * kFuseBlock + (int32_t)threadIdx.x, t = t_of[r];
+        const unsigned long long c = (unsigned long long)vweight(vwgt, v);
+        labels[v] = t;
+        if (lab8) lab8[v] = (uint8_t)t;
+        atomicAdd(weight(old[r]), 0ull - c);
+        atomicAdd(weight(t), c);
+        moves++;
+    }
 #pragma unroll
     for (int r = 0; r < kFuseRows; r++) {
         const int32_t p = wbase + r * kWave + lane;
-        if (p >= m || !adm[p]) continue;
+        if (r >= rows || p >= m || !adm[p]) continue;
         const uint32_t t = item[r] >> vbits;
         const int32_t vx = (int32_t)(item[r] & vmask);
-        const int32_t old = labels[vx];
-        const long long c = (long long)vweight(vwgt, vx);
+        const int32_t from = labels[vx];
         labels[vx] = (int32_t)t;
         if (lab8) lab8[vx] = (uint8_t)t;
+        atomicAdd(weight(from), 0ull - (unsigned long long)vweight(vwgt, vx));
         // admitted movers form a prefix of their target's segment: its last one adds the segment's weight
         const bool tail = p + 1 == m || !adm[p + 1] || (cur[p + 1] >> vbits) != t;
-        unsigned long long *wo = wlds ? (unsigned long long *)&Wl[old] : (unsigned long long *)&W[old];
-        atomicAdd(wo, (unsigned long long)(-c));
-        if (tail) {
-            unsigned long long *wt = wlds ? (unsigned long long *)&Wl[t] : (unsigned long long *)&W[t];
-            atomicAdd(wt, (unsigned long long)pre[r]);
-        }
+        if (tail) atomicAdd(weight((int32_t)t), (unsigned long long)pre[r]);
         moves++;
+        went |= 1u << r;
     }
     int32_t total = 0;
     (void)fuse_excl_scan<int32_t>(moves, tmpi, &total);  // ends with a barrier
     if (wlds)  // this workgroup is the only writer of W in this launch
         for (int i = threadIdx.x; i < nlabels; i += kFuseBlock) W[i] = Wl[i];
-    if (threadIdx.x == 0) {  // round bookkeeping (k_round_end with this round's moves)
+    if (todo && total) {  // uniform: the admitted movers, in any order, then 16 lanes each mark the neighbours
+#pragma unroll
+        for (int r = 0; r < kFuseRows; r++) {
+            if ((go >> r) & 1) buf[atomicAdd(&nlist, 1)] = (uint32_t)(r * kFuseBlock + (int32_t)threadIdx.x);
+            if ((went >> r) & 1) buf[atomicAdd(&nlist, 1)] = item[r] & vmask;
+        }
+        __syncthreads();
+        for (int32_t i = threadIdx.x / 16; i < total; i += kFuseBlock / 16) {
+            const int32_t v = (int32_t)buf[i];
+            if (threadIdx.x % 16 == 0) todo[v] = kTodoBoth;
+            for (int32_t e = xadj[v] + (int32_t)threadIdx.x % 16; e < xadj[v + 1]; e += 16)
+                todo[adjncy[e]] = kTodoBoth;
+        }
+    }
+    if (threadIdx.x == 0) {  // round bookkeeping
         dev->round = round + 1;
         if (!done) {
             dev->rounds_run = round + 1;
@@ -2211,6 +2290,202 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(const int32_t *prop,
             dev->prev_moves = total;
             dev->round_moves = 0;
         }
+    }
+}
+
+// ---------------------------------------------------------------- settled small levels
+//
+// Refinement of a small level after its first rounds: few vertices are left to
+// evaluate, and a round's launches cost more than its work. One workgroup runs
+// all remaining rounds of at most kFuseMax vertices in one launch, labels, todo
+// bits and block weights in LDS: it collects the vertices to evaluate in
+// ascending order, evaluates each with 16 lanes (a dense table of KT sums per
+// lane group, labels from LDS), admits the movers in order and marks their
+// neighbours. The host does not launch it for graphs of more than kSettledNnz
+// entries or with vertices above the 64-lane tier (a hub's row would keep 16
+// lanes busy for long: 1.4 ms a run on R-MAT's coarse levels), and it returns as soon as more than kSettledMost vertices are to be
+// evaluated at once (the rounds go on with the launched kernels then).
+constexpr int kSettledGroups = kFuseBlock / 16;
+constexpr int kSettledMost = 2048;
+constexpr int64_t kSettledNnz = 1 << 19;
+template <int KT>
+__global__ __launch_bounds__(kFuseBlock) void k_rounds_settled(LPArgs a, int32_t n, int32_t nlabels, int32_t rounds,
+                                                               int32_t *labels, int64_t *Wg, uint8_t *lab8g,
+                                                               LPDev *dev, const uint8_t *todog) {
+    __shared__ __align__(16) uint8_t lab[kFuseMax];
+    __shared__ __align__(16) uint8_t todo[kFuseMax];
+    __shared__ int32_t tab[kSettledGroups * (KT + 1)];
+    __shared__ long long W[KT], cap[KT], run[KT], delta[KT];
+    __shared__ uint16_t list[kSettledMost];   // vertices to evaluate, then the movers, ascending
+    __shared__ uint8_t tgt[kSettledMost];     // their target
+    __shared__ uint8_t want[kSettledMost];    // 1: the evaluation found a target, then: admitted
+    __shared__ int32_t cw[kFuseBlock];        // weights of the movers at hand
+    __shared__ int32_t tmpi[kFuseWaves];
+    const int lane = lane_id(), gl = threadIdx.x % 16, grp = threadIdx.x / 16;
+    const uint64_t gm = 0xFFFFull << (lane / 16 * 16);
+    int32_t *const val = tab + grp * (KT + 1);
+    if (dev->done) return;  // uniform: nobody writes it before the last barrier
+    for (int32_t i = threadIdx.x; i < kFuseMax; i += kFuseBlock) {
+        lab[i] = i < n ? lab8g[i] : 0;
+        todo[i] = i < n ? todog[i] : 0;
+    }
+    for (int32_t i = threadIdx.x; i < KT; i += kFuseBlock) {
+        W[i] = i < nlabels ? Wg[i] : 0;
+        cap[i] = i < nlabels ? capof(a, i) : 0;
+    }
+    for (int32_t i = gl; i < KT; i += 16) val[i] = 0;
+    int32_t round = dev->round, prev = dev->prev_moves;
+    int64_t all_moves = 0;
+    bool done = false;
+    __syncthreads();
+    while (round < rounds && !done) {
+        const uint8_t bit = a.dir_alternate ? (uint8_t)(1 << (round & 1)) : (uint8_t)1;
+        const int32_t dmode = a.dir_alternate ? ((round & 1) == 0 ? 1 : 2) : 0;
+        // ---- the vertices to evaluate, ascending: 16 consecutive ones per thread
+        uint32_t live = 0;
+        {
+            const uint32_t *q = reinterpret_cast<const uint32_t *>(todo) + threadIdx.x * 4;
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const uint32_t x = q[i];
+#pragma unroll
+                for (int j = 0; j < 4; j++)
+                    if ((x >> (8 * j)) & bit) live |= 1u << (4 * i + j);
+            }
+        }
+        int32_t m = 0;
+        int32_t at = fuse_excl_scan<int32_t>(__popc(live), tmpi, &m);
+        if (m > kSettledMost) break;  // uniform
+        for (int i = 0; i < 16; i++)
+            if ((live >> i) & 1) list[at++] = (uint16_t)(threadIdx.x * 16 + i);
+        for (int32_t i = threadIdx.x; i < KT; i += kFuseBlock) {
+            run[i] = 0;
+            delta[i] = 0;
+        }
+        __syncthreads();
+        // ---- evaluation; the next vertex's row and first entries are loaded during the current one's selection
+        int32_t nv = grp < m ? list[grp] : -1;
+        int32_t nb = nv >= 0 ? a.xadj[nv] : 0, ne = nv >= 0 ? a.xadj[nv + 1] : 0;
+        int32_t nu = nb + gl < ne ? a.adjncy[nb + gl] : -1;
+        int32_t nw = nu >= 0 && a.adjwgt ? a.adjwgt[nb + gl] : 1;
+        for (int32_t i0 = 0; i0 < m; i0 += kSettledGroups) {
+            const int32_t i = i0 + grp;
+            const bool valid = i < m;
+            const int32_t v = valid ? nv : 0, b = nb, e = ne;
+            const int32_t own = lab[v];
+            int32_t oc = 0;
+            if (nu >= 0) {
+                const int32_t L = lab[nu];
+                if (L == own) oc += nw;
+                else if (dir_ok(L, own, dmode)) lds_add<int32_t>(&val[L], nw);
+            }
+            nv = i + kSettledGroups < m ? list[i + kSettledGroups] : -1;
+            nb = nv >= 0 ? a.xadj[nv] : 0;
+            ne = nv >= 0 ? a.xadj[nv + 1] : 0;
+            for (int32_t q = b + 16 + gl; q < e; q += 16) {
+                const int32_t L = lab[a.adjncy[q]], w = a.adjwgt ? a.adjwgt[q] : 1;
+                if (L == own) oc += w;
+                else if (dir_ok(L, own, dmode)) lds_add<int32_t>(&val[L], w);
+            }
+            nu = nb + gl < ne ? a.adjncy[nb + gl] : -1;
+            nw = nu >= 0 && a.adjwgt ? a.adjwgt[nb + gl] : 1;
+            wave_sync();
+            oc = group_sum<16>(oc);
+            const int64_t cv = vweight(a.vwgt, v);
+            int32_t bc = 0, bl = INT_MAX;
+            bool over = false;
+            for (int32_t L = gl; L < KT; L += 16) {
+                const int32_t c = val[L];
+                val[L] = 0;
+                over |= c > oc;
+                if (c > 0 && W[L] + cv <= cap[L] && better(c, L, bc, bl)) {
+                    bc = c;
+                    bl = L;
+                }
+            }
+            const uint64_t om = __ballot(over);
+            group_best<16, int32_t>(bc, bl);
+            if (valid && gl == 0) {
+                const bool go = bl != INT_MAX && bc > oc;
+                want[i] = go;
+                tgt[i] = (uint8_t)(go ? bl : 0);
+                if (!(om & gm)) todo[v] &= (uint8_t)~bit;
+            }
+            wave_sync();
+        }
+        __syncthreads();
+        // ---- the movers, ascending (list and tgt are compacted in place: a mover's place only falls)
+        int32_t mm = 0;
+        for (int32_t i0 = 0; i0 < m; i0 += kFuseBlock) {
+            const int32_t i = i0 + threadIdx.x;
+            const bool go = i < m && want[i];
+            const int32_t v = go ? list[i] : 0;
+            const uint8_t t = go ? tgt[i] : 0;
+            int32_t tot = 0;
+            const int32_t ex = fuse_excl_scan<int32_t>(go, tmpi, &tot);
+            if (go) {
+                list[mm + ex] = (uint16_t)v;
+                tgt[mm + ex] = t;
+            }
+            mm += tot;
+            __syncthreads();
+        }
+        // ---- admission in order, kFuseBlock movers at a time
+        int32_t moves = 0;
+        for (int32_t i0 = 0; i0 < mm; i0 += kFuseBlock) {
+            const int32_t i = i0 + threadIdx.x;
+            const bool valid = i < mm;
+            const int32_t v = valid ? list[i] : 0, t = valid ? tgt[i] : 0;
+            const long long c = valid ? (long long)vweight(a.vwgt, v) : 0;
+            long long pre = c + (valid ? run[t] : 0);
+            cw[threadIdx.x] = (int32_t)c;
+            __syncthreads();
+            if (valid)
+                for (int32_t j = i0; j < i; j++)
+                    if (tgt[j] == t) pre += cw[j - i0];
+            const bool go = valid && W[t] + pre <= cap[t];
+            __syncthreads();
+            if (valid) {
+                want[i] = go;
+                atomicAdd((unsigned long long *)&run[t], (unsigned long long)c);
+                if (go) {
+                    const int32_t old = lab[v];
+                    lab[v] = (uint8_t)t;
+                    labels[v] = t;
+                    todo[v] = kTodoBoth;
+                    atomicAdd((unsigned long long *)&delta[t], (unsigned long long)c);
+                    atomicAdd((unsigned long long *)&delta[old], 0ull - (unsigned long long)c);
+                    moves++;
+                }
+            }
+            __syncthreads();
+        }
+        // ---- neighbours of the admitted movers, 16 lanes per mover
+        for (int32_t i = grp; i < mm; i += kSettledGroups) {
+            if (!want[i]) continue;
+            const int32_t v = list[i];
+            for (int32_t q = a.xadj[v] + gl; q < a.xadj[v + 1]; q += 16) todo[a.adjncy[q]] = kTodoBoth;
+        }
+        for (int32_t i = threadIdx.x; i < KT; i += kFuseBlock) W[i] += delta[i];
+        int32_t total = 0;
+        (void)fuse_excl_scan<int32_t>(moves, tmpi, &total);  // ends with a barrier
+        all_moves += total;
+        done = round >= 1 && total == 0 && prev == 0;
+        prev = total;
+        round++;
+    }
+    __syncthreads();
+    for (int32_t i = threadIdx.x; i < nlabels; i += kFuseBlock) Wg[i] = W[i];
+    for (int32_t i = threadIdx.x; i < n; i += kFuseBlock) {
+        lab8g[i] = lab[i];
+        const_cast<uint8_t *>(todog)[i] = todo[i];
+    }
+    if (threadIdx.x == 0) {
+        dev->round = round;
+        dev->rounds_run = round;
+        dev->total_moves += all_moves;
+        dev->prev_moves = prev;
+        dev->done = done;
     }
 }
 
@@ -2696,6 +2971,9 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
             tk.bound[5] = std::max(tk.bound[4], tu.dense_split);
             tk.bound[6] = tk.bound[7] = tk.bound[8] = tk.bound[9] = tk.bound[5];
         }
+        // small levels: one launch of 32 lanes per vertex instead of up to four
+        // (each launch costs a few microseconds, and the chip is not full)
+        if (n <= kFuseMax) tk.bound[1] = tk.bound[2] = tk.bound[3] = 0;
         for (int t = 1; t < kTiers - 1; t++) tk.bound[t] = std::max(tk.bound[t], tk.bound[t - 1]);
     }
     // few workgroups: each adds its counts to one cache line
@@ -2893,7 +3171,7 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     }
     const int key_bits = bits_for(nlabels > 0 ? nlabels - 1 : 0);
     const int vbits = bits_for(n > 0 ? n - 1 : 0);
-    const bool fuse_rest = !group && !active && n <= kFuseMax && vbits + key_bits <= 32;
+    const bool fuse_rest = !group && !active && n <= kFuseMax && nlabels <= kFuseMax && vbits + key_bits <= 32;
     AdmitCtx ac{};
     if (!fuse_rest) {
         ac.n = n;
@@ -2933,10 +3211,10 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
             ac.segv = reinterpret_cast<int32_t *>(tkey);
             ac.segp = reinterpret_cast<int32_t *>(tkey2);
             GP_TRY(sc.alloc(&ac.ccnt, nlabels));
-            GP_TRY(sc.alloc(&ac.coff, nlabels));
             // a contested target has at least two proposers (each alone fits)
             GP_TRY(sc.alloc(&ac.ct, n / 2));
             GP_TRY(sc.alloc(&ac.ctW, n / 2));
+            GP_TRY(sc.alloc(&ac.ctS, n / 2));
             GP_TRY(sc.alloc(&ac.nct, 2));
             GP_HIP(hipMemsetAsync(ac.ccnt, 0, sizeof(int32_t) * (size_t)nlabels, s));
             GP_HIP(hipMemsetAsync(ac.nct, 0, sizeof(int32_t) * 2, s));
@@ -2962,7 +3240,10 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     // settled vertices are skipped in refinement (labels are blocks of at least
     // four vertices on average) where the round tail leaves lists of the movers;
     // in clustering most vertices neighbour a mover in every round
-    if (!fuse_rest && !act && (int64_t)nlabels * 4 <= n) {
+    // (on small levels, where one launch can then run all later rounds)
+    const bool settled = fuse_rest && dense && !wide && nbig == 0 && g.nnz <= kSettledNnz && (int64_t)nlabels * 4 <= n &&
+                         rounds > 2 && !use_round_graphs() && !prof_blocks_replay();
+    if (settled || (!fuse_rest && !act && (int64_t)nlabels * 4 <= n)) {
         GP_TRY(sc.alloc(&ac.todo, n));
         GP_HIP(hipMemsetAsync(ac.todo, kTodoBoth, (size_t)n, s));
     }
@@ -3089,7 +3370,7 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         }
         if (fuse_rest) {  // small level: the rest of the round in one launch
             hipLaunchKernelGGL(k_round_small, dim3(1), dim3(kFuseBlock), 0, s, prop, (int32_t)n, vbits, key_bits,
-                               g.vwgt, W, U, capv, (int32_t)nlabels, labels, lab8, dev);
+                               g.vwgt, W, U, capv, (int32_t)nlabels, labels, lab8, dev, ac.todo, g.xadj, g.adjncy);
             GP_LAUNCH_CHECK();
             return GP_OK;
         }
@@ -3133,7 +3414,34 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         return GP_OK;
     };
     GP_TRY(emit_round(s));
-    if (rounds > 1) {
+    if (settled) {
+        {
+            const ProfSuspend quiet(prof_first_round_only());
+            GP_TRY(emit_round(s));
+        }
+        LPArgs a{};
+        a.xadj = g.xadj;
+        a.adjncy = g.adjncy;
+        a.adjwgt = g.adjwgt;
+        a.vwgt = g.vwgt;
+        a.U = U;
+        a.capv = capv;
+        a.dir_alternate = dir_alternate;
+        const dim3 one(1), block(kFuseBlock);
+        if (KTd == 16)
+            hipLaunchKernelGGL(k_rounds_settled<16>, one, block, 0, s, a, n, nlabels, rounds, labels, W, lab8, dev, ac.todo);
+        else if (KTd == 64)
+            hipLaunchKernelGGL(k_rounds_settled<64>, one, block, 0, s, a, n, nlabels, rounds, labels, W, lab8, dev, ac.todo);
+        else
+            hipLaunchKernelGGL(k_rounds_settled<256>, one, block, 0, s, a, n, nlabels, rounds, labels, W, lab8, dev, ac.todo);
+        GP_LAUNCH_CHECK();
+        LPDev h;
+        GP_HIP(hipMemcpyAsync(&h, dev, sizeof(LPDev), hipMemcpyDeviceToHost, s));
+        GP_HIP(hipStreamSynchronize(s));
+        const ProfSuspend quiet(prof_first_round_only());
+        // (it stopped before them where too many vertices were to be evaluated)
+        for (int32_t r = h.done ? rounds : h.round; r < rounds; r++) GP_TRY(emit_round(s));
+    } else if (rounds > 1) {
         bool replayed = false;
         if (use_round_graphs() && !prof_blocks_replay() && !sc.is_static()) {
             hipStream_t cs = capture_stream();
