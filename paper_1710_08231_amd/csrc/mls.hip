@@ -94,12 +94,6 @@ __global__ void k_begin_global(Ctl *c, const int32_t *count) {
     c->nnext = 0;
 }
 
-__global__ void k_begin_local(Ctl *c) {
-    c->ti = 0;
-    c->nnext = 0;
-    c->lgain = 0;
-}
-
 __global__ void k_next_to_todo(const int32_t *next, int32_t *todo, Ctl *c) {
     const int32_t nn = c->nnext;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nn; i += (int64_t)gridDim.x * blockDim.x)
@@ -117,38 +111,60 @@ __global__ void k_reset_marks(Ctl *c) { c->nmark = 0; }
 
 // ---------------------------------------------------------------- one batch
 
-// The next seeds: unmarked todo entries from the cursor, at most `batch`.
-__global__ __launch_bounds__(kAB) void k_window(const int32_t *todo, const int32_t *marked, int32_t batch, Ctl *c,
-                                                int32_t *sel, int32_t *selpos) {
-    __shared__ int32_t tmp[kAB / kWave + 1];
-    __shared__ int32_t s_sel, s_end;
-    const int32_t ti = c->ti, ntodo = c->ntodo;
+__device__ __forceinline__ int32_t ld_l2(const int32_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The next seeds: unmarked todo entries from the cursor, at most `batch`; without
+// any the cursor goes to the end. One workgroup; marks may have been set by it.
+struct Window {
+    const int32_t *todo, *marked;
+    int32_t batch;
+    int32_t *sel, *selpos;
+};
+struct WindowLds {
+    int32_t tmp[kAB / kWave + 1];
+    int32_t sel, end;
+};
+__device__ void next_window(const Window &wd, Ctl *c, int32_t ti, int32_t ntodo, WindowLds &L) {
     if (threadIdx.x == 0) {
-        s_sel = 0;
-        s_end = ntodo;
+        L.sel = 0;
+        L.end = ntodo;
     }
     __syncthreads();
     for (int32_t p0 = ti; p0 < ntodo; p0 += kAB) {
-        const int32_t base = s_sel;
+        const int32_t base = L.sel;
         const int32_t idx = p0 + (int32_t)threadIdx.x;
-        const int32_t f = (idx < ntodo && !marked[todo[idx]]) ? 1 : 0;
+        const int32_t v = idx < ntodo ? wd.todo[idx] : -1;
+        const int32_t f = (v >= 0 && !ld_l2(wd.marked + v)) ? 1 : 0;
         int32_t tot = 0;
-        const int32_t r = block_excl_scan<kAB, int32_t>(f, tmp, &tot);
-        if (f && base + r < batch) {
-            sel[base + r] = todo[idx];
-            selpos[base + r] = idx;
-            if (base + r == batch - 1) s_end = idx + 1;
+        const int32_t r = block_excl_scan<kAB, int32_t>(f, L.tmp, &tot);
+        if (f && base + r < wd.batch) {
+            wd.sel[base + r] = v;
+            wd.selpos[base + r] = idx;
+            if (base + r == wd.batch - 1) L.end = idx + 1;
         }
         __syncthreads();
-        if (threadIdx.x == 0) s_sel = min(batch, base + tot);
+        if (threadIdx.x == 0) L.sel = min(wd.batch, base + tot);
         __syncthreads();
-        if (s_sel >= batch) break;
+        if (L.sel >= wd.batch) break;
     }
     if (threadIdx.x == 0) {
-        c->nsel = s_sel;
-        c->tiw = s_end;
+        c->ti = L.sel > 0 ? ti : ntodo;
+        c->nsel = L.sel;
+        c->tiw = L.end;
         c->clash = INT_MAX;
     }
+}
+
+// Start of a local iteration: its first window.
+__global__ __launch_bounds__(kAB) void k_begin_local(Window wd, Ctl *c) {
+    __shared__ WindowLds L;
+    if (threadIdx.x == 0) {
+        c->nnext = 0;
+        c->lgain = 0;
+    }
+    next_window(wd, c, 0, c->ntodo, L);
 }
 
 // Claims of the window seeds' closed neighbourhoods. first[u] keeps the
@@ -157,17 +173,23 @@ __global__ __launch_bounds__(kAB) void k_window(const int32_t *todo, const int32
 // two smallest claimants of u comes second sees the other and offers the
 // larger index, i.e. u's second-smallest claimant; the smallest offer over
 // all u is the first seed whose neighbourhood meets an earlier one's.
-__global__ __launch_bounds__(256) void k_claim(MG g, const int32_t *sel, Ctl *c, unsigned long long *first) {
-    const int32_t i = blockIdx.x;
-    if (i >= c->nsel) return;
-    const int32_t s = sel[i];
+// A seed at or behind a clash already found need not claim: it could only offer
+// indices behind it.
+__device__ __forceinline__ void claim(const MG &g, int32_t i, int32_t s, int32_t b, int32_t e, Ctl *c,
+                                      unsigned long long *first, int tid, int nt) {
     const uint32_t tag = ~c->epoch;
-    const int32_t b = g.xadj[s], e = g.xadj[s + 1];
-    for (int32_t t = b - 1 + (int32_t)threadIdx.x; t < e; t += blockDim.x) {
+    for (int32_t t = b - 1 + tid; t < e; t += nt) {
         const int32_t u = t < b ? s : g.adjncy[t];
         const unsigned long long old = atomicMin(&first[u], ((unsigned long long)tag << 32) | (uint32_t)i);
         if ((uint32_t)(old >> 32) == tag) atomicMin(&c->clash, max((int32_t)(uint32_t)old, i));
     }
+}
+
+__global__ __launch_bounds__(256) void k_claim(MG g, const int32_t *sel, Ctl *c, unsigned long long *first) {
+    const int32_t i = blockIdx.x;
+    if (i >= c->nsel) return;
+    const int32_t s = sel[i];
+    claim(g, i, s, g.xadj[s], g.xadj[s + 1], c, first, threadIdx.x, 256);
 }
 
 struct SearchArgs {
@@ -178,7 +200,8 @@ struct SearchArgs {
     const int64_t *B;
     const int32_t *marked;
     const int32_t *sel;
-    const Ctl *c;
+    Ctl *c;
+    unsigned long long *first;
     int32_t q, max_idle;
     int32_t *mv_v, *mv_f, *mv_t, *mv_n;  // kept prefix of search j at j * kMlsMaxQueue
     int32_t *mk_v, *mk_n;                // vertices search j queued (its marks)
@@ -226,16 +249,11 @@ __device__ __forceinline__ int32_t label_in(const SearchArgs &a, const WaveLds &
     return s >= 0 ? L.plab[s] : a.part[x];
 }
 
+// largest bc of the wave, and the smallest bl among the lanes that hold it
 __device__ __forceinline__ void best_pair(long long &bc, int32_t &bl) {
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) {
-        const long long oc = __shfl_xor(bc, d, kWave);
-        const int32_t ol = __shfl_xor(bl, d, kWave);
-        if (oc > bc || (oc == bc && ol < bl)) {
-            bc = oc;
-            bl = ol;
-        }
-    }
+    const long long c = wave_max(bc);
+    bl = wave_min(bc == c ? bl : INT_MAX);
+    bc = c;
 }
 
 // From a vertex's connection sums: the best adjacent other block with room
@@ -329,12 +347,7 @@ __device__ void eval_flags(const SearchArgs &a, WaveLds &L, int32_t queued) {
             b0 = a.g.xadj[u];
             d = a.g.xadj[u + 1] - b0;
         }
-        int32_t inc = d;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int32_t y = __shfl_up(inc, o, kWave);
-            if (lane >= o) inc += y;
-        }
+        const int32_t inc = wave_incl_scan(d);
         if (member) {
             L.gpre[r] = inc - d;
             L.gbase[r] = b0;
@@ -369,6 +382,18 @@ __device__ void eval_flags(const SearchArgs &a, WaveLds &L, int32_t queued) {
     }
 }
 
+// The lane of the largest (kk, then smallest vv) among those with `in`, -1: none; kk: its key.
+__device__ __forceinline__ int32_t queue_max(long long &kk, int32_t vv, bool in) {
+    const long long keep = kk;
+    const uint64_t any = __ballot(in);
+    if (!any) return -1;
+    if (__ballot(in && kk != (int32_t)kk) == 0) kk = wave_max(in ? (int32_t)kk : INT_MIN);  // half the steps
+    else kk = wave_max(in ? kk : LLONG_MIN);
+    const bool top = in && keep == kk;
+    const int32_t v = wave_min(top ? vv : INT_MAX);
+    return __ffsll((unsigned long long)__ballot(top && vv == v)) - 1;
+}
+
 __global__ __launch_bounds__(kWave * kSW) void k_search(SearchArgs a) {
     __shared__ WaveLds lds[kSW];
     const int w = threadIdx.x / kWave, lane = lane_id();
@@ -395,19 +420,7 @@ __global__ __launch_bounds__(kWave * kSW) void k_search(SearchArgs a) {
         // the queued vertex of largest gain, ties -> lower id
         const bool in = lane < queued && L.inh[lane];
         long long kk = in ? L.key[lane] : LLONG_MIN;
-        int32_t vv = in ? L.qv[lane] : INT_MAX;
-        int32_t ss = in ? lane : -1;
-#pragma unroll
-        for (int d = kWave / 2; d > 0; d >>= 1) {
-            const long long ok = __shfl_xor(kk, d, kWave);
-            const int32_t ov = __shfl_xor(vv, d, kWave);
-            const int32_t os = __shfl_xor(ss, d, kWave);
-            if (ok > kk || (ok == kk && ov < vv)) {
-                kk = ok;
-                vv = ov;
-                ss = os;
-            }
-        }
+        const int32_t ss = queue_max(kk, in ? L.qv[lane] : INT_MAX, in);
         if (ss < 0) break;  // queue empty
         long long gn;
         int32_t t;
@@ -460,6 +473,299 @@ __global__ __launch_bounds__(kWave * kSW) void k_search(SearchArgs a) {
     }
 }
 
+// ---- the same search with the connection sums kept
+//
+// Up to KT blocks, the sums of every queued vertex stay in LDS: they are taken
+// from its edges once, when it is queued, and a move of the search changes those
+// of its queued neighbours by the edge's weight. The gains are those of a
+// recomputation (whole numbers). Queue slot = lane: a slot's vertex, label and key
+// are that lane's registers, and all gains come from one pass over the blocks.
+// The queued vertices' rows are kept too while they fit kRowCache entries, so a
+// move that queues nothing new touches LDS only.
+// Bound: one wave's instructions and the latency of its dependent steps, about
+// 2.5 us a move. rgg 2^17, k = 16, queue 64: a batch took 225 us with the sums taken
+// from the edges for every gain, and takes 80 us, its claims (5 us before) included.
+constexpr int kRowCache = 1024;
+constexpr int32_t kMarkBit = INT_MIN;
+constexpr int kRowBatch = 4;  // edges a lane has in flight while new rows are read
+
+template <int KT>
+struct RowsLds {
+    long long conn[KT][kMlsMaxQueue];  // [block][slot]
+    long long room[KT];                // L_max less the block's weight, in the search's view
+    int2 h[kHT];                       // queued vertex -> slot
+    int32_t plab[kMlsMaxQueue];        // labels of the slots in the search's view
+    int32_t inh[kMlsMaxQueue], flag[kMlsMaxQueue];
+    int32_t qv[kMlsMaxQueue], row[kMlsMaxQueue], deg[kMlsMaxQueue], cw[kMlsMaxQueue];
+    int32_t pre[kMlsMaxQueue + 1];
+    // the cached rows: neighbour and edge weight; of neighbours outside the queue when
+    // the row was read: label (kMarkBit: marked), row start, degree, weight
+    int32_t cu[kRowCache], cwt[kRowCache], cp[kRowCache], cb[kRowCache], cd[kRowCache], cvw[kRowCache];
+};
+
+template <int KT>
+__device__ __forceinline__ int32_t r_find(const RowsLds<KT> &L, int32_t x) {
+    uint32_t h = hslot(x);
+    for (;;) {
+        const int2 e = L.h[h];
+        if (e.x == x) return e.y;
+        if (e.x < 0) return -1;
+        h = (h + 1) & (kHT - 1);
+    }
+}
+
+__device__ __forceinline__ int32_t clash_now(const SearchArgs &a) {
+    return __builtin_amdgcn_readfirstlane(ld_l2(&a.c->clash));
+}
+
+// x of lane l, l the same in every lane
+__device__ __forceinline__ int32_t lane_of(int32_t x, int32_t l) { return __builtin_amdgcn_readlane(x, l); }
+
+// What queueing vertex x needs to know of it.
+struct Vtx {
+    int32_t p, row, deg, cw;
+};
+__device__ __forceinline__ Vtx read_vtx(const SearchArgs &a, int32_t x) {
+    const int32_t mk = a.marked[x], p = a.part[x], b = a.g.xadj[x], e = a.g.xadj[x + 1];
+    return Vtx{mk ? p | kMarkBit : p, b, e - b, a.g.vwgt ? a.g.vwgt[x] : 1};
+}
+
+// Queues the unmarked vertices of the list that are not queued yet, as scan_list
+// does; returns the new length. from >= 0: the list is the row of a vertex that went
+// from block `from` to `to`: the sums of its queued neighbours follow, and those
+// in the queue are flagged. at >= 0: the list is a cached row.
+template <int KT>
+__device__ __forceinline__ int32_t rows_scan(const SearchArgs &a, RowsLds<KT> &L, int32_t at, const int32_t *list,
+                                             const int32_t *wts, int32_t len, int32_t queued, int32_t from,
+                                             int32_t to) {
+    const int lane = lane_id();
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
+    const int32_t q0 = queued;
+    for (int32_t i0 = 0; i0 < len; i0 += kWave) {
+        if (from < 0 && queued >= a.q) break;
+        const int32_t i = i0 + lane;
+        int32_t x = -1, w = 1;
+        if (i < len) {
+            x = at >= 0 ? L.cu[at + i] : list[i];
+            if (from >= 0) w = at >= 0 ? L.cwt[at + i] : wts ? wts[i] : 1;
+        }
+        const int32_t s = x >= 0 ? r_find(L, x) : -1;
+        if (s >= 0 && s < q0 && from >= 0) {
+            atomicAdd((unsigned long long *)&L.conn[from][s], 0ull - (unsigned long long)w);
+            atomicAdd((unsigned long long *)&L.conn[to][s], (unsigned long long)w);
+            if (L.inh[s]) L.flag[s] = 1;
+        }
+        bool cand = x >= 0 && s < 0;
+        if (queued < a.q && __ballot(cand)) {
+            Vtx v{};
+            if (cand) {
+                if (at >= 0) v = Vtx{L.cp[at + i], L.cb[at + i], L.cd[at + i], L.cvw[at + i]};
+                else v = read_vtx(a, x);
+                cand = !(v.p & kMarkBit);
+            }
+            const uint64_t m = __ballot(cand);
+            wave_sync();
+            const int32_t room = a.q - queued;
+            const int32_t r = (int32_t)__popcll(m & lt);
+            if (cand && r < room) {
+                const int32_t slot = queued + r;
+                L.qv[slot] = x;
+                L.plab[slot] = v.p;
+                L.cw[slot] = v.cw;
+                L.row[slot] = v.row;
+                L.deg[slot] = v.deg;
+                L.flag[slot] = 2;
+                uint32_t h = hslot(x);
+                while (atomicCAS(&L.h[h].x, -1, x) != -1) h = (h + 1) & (kHT - 1);
+                L.h[h].y = slot;
+            }
+            queued += min((int32_t)__popcll(m), room);
+            wave_sync();
+        }
+    }
+    wave_sync();
+    return queued;
+}
+
+template <int KT>
+__global__ __launch_bounds__(kWave) void k_search_rows(SearchArgs a) {
+    __shared__ RowsLds<KT> L;
+    const int lane = lane_id();
+    const int32_t j = blockIdx.x;
+    if (j >= a.c->nsel || j >= clash_now(a)) return;
+    const int32_t s = a.sel[j];
+    const int32_t sb = a.g.xadj[s], se = a.g.xadj[s + 1];
+    claim(a.g, j, s, sb, se, a.c, a.first, lane, kWave);
+    // the clash only falls while the claims come in: a search behind it is not wanted
+    if (j >= clash_now(a)) return;
+    for (int i = lane; i < kHT; i += kWave) L.h[i].x = -1;
+    for (int b = 0; b < KT; b++) L.conn[b][lane] = 0;
+    for (int b = lane; b < KT; b += kWave) L.room[b] = b < a.k ? a.lmax - a.B[b] : LLONG_MIN;
+    L.inh[lane] = 0;
+    L.flag[lane] = 0;
+    wave_sync();
+    // the seed, then its neighbours in adjacency order
+    int32_t queued = rows_scan(a, L, -1, a.sel + j, nullptr, 1, 0, -1, 0);
+    queued = rows_scan(a, L, -1, a.g.adjncy + sb, nullptr, se - sb, queued, -1, 0);
+    // slot `lane`: vertex, weight, label, row, place in the row cache (-1: not there); key: gain in the queue
+    int32_t qv = 0, cw = 0, own = 0, row = 0, deg = 0, at = -1;
+    long long key = LLONG_MIN;
+    bool in = false;
+    int32_t first = 0, used = 0;  // slots before `first` have their sums
+    int32_t nlog = 0, bestlen = 0, idle = 0;
+    int32_t lv = 0, lf = 0, lt = 0;  // the move log, entry `lane`
+    long long cum = 0, best = 0;
+    for (;;) {
+        if (first < queued) {
+            const int32_t clash = ld_l2(&a.c->clash);
+            // sums of the newly queued slots from their edges
+            const bool mine = lane >= first && lane < queued;
+            if (mine) {
+                qv = L.qv[lane];
+                cw = L.cw[lane];
+                own = L.plab[lane];
+                row = L.row[lane];
+                deg = L.deg[lane];
+            }
+            const int32_t d = mine ? deg : 0;
+            const int32_t inc = wave_incl_scan(d);
+            const int32_t total = __shfl(inc, kWave - 1, kWave);
+            const bool keep = total <= kRowCache - used;
+            if (mine) {
+                L.pre[lane] = inc - d;
+                at = keep ? used + inc - d : -1;
+            }
+            if (lane == 0) L.pre[queued] = total;
+            wave_sync();
+            int32_t q = first;
+            for (int32_t f0 = lane; f0 < total; f0 += kRowBatch * kWave) {
+                int32_t sl[kRowBatch], x[kRowBatch], w[kRowBatch];
+                Vtx v[kRowBatch];
+#pragma unroll
+                for (int i = 0; i < kRowBatch; i++) {
+                    const int32_t f = f0 + i * kWave;
+                    sl[i] = -1;
+                    if (f < total) {
+                        while (f >= L.pre[q + 1]) q++;
+                        const int32_t e = L.row[q] + (f - L.pre[q]);
+                        sl[i] = q;
+                        x[i] = a.g.adjncy[e];
+                        w[i] = a.g.adjwgt ? a.g.adjwgt[e] : 1;
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < kRowBatch; i++) {
+                    v[i] = Vtx{};
+                    if (sl[i] < 0) continue;
+                    const int32_t t = r_find(L, x[i]);
+                    if (t >= 0) v[i].p = L.plab[t];
+                    else if (keep) v[i] = read_vtx(a, x[i]);
+                    else v[i].p = a.part[x[i]];
+                }
+#pragma unroll
+                for (int i = 0; i < kRowBatch; i++) {
+                    if (sl[i] < 0) continue;
+                    atomicAdd((unsigned long long *)&L.conn[v[i].p & ~kMarkBit][sl[i]], (unsigned long long)w[i]);
+                    if (keep) {
+                        const int32_t c = used + f0 + i * kWave;
+                        L.cu[c] = x[i];
+                        L.cwt[c] = w[i];
+                        L.cp[c] = v[i].p;
+                        L.cb[c] = v[i].row;
+                        L.cd[c] = v[i].deg;
+                        L.cvw[c] = v[i].cw;
+                    }
+                }
+            }
+            if (j >= __builtin_amdgcn_readfirstlane(clash)) return;
+            if (keep) used += total;
+            first = queued;
+            wave_sync();
+        }
+        // every slot's best adjacent other block with room (ties: lowest block) and gain
+        long long gain = 0;
+        int32_t tgt = -1;
+        const int kb = KT == 16 ? KT : a.k;
+#pragma unroll 16
+        for (int b = 0; b < kb; b++) {
+            const long long cb = L.conn[b][lane], rb = L.room[b];
+            const bool up = (b != own) & (cb > gain) & (cw <= rb);
+            gain = up ? cb : gain;
+            tgt = up ? b : tgt;
+        }
+        gain -= L.conn[own][lane];
+        const int32_t fl = L.flag[lane];
+        if (fl) {
+            // a re-evaluated entry takes its new gain or leaves, a new one enters if it has a move
+            if (tgt >= 0) {
+                key = gain;
+                in = true;
+            } else if (fl == 1) {
+                in = false;
+            }
+            L.flag[lane] = 0;
+            L.inh[lane] = in;
+        }
+        // the queued vertex of largest gain, ties -> lower id; a stale gain goes back first
+        int32_t ss;
+        for (;;) {
+            long long kk = key;
+            ss = queue_max(kk, qv, in);
+            if (ss < 0) break;
+            if (__ballot(lane == ss && tgt >= 0 && gain == key)) break;
+            if (lane == ss) {
+                if (tgt < 0) {
+                    in = false;
+                    L.inh[lane] = 0;
+                } else {
+                    key = gain;
+                }
+            }
+        }
+        if (ss < 0) break;  // queue empty
+        ss = __builtin_amdgcn_readfirstlane(ss);
+        const int32_t mv = lane_of(qv, ss), from = lane_of(own, ss), t = lane_of(tgt, ss), mat = lane_of(at, ss),
+                      mrow = lane_of(row, ss), mdeg = lane_of(deg, ss);
+        cum += (long long)(((uint64_t)(uint32_t)lane_of((int32_t)(gain >> 32), ss) << 32) |
+                           (uint32_t)lane_of((int32_t)gain, ss));
+        if (lane == nlog) {
+            lv = mv;
+            lf = from;
+            lt = t;
+        }
+        if (lane == ss) {
+            in = false;
+            own = t;
+            L.inh[lane] = 0;
+            L.plab[lane] = t;
+            L.room[from] += cw;
+            L.room[t] -= cw;
+        }
+        wave_sync();
+        nlog++;
+        if (cum > best) {
+            best = cum;
+            bestlen = nlog;
+            idle = 0;
+        } else if (++idle >= a.max_idle) {
+            break;
+        }
+        queued = rows_scan(a, L, mat, a.g.adjncy + mrow, a.g.adjwgt ? a.g.adjwgt + mrow : nullptr, mdeg, queued, from,
+                           t);
+    }
+    const int64_t o = (int64_t)j * kMlsMaxQueue;
+    if (lane < bestlen) {
+        a.mv_v[o + lane] = lv;
+        a.mv_f[o + lane] = lf;
+        a.mv_t[o + lane] = lt;
+    }
+    if (lane < queued) a.mk_v[o + lane] = L.qv[lane];
+    if (lane == 0) {
+        a.mv_n[j] = bestlen;
+        a.mk_n[j] = queued;
+    }
+}
+
 struct ApplyArgs {
     MG g;
     int32_t k;
@@ -468,108 +774,150 @@ struct ApplyArgs {
     int64_t *B;
     int32_t *marked, *marklist, *next;
     Ctl *c;
-    const int32_t *selpos;
     const int32_t *mv_v, *mv_f, *mv_t, *mv_n, *mk_v, *mk_n;
+    Window wd;
 };
-
-__device__ __forceinline__ int32_t ld_part(const int32_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // ApplyMoves: the batch's kept prefixes in seed order, every gain recomputed
 // on the current partition; a prefix is cut at a vertex that already left its
-// block or a target without room, and kept up to its best recomputed gain.
+// block or a target without room, and kept up to its best recomputed gain. A
+// prefix's vertices are distinct, so all its gains come from one pass over its
+// rows: a neighbour's label is the target of an earlier move of the prefix, or
+// the label that it had before the prefix. Then the next batch's seeds.
+// One workgroup; bound: a few dependent accesses to memory for each prefix that
+// is not empty (most are: rgg 2^17, k = 16 keeps 377 moves in 1385 searches).
 __global__ __launch_bounds__(kAB) void k_apply(ApplyArgs a) {
     __shared__ long long sB[kMlsMaxK];
-    __shared__ long long red[2][kAB / kWave];
-    const int32_t nsel = a.c->nsel;
-    if (nsel == 0) {
-        if (threadIdx.x == 0) a.c->ti = a.c->ntodo;
-        return;
-    }
-    const int32_t ns = min(a.c->clash, nsel);
+    __shared__ long long gain[kMlsMaxQueue];
+    __shared__ int32_t mv[kMlsMaxQueue], mf[kMlsMaxQueue], mt[kMlsMaxQueue], mw[kMlsMaxQueue], now[kMlsMaxQueue],
+        base[kMlsMaxQueue], pre[kMlsMaxQueue + 1];
+    __shared__ int2 h[kHT];  // moved vertex -> place in the prefix
+    __shared__ int32_t list[kAB], nml[kAB], tmp[kAB / kWave + 1];
+    __shared__ WindowLds wl;
+    __shared__ int32_t s_len;
+    __shared__ long long s_gain;
+    Ctl *c = a.c;
+    const int32_t nsel = c->nsel;
+    if (nsel == 0) return;  // the cursor is at the end
+    const int32_t ns = min(c->clash, nsel), ntodo = c->ntodo;
+    const int32_t ti = c->clash < nsel ? a.wd.selpos[c->clash] : c->tiw;
     for (int b = threadIdx.x; b < a.k; b += kAB) sB[b] = a.B[b];
-    __syncthreads();
     const int lane = lane_id(), w = threadIdx.x / kWave;
+    // the batch's marks hold for the rest of the local iteration
+    for (int32_t j = w; j < ns; j += kAB / kWave) {
+        const int32_t mk = a.mk_n[j];
+        const int32_t u = lane < mk ? a.mk_v[(int64_t)j * kMlsMaxQueue + lane] : 0;
+        const bool fresh = lane < mk && atomicExch(&a.marked[u], 1) == 0;
+        const uint64_t m = __ballot(fresh);
+        if (!m) continue;
+        int32_t at = 0;
+        if (lane == 0) at = atomicAdd(&c->nmark, (int32_t)__popcll(m));
+        at = __shfl(at, 0, kWave);
+        if (fresh) a.marklist[at + (int32_t)__popcll(m & (lane == 0 ? 0ull : (~0ull >> (kWave - lane))))] = u;
+    }
     long long lg = 0, kept = 0;
-    int32_t nnext = a.c->nnext;
-    for (int32_t j = 0; j < ns; j++) {
-        const int64_t o = (int64_t)j * kMlsMaxQueue;
-        const int32_t nm = a.mv_n[j];
-        long long cum = 0, best = 0;
-        int32_t na = 0, bestlen = 0;
-        for (int32_t m = 0; m < nm; m++) {
-            const int32_t v = a.mv_v[o + m], f = a.mv_f[o + m], t = a.mv_t[o + m];
-            const long long cv = vw(a.g, v);
-            if (ld_part(a.part + v) != f || sB[t] + cv > a.lmax) break;  // uniform
-            long long ct = 0, cf = 0;
-            for (int32_t e = a.g.xadj[v] + threadIdx.x; e < a.g.xadj[v + 1]; e += kAB) {
-                const int32_t pu = ld_part(a.part + a.g.adjncy[e]);
-                if (pu == t) ct += ew(a.g, e);
-                else if (pu == f) cf += ew(a.g, e);
-            }
-            ct = wave_sum(ct);
-            cf = wave_sum(cf);
-            if (lane == 0) {
-                red[0][w] = ct;
-                red[1][w] = cf;
+    int32_t nnext = c->nnext;
+    for (int32_t j0 = 0; j0 < ns; j0 += kAB) {
+        // the searches with moves among the next kAB
+        const int32_t n_here = j0 + (int32_t)threadIdx.x < ns ? a.mv_n[j0 + threadIdx.x] : 0;
+        int32_t nl = 0;
+        const int32_t p = block_excl_scan<kAB, int32_t>(n_here > 0, tmp, &nl);
+        if (n_here > 0) {
+            list[p] = j0 + threadIdx.x;
+            nml[p] = n_here;
+        }
+        __syncthreads();
+        for (int32_t l = 0; l < nl; l++) {
+            const int32_t nm = nml[l];
+            const int64_t o = (int64_t)list[l] * kMlsMaxQueue;
+            for (int i = threadIdx.x; i < kHT; i += kAB) h[i].x = -1;
+            int32_t v = 0, d = 0;
+            if (w == 0) {
+                if (lane < nm) {
+                    v = a.mv_v[o + lane];
+                    mv[lane] = v;
+                    mf[lane] = a.mv_f[o + lane];
+                    mt[lane] = a.mv_t[o + lane];
+                    now[lane] = ld_l2(a.part + v);
+                    mw[lane] = a.g.vwgt ? a.g.vwgt[v] : 1;
+                    base[lane] = a.g.xadj[v];
+                    d = a.g.xadj[v + 1] - base[lane];
+                    gain[lane] = 0;
+                }
+                const int32_t inc = wave_incl_scan(d);
+                if (lane < nm) pre[lane] = inc - d;
+                if (lane == kWave - 1) pre[nm] = inc;
             }
             __syncthreads();
-            ct = 0;
-            cf = 0;
-            for (int i = 0; i < kAB / kWave; i++) {
-                ct += red[0][i];
-                cf += red[1][i];
+            if (w == 0 && lane < nm) {
+                uint32_t x = hslot(v);
+                while (atomicCAS(&h[x].x, -1, v) != -1) x = (x + 1) & (kHT - 1);
+                h[x].y = lane;
             }
+            __syncthreads();
+            const int32_t total = pre[nm];
+            int32_t m = 0;
+            for (int32_t f = threadIdx.x; f < total; f += kAB) {
+                while (f >= pre[m + 1]) m++;
+                const int32_t e = base[m] + (f - pre[m]);
+                const int32_t u = a.g.adjncy[e];
+                int32_t lab = ld_l2(a.part + u);
+                for (uint32_t x = hslot(u); h[x].x >= 0; x = (x + 1) & (kHT - 1))
+                    if (h[x].x == u) {
+                        if (h[x].y < m) lab = mt[h[x].y];
+                        break;
+                    }
+                const long long ew1 = a.g.adjwgt ? a.g.adjwgt[e] : 1;
+                if (lab == mt[m]) atomicAdd((unsigned long long *)&gain[m], (unsigned long long)ew1);
+                else if (lab == mf[m]) atomicAdd((unsigned long long *)&gain[m], 0ull - (unsigned long long)ew1);
+            }
+            __syncthreads();
             if (threadIdx.x == 0) {
-                sB[f] -= cv;
-                sB[t] += cv;
-                __hip_atomic_store(a.part + v, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                long long cum = 0, best = 0;
+                int32_t na = 0, len = 0;
+                for (; na < nm; na++) {
+                    const int32_t f = mf[na], t = mt[na];
+                    if (now[na] != f || sB[t] + mw[na] > a.lmax) break;
+                    sB[f] -= mw[na];
+                    sB[t] += mw[na];
+                    cum += gain[na];
+                    if (cum > best) {
+                        best = cum;
+                        len = na + 1;
+                    }
+                }
+                for (int32_t i = na - 1; i >= len; i--) {
+                    sB[mt[i]] -= mw[i];
+                    sB[mf[i]] += mw[i];
+                }
+                s_len = len;
+                s_gain = best;
             }
+            __syncthreads();
+            const int32_t len = s_len;
+            if ((int32_t)threadIdx.x < len) {
+                __hip_atomic_store(a.part + mv[threadIdx.x], mt[threadIdx.x], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+                a.next[nnext + threadIdx.x] = mv[threadIdx.x];
+            }
+            nnext += len;
+            lg += s_gain;
+            kept += len;
             __threadfence();
             __syncthreads();
-            na++;
-            cum += ct - cf;
-            if (cum > best) {
-                best = cum;
-                bestlen = na;
-            }
-        }
-        for (int32_t i = na - 1; i >= bestlen; i--) {
-            if (threadIdx.x == 0) {
-                const int32_t v = a.mv_v[o + i];
-                const long long cv = vw(a.g, v);
-                sB[a.mv_t[o + i]] -= cv;
-                sB[a.mv_f[o + i]] += cv;
-                __hip_atomic_store(a.part + v, a.mv_f[o + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-        __threadfence();
-        __syncthreads();
-        for (int32_t i = threadIdx.x; i < bestlen; i += kAB) a.next[nnext + i] = a.mv_v[o + i];
-        nnext += bestlen;
-        lg += best;
-        kept += bestlen;
-    }
-    // the batch's marks hold for the rest of the local iteration
-    for (int32_t j = 0; j < ns; j++) {
-        const int64_t o = (int64_t)j * kMlsMaxQueue;
-        for (int32_t i = threadIdx.x; i < a.mk_n[j]; i += kAB) {
-            const int32_t u = a.mk_v[o + i];
-            if (atomicExch(&a.marked[u], 1) == 0) a.marklist[atomicAdd(&a.c->nmark, 1)] = u;
         }
     }
-    __syncthreads();
     for (int b = threadIdx.x; b < a.k; b += kAB) a.B[b] = sB[b];
     if (threadIdx.x == 0) {
-        Ctl *c = a.c;
         c->lgain += lg;
         c->kept += kept;
         c->searches += ns;
         c->nnext = nnext;
-        c->ti = c->clash < nsel ? a.selpos[c->clash] : c->tiw;
         c->epoch++;
     }
+    __threadfence();
+    __syncthreads();
+    next_window(a.wd, c, ti, ntodo, wl);
 }
 
 __global__ void k_ctl_init(Ctl *c) {
@@ -637,8 +985,9 @@ int mls_refine(const DevGraph &g, int32_t k, int64_t lmax, int32_t *part, int64_
     hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(1), 0, s, c);
     GP_LAUNCH_CHECK();
 
-    SearchArgs sa{mg, k, lmax, part, B, marked, sel, c, queue, max_idle, mv_v, mv_f, mv_t, mv_n, mk_v, mk_n};
-    ApplyArgs aa{mg, k, lmax, part, B, marked, marklist, next, c, selpos, mv_v, mv_f, mv_t, mv_n, mk_v, mk_n};
+    const Window wd{todo, marked, batch, sel, selpos};
+    SearchArgs sa{mg, k, lmax, part, B, marked, sel, c, first, queue, max_idle, mv_v, mv_f, mv_t, mv_n, mk_v, mk_n};
+    ApplyArgs aa{mg, k, lmax, part, B, marked, marklist, next, c, mv_v, mv_f, mv_t, mv_n, mk_v, mk_n, wd};
     const unsigned gsearch = (unsigned)((batch + kSW - 1) / kSW);
     constexpr int kBatchesPerCheck = 8;
 
@@ -668,13 +1017,20 @@ int mls_refine(const DevGraph &g, int32_t k, int64_t lmax, int32_t *part, int64_
         int64_t gtotal = 0;
         for (int32_t li = 0;; li++) {
             res.local_iters++;
-            hipLaunchKernelGGL(k_begin_local, dim3(1), dim3(1), 0, s, c);
+            hipLaunchKernelGGL(k_begin_local, dim3(1), dim3(kAB), 0, s, wd, c);
             GP_LAUNCH_CHECK();
             for (;;) {
                 for (int r = 0; r < kBatchesPerCheck; r++) {
-                    hipLaunchKernelGGL(k_window, dim3(1), dim3(kAB), 0, s, todo, marked, batch, c, sel, selpos);
-                    hipLaunchKernelGGL(k_claim, dim3(batch), dim3(256), 0, s, mg, sel, c, first);
-                    hipLaunchKernelGGL(k_search, dim3(gsearch), dim3(kWave * kSW), 0, s, sa);
+                    // with the sums kept up to 64 blocks, where those of a full queue take 32 KB of
+                    // LDS: rgg 2^15, batches of 1024: k = 16 27.3 -> 9.8 ms a call, k = 64 45.0 -> 22.9
+                    if (k <= 16) {
+                        hipLaunchKernelGGL(k_search_rows<16>, dim3(batch), dim3(kWave), 0, s, sa);
+                    } else if (k <= 64) {
+                        hipLaunchKernelGGL(k_search_rows<64>, dim3(batch), dim3(kWave), 0, s, sa);
+                    } else {
+                        hipLaunchKernelGGL(k_claim, dim3(batch), dim3(256), 0, s, mg, sel, c, first);
+                        hipLaunchKernelGGL(k_search, dim3(gsearch), dim3(kWave * kSW), 0, s, sa);
+                    }
                     hipLaunchKernelGGL(k_apply, dim3(1), dim3(kAB), 0, s, aa);
                     GP_LAUNCH_CHECK();
                 }
