@@ -40,6 +40,7 @@ struct LPArgs {
     const uint8_t *lab8;   // dense mode (<= 256 labels): byte copy of labels for the neighbour gathers
     const uint8_t *act;    // active-set rounds: evaluations each vertex still owes (0: no proposal); null: all
     uint8_t *todo;         // bit of the round's direction clear: the vertex is settled in it; null: none is
+    const int32_t *lroom;  // labels with the class of their room in the top byte (k_label_room); null: use labels
     const int32_t *group;  // batched graphs: group of each vertex; null: one graph
     const GroupState *gs;  // batched graphs: per-group state
 };
@@ -135,6 +136,45 @@ struct TierList {
 };
 
 __device__ __forceinline__ int64_t capof(const LPArgs &a, int32_t L) { return a.capv ? a.capv[L] : a.U; }
+
+// Class of a weight: monotone, exact below 16, eight steps per doubling above.
+constexpr int kRoomShift = 24;  // labels below 2^24 leave a byte for the class
+__device__ __forceinline__ uint32_t room_class(int64_t x) {
+    if (x < 16) return x < 0 ? 0u : (uint32_t)x;
+    if (x > INT_MAX) return 254;
+    const int e = 31 - __clz((int32_t)x);
+    return 16u + 8u * (uint32_t)(e - 4) + (((uint32_t)x >> (e - 3)) & 7u);
+}
+
+// Labels as the neighbour gathers of a round read them. With lroom a label whose
+// room's class is below the class of the vertex's weight has no room for it
+// (the classes are monotone) and is never entered in the vertex's table; the
+// others are tested exactly when the best one is taken.
+struct Labs {
+    const int32_t *__restrict__ x;
+    int32_t mask;
+    bool rooms;
+    __device__ __forceinline__ explicit Labs(const LPArgs &a)
+        : x(a.lroom ? a.lroom : a.labels), mask(a.lroom ? (1 << kRoomShift) - 1 : -1), rooms(a.lroom != nullptr) {}
+    __device__ __forceinline__ int32_t label(int32_t raw) const { return raw & mask; }
+    __device__ __forceinline__ uint32_t need(const LPArgs &a, int32_t v) const {
+        return rooms ? room_class(vweight(a.vwgt, v)) : 0u;
+    }
+    __device__ __forceinline__ bool fits(int32_t raw, uint32_t need) const {
+        return ((uint32_t)raw >> kRoomShift) >= need;
+    }
+};
+
+// lroom of every vertex. R-MAT clusters fill up early: on R-MAT-22 77 to 99% of
+// the large vertices' best labels had no room, and each such vertex read the
+// weights of all labels of its table.
+__global__ __launch_bounds__(256) void k_label_room(LPArgs a, int32_t n, int32_t *out) {
+    if (*a.done) return;
+    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < n; v += (int64_t)gridDim.x * 256) {
+        const int32_t L = a.labels[v];
+        if (L >= 0) out[v] = L | (int32_t)(room_class(capof(a, L) - a.W[L]) << kRoomShift);
+    }
+}
 
 // 0: any direction, 1: only smaller labels, 2: only larger labels
 __device__ __forceinline__ int32_t cur_dirmode(const LPArgs &a) {
@@ -440,6 +480,7 @@ __global__ __launch_bounds__(kPropBlock) void k_pgroup(LPArgs a, TierList lists,
     const int32_t count = (int32_t)(lists.ts[tier + 1] - t0);
     const int32_t *__restrict__ verts = lists.verts + t0;
     const int32_t dmode = cur_dirmode(a);
+    const Labs lb(a);
     constexpr int GPW = kWave / GL;
     constexpr int NW = kPropBlock / kWave;
     constexpr int LOG2 = __builtin_ctz(TBL);
@@ -464,6 +505,7 @@ __global__ __launch_bounds__(kPropBlock) void k_pgroup(LPArgs a, TierList lists,
         const int32_t beg = valid ? a.xadj[v] : 0;
         const int32_t end = valid ? a.xadj[v + 1] : beg;
         const int32_t own = valid ? a.labels[v] : -1;
+        const uint32_t need = valid ? lb.need(a, v) : 0u;
         int32_t oc = 0;
         unsigned long long mybest = 0;
         uint32_t touched[MAXE];  // fixed positions (registers): entry it*2 + j, ~0u when none
@@ -478,11 +520,12 @@ __global__ __launch_bounds__(kPropBlock) void k_pgroup(LPArgs a, TierList lists,
             const int32_t u0 = e0 < end ? a.adjncy[e0] : -1, u1 = e1 < end ? a.adjncy[e1] : -1;
             const int32_t w0 = (e0 < end && a.adjwgt) ? a.adjwgt[e0] : 1;
             const int32_t w1 = (e1 < end && a.adjwgt) ? a.adjwgt[e1] : 1;
-            const int32_t L0 = u0 >= 0 ? a.labels[u0] : -1, L1 = u1 >= 0 ? a.labels[u1] : -1;
+            const int32_t r0 = u0 >= 0 ? lb.x[u0] : -1, r1 = u1 >= 0 ? lb.x[u1] : -1;
+            const int32_t L0 = lb.label(r0), L1 = lb.label(r1);
             uint32_t sum;
             if (u0 >= 0) {
                 if (L0 == own) oc += w0;
-                else if (dir_ok(L0, own, dmode)) {
+                else if (lb.fits(r0, need) && dir_ok(L0, own, dmode)) {
                     touched[2 * it] = slot_add(tbl, TBL - 1, LOG2, L0, (uint32_t)w0, &sum);
                     const unsigned long long pb = pack_best(sum, L0);
                     mybest = pb > mybest ? pb : mybest;
@@ -490,7 +533,7 @@ __global__ __launch_bounds__(kPropBlock) void k_pgroup(LPArgs a, TierList lists,
             }
             if (u1 >= 0) {
                 if (L1 == own) oc += w1;
-                else if (dir_ok(L1, own, dmode)) {
+                else if (lb.fits(r1, need) && dir_ok(L1, own, dmode)) {
                     touched[2 * it + 1] = slot_add(tbl, TBL - 1, LOG2, L1, (uint32_t)w1, &sum);
                     const unsigned long long pb = pack_best(sum, L1);
                     mybest = pb > mybest ? pb : mybest;
@@ -659,6 +702,7 @@ __global__ __launch_bounds__(BLOCK) void k_pblock(LPArgs a, TierList lists, int 
     const int32_t count = (int32_t)(lists.ts[tier + 1] - t0);
     const int32_t *__restrict__ verts = lists.verts + t0;
     const int32_t dmode = cur_dirmode(a);
+    const Labs lb(a);
     const uint8_t bit = round_bit(a);
     constexpr int NW = BLOCK / kWave;
     constexpr int MAXE = 4 * ((TBL / 2 + 4 * BLOCK - 1) / (4 * BLOCK));  // entries per thread
@@ -675,7 +719,7 @@ __global__ __launch_bounds__(BLOCK) void k_pblock(LPArgs a, TierList lists, int 
     int32_t own = idx < count ? a.labels[v] : -1;
     if (idx < count && inactive(a, v, bit)) end = beg;
     // entry it of this thread is beg + threadIdx.x + it * BLOCK
-    int32_t L[MAXE], wv[MAXE];
+    int32_t L[MAXE], wv[MAXE];  // labels as gathered
     {
         int32_t u[MAXE];
 #pragma unroll
@@ -685,7 +729,7 @@ __global__ __launch_bounds__(BLOCK) void k_pblock(LPArgs a, TierList lists, int 
             wv[it] = (e < end && a.adjwgt) ? a.adjwgt[e] : 1;
         }
 #pragma unroll
-        for (int it = 0; it < MAXE; it++) L[it] = u[it] >= 0 ? a.labels[u[it]] : -2;
+        for (int it = 0; it < MAXE; it++) L[it] = u[it] >= 0 ? lb.x[u[it]] : -2;
     }
     for (; idx < count; idx += gridDim.x) {
         const int64_t nidx = idx + gridDim.x;
@@ -693,6 +737,7 @@ __global__ __launch_bounds__(BLOCK) void k_pblock(LPArgs a, TierList lists, int 
         int lg = 6;
         while ((1 << lg) < 2 * (end - beg) && (1 << lg) < TBL) lg++;
         const uint32_t cap = 1u << lg;
+        const uint32_t need = lb.need(a, v);
         int32_t oc = 0;
         unsigned long long mybest = 0;
         uint32_t touched[MAXE];  // fixed positions (registers), ~0u when none
@@ -700,11 +745,12 @@ __global__ __launch_bounds__(BLOCK) void k_pblock(LPArgs a, TierList lists, int 
         for (int it = 0; it < MAXE; it++) {
             touched[it] = ~0u;
             if (L[it] == -2) continue;  // no entry
-            if (L[it] == own) oc += wv[it];
-            else if (dir_ok(L[it], own, dmode)) {
+            const int32_t l = lb.label(L[it]);
+            if (l == own) oc += wv[it];
+            else if (lb.fits(L[it], need) && dir_ok(l, own, dmode)) {
                 uint32_t sum;
-                touched[it] = slot_add(tbl, cap - 1, lg, L[it], (uint32_t)wv[it], &sum);
-                const unsigned long long pb = pack_best(sum, L[it]);
+                touched[it] = slot_add(tbl, cap - 1, lg, l, (uint32_t)wv[it], &sum);
+                const unsigned long long pb = pack_best(sum, l);
                 mybest = pb > mybest ? pb : mybest;
             }
         }
@@ -725,7 +771,7 @@ __global__ __launch_bounds__(BLOCK) void k_pblock(LPArgs a, TierList lists, int 
         oc = block_sum<BLOCK>(oc, tc);  // its barriers also publish wbest and the table
         // the next vertex's neighbour labels are in flight during the selection
 #pragma unroll
-        for (int it = 0; it < MAXE; it++) L[it] = nu[it] >= 0 ? a.labels[nu[it]] : -2;
+        for (int it = 0; it < MAXE; it++) L[it] = nu[it] >= 0 ? lb.x[nu[it]] : -2;
         unsigned long long best = wbest[0];
         for (int i = 1; i < NW; i++) best = wbest[i] > best ? wbest[i] : best;
         const int32_t bc = (int32_t)(best >> 32);
@@ -1008,6 +1054,7 @@ constexpr int kHubBlock = 1024;
 __global__ __launch_bounds__(kHubBlock) void k_hub_insert(LPArgs a, HubPlan hp) {
     if (*a.done) return;
     const int32_t dmode = cur_dirmode(a);
+    const Labs lb(a);
     __shared__ int32_t skey[kHubLds];
     __shared__ int32_t sval[kHubLds];
     __shared__ int32_t scur[kHubMaxBuck];
@@ -1028,13 +1075,14 @@ __global__ __launch_bounds__(kHubBlock) void k_hub_insert(LPArgs a, HubPlan hp) 
     for (int i = threadIdx.x; i < nb; i += kHubBlock) scur[i] = 0;
     __syncthreads();
     const int32_t own = a.labels[v];
+    const uint32_t need = lb.need(a, v);
     int32_t oc = 0;
     for (int32_t e = beg + threadIdx.x; e < end; e += kHubBlock) {
         const int32_t u = a.adjncy[e];
         const int32_t wv = a.adjwgt ? a.adjwgt[e] : 1;
-        const int32_t L = a.labels[u];
+        const int32_t raw = lb.x[u], L = lb.label(raw);
         if (L == own) oc += wv;
-        else if (dir_ok(L, own, dmode)) tbl_insert<int32_t>(skey, sval, tcap - 1, tlg, L, wv);
+        else if (lb.fits(raw, need) && dir_ok(L, own, dmode)) tbl_insert<int32_t>(skey, sval, tcap - 1, tlg, L, wv);
     }
     __syncthreads();
     // pairs per bucket, then one reservation per non-empty bucket in its region
@@ -3248,6 +3296,18 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         GP_HIP(hipMemsetAsync(ac.todo, kTodoBoth, (size_t)n, s));
     }
 
+    // ---- labels with the class of their room, for the tables of the 64-lane,
+    // workgroup and hub tiers: worth a pass over the vertices and their labels'
+    // weights in every round where those tiers gather four labels per vertex
+    int32_t *lroom = nullptr;
+    {
+        unsigned long long gathers = 0;
+        for (int t = 5; t < kTiers; t++) gathers += hedge[t];
+        if (!dense && !wide && !ac.todo && n <= (1 << kRoomShift) && nlabels <= (1 << kRoomShift) && !fuse_rest &&
+            gathers >= 4ull * (unsigned long long)n)
+            GP_TRY(sc.alloc(&lroom, n));
+    }
+
     // ---- dense mode: connection rows of the vertices above KT/8 neighbours
     // (the plain rounds keep gathering for the others). Not for the levels
     // whose round tail runs in one workgroup, nor in a caller's workspace or
@@ -3325,8 +3385,13 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         a.lab8 = lab8;
         a.act = act;
         a.todo = ac.todo;
+        a.lroom = lroom;
         a.group = group;
         a.gs = gstate;
+        if (lroom) {
+            hipLaunchKernelGGL(k_label_room, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, a, n, lroom);
+            GP_LAUNCH_CHECK();
+        }
         if (act && afirst < n) {
             RT_TRY(compact(ActFlag{verts + afirst, act, &dev->done}, ActEmit{verts, averts, atier, tsh, afirst},
                            n - afirst, nullptr, acount, sc));
