@@ -497,48 +497,69 @@ __global__ __launch_bounds__(kPropBlock) void k_pgroup(LPArgs a, TierList lists,
     const unsigned b = xcd_block(blockIdx.x, gridDim.x);
     const int64_t stride = (int64_t)gridDim.x * NW * span;
     for (int64_t wb = ((int64_t)b * NW + w) * span; wb < count; wb += stride) {
-    int32_t nlive = GPW;
-    if constexpr (SKIP) nlive = wave_live(a, verts, wb, span, count, bit, slive[w]);
+    // without SKIP all of the wave's entries in one go, as in k_plane
+    int32_t nlive = 0;
+    if constexpr (SKIP) {
+        nlive = wave_live(a, verts, wb, span, count, bit, slive[w]);
+        if (nlive == 0) continue;
+    } else {
+        nlive = (int32_t)((count - wb + stride - 1) / stride) * GPW;
+    }
+    int32_t li = grp;       // the next vertex: place in the list of live ones,
+    int64_t lj = wb + grp;  // or list entry
+    const auto next = [&]() -> int32_t {
+        int32_t x = -1;
+        if constexpr (SKIP) {
+            if (li < nlive) x = slive[w][li];
+            li += GPW;
+        } else {
+            if (lj < count) x = verts[lj];
+            lj += stride;
+        }
+        return x;
+    };
+    int32_t v = next();
+    int32_t beg = v >= 0 ? a.xadj[v] : 0;
+    int32_t end = v >= 0 ? a.xadj[v + 1] : 0;
+    int32_t own = v >= 0 ? a.labels[v] : -1;
+    int32_t u[MAXE], wt[MAXE];  // entry i of this lane is beg + gl + i * GL
+#pragma unroll
+    for (int i = 0; i < MAXE; i++) {
+        const int32_t e = beg + gl + i * GL;
+        u[i] = e < end ? a.adjncy[e] : -1;
+        wt[i] = e < end && a.adjwgt ? a.adjwgt[e] : 1;
+    }
     for (int32_t i0 = 0; i0 < nlive; i0 += GPW) {
-        const bool valid = SKIP ? i0 + grp < nlive : wb + grp < count;
-        const int32_t v = !valid ? 0 : (SKIP ? slive[w][i0 + grp] : verts[wb + grp]);
-        const int32_t beg = valid ? a.xadj[v] : 0;
-        const int32_t end = valid ? a.xadj[v + 1] : beg;
-        const int32_t own = valid ? a.labels[v] : -1;
+        const bool valid = v >= 0;
         const uint32_t need = valid ? lb.need(a, v) : 0u;
+#pragma unroll
+        for (int i = 0; i < MAXE; i++) u[i] = u[i] >= 0 ? lb.x[u[i]] : -2;  // labels as gathered
+        // the next vertex's row and label; its entries are requested below
+        const int32_t nv = next();
+        const int32_t nbeg = nv >= 0 ? a.xadj[nv] : 0;
+        const int32_t nend = nv >= 0 ? a.xadj[nv + 1] : 0;
+        const int32_t nown = nv >= 0 ? a.labels[nv] : -1;
         int32_t oc = 0;
         unsigned long long mybest = 0;
-        uint32_t touched[MAXE];  // fixed positions (registers): entry it*2 + j, ~0u when none
-        const int nch = (end - beg + GL - 1) / GL;
-        const int maxch = wave_max(nch);
+        uint32_t touched[MAXE];  // ~0u when none
 #pragma unroll
-        for (int it = 0; it < MAXE / 2; it++) {
-            touched[2 * it] = ~0u;
-            touched[2 * it + 1] = ~0u;
-            if (2 * it >= maxch) continue;
-            const int32_t e0 = beg + 2 * it * GL + gl, e1 = e0 + GL;
-            const int32_t u0 = e0 < end ? a.adjncy[e0] : -1, u1 = e1 < end ? a.adjncy[e1] : -1;
-            const int32_t w0 = (e0 < end && a.adjwgt) ? a.adjwgt[e0] : 1;
-            const int32_t w1 = (e1 < end && a.adjwgt) ? a.adjwgt[e1] : 1;
-            const int32_t r0 = u0 >= 0 ? lb.x[u0] : -1, r1 = u1 >= 0 ? lb.x[u1] : -1;
-            const int32_t L0 = lb.label(r0), L1 = lb.label(r1);
-            uint32_t sum;
-            if (u0 >= 0) {
-                if (L0 == own) oc += w0;
-                else if (lb.fits(r0, need) && dir_ok(L0, own, dmode)) {
-                    touched[2 * it] = slot_add(tbl, TBL - 1, LOG2, L0, (uint32_t)w0, &sum);
-                    const unsigned long long pb = pack_best(sum, L0);
-                    mybest = pb > mybest ? pb : mybest;
-                }
+        for (int i = 0; i < MAXE; i++) {
+            touched[i] = ~0u;
+            if (u[i] == -2) continue;
+            const int32_t L = lb.label(u[i]);
+            if (L == own) oc += wt[i];
+            else if (lb.fits(u[i], need) && dir_ok(L, own, dmode)) {
+                uint32_t sum;
+                touched[i] = slot_add(tbl, TBL - 1, LOG2, L, (uint32_t)wt[i], &sum);
+                const unsigned long long pb = pack_best(sum, L);
+                mybest = pb > mybest ? pb : mybest;
             }
-            if (u1 >= 0) {
-                if (L1 == own) oc += w1;
-                else if (lb.fits(r1, need) && dir_ok(L1, own, dmode)) {
-                    touched[2 * it + 1] = slot_add(tbl, TBL - 1, LOG2, L1, (uint32_t)w1, &sum);
-                    const unsigned long long pb = pack_best(sum, L1);
-                    mybest = pb > mybest ? pb : mybest;
-                }
-            }
+        }
+#pragma unroll
+        for (int i = 0; i < MAXE; i++) {
+            const int32_t e = nbeg + gl + i * GL;
+            u[i] = e < nend ? a.adjncy[e] : -1;
+            wt[i] = e < nend && a.adjwgt ? a.adjwgt[e] : 1;
         }
         wave_sync();
         oc = group_sum<GL>(oc);
@@ -577,7 +598,12 @@ __global__ __launch_bounds__(kPropBlock) void k_pgroup(LPArgs a, TierList lists,
         for (int i = 0; i < MAXE; i++)
             if (touched[i] != ~0u) tbl[touched[i]] = kSlotEmpty;
         wave_sync();
+        v = nv;
+        beg = nbeg;
+        end = nend;
+        own = nown;
     }
+    if (!SKIP) break;
     wave_sync();
     }
 }
@@ -1077,12 +1103,24 @@ __global__ __launch_bounds__(kHubBlock) void k_hub_insert(LPArgs a, HubPlan hp) 
     const int32_t own = a.labels[v];
     const uint32_t need = lb.need(a, v);
     int32_t oc = 0;
-    for (int32_t e = beg + threadIdx.x; e < end; e += kHubBlock) {
-        const int32_t u = a.adjncy[e];
-        const int32_t wv = a.adjwgt ? a.adjwgt[e] : 1;
-        const int32_t raw = lb.x[u], L = lb.label(raw);
-        if (L == own) oc += wv;
-        else if (lb.fits(raw, need) && dir_ok(L, own, dmode)) tbl_insert<int32_t>(skey, sval, tcap - 1, tlg, L, wv);
+    // the chunk's gathers in flight together
+    constexpr int kE = kHubChunk / kHubBlock;
+    int32_t raw[kE], wv[kE];
+#pragma unroll
+    for (int i = 0; i < kE; i++) {
+        const int32_t e = beg + (int32_t)threadIdx.x + i * kHubBlock;
+        raw[i] = e < end ? a.adjncy[e] : -1;
+        wv[i] = e < end && a.adjwgt ? a.adjwgt[e] : 1;
+    }
+#pragma unroll
+    for (int i = 0; i < kE; i++) raw[i] = raw[i] >= 0 ? lb.x[raw[i]] : -2;
+#pragma unroll
+    for (int i = 0; i < kE; i++) {
+        if (raw[i] == -2) continue;
+        const int32_t L = lb.label(raw[i]);
+        if (L == own) oc += wv[i];
+        else if (lb.fits(raw[i], need) && dir_ok(L, own, dmode))
+            tbl_insert<int32_t>(skey, sval, tcap - 1, tlg, L, wv[i]);
     }
     __syncthreads();
     // pairs per bucket, then one reservation per non-empty bucket in its region
@@ -1158,14 +1196,25 @@ __global__ __launch_bounds__(kRedBlock) void k_hub_reduce(LPArgs a, HubPlan hp) 
     __syncthreads();
     const int64_t cv = vweight(a.vwgt, hp.hubs[h]);
     unsigned long long best = 0;
-    for (int i = threadIdx.x; i < cap; i += kRedBlock) {
-        const int32_t L = skey[i];
-        if (L >= 0 && a.W[L] + cv <= capof(a, L)) {
-            const unsigned long long pk = pack_best(sval[i], L);
+    for (int i = threadIdx.x; i < cap; i += kRedBlock)
+        if (skey[i] >= 0) {
+            const unsigned long long pk = pack_best(sval[i], skey[i]);
             best = pk > best ? pk : best;
         }
-    }
     best = block_max<kRedBlock>(best, tmp);
+    if (best) {  // uniform: the bucket's strongest label, or, without room, the strongest with room
+        const int32_t L0 = INT_MAX - (int32_t)(uint32_t)best;
+        if (a.W[L0] + cv > capof(a, L0)) {
+            best = 0;
+            for (int i = threadIdx.x; i < cap; i += kRedBlock) {
+                const int32_t L = skey[i];
+                if (L < 0) continue;
+                const unsigned long long pk = pack_best(sval[i], L);
+                if (pk > best && a.W[L] + cv <= capof(a, L)) best = pk;
+            }
+            best = block_max<kRedBlock>(best, tmp);
+        }
+    }
     if (threadIdx.x == 0) {
         if (best) atomicMax(&hp.best[h], best);
         hp.fill[gb] = 0;
