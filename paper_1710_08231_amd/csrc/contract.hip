@@ -143,6 +143,7 @@ __global__ void k_halve(int64_t *x) { *x /= 2; }
 // ---------------------------------------------------------------- row-grouped contraction
 
 constexpr int kRowWaveMax = 128;    // D_i <= 128: one wave per row
+constexpr int kRowSmallMax = 512;   // D_i <= 512: one small workgroup per row
 constexpr int kRowBlockMax = 2048;  // D_i <= 2048: one workgroup per row
 constexpr int kRowChunk = 2048;     // larger rows: flattened entries per aggregating workgroup
 static_assert(kRowWaveMax % kWave == 0, "wave rows: whole entries per lane");
@@ -273,29 +274,36 @@ __global__ __launch_bounds__(256) void k_crow_wave(RowCtx c, const int32_t *rows
     }
 }
 
-// One workgroup per row. 80 KB of LDS fits two workgroups per CU, so the
-// workgroup is wide (kCB threads) to keep enough waves in flight for the
-// gathers.
-constexpr int kCB = 512;
+// One workgroup of CB threads per row of at most MAXD entries. Two classes: up to
+// kRowSmallMax entries 128 threads with 13 KB of LDS (twelve workgroups per CU),
+// above that kCB threads with 80 KB (two per CU, so the workgroup is wide to
+// keep enough waves in flight for the gathers). Bound: the latency of a row's
+// dependent gathers and its barriers, hence rows in flight: with one class the
+// rows of 129 to 512 entries left most of 512 threads idle (512 graphs: 14.0 ms
+// for 7 levels with one class, 9.1 with two; R-MAT-24: 20.8 and 18.7).
+constexpr int kCB = 512, kCBSmall = 128;
 constexpr int kRankMax = 1024;  // rows with at most this many distinct columns are sorted by counting ranks
 static_assert(kRankMax % kCB == 0, "rank sort: whole columns per thread");
 static_assert(kRowBlockMax % kCB == 0 && kRowChunk % kCB == 0, "block rows: whole entries per thread");
-__global__ __launch_bounds__(kCB) void k_crow_block(RowCtx c, const int32_t *rows, int32_t count) {
-    constexpr int CAP = 2 * kRowBlockMax;
+static_assert(kRowSmallMax % kCBSmall == 0 && kRowSmallMax <= kRankMax, "small rows: whole entries, sorted by ranks");
+template <int CB, int MAXD>
+__global__ __launch_bounds__(CB) void k_crow_block(RowCtx c, const int32_t *rows, int32_t count) {
+    constexpr int CAP = 2 * MAXD;
+    constexpr int RANK = MAXD < kRankMax ? MAXD : kRankMax;
     __shared__ int32_t skey[CAP];
     __shared__ long long sval[CAP];
     // sF (member prefix) is only read while gathering and lj (the distinct
     // columns) only written after that, so they share one array; li holds
     // each column's table slot, whose weight is read at the output. This
-    // keeps the workgroup under 80 KB: two per CU.
-    __shared__ __align__(16) int32_t sFlj[kRowBlockMax + 4];
-    __shared__ uint16_t li[kRowBlockMax];
+    // keeps the large class's workgroup under 80 KB: two per CU.
+    __shared__ __align__(16) int32_t sFlj[MAXD + 4];
+    __shared__ uint16_t li[MAXD];
     __shared__ int32_t s_r;
     int32_t *const sF = sFlj, *const lj = sFlj;
-    static_assert(2 * kRowBlockMax <= 65536, "slot index fits 16 bits");
+    static_assert(2 * MAXD <= 65536, "slot index fits 16 bits");
     const int lane = lane_id();
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
-    for (int q = threadIdx.x; q < CAP; q += kCB) {
+    for (int q = threadIdx.x; q < CAP; q += CB) {
         skey[q] = -1;
         sval[q] = 0;
     }
@@ -304,17 +312,17 @@ __global__ __launch_bounds__(kCB) void k_crow_block(RowCtx c, const int32_t *row
         const int32_t i = rows[idx];
         const int32_t m0 = c.mstart[i], m1 = c.mstart[i + 1];
         const int32_t base = c.flat[m0], D = c.flat[m1] - base, M = m1 - m0;
-        for (int q = threadIdx.x; q <= M; q += kCB) sF[q] = c.flat[m0 + q] - base;
+        for (int q = threadIdx.x; q <= M; q += CB) sF[q] = c.flat[m0 + q] - base;
         if (threadIdx.x == 0) s_r = 0;
         __syncthreads();
         int lg = 1;
         while ((1 << lg) < 2 * D) lg++;
         const uint32_t cap = 1u << lg;
-        gather_insert<kRowBlockMax / kCB, kCB>(c, sF, m0, M - 1, threadIdx.x, D, i, skey, sval, cap - 1, lg);
+        gather_insert<MAXD / CB, CB>(c, sF, m0, M - 1, threadIdx.x, D, i, skey, sval, cap - 1, lg);
         __syncthreads();
         // compaction of the occupied slots, in any order (the columns are
         // sorted next): one LDS reservation per wave
-        for (uint32_t s0 = 0; s0 < cap; s0 += kCB) {
+        for (uint32_t s0 = 0; s0 < cap; s0 += CB) {
             const uint32_t sl = s0 + threadIdx.x;
             const bool occ = sl < cap && skey[sl] >= 0;
             const uint64_t m = __ballot(occ);
@@ -329,13 +337,13 @@ __global__ __launch_bounds__(kCB) void k_crow_block(RowCtx c, const int32_t *row
         }
         __syncthreads();
         const int32_t r = s_r;
-        if (r <= kRankMax) {
+        if (r <= RANK) {
             // the columns are distinct: each one's rank is the number of
             // smaller ones, counted over broadcast LDS reads (no barriers)
-            int32_t jv[kRankMax / kCB], rk[kRankMax / kCB];
+            int32_t jv[RANK / CB], rk[RANK / CB];
 #pragma unroll
-            for (int q = 0; q < kRankMax / kCB; q++) {
-                jv[q] = threadIdx.x + q * kCB < r ? lj[threadIdx.x + q * kCB] : INT_MAX;
+            for (int q = 0; q < RANK / CB; q++) {
+                jv[q] = threadIdx.x + q * CB < r ? lj[threadIdx.x + q * CB] : INT_MAX;
                 rk[q] = 0;
             }
             const int4 *l4 = reinterpret_cast<const int4 *>(lj);
@@ -343,32 +351,32 @@ __global__ __launch_bounds__(kCB) void k_crow_block(RowCtx c, const int32_t *row
             for (; x + 4 <= r; x += 4) {
                 const int4 y = l4[x >> 2];
 #pragma unroll
-                for (int q = 0; q < kRankMax / kCB; q++)
+                for (int q = 0; q < RANK / CB; q++)
                     rk[q] += (int32_t)(y.x < jv[q]) + (int32_t)(y.y < jv[q]) + (int32_t)(y.z < jv[q]) +
                              (int32_t)(y.w < jv[q]);
             }
             for (; x < r; x++) {
                 const int32_t y = lj[x];
 #pragma unroll
-                for (int q = 0; q < kRankMax / kCB; q++) rk[q] += (int32_t)(y < jv[q]);
+                for (int q = 0; q < RANK / CB; q++) rk[q] += (int32_t)(y < jv[q]);
             }
 #pragma unroll
-            for (int q = 0; q < kRankMax / kCB; q++) {
-                const int32_t t = threadIdx.x + q * kCB;
+            for (int q = 0; q < RANK / CB; q++) {
+                const int32_t t = threadIdx.x + q * CB;
                 if (t < r) {
                     c.tj[base + rk[q]] = jv[q];
                     c.tw[base + rk[q]] = sval[li[t]];
                 }
             }
-        } else {
+        } else if constexpr (MAXD > RANK) {
             int32_t P = 1;
             while (P < r) P <<= 1;
-            for (int32_t q = r + threadIdx.x; q < P; q += kCB) lj[q] = INT_MAX;
+            for (int32_t q = r + threadIdx.x; q < P; q += CB) lj[q] = INT_MAX;
             __syncthreads();
             // bitonic sort of lj/lw[0, P) by column
             for (int32_t kk = 2; kk <= P; kk <<= 1) {
                 for (int32_t jj = kk >> 1; jj > 0; jj >>= 1) {
-                    for (int32_t q = threadIdx.x; q < P; q += kCB) {
+                    for (int32_t q = threadIdx.x; q < P; q += CB) {
                         const int32_t o = q ^ jj;
                         if (o > q) {
                             const bool up = (q & kk) == 0;
@@ -385,14 +393,14 @@ __global__ __launch_bounds__(kCB) void k_crow_block(RowCtx c, const int32_t *row
                     __syncthreads();
                 }
             }
-            for (int32_t q = threadIdx.x; q < r; q += kCB) {
+            for (int32_t q = threadIdx.x; q < r; q += CB) {
                 c.tj[base + q] = lj[q];
                 c.tw[base + q] = sval[li[q]];
             }
         }
         if (threadIdx.x == 0) c.rcnt[i] = r;
         __syncthreads();  // every weight is read before the table is emptied
-        for (uint32_t q = threadIdx.x; q < cap; q += kCB) {
+        for (uint32_t q = threadIdx.x; q < cap; q += CB) {
             skey[q] = -1;
             sval[q] = 0;
         }
@@ -499,17 +507,7 @@ struct PairHeadEmit {
     int32_t *head;
     __device__ void operator()(int64_t p, int32_t r) const { head[r] = (int32_t)p; }
 };
-struct ValIn64 {
-    const int32_t *v;
-    __device__ long long operator()(int64_t p) const { return (long long)v[p]; }
-};
-struct InclOut64 {
-    long long *S;
-    __device__ void operator()(int64_t p, long long ex, long long v) const { S[p] = ex + v; }
-};
-
-// One batch of big rows, its sorted pairs (key, S: inclusive weight prefix)
-// and run heads (positions within the batch's region). Runs are sorted by
+// One batch of big rows, its sorted pairs and run heads (positions within the batch's region). Runs are sorted by
 // row rank: roff[g] = first run of the batch's rank >= g, for g in [0, nrows].
 __global__ void k_cbig_rowoff(const uint32_t *key, const int32_t *head, const int32_t *nruns, int jbits,
                               int32_t nrows, int32_t *roff) {
@@ -521,22 +519,44 @@ __global__ void k_cbig_rowoff(const uint32_t *key, const int32_t *head, const in
     }
 }
 
-__global__ void k_cbig_place(RowCtx c, const int32_t *rows, const uint32_t *key, int jbits, const int32_t *head,
-                             const int32_t *nruns, const int32_t *m_dev, const long long *S, const int32_t *roff,
-                             int32_t nrows) {
+// A run's sum: by its lane up to kRunLane pairs, by the whole wave above (a run
+// has at most one pair per chunk of its row, most have one or two).
+constexpr int kRunLane = 16;
+__global__ __launch_bounds__(256) void k_cbig_place(RowCtx c, const int32_t *rows, const uint32_t *key,
+                                                    const int32_t *val, int jbits, const int32_t *head,
+                                                    const int32_t *nruns, const int32_t *m_dev, const int32_t *roff,
+                                                    int32_t nrows) {
     const int32_t R = *nruns, m = *m_dev;
     const uint32_t jm = jbits >= 32 ? ~0u : ((1u << jbits) - 1u);
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < R; r += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t p0 = head[r], p1 = (r + 1 < R) ? head[r + 1] - 1 : m - 1;
-        const uint32_t k = key[p0];
-        const int32_t g = (int32_t)(k >> jbits);
-        const int32_t i = rows[g];
-        const int32_t base = c.flat[c.mstart[i]];
-        const int64_t pos = r - roff[g];
-        c.tj[base + pos] = (int32_t)(k & jm);
-        c.tw[base + pos] = S[p1] - (p0 > 0 ? S[p0 - 1] : 0);
+    const int lane = lane_id();
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t r0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x - lane; r0 < R; r0 += step) {
+        const int64_t r = r0 + lane;
+        const bool live = r < R;
+        const int32_t p0 = live ? head[r] : 0, p1 = live ? (r + 1 < R ? head[r + 1] : m) : 0;
+        long long sum = 0;
+        if (p1 - p0 <= kRunLane)
+            for (int32_t p = p0; p < p1; p++) sum += val[p];
+        uint64_t big = __ballot(p1 - p0 > kRunLane);
+        while (big) {
+            const int src = __ffsll((unsigned long long)big) - 1;
+            big &= big - 1;
+            const int32_t q0 = __shfl(p0, src, kWave), q1 = __shfl(p1, src, kWave);
+            long long x = 0;
+            for (int32_t p = q0 + lane; p < q1; p += kWave) x += val[p];
+            x = wave_sum(x);
+            if (lane == src) sum = x;
+        }
+        if (live) {
+            const uint32_t k = key[p0];
+            const int32_t g = (int32_t)(k >> jbits);
+            const int32_t base = c.flat[c.mstart[rows[g]]];
+            const int64_t pos = r - roff[g];
+            c.tj[base + pos] = (int32_t)(k & jm);
+            c.tw[base + pos] = sum;
+        }
     }
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < nrows; g += (int64_t)gridDim.x * blockDim.x)
+    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < nrows; g += step)
         c.rcnt[rows[g]] = roff[g + 1] - roff[g];
 }
 
@@ -568,8 +588,8 @@ __global__ void k_members(const int32_t *f2c, const int32_t *xadj, int32_t n, co
 
 __global__ void k_row_class(const int32_t *mstart, const int32_t *flat, int32_t nc, uint32_t *key, int32_t *val,
                             int32_t *ccount) {
-    __shared__ int32_t h[3];
-    if (threadIdx.x < 3) h[threadIdx.x] = 0;
+    __shared__ int32_t h[4];
+    if (threadIdx.x < 4) h[threadIdx.x] = 0;
     __syncthreads();
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nc; i += (int64_t)gridDim.x * blockDim.x) {
         // size = max(entries, members): members without neighbours (possible for
@@ -577,13 +597,13 @@ __global__ void k_row_class(const int32_t *mstart, const int32_t *flat, int32_t 
         const int32_t D = flat[mstart[i + 1]] - flat[mstart[i]];
         const int32_t M = mstart[i + 1] - mstart[i];
         const int32_t sz = D > M ? D : M;
-        const uint32_t k = sz <= kRowWaveMax ? 0u : (sz <= kRowBlockMax ? 1u : 2u);
+        const uint32_t k = sz <= kRowWaveMax ? 0u : sz <= kRowSmallMax ? 1u : sz <= kRowBlockMax ? 2u : 3u;
         key[i] = k;
         val[i] = (int32_t)i;
         atomicAdd(&h[k], 1);
     }
     __syncthreads();
-    if (threadIdx.x < 3 && h[threadIdx.x]) atomicAdd(&ccount[threadIdx.x], h[threadIdx.x]);
+    if (threadIdx.x < 4 && h[threadIdx.x]) atomicAdd(&ccount[threadIdx.x], h[threadIdx.x]);
 }
 
 // one wave per big row: its lanes write the row's (possibly thousands of) chunk owners
@@ -597,21 +617,40 @@ __global__ __launch_bounds__(256) void k_expand_owner(const int32_t *first, cons
     }
 }
 
-// one wave per coarse row: copy its sorted columns to the output CSR
-__global__ void k_copy_rows(RowCtx c, const int32_t *xadj_c, int32_t nc, int32_t *adjncy_c, int32_t *adjwgt_c,
-                            int32_t *overflow) {
-    const int lane = lane_id();
+// Copies the rows' sorted columns to the output CSR: G lanes per coarse row, rows
+// above kCopyLong entries by their whole wave. Each row starts with a chain of
+// three dependent loads, so short rows go several to a wave: at 128 fine entries
+// per coarse row and more (R-MAT-24: 9.4 ms for 9 levels with a wave each, 16.4
+// with four to a wave) each has its own.
+constexpr int kCopyLong = 128;
+template <int G>
+__global__ __launch_bounds__(256) void k_copy_rows(RowCtx c, const int32_t *xadj_c, int32_t nc, int32_t *adjncy_c,
+                                                   int32_t *adjwgt_c, int32_t *overflow) {
+    const int lane = lane_id(), gl = lane % G;
+    constexpr int RPW = kWave / G;
     const int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
     int bad = 0;
-    for (int64_t i = wid; i < nc; i += nwaves) {
-        const int32_t src = c.flat[c.mstart[i]];
-        const int32_t dst = xadj_c[i], r = xadj_c[i + 1] - dst;
-        for (int32_t q = lane; q < r; q += kWave) {
+    const auto copy = [&](int32_t src, int32_t dst, int32_t r, int first, int step) {
+        for (int32_t q = first; q < r; q += step) {
             const long long wv = c.tw[src + q];
             bad |= wv > INT_MAX;
             adjncy_c[dst + q] = c.tj[src + q];
             adjwgt_c[dst + q] = (int32_t)wv;
+        }
+    };
+    for (int64_t i0 = wid * RPW; i0 < nc; i0 += nwaves * RPW) {
+        const int64_t i = i0 + lane / G;
+        int32_t src = 0, dst = 0, r = 0;
+        if (i < nc) {
+            dst = xadj_c[i];
+            r = xadj_c[i + 1] - dst;
+            src = c.flat[c.mstart[i]];
+        }
+        if (r <= kCopyLong) copy(src, dst, r, gl, G);
+        for (int g = 0; g < RPW; g++) {
+            const int32_t rg = __shfl(r, g * G, kWave);
+            if (rg > kCopyLong) copy(__shfl(src, g * G, kWave), __shfl(dst, g * G, kWave), rg, lane, kWave);
         }
     }
     if (bad) *overflow = 1;
@@ -751,25 +790,31 @@ int contract(const DevGraph &g, const int32_t *labels, bool skip_isolated, Coars
         GP_TRY(sc.alloc(&ck2, nc));
         GP_TRY(sc.alloc(&cv, nc));
         GP_TRY(sc.alloc(&cv2, nc));
-        GP_TRY(sc.alloc(&ccount, 3));
-        GP_HIP(hipMemsetAsync(ccount, 0, sizeof(int32_t) * 3, s));
+        GP_TRY(sc.alloc(&ccount, 4));
+        GP_HIP(hipMemsetAsync(ccount, 0, sizeof(int32_t) * 4, s));
         hipLaunchKernelGGL(k_row_class, dim3(grid_for(nc, 256, 4096)), dim3(256), 0, s, mstart, flat, nc, ck, cv,
                            ccount);
         GP_LAUNCH_CHECK();
         GP_TRY((radix_sort<uint32_t, int32_t>(&ck, &cv, &ck2, &cv2, nc, nullptr, 2, sc)));
-        int32_t hc[3];
+        int32_t hc[4];
         GP_HIP(hipMemcpyAsync(hc, ccount, sizeof(hc), hipMemcpyDeviceToHost, s));
         GP_HIP(hipStreamSynchronize(s));
-        const int32_t *rows_w = cv, *rows_b = cv + hc[0], *rows_g = cv + hc[0] + hc[1];
+        const int32_t *rows_w = cv, *rows_s = cv + hc[0], *rows_b = rows_s + hc[1], *rows_g = rows_b + hc[2];
         if (hc[0] > 0) {
             hipLaunchKernelGGL(k_crow_wave, dim3(grid_for(hc[0], 4, 65536)), dim3(256), 0, s, c, rows_w, hc[0]);
             GP_LAUNCH_CHECK();
         }
         if (hc[1] > 0) {
-            hipLaunchKernelGGL(k_crow_block, dim3(grid_for(hc[1], 1, 8192)), dim3(kCB), 0, s, c, rows_b, hc[1]);
+            hipLaunchKernelGGL((k_crow_block<kCBSmall, kRowSmallMax>), dim3(grid_for(hc[1], 1, 32768)), dim3(kCBSmall),
+                               0, s, c, rows_s, hc[1]);
             GP_LAUNCH_CHECK();
         }
-        const int32_t nb = hc[2];
+        if (hc[2] > 0) {
+            hipLaunchKernelGGL((k_crow_block<kCB, kRowBlockMax>), dim3(grid_for(hc[2], 1, 8192)), dim3(kCB), 0, s, c,
+                               rows_b, hc[2]);
+            GP_LAUNCH_CHECK();
+        }
+        const int32_t nb = hc[3];
         if (nb > 0) {
             int32_t *nch = nullptr, *cfirst = nullptr, *d_tot = nullptr, *cown = nullptr, *cursor = nullptr,
                     *head = nullptr, *d_runs = nullptr, *roff = nullptr;
@@ -796,13 +841,11 @@ int contract(const DevGraph &g, const int32_t *labels, bool skip_isolated, Coars
             hoff[nbatch] = bcap;
             uint32_t *bk = nullptr, *bk2 = nullptr;
             int32_t *bv = nullptr, *bv2 = nullptr;
-            long long *S = nullptr;
             int64_t *boff = nullptr;
             GP_TRY(sc.alloc(&bk, bcap));
             GP_TRY(sc.alloc(&bk2, bcap));
             GP_TRY(sc.alloc(&bv, bcap));
             GP_TRY(sc.alloc(&bv2, bcap));
-            GP_TRY(sc.alloc(&S, bcap));
             GP_TRY(sc.alloc(&head, bcap));
             GP_TRY(sc.alloc(&cursor, nbatch));
             GP_TRY(sc.alloc(&d_runs, nbatch));
@@ -836,7 +879,6 @@ int contract(const DevGraph &g, const int32_t *labels, bool skip_isolated, Coars
                     // the count would make the call's scratch vary from run to run
                     // (the result does not: the triples are sorted and summed)
                     GP_TRY((radix_sort<uint32_t, int32_t>(&k1, &v1, &k2, &v2, cap, cursor + t, kbits, sc)));
-                    GP_TRY((scan<long long>(ValIn64{v1}, InclOut64{S + o}, cap, cursor + t, (long long *)nullptr, sc)));
                     GP_TRY(compact(PairHead{k1}, PairHeadEmit{head + o}, cap, cursor + t, d_runs + t, sc));
                 }
                 int32_t *ro = roff + (int64_t)t * (rows_per + 1);
@@ -844,8 +886,8 @@ int contract(const DevGraph &g, const int32_t *labels, bool skip_isolated, Coars
                                    k1, head + o, d_runs + t, jbits, nrows, ro);
                 GP_LAUNCH_CHECK();
                 hipLaunchKernelGGL(k_cbig_place, dim3(grid_for((int64_t)hm[t] + nrows, 256, 65536)), dim3(256), 0, s, c,
-                                   rows_g + (int64_t)t * rows_per, k1, jbits, head + o, d_runs + t, cursor + t, S + o,
-                                   ro, nrows);
+                                   rows_g + (int64_t)t * rows_per, k1, v1, jbits, head + o, d_runs + t, cursor + t, ro,
+                                   nrows);
                 GP_LAUNCH_CHECK();
             }
         }
@@ -854,8 +896,12 @@ int contract(const DevGraph &g, const int32_t *labels, bool skip_isolated, Coars
         GP_TRY(sc.alloc(&d_nnzc, 1));
         GP_TRY((scan<int32_t>(CountIn{rcnt}, CountOut{out.xadj}, nc, nullptr, d_nnzc, sc)));
         GP_HIP(hipMemcpyAsync(out.xadj + nc, d_nnzc, sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-        hipLaunchKernelGGL(k_copy_rows, dim3(grid_for((int64_t)nc * kWave, 256, 65536)), dim3(256), 0, s, c, out.xadj,
-                           nc, out.adjncy, out.adjwgt, flags);
+        if (g.nnz / nc >= 128)
+            hipLaunchKernelGGL(k_copy_rows<64>, dim3(grid_for((int64_t)nc * 64, 256, 65536)), dim3(256), 0, s, c,
+                               out.xadj, nc, out.adjncy, out.adjwgt, flags);
+        else
+            hipLaunchKernelGGL(k_copy_rows<16>, dim3(grid_for((int64_t)nc * 16, 256, 65536)), dim3(256), 0, s, c,
+                               out.xadj, nc, out.adjncy, out.adjwgt, flags);
         GP_LAUNCH_CHECK();
         GP_HIP(hipMemcpyAsync(&nnz_c, d_nnzc, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     } else {
