@@ -509,20 +509,16 @@ __device__ __forceinline__ T block_excl_scan(T x, T *tmp, T *total) {
     T inc = wave_incl_scan(x);
     if (lane == kWave - 1) tmp[w] = inc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        T acc = 0;
-        for (int i = 0; i < NW; i++) {
-            T t = tmp[i];
-            tmp[i] = acc;
-            acc += t;
-        }
-        tmp[NW] = acc;
+    T before = 0, all = 0;  // every wave adds up the totals itself: no second exchange
+#pragma unroll
+    for (int i = 0; i < NW; i++) {
+        const T t = tmp[i];
+        if (i < w) before += t;
+        all += t;
     }
     __syncthreads();
-    T r = tmp[w] + inc - x;
-    if (total) *total = tmp[NW];
-    __syncthreads();
-    return r;
+    if (total) *total = all;
+    return before + inc - x;
 }
 
 template <int BLOCK, typename T>

@@ -29,6 +29,9 @@ namespace gp {
 namespace {
 
 constexpr int kBB = 1024;  // bisection workgroup
+constexpr int kBBSmall = 256;  // where there are more workgroups than the chip holds at once
+constexpr int kBisectLds = 4096;  // largest graph whose bisection keeps its marks in LDS (48 KB)
+constexpr int kKeep = 4;
 
 // splitmix64 finaliser of x + gamma (Steele, Lea & Flood 2014)
 __device__ __forceinline__ uint64_t splitmix(uint64_t x) {
@@ -68,10 +71,18 @@ __device__ __forceinline__ int32_t frontier_pos(const int32_t *pre, int32_t f, i
     return lo;
 }
 
-__global__ __launch_bounds__(kBB) void k_bisect(BisectArgs a) {
-    __shared__ int64_t t64[kBB / kWave + 1];
-    __shared__ int32_t t32[kBB / kWave + 1];
-    __shared__ int32_t sh_tail, sh_stop, sh_found;
+// One workgroup of BB threads per (try, subproblem). LDS: the marks and claims
+// (claim of an unmarked vertex of S, -1: marked or not in S) and the frontier's
+// degree prefix and row starts are kept in LDS, three words per vertex of the
+// largest graph. Bound: the latency of a frontier's steps and their barriers
+// (512 graphs, 4 tries each: 22.1 ms with the marks in memory and 1024 threads
+// everywhere, 11.1 so).
+template <int BB, bool LDS>
+__global__ __launch_bounds__(BB) void k_bisect(BisectArgs a, int32_t maxn) {
+    extern __shared__ int32_t bisect_lds[];
+    int32_t *const sclaim = bisect_lds, *const spre = sclaim + maxn, *const srow = spre + maxn;
+    __shared__ int64_t t64[BB / kWave + 1];
+    __shared__ int32_t t32[BB / kWave + 1];
     const int attempt = blockIdx.x / a.nsub, sp = blockIdx.x % a.nsub;
     const int32_t gr = a.sub_g[sp];
     const int32_t lbase = a.sub_base[sp], ks = a.sub_ks[sp], kl = (ks + 1) / 2;
@@ -86,23 +97,32 @@ __global__ __launch_bounds__(kBB) void k_bisect(BisectArgs a) {
     int32_t *order = a.order + rg;
     int32_t *pre = a.pre + rg + sp + (int64_t)attempt * a.nsub;
 
+    const auto set_mark = [&](int32_t v) {
+        if (LDS) sclaim[v - vlo] = -1;
+        else mark[v] = 1;
+    };
+    const auto marked = [&](int32_t v) { return LDS ? sclaim[v - vlo] < 0 : mark[v] != 0; };
+
     // ---- S in ascending order, its weight; reset marks and claims
     int32_t size = 0;
     int64_t cs = 0;
-    for (int32_t v0 = vlo; v0 < vhi; v0 += kBB) {
+    for (int32_t v0 = vlo; v0 < vhi; v0 += BB) {
         const int32_t v = v0 + threadIdx.x;
         const bool in = v < vhi && blk[v] == base;
         int32_t tot;
-        const int32_t ex = block_excl_scan<kBB>((int32_t)in, t32, &tot);
+        const int32_t ex = block_excl_scan<BB>((int32_t)in, t32, &tot);
+        if (LDS && v < vhi) sclaim[v - vlo] = in ? INT_MAX : -1;
         if (in) {
             slist[size + ex] = v;
-            mark[v] = 0;
-            claim[v] = INT_MAX;
+            if (!LDS) {
+                mark[v] = 0;
+                claim[v] = INT_MAX;
+            }
             cs += vw(a.vwgt, v);
         }
         size += tot;
     }
-    cs = block_sum<kBB>(cs, t64);
+    cs = block_sum<BB>(cs, t64);
     if (size == 0) return;
     const int64_t q = cs / ks, rm = cs % ks;
     const int64_t target = q * kl + (rm * kl + ks - 1) / ks;
@@ -112,7 +132,7 @@ __global__ __launch_bounds__(kBB) void k_bisect(BisectArgs a) {
     __syncthreads();
     if (threadIdx.x == 0) {
         order[0] = start;
-        mark[start] = 1;
+        set_mark(start);
     }
     __syncthreads();
 
@@ -121,58 +141,87 @@ __global__ __launch_bounds__(kBB) void k_bisect(BisectArgs a) {
     for (;;) {
         // ---- pops of this frontier: first position where the left side reaches the target
         const int32_t f = tail - head;
-        for (int32_t c0 = 0; c0 < f && stop < 0; c0 += kBB) {
+        for (int32_t c0 = 0; c0 < f && stop < 0; c0 += BB) {
             const int32_t i = c0 + threadIdx.x;
             const int64_t w = i < f ? vw(a.vwgt, order[head + i]) : 0;
             int64_t tot;
-            const int64_t ex = block_excl_scan<kBB>(w, t64, &tot);
+            const int64_t ex = block_excl_scan<BB>(w, t64, &tot);
             const int32_t hit = (i < f && cum + ex + w >= target) ? i : INT_MAX;
-            const int32_t first = block_min<kBB>(hit, t32);
+            const int32_t first = block_min<BB>(hit, t32);
             if (first != INT_MAX) stop = head + first;
             cum += tot;
         }
         if (stop >= 0) break;
         // ---- expand: degree prefix over the frontier (edges inside S only are claimed)
         int32_t ef = 0;
-        for (int32_t c0 = 0; c0 < f; c0 += kBB) {
+        for (int32_t c0 = 0; c0 < f; c0 += BB) {
             const int32_t i = c0 + threadIdx.x;
-            int32_t d = 0;
+            int32_t d = 0, row = 0;
             if (i < f) {
                 const int32_t v = order[head + i];
-                d = a.xadj[v + 1] - a.xadj[v];
+                row = a.xadj[v];
+                d = a.xadj[v + 1] - row;
             }
             int32_t tot;
-            const int32_t ex = block_excl_scan<kBB>(d, t32, &tot);
-            if (i < f) pre[i] = ef + ex;
+            const int32_t ex = block_excl_scan<BB>(d, t32, &tot);
+            if (i < f) {
+                if (LDS) {
+                    spre[i] = ef + ex;
+                    srow[i] = row - (ef + ex);
+                } else {
+                    pre[i] = ef + ex;
+                }
+            }
             ef += tot;
         }
         __syncthreads();
-        for (int32_t r = threadIdx.x; r < ef; r += kBB) {
-            const int32_t i = frontier_pos(pre, f, r);
-            const int32_t v = order[head + i];
-            const int32_t u = a.adjncy[a.xadj[v] + (r - pre[i])];
-            if (blk[u] == base && !mark[u]) atomicMin(&claim[u], r);
-        }
-        __syncthreads();
-        int32_t nt = tail;
-        for (int32_t r0 = 0; r0 < ef; r0 += kBB) {
-            const int32_t r = r0 + threadIdx.x;
-            int32_t u = -1;
-            if (r < ef) {
-                const int32_t i = frontier_pos(pre, f, r);
-                const int32_t v = order[head + i];
-                const int32_t cand = a.adjncy[a.xadj[v] + (r - pre[i])];
-                if (blk[cand] == base && !mark[cand] &&
-                    __hip_atomic_load(&claim[cand], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == r)
-                    u = cand;
+        // edge rank r: an unmarked vertex of S at its end, or -1
+        const auto reached = [&](int32_t r) -> int32_t {
+            int32_t u;
+            if (LDS) {
+                u = a.adjncy[srow[frontier_pos(spre, f, r)] + r];
+                return (uint32_t)(u - vlo) < (uint32_t)(vhi - vlo) && sclaim[u - vlo] >= 0 ? u : -1;
             }
-            int32_t tot;
-            const int32_t ex = block_excl_scan<kBB>((int32_t)(u >= 0), t32, &tot);
-            if (u >= 0) order[nt + ex] = u;
-            nt += tot;
+            const int32_t i = frontier_pos(pre, f, r);
+            u = a.adjncy[a.xadj[order[head + i]] + (r - pre[i])];
+            return blk[u] == base && !mark[u] ? u : -1;
+        };
+        int32_t c[kKeep];  // the first ends are kept for the second pass
+#pragma unroll
+        for (int j = 0; j < kKeep; j++) {
+            const int32_t r = j * BB + (int32_t)threadIdx.x;
+            c[j] = r < ef ? reached(r) : -1;
+        }
+#pragma unroll
+        for (int j = 0; j < kKeep; j++)
+            if (c[j] >= 0) atomicMin(LDS ? &sclaim[c[j] - vlo] : &claim[c[j]], j * BB + (int32_t)threadIdx.x);
+        for (int32_t r = kKeep * BB + (int32_t)threadIdx.x; r < ef; r += BB) {
+            const int32_t u = reached(r);
+            if (u >= 0) atomicMin(LDS ? &sclaim[u - vlo] : &claim[u], r);
         }
         __syncthreads();
-        for (int32_t p = tail + threadIdx.x; p < nt; p += kBB) mark[order[p]] = 1;
+        // the smallest rank takes the vertex; it is marked by its winner (the
+        // others of its ranks only compare the claim with their own)
+        int32_t nt = tail;
+        const auto take = [&](int32_t r, int32_t u) {
+            if (u >= 0 &&
+                (LDS ? sclaim[u - vlo] : __hip_atomic_load(&claim[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != r)
+                u = -1;
+            int32_t tot;
+            const int32_t ex = block_excl_scan<BB>((int32_t)(u >= 0), t32, &tot);
+            if (u >= 0) {
+                order[nt + ex] = u;
+                set_mark(u);
+            }
+            nt += tot;
+        };
+#pragma unroll
+        for (int j = 0; j < kKeep; j++)
+            if (j * BB < ef) take(j * BB + (int32_t)threadIdx.x, c[j]);
+        for (int32_t r0 = kKeep * BB; r0 < ef; r0 += BB) {
+            const int32_t r = r0 + (int32_t)threadIdx.x;
+            take(r, r < ef ? reached(r) : -1);
+        }
         __syncthreads();
         head = tail;
         tail = nt;
@@ -181,9 +230,9 @@ __global__ __launch_bounds__(kBB) void k_bisect(BisectArgs a) {
             int32_t found = INT_MAX;
             while (found == INT_MAX && scanp < size) {
                 const int32_t i = scanp + threadIdx.x;
-                const int32_t hit = (i < size && !mark[slist[i]]) ? i : INT_MAX;
-                found = block_min<kBB>(hit, t32);
-                if (found == INT_MAX) scanp += kBB;
+                const int32_t hit = (i < size && !marked(slist[i])) ? i : INT_MAX;
+                found = block_min<BB>(hit, t32);
+                if (found == INT_MAX) scanp += BB;
             }
             if (found == INT_MAX) {  // cannot happen: target <= c(S)
                 stop = tail - 1;
@@ -192,16 +241,16 @@ __global__ __launch_bounds__(kBB) void k_bisect(BisectArgs a) {
             scanp = found;
             if (threadIdx.x == 0) {
                 order[tail] = slist[found];
-                mark[slist[found]] = 1;
+                set_mark(slist[found]);
             }
             __syncthreads();
             tail++;
         }
     }
     // ---- left side = order[0..stop]; the rest of S gets base + kl
-    for (int32_t i = threadIdx.x; i < size; i += kBB) blk[slist[i]] = base + kl;
+    for (int32_t i = threadIdx.x; i < size; i += BB) blk[slist[i]] = base + kl;
     __syncthreads();
-    for (int32_t p = threadIdx.x; p <= stop; p += kBB) blk[order[p]] = base;
+    for (int32_t p = threadIdx.x; p <= stop; p += BB) blk[order[p]] = base;
 }
 
 // ---- 2-way FM after a bisection (§III-B: the bisection is improved by local
@@ -1005,6 +1054,8 @@ int initial_partition_batch(const DevGraph &g, bool skip_isolated, const BatchIn
     hipLaunchKernelGGL(k_init_blk, dim3(grid_for((int64_t)n * attempts, 256, 65536)), dim3(256), 0, s, n, attempts,
                        g.xadj, skip_isolated, bi.d_gid, bi.d_kbase, blk);
     GP_LAUNCH_CHECK();
+    int32_t maxn = 0;
+    for (size_t i = 0; i + 1 < bi.voff.size(); i++) maxn = std::max(maxn, bi.voff[i + 1] - bi.voff[i]);
     std::vector<int32_t> hg, hb, hk;
     std::vector<int64_t> hr;
     for (auto &d : depth) {
@@ -1026,7 +1077,13 @@ int initial_partition_batch(const DevGraph &g, bool skip_isolated, const BatchIn
         GP_HIP(hipMemcpyAsync(reg, hr.data(), sizeof(int64_t) * hr.size(), hipMemcpyHostToDevice, s));
         BisectArgs a{n,    g.xadj, g.adjncy, g.vwgt, blk,        mark,       claim,           slist,
                      order, pre,   reg,      off,    sg,   sb, sk, bi.d_voff, bi.d_kbase, (int32_t)d.size(), seed};
-        hipLaunchKernelGGL(k_bisect, dim3((unsigned)(d.size() * bis)), dim3(kBB), 0, s, a);
+        // marks in LDS up to kBisectLds vertices; 256 threads once 1024 would not
+        // all be resident (two such workgroups per CU)
+        const unsigned nwg = (unsigned)(d.size() * bis);
+        const size_t lds = (size_t)maxn * 3 * sizeof(int32_t);
+        if (maxn > kBisectLds) hipLaunchKernelGGL((k_bisect<kBB, false>), dim3(nwg), dim3(kBB), 0, s, a, maxn);
+        else if (nwg > 512) hipLaunchKernelGGL((k_bisect<kBBSmall, true>), dim3(nwg), dim3(kBBSmall), lds, s, a, maxn);
+        else hipLaunchKernelGGL((k_bisect<kBB, true>), dim3(nwg), dim3(kBB), lds, s, a, maxn);
         GP_LAUNCH_CHECK();
         if (fm_passes > 0) {
             FmArgs fa{g.xadj, g.adjncy, g.adjwgt, g.vwgt, n,   blk,        mark,       gain,
