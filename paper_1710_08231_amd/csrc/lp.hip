@@ -739,11 +739,26 @@ __global__ __launch_bounds__(BLOCK) void k_pblock(LPArgs a, TierList lists, int 
     for (int i = threadIdx.x; i < TBL; i += BLOCK) tbl[i] = kSlotEmpty;
     __syncthreads();
     const int lane = lane_id(), w = threadIdx.x / kWave;
-    int64_t idx = xcd_block(blockIdx.x, gridDim.x);
-    int32_t v = idx < count ? verts[idx] : 0;
-    int32_t beg = idx < count ? a.xadj[v] : 0, end = idx < count ? a.xadj[v + 1] : 0;
-    int32_t own = idx < count ? a.labels[v] : -1;
-    if (idx < count && inactive(a, v, bit)) end = beg;
+    // the workgroup's vertices to evaluate: 64 list entries are looked at at once
+    // (every wave keeps them), inactive ones cost no more than that
+    int64_t at = xcd_block(blockIdx.x, gridDim.x);
+    uint64_t live = 0;
+    int32_t lv = 0;
+    const auto next = [&]() -> int32_t {
+        while (!live && at < count) {
+            const int64_t e = at + (int64_t)lane * gridDim.x;
+            lv = e < count ? verts[e] : -1;
+            live = __ballot(lv >= 0 && !inactive(a, lv, bit));
+            at += (int64_t)kWave * gridDim.x;
+        }
+        if (!live) return -1;
+        const int l = __ffsll((unsigned long long)live) - 1;
+        live &= live - 1;
+        return __builtin_amdgcn_readlane(lv, __builtin_amdgcn_readfirstlane(l));
+    };
+    int32_t v = next();
+    int32_t beg = v >= 0 ? a.xadj[v] : 0, end = v >= 0 ? a.xadj[v + 1] : 0;
+    int32_t own = v >= 0 ? a.labels[v] : -1;
     // entry it of this thread is beg + threadIdx.x + it * BLOCK
     int32_t L[MAXE], wv[MAXE];  // labels as gathered
     {
@@ -757,9 +772,8 @@ __global__ __launch_bounds__(BLOCK) void k_pblock(LPArgs a, TierList lists, int 
 #pragma unroll
         for (int it = 0; it < MAXE; it++) L[it] = u[it] >= 0 ? lb.x[u[it]] : -2;
     }
-    for (; idx < count; idx += gridDim.x) {
-        const int64_t nidx = idx + gridDim.x;
-        const int32_t nv = nidx < count ? verts[nidx] : 0;
+    while (v >= 0) {
+        const int32_t nv = next();
         int lg = 6;
         while ((1 << lg) < 2 * (end - beg) && (1 << lg) < TBL) lg++;
         const uint32_t cap = 1u << lg;
@@ -781,10 +795,9 @@ __global__ __launch_bounds__(BLOCK) void k_pblock(LPArgs a, TierList lists, int 
             }
         }
         // the next vertex: row, label, then its neighbour ids and weights
-        const int32_t nbeg = nidx < count ? a.xadj[nv] : 0;
-        int32_t nend = nidx < count ? a.xadj[nv + 1] : 0;
-        const int32_t nown = nidx < count ? a.labels[nv] : -1;
-        if (nidx < count && inactive(a, nv, bit)) nend = nbeg;
+        const int32_t nbeg = nv >= 0 ? a.xadj[nv] : 0;
+        const int32_t nend = nv >= 0 ? a.xadj[nv + 1] : 0;
+        const int32_t nown = nv >= 0 ? a.labels[nv] : -1;
         int32_t nu[MAXE];
 #pragma unroll
         for (int it = 0; it < MAXE; it++) {
