@@ -234,16 +234,23 @@ __global__ __launch_bounds__(256) void k_crow_wave(RowCtx c, const int32_t *rows
         sval[w][q] = 0;
     }
     wave_sync();
-    for (int64_t idx = (int64_t)blockIdx.x * NW + w; idx < count; idx += (int64_t)gridDim.x * NW) {
-        const int32_t i = rows[idx];
-        const int32_t m0 = c.mstart[i], m1 = c.mstart[i + 1];
-        const int32_t base = c.flat[m0], D = c.flat[m1] - base, M = m1 - m0;
+    // a row's id, members and entry range are requested while the row before is
+    // worked on: each is a step of the row's chain of dependent loads
+    const int64_t stride = (int64_t)gridDim.x * NW;
+    int64_t idx = (int64_t)blockIdx.x * NW + w;
+    int32_t i = idx < count ? rows[idx] : 0;
+    int32_t m0 = c.mstart[i], m1 = c.mstart[i + 1];
+    int32_t base = c.flat[m0], top = c.flat[m1];
+    for (; idx < count; idx += stride) {
+        const int32_t D = top - base, M = m1 - m0;
+        const int32_t ni = idx + stride < count ? rows[idx + stride] : 0;
         for (int q = lane; q <= M; q += kWave) sF[w][q] = c.flat[m0 + q] - base;
         wave_sync();
         int lg = 1;
         while ((1 << lg) < 2 * D) lg++;
         const uint32_t cap = 1u << lg;
         gather_insert<kRowWaveMax / kWave, kWave>(c, sF[w], m0, M - 1, lane, D, i, skey[w], sval[w], cap - 1, lg);
+        const int32_t nm0 = c.mstart[ni], nm1 = c.mstart[ni + 1];
         wave_sync();
         int32_t r = 0;
         for (uint32_t s0 = 0; s0 < cap; s0 += kWave) {
@@ -258,6 +265,7 @@ __global__ __launch_bounds__(256) void k_crow_wave(RowCtx c, const int32_t *rows
             r += __popcll(m);
         }
         wave_sync();
+        const int32_t nbase = c.flat[nm0], ntop = c.flat[nm1];
         for (int32_t q = lane; q < r; q += kWave) {
             const int32_t jj = lj[w][q];
             int32_t rank = 0;
@@ -271,6 +279,11 @@ __global__ __launch_bounds__(256) void k_crow_wave(RowCtx c, const int32_t *rows
             sval[w][q] = 0;
         }
         wave_sync();
+        i = ni;
+        m0 = nm0;
+        m1 = nm1;
+        base = nbase;
+        top = ntop;
     }
 }
 
