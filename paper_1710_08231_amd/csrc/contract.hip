@@ -746,11 +746,11 @@ int contract(const DevGraph &g, const int32_t *labels, bool skip_isolated, Coars
     GP_TRY(sc.alloc(&used, n));
     GP_TRY(sc.alloc(&id, n));
     GP_TRY(sc.alloc(&d_nc, 1));
-    GP_TRY(sc.alloc(&flags, 1));
+    GP_TRY(sc.alloc(&flags, 2));  // overflow, coarse entries: read back together
     GP_TRY(sc.alloc(&cw, n));
     GP_HIP(hipMemsetAsync(used, 0, sizeof(int32_t) * (size_t)n, s));
     GP_HIP(hipMemsetAsync(cw, 0, sizeof(int64_t) * (size_t)n, s));
-    GP_HIP(hipMemsetAsync(flags, 0, sizeof(int32_t), s));
+    GP_HIP(hipMemsetAsync(flags, 0, 2 * sizeof(int32_t), s));
     const unsigned gv = grid_for(n, 256, 65536);
     hipLaunchKernelGGL(k_mark_used, dim3(gv), dim3(256), 0, s, labels, g.xadj, n, skip_isolated, used);
     GP_LAUNCH_CHECK();
@@ -784,9 +784,11 @@ int contract(const DevGraph &g, const int32_t *labels, bool skip_isolated, Coars
         GP_TRY((scan<int32_t>(LoadIn<int32_t>{cnt}, StoreExcl<int32_t>{mstart}, nc, nullptr, mstart + nc, sc)));
         hipLaunchKernelGGL(k_members, dim3(gv), dim3(256), 0, s, out.f2c, g.xadj, n, mstart, fill, mrow, mdeg);
         GP_LAUNCH_CHECK();
-        int32_t ni = 0;
-        GP_HIP(hipMemcpyAsync(&ni, mstart + nc, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        GP_HIP(hipStreamSynchronize(s));
+        int32_t ni = n;  // members: every vertex, unless some are left out
+        if (skip_isolated) {
+            GP_HIP(hipMemcpyAsync(&ni, mstart + nc, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+            GP_HIP(hipStreamSynchronize(s));
+        }
         GP_TRY((scan<int32_t>(LoadIn<int32_t>{mdeg}, StoreExcl<int32_t>{flat}, ni, nullptr, flat + ni, sc)));
 
         int32_t *tj = nullptr, *rcnt = nullptr;
@@ -905,8 +907,7 @@ int contract(const DevGraph &g, const int32_t *labels, bool skip_isolated, Coars
             }
         }
         // ---- coarse row offsets and the compacted rows
-        int32_t *d_nnzc = nullptr;
-        GP_TRY(sc.alloc(&d_nnzc, 1));
+        int32_t *const d_nnzc = flags + 1;
         GP_TRY((scan<int32_t>(CountIn{rcnt}, CountOut{out.xadj}, nc, nullptr, d_nnzc, sc)));
         GP_HIP(hipMemcpyAsync(out.xadj + nc, d_nnzc, sizeof(int32_t), hipMemcpyDeviceToDevice, s));
         if (g.nnz / nc >= 128)
@@ -916,14 +917,14 @@ int contract(const DevGraph &g, const int32_t *labels, bool skip_isolated, Coars
             hipLaunchKernelGGL(k_copy_rows<16>, dim3(grid_for((int64_t)nc * 16, 256, 65536)), dim3(256), 0, s, c,
                                out.xadj, nc, out.adjncy, out.adjwgt, flags);
         GP_LAUNCH_CHECK();
-        GP_HIP(hipMemcpyAsync(&nnz_c, d_nnzc, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     } else {
         GP_HIP(hipMemsetAsync(out.xadj, 0, sizeof(int32_t) * (size_t)(nc + 1), s));
     }
-    int32_t ovf = 0;
-    GP_HIP(hipMemcpyAsync(&ovf, flags, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    int32_t hflags[2];
+    GP_HIP(hipMemcpyAsync(hflags, flags, sizeof(hflags), hipMemcpyDeviceToHost, s));
     GP_HIP(hipStreamSynchronize(s));
-    if (ovf) {
+    nnz_c = hflags[1];
+    if (hflags[0]) {
         set_error("contract: a coarse vertex or edge weight exceeds int32");
         return GP_ERR_OVERFLOW;
     }

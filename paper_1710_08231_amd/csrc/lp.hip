@@ -3059,11 +3059,11 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     GP_TRY(sc.alloc(&tkey2, n));
     GP_TRY(sc.alloc(&tval, n));
     GP_TRY(sc.alloc(&tval2, n));
-    unsigned long long *tedge = nullptr;
-    GP_TRY(sc.alloc(&tcnt, kTiers));
-    GP_TRY(sc.alloc(&tedge, kTiers));
-    GP_HIP(hipMemsetAsync(tcnt, 0, sizeof(int32_t) * kTiers, s));
-    GP_HIP(hipMemsetAsync(tedge, 0, sizeof(unsigned long long) * kTiers, s));
+    unsigned long long *tedge = nullptr;  // edges of each tier, then their vertex counts: cleared and read together
+    constexpr size_t kTierWords = kTiers + (kTiers + 1) / 2;
+    GP_TRY(sc.alloc(&tedge, kTierWords));
+    tcnt = reinterpret_cast<int32_t *>(tedge + kTiers);
+    GP_HIP(hipMemsetAsync(tedge, 0, sizeof(unsigned long long) * kTierWords, s));
     TierKey tk{g.xadj, labels, frozen, wide, {}};
     {
         const Tuning &tu = tuning();
@@ -3090,11 +3090,11 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     hipLaunchKernelGGL(k_tier_keys, dim3(grid_for(n, 256 * 8, 1024)), dim3(256), 0, s, tk, n, tkey, tval, tcnt, tedge);
     GP_LAUNCH_CHECK();
     GP_TRY((radix_sort<uint32_t, int32_t>(&tkey, &tval, &tkey2, &tval2, n, nullptr, 4, sc)));
-    int32_t hcnt[kTiers];
-    unsigned long long hedge[kTiers];
-    GP_HIP(hipMemcpyAsync(hcnt, tcnt, sizeof(hcnt), hipMemcpyDeviceToHost, s));
+    unsigned long long hedge[kTierWords];
     GP_HIP(hipMemcpyAsync(hedge, tedge, sizeof(hedge), hipMemcpyDeviceToHost, s));
     GP_HIP(hipStreamSynchronize(s));
+    int32_t hcnt[kTiers];
+    memcpy(hcnt, hedge + kTiers, sizeof(hcnt));
     int64_t tstart[kTiers + 1];
     tstart[0] = 0;
     for (int t = 0; t < kTiers; t++) tstart[t + 1] = tstart[t] + hcnt[t];
