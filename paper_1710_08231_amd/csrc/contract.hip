@@ -10,8 +10,9 @@
 //   row i's entries (j = f2c[u], w) with j != i are summed in a hash table
 //   keyed by j — in LDS for D_i <= 2048 (one wave per row up to 128 entries,
 //   one workgroup per row above), then the distinct columns are sorted in LDS;
-//   rows above 2048 entries are inserted chunk-wise into per-row global
-//   tables and only their distinct (row, column) pairs are radix sorted;
+//   rows of at most 32 entries need no table (16 or 32 lanes per row); rows
+//   above 2048 entries are summed chunk-wise and only a chunk's distinct
+//   (row, column) pairs are radix sorted;
 //   a scan of the per-row column counts gives the coarse row offsets and a
 //   copy compacts the rows.
 #include <algorithm>
@@ -142,6 +143,7 @@ __global__ void k_halve(int64_t *x) { *x /= 2; }
 
 // ---------------------------------------------------------------- row-grouped contraction
 
+constexpr int kRowClasses = 6;      // 16 lanes, 32 lanes, a wave, two workgroup sizes, chunks
 constexpr int kRowWaveMax = 128;    // D_i <= 128: one wave per row
 constexpr int kRowSmallMax = 512;   // D_i <= 512: one small workgroup per row
 constexpr int kRowBlockMax = 2048;  // D_i <= 2048: one workgroup per row
@@ -218,6 +220,79 @@ __device__ __forceinline__ void gather_insert(const RowCtx &c, const int32_t *F,
 #pragma unroll
     for (int q = 0; q < UB; q++)
         if (first + q * STRIDE < tend && x[q] != i) col_insert(skey, sval, mask, lg, x[q], wt[q]);
+}
+
+// Rows of at most G entries (and members), G lanes each, one entry per lane: the
+// lanes of one column add up its weights from LDS, the first of them holds it, and
+// its rank is the number of smaller held columns. Bound: the latency of a row's
+// chain of dependent loads, so the number of rows in flight: kWave / G per wave
+// instead of one, without a table (grid 256^3, all levels: rows of up to 128
+// entries 22.3 ms with a wave and a table each, 11.3 with these two classes).
+template <int G>
+__global__ __launch_bounds__(256) void k_crow_lanes(RowCtx c, const int32_t *rows, int32_t count) {
+    constexpr int NG = 256 / G, RPW = kWave / G;
+    __shared__ int32_t sF[NG][G + 1];
+    __shared__ __align__(16) int32_t sj[NG][G], sw[NG][G];
+    const int lane = lane_id(), gl = lane % G, grp = threadIdx.x / G;
+    const int64_t stride = (int64_t)gridDim.x * NG;
+    const int64_t wave0 = (int64_t)blockIdx.x * NG + (threadIdx.x / kWave) * RPW;  // the wave's first row
+    int64_t idx = wave0 + lane / G;
+    int32_t i = idx < count ? rows[idx] : 0;
+    int32_t m0 = c.mstart[i], m1 = c.mstart[i + 1];
+    int32_t base = c.flat[m0], top = c.flat[m1];
+    for (int64_t w0 = wave0; w0 < count; w0 += stride, idx += stride) {
+        const bool valid = idx < count;
+        const int32_t D = valid ? top - base : 0, M = m1 - m0;
+        const int32_t ni = idx + stride < count ? rows[idx + stride] : 0;
+        if (valid && gl < M) sF[grp][gl] = c.flat[m0 + gl] - base;
+        wave_sync();
+        int32_t j = -1, wt = 0;
+        if (gl < D) {
+            const int32_t p = upper_pos(sF[grp], 0, M - 1, gl);
+            const int32_t e = c.mrow[m0 + p] + (gl - sF[grp][p]);
+            wt = c.adjwgt ? c.adjwgt[e] : 1;
+            j = c.f2c[c.adjncy[e]];
+            if (j == i) j = -1;
+        }
+        const int32_t nm0 = c.mstart[ni], nm1 = c.mstart[ni + 1];
+        sj[grp][gl] = j;
+        sw[grp][gl] = wt;
+        wave_sync();
+        const int32_t maxD = wave_max(D);
+        long long sum = 0;
+        uint32_t same = 0;  // entries of this lane's column
+        for (int x = 0; x < maxD; x += 4) {
+            const int4 y = *reinterpret_cast<const int4 *>(&sj[grp][x]);
+            const int4 z = *reinterpret_cast<const int4 *>(&sw[grp][x]);
+            sum += (y.x == j ? z.x : 0) + (long long)(y.y == j ? z.y : 0) + (y.z == j ? z.z : 0) +
+                   (long long)(y.w == j ? z.w : 0);
+            same |= ((uint32_t)(y.x == j) | (uint32_t)(y.y == j) << 1 | (uint32_t)(y.z == j) << 2 |
+                     (uint32_t)(y.w == j) << 3)
+                    << x;
+        }
+        const bool holds = j >= 0 && (same & ((1u << gl) - 1u)) == 0;
+        wave_sync();
+        sj[grp][gl] = holds ? j : INT_MAX;
+        wave_sync();
+        const int32_t nbase = c.flat[nm0], ntop = c.flat[nm1];
+        int32_t rank = 0;
+        for (int x = 0; x < maxD; x += 4) {
+            const int4 y = *reinterpret_cast<const int4 *>(&sj[grp][x]);
+            rank += (int32_t)(y.x < j) + (int32_t)(y.y < j) + (int32_t)(y.z < j) + (int32_t)(y.w < j);
+        }
+        if (holds) {
+            c.tj[base + rank] = j;
+            c.tw[base + rank] = sum;
+        }
+        const uint64_t hm = __ballot(holds);
+        if (valid && gl == 0) c.rcnt[i] = (int32_t)__popcll((hm >> (lane / G * G)) & ((1ull << G) - 1ull));
+        wave_sync();
+        i = ni;
+        m0 = nm0;
+        m1 = nm1;
+        base = nbase;
+        top = ntop;
+    }
 }
 
 __global__ __launch_bounds__(256) void k_crow_wave(RowCtx c, const int32_t *rows, int32_t count) {
@@ -601,8 +676,8 @@ __global__ void k_members(const int32_t *f2c, const int32_t *xadj, int32_t n, co
 
 __global__ void k_row_class(const int32_t *mstart, const int32_t *flat, int32_t nc, uint32_t *key, int32_t *val,
                             int32_t *ccount) {
-    __shared__ int32_t h[4];
-    if (threadIdx.x < 4) h[threadIdx.x] = 0;
+    __shared__ int32_t h[kRowClasses];
+    if (threadIdx.x < kRowClasses) h[threadIdx.x] = 0;
     __syncthreads();
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nc; i += (int64_t)gridDim.x * blockDim.x) {
         // size = max(entries, members): members without neighbours (possible for
@@ -610,13 +685,13 @@ __global__ void k_row_class(const int32_t *mstart, const int32_t *flat, int32_t 
         const int32_t D = flat[mstart[i + 1]] - flat[mstart[i]];
         const int32_t M = mstart[i + 1] - mstart[i];
         const int32_t sz = D > M ? D : M;
-        const uint32_t k = sz <= kRowWaveMax ? 0u : sz <= kRowSmallMax ? 1u : sz <= kRowBlockMax ? 2u : 3u;
+        const uint32_t k = sz <= 16 ? 0u : sz <= 32 ? 1u : sz <= kRowWaveMax ? 2u : sz <= kRowSmallMax ? 3u : sz <= kRowBlockMax ? 4u : 5u;
         key[i] = k;
         val[i] = (int32_t)i;
         atomicAdd(&h[k], 1);
     }
     __syncthreads();
-    if (threadIdx.x < 4 && h[threadIdx.x]) atomicAdd(&ccount[threadIdx.x], h[threadIdx.x]);
+    if (threadIdx.x < kRowClasses && h[threadIdx.x]) atomicAdd(&ccount[threadIdx.x], h[threadIdx.x]);
 }
 
 // one wave per big row: its lanes write the row's (possibly thousands of) chunk owners
@@ -805,31 +880,40 @@ int contract(const DevGraph &g, const int32_t *labels, bool skip_isolated, Coars
         GP_TRY(sc.alloc(&ck2, nc));
         GP_TRY(sc.alloc(&cv, nc));
         GP_TRY(sc.alloc(&cv2, nc));
-        GP_TRY(sc.alloc(&ccount, 4));
-        GP_HIP(hipMemsetAsync(ccount, 0, sizeof(int32_t) * 4, s));
+        GP_TRY(sc.alloc(&ccount, kRowClasses));
+        GP_HIP(hipMemsetAsync(ccount, 0, sizeof(int32_t) * kRowClasses, s));
         hipLaunchKernelGGL(k_row_class, dim3(grid_for(nc, 256, 4096)), dim3(256), 0, s, mstart, flat, nc, ck, cv,
                            ccount);
         GP_LAUNCH_CHECK();
-        GP_TRY((radix_sort<uint32_t, int32_t>(&ck, &cv, &ck2, &cv2, nc, nullptr, 2, sc)));
-        int32_t hc[4];
+        GP_TRY((radix_sort<uint32_t, int32_t>(&ck, &cv, &ck2, &cv2, nc, nullptr, 3, sc)));
+        int32_t hc[kRowClasses];
         GP_HIP(hipMemcpyAsync(hc, ccount, sizeof(hc), hipMemcpyDeviceToHost, s));
         GP_HIP(hipStreamSynchronize(s));
-        const int32_t *rows_w = cv, *rows_s = cv + hc[0], *rows_b = rows_s + hc[1], *rows_g = rows_b + hc[2];
+        const int32_t *rows_16 = cv, *rows_32 = cv + hc[0], *rows_w = rows_32 + hc[1], *rows_s = rows_w + hc[2],
+                      *rows_b = rows_s + hc[3], *rows_g = rows_b + hc[4];
         if (hc[0] > 0) {
-            hipLaunchKernelGGL(k_crow_wave, dim3(grid_for(hc[0], 4, 65536)), dim3(256), 0, s, c, rows_w, hc[0]);
+            hipLaunchKernelGGL(k_crow_lanes<16>, dim3(grid_for(hc[0], 16, 16384)), dim3(256), 0, s, c, rows_16, hc[0]);
             GP_LAUNCH_CHECK();
         }
         if (hc[1] > 0) {
-            hipLaunchKernelGGL((k_crow_block<kCBSmall, kRowSmallMax>), dim3(grid_for(hc[1], 1, 32768)), dim3(kCBSmall),
-                               0, s, c, rows_s, hc[1]);
+            hipLaunchKernelGGL(k_crow_lanes<32>, dim3(grid_for(hc[1], 8, 16384)), dim3(256), 0, s, c, rows_32, hc[1]);
             GP_LAUNCH_CHECK();
         }
         if (hc[2] > 0) {
-            hipLaunchKernelGGL((k_crow_block<kCB, kRowBlockMax>), dim3(grid_for(hc[2], 1, 8192)), dim3(kCB), 0, s, c,
-                               rows_b, hc[2]);
+            hipLaunchKernelGGL(k_crow_wave, dim3(grid_for(hc[2], 4, 65536)), dim3(256), 0, s, c, rows_w, hc[2]);
             GP_LAUNCH_CHECK();
         }
-        const int32_t nb = hc[3];
+        if (hc[3] > 0) {
+            hipLaunchKernelGGL((k_crow_block<kCBSmall, kRowSmallMax>), dim3(grid_for(hc[3], 1, 32768)), dim3(kCBSmall),
+                               0, s, c, rows_s, hc[3]);
+            GP_LAUNCH_CHECK();
+        }
+        if (hc[4] > 0) {
+            hipLaunchKernelGGL((k_crow_block<kCB, kRowBlockMax>), dim3(grid_for(hc[4], 1, 8192)), dim3(kCB), 0, s, c,
+                               rows_b, hc[4]);
+            GP_LAUNCH_CHECK();
+        }
+        const int32_t nb = hc[5];
         if (nb > 0) {
             int32_t *nch = nullptr, *cfirst = nullptr, *d_tot = nullptr, *cown = nullptr, *cursor = nullptr,
                     *head = nullptr, *d_runs = nullptr, *roff = nullptr;
