@@ -2600,7 +2600,7 @@ __global__ __launch_bounds__(kFuseBlock) void k_rounds_settled(LPArgs a, int32_t
 }
 
 // ---------------------------------------------------------------- active-set rounds
-// act[v] = evaluations v still owes (see k_act_step, k_admit, k_act_mark).
+// act[v] = evaluations v still owes (see k_act_step, the admission kernels, k_act_mark).
 
 __global__ void k_act_fill(uint8_t *act, int32_t n, uint8_t c) {
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
