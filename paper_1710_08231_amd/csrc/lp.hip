@@ -2413,10 +2413,17 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32
 // lane group, labels from LDS), admits the movers in order and marks their
 // neighbours. The host does not launch it for graphs of more than kSettledNnz
 // entries or with vertices above the 64-lane tier (a hub's row would keep 16
-// lanes busy for long: 1.4 ms a run on R-MAT's coarse levels), and it returns as soon as more than kSettledMost vertices are to be
-// evaluated at once (the rounds go on with the launched kernels then).
+// lanes busy for long: 1.4 ms a run on R-MAT's coarse levels), and it returns as
+// soon as more than settled_most vertices are to be evaluated at once (the rounds
+// go on with the launched kernels then).
 constexpr int kSettledGroups = kFuseBlock / 16;
 constexpr int kSettledMost = 2048;
+// Vertices to evaluate in a round up to which one workgroup beats the round's own
+// launches (about 20 us): a step of kSettledGroups vertices takes longer the more
+// labels there are. With 2048 for all, refinement of an rgg of 2500 vertices, k = 64,
+// took 1.6 ms (1.2 with launches only, 0.87 with 512 and 0.92 with 1024); above 64
+// labels the launches won (12 x 14 x 11 grid, k = 256: 0.82 against 1.28 ms).
+constexpr int settled_most(int KT) { return KT == 16 ? kSettledMost : 1024; }
 constexpr int64_t kSettledNnz = 1 << 19;
 template <int KT>
 __global__ __launch_bounds__(kFuseBlock) void k_rounds_settled(LPArgs a, int32_t n, int32_t nlabels, int32_t rounds,
@@ -2465,7 +2472,7 @@ __global__ __launch_bounds__(kFuseBlock) void k_rounds_settled(LPArgs a, int32_t
         }
         int32_t m = 0;
         int32_t at = fuse_excl_scan<int32_t>(__popc(live), tmpi, &m);
-        if (m > kSettledMost) break;  // uniform
+        if (m > settled_most(KT)) break;  // uniform
         for (int i = 0; i < 16; i++)
             if ((live >> i) & 1) list[at++] = (uint16_t)(threadIdx.x * 16 + i);
         for (int32_t i = threadIdx.x; i < KT; i += kFuseBlock) {
@@ -3083,7 +3090,12 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         }
         // small levels: one launch of 32 lanes per vertex instead of up to four
         // (each launch costs a few microseconds, and the chip is not full)
-        if (n <= kFuseMax) tk.bound[1] = tk.bound[2] = tk.bound[3] = 0;
+        // Above 16 labels a 32-lane table costs more than its launch where nearly all
+        // vertices have at most 8 neighbours: those keep the 8-lane kernel.
+        if (n <= kFuseMax) {
+            tk.bound[1] = tk.bound[2] = tk.bound[3] = 0;
+            if (dense_tiers && nlabels > 16 && g.nnz <= 8 * (int64_t)n) tk.bound[2] = tk.bound[3] = 8;
+        }
         for (int t = 1; t < kTiers - 1; t++) tk.bound[t] = std::max(tk.bound[t], tk.bound[t - 1]);
     }
     // few workgroups: each adds its counts to one cache line
@@ -3351,7 +3363,10 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     // four vertices on average) where the round tail leaves lists of the movers;
     // in clustering most vertices neighbour a mover in every round
     // (on small levels, where one launch can then run all later rounds)
-    const bool settled = fuse_rest && dense && !wide && nbig == 0 && g.nnz <= kSettledNnz && (int64_t)nlabels * 4 <= n &&
+    // (between 17 and 64 labels only up to 2048 vertices: above, more than settled_most
+    // of them stay active and the try is lost, 50 us of about 900)
+    const bool settled = fuse_rest && dense && (nlabels <= 16 || (nlabels <= 64 && n <= 2048)) && !wide && nbig == 0 &&
+                         g.nnz <= kSettledNnz && (int64_t)nlabels * 4 <= n &&
                          rounds > 2 && !use_round_graphs() && !prof_blocks_replay();
     if (settled || (!fuse_rest && !act && (int64_t)nlabels * 4 <= n)) {
         GP_TRY(sc.alloc(&ac.todo, n));
@@ -3555,19 +3570,25 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         a.capv = capv;
         a.dir_alternate = dir_alternate;
         const dim3 one(1), block(kFuseBlock);
-        if (KTd == 16)
-            hipLaunchKernelGGL(k_rounds_settled<16>, one, block, 0, s, a, n, nlabels, rounds, labels, W, lab8, dev, ac.todo);
-        else if (KTd == 64)
-            hipLaunchKernelGGL(k_rounds_settled<64>, one, block, 0, s, a, n, nlabels, rounds, labels, W, lab8, dev, ac.todo);
-        else
-            hipLaunchKernelGGL(k_rounds_settled<256>, one, block, 0, s, a, n, nlabels, rounds, labels, W, lab8, dev, ac.todo);
-        GP_LAUNCH_CHECK();
-        LPDev h;
-        GP_HIP(hipMemcpyAsync(&h, dev, sizeof(LPDev), hipMemcpyDeviceToHost, s));
-        GP_HIP(hipStreamSynchronize(s));
+        // It stops before the end where too many vertices are to be evaluated:
+        // then some launched rounds, another try, more of them, and the last one
+        // (a try that stops at once costs 50 us: only with 16 labels, where most pay;
+        // 20 x 24 x 21 grid, k = 3: 663 -> 472 us).
         const ProfSuspend quiet(prof_first_round_only());
-        // (it stopped before them where too many vertices were to be evaluated)
-        for (int32_t r = h.done ? rounds : h.round; r < rounds; r++) GP_TRY(emit_round(s));
+        for (int32_t more = 2;; more *= 2) {
+            if (KTd == 16)
+                hipLaunchKernelGGL(k_rounds_settled<16>, one, block, 0, s, a, n, nlabels, rounds, labels, W, lab8, dev, ac.todo);
+            else
+                hipLaunchKernelGGL(k_rounds_settled<64>, one, block, 0, s, a, n, nlabels, rounds, labels, W, lab8, dev, ac.todo);
+            GP_LAUNCH_CHECK();
+            LPDev h;
+            GP_HIP(hipMemcpyAsync(&h, dev, sizeof(LPDev), hipMemcpyDeviceToHost, s));
+            GP_HIP(hipStreamSynchronize(s));
+            const int32_t left = h.done ? 0 : rounds - h.round;
+            const bool last = KTd != 16 || more > 4 || left <= more;
+            for (int32_t r = 0; r < (last ? left : more); r++) GP_TRY(emit_round(s));
+            if (last) break;
+        }
     } else if (rounds > 1) {
         bool replayed = false;
         if (use_round_graphs() && !prof_blocks_replay() && !sc.is_static()) {
