@@ -284,19 +284,18 @@ __device__ __forceinline__ void round_end(const AdmitCtx &c, int32_t extra, int3
 }
 
 // One workgroup per label sums its weight changes; the first also ends the round.
-// (A workgroup that sees the stop flag just set has nothing to add: a round that
-// sets it moved nothing.)
+// Only the first reads the stop flag, because it is the one that sets it: a wave
+// of another workgroup could see it before or after. The others need no test:
+// the round that sets the flag moved nothing and left all zeros in part, and the
+// rounds after it write none.
 __global__ __launch_bounds__(256) void k_dadm_end(AdmitCtx c) {
     __shared__ int64_t t64[256 / kWave + 1];
     __shared__ int32_t t32[256 / kWave + 1];
     const int32_t t = blockIdx.x;
-    if (!c.dev->done) {
-        int64_t s = 0;
-        for (int32_t i = threadIdx.x; i < c.ntiles; i += 256) s += c.part[(int64_t)t * c.ntiles + i];
-        s = block_sum<256>(s, t64);
-        if (threadIdx.x == 0 && s) c.W[t] += s;
-    }
-    __syncthreads();
+    int64_t s = 0;
+    for (int32_t i = threadIdx.x; i < c.ntiles; i += 256) s += c.part[(int64_t)t * c.ntiles + i];
+    s = block_sum<256>(s, t64);
+    if (threadIdx.x == 0 && s) c.W[t] += s;
     if (t == 0) round_end(c, 0, c.dev->done ? 0 : c.ncol, t32);
 }
 
