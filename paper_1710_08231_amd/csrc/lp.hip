@@ -402,9 +402,18 @@ __global__ __launch_bounds__(kPropBlock) void k_propose_group(LPArgs a, TierList
 // room under its bound (then for the best label with room), exactly as before.
 constexpr unsigned long long kSlotEmpty = 0xFFFFFFFF00000000ull;
 
-__device__ __forceinline__ unsigned long long pack_best(uint32_t c, int32_t L) {
+// The one packing of (connection, label), larger for a larger connection, then for
+// a smaller label, and never 0; its label.
+__host__ __device__ constexpr unsigned long long pack_best(uint32_t c, int32_t L) {
     return ((unsigned long long)c << 32) | (uint32_t)(~(uint32_t)L);
 }
+__host__ __device__ constexpr int32_t best_label(unsigned long long p) { return (int32_t)~(uint32_t)p; }
+// also with a connection held as int32_t (the hub tables), at both ends of the labels
+static_assert(best_label(pack_best(int32_t(5), 0)) == 0 && best_label(pack_best(5u, 0)) == 0, "packing");
+static_assert(best_label(pack_best(int32_t(INT_MAX), INT_MAX)) == INT_MAX, "packing");
+static_assert(pack_best(int32_t(1), 3) == pack_best(1u, 3) && pack_best(1, 2) > pack_best(1, 3) &&
+                  pack_best(2, 3) > pack_best(1, 2) && pack_best(0u, INT_MAX) != 0,
+              "packing");
 
 // Adds w to label L's slot (inserting it); returns the slot, *sum the label's sum after the add.
 __device__ __forceinline__ uint32_t slot_add(unsigned long long *tbl, uint32_t mask, int lg, int32_t L, uint32_t w,
@@ -565,7 +574,7 @@ __global__ __launch_bounds__(kPropBlock) void k_pgroup(LPArgs a, TierList lists,
         oc = group_sum<GL>(oc);
         mybest = group_max_u64<GL>(mybest);
         const int32_t bc = (int32_t)(mybest >> 32);
-        const int32_t bl = mybest ? (int32_t)~(uint32_t)mybest : INT_MAX;
+        const int32_t bl = mybest ? best_label(mybest) : INT_MAX;
         const int64_t cv = valid ? vweight(a.vwgt, v) : 0;
         int32_t target = -1;
         bool need2 = false;
@@ -683,7 +692,7 @@ __global__ __launch_bounds__(kPropBlock) void k_plane(LPArgs a, TierList lists, 
             const bool cand = L >= 0 && L != own && dir_ok(L, own, dmode);
             const unsigned long long best = group_max_u64<GL>(cand ? pack_best((uint32_t)c, L) : 0ull);
             const int32_t bc = (int32_t)(best >> 32);
-            const int32_t bl = best ? (int32_t)~(uint32_t)best : INT_MAX;
+            const int32_t bl = best ? best_label(best) : INT_MAX;
             const int64_t cv = v >= 0 ? vweight(a.vwgt, v) : 0;
             int32_t target = -1;
             bool need2 = false;
@@ -814,7 +823,7 @@ __global__ __launch_bounds__(BLOCK) void k_pblock(LPArgs a, TierList lists, int 
         unsigned long long best = wbest[0];
         for (int i = 1; i < NW; i++) best = wbest[i] > best ? wbest[i] : best;
         const int32_t bc = (int32_t)(best >> 32);
-        const int32_t bl = best ? (int32_t)~(uint32_t)best : INT_MAX;
+        const int32_t bl = best ? best_label(best) : INT_MAX;
         const int64_t cv = vweight(a.vwgt, v);
         int32_t target = -1;
         if (bl != INT_MAX && bc > oc) {
@@ -1032,12 +1041,11 @@ __global__ __launch_bounds__(BLOCK) void k_propose_hub(LPArgs a, const int32_t *
 // distinct labels into the hub's buckets (a hash of the label picks one),
 // writing each bucket's pairs as one contiguous run of that bucket's region.
 // One workgroup per bucket then sums the bucket's pairs in LDS and offers the
-// best label with room, packed into a 64-bit key merged with atomicMax: high
-// word conn, low word INT_MAX - label, so the maximum is the largest
-// connection with the smallest label. Used for 32-bit connection sums (the
-// packed key needs conn < 2^31). Nothing is hashed into global memory unless a
-// bucket's region overflows: its pairs then go to the hub's overflow table,
-// which a third kernel scans (and empties) only for such hubs.
+// best label with room, packed by pack_best into a 64-bit key merged with
+// atomicMax. Used for 32-bit connection sums (the key has 32 bits for them).
+// Nothing is hashed into global memory unless a bucket's region overflows: its
+// pairs then go to the hub's overflow table, which a third kernel scans (and
+// empties) only for such hubs.
 constexpr int kHubChunk = 4096;
 constexpr int kHubSlice = 4096;
 constexpr int kHubPer = 2048;       // buckets per hub: degree / kHubPer, rounded up
@@ -1065,10 +1073,6 @@ struct HubPlan {
     unsigned long long *own;   // [nh] connection to the hub's own label
     unsigned long long *best;  // [nh] best packed (conn, label) with room
 };
-
-__device__ __forceinline__ unsigned long long pack_best(int32_t c, int32_t L) {
-    return ((unsigned long long)(uint32_t)c << 32) | (unsigned long long)(uint32_t)(INT_MAX - L);
-}
 
 // Bucket of a label: MurmurHash3's 32-bit finaliser (fmix32), scaled to nb by a
 // multiply-high. Independent of the top bits of hash_label that place the
@@ -1209,25 +1213,14 @@ __global__ __launch_bounds__(kRedBlock) void k_hub_reduce(LPArgs a, HubPlan hp) 
     __syncthreads();
     const int64_t cv = vweight(a.vwgt, hp.hubs[h]);
     unsigned long long best = 0;
-    for (int i = threadIdx.x; i < cap; i += kRedBlock)
-        if (skey[i] >= 0) {
-            const unsigned long long pk = pack_best(sval[i], skey[i]);
+    for (int i = threadIdx.x; i < cap; i += kRedBlock) {
+        const int32_t L = skey[i];
+        if (L >= 0 && a.W[L] + cv <= capof(a, L)) {
+            const unsigned long long pk = pack_best(sval[i], L);
             best = pk > best ? pk : best;
         }
-    best = block_max<kRedBlock>(best, tmp);
-    if (best) {  // uniform: the bucket's strongest label, or, without room, the strongest with room
-        const int32_t L0 = INT_MAX - (int32_t)(uint32_t)best;
-        if (a.W[L0] + cv > capof(a, L0)) {
-            best = 0;
-            for (int i = threadIdx.x; i < cap; i += kRedBlock) {
-                const int32_t L = skey[i];
-                if (L < 0) continue;
-                const unsigned long long pk = pack_best(sval[i], L);
-                if (pk > best && a.W[L] + cv <= capof(a, L)) best = pk;
-            }
-            best = block_max<kRedBlock>(best, tmp);
-        }
     }
+    best = block_max<kRedBlock>(best, tmp);
     if (threadIdx.x == 0) {
         if (best) atomicMax(&hp.best[h], best);
         hp.fill[gb] = 0;
@@ -1277,7 +1270,7 @@ __global__ void k_hub_decide(LPArgs a, HubPlan hp, int32_t nh) {
         int32_t target = -1;
         if (b) {
             const int64_t c = (int64_t)(b >> 32);
-            const int32_t L = INT_MAX - (int32_t)(uint32_t)(b & 0xFFFFFFFFull);
+            const int32_t L = best_label(b);
             if (c > oc) target = L;
         }
         a.prop[hp.hubs[h]] = target;
