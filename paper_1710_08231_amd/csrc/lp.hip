@@ -2032,6 +2032,10 @@ struct TierKey {
     const uint8_t *frozen;  // optional: vertices with frozen[v] != 0 go to tier 0 (keep their label)
     bool wide;
     int32_t bound[kTiers];  // upper degree bound of each tier (non-decreasing, the last is INT_MAX)
+    // in a list that is evaluated (tiers 1 and up)
+    __device__ __forceinline__ bool listed(int64_t v) const {
+        return xadj[v + 1] > xadj[v] && !(active && active[v] < 0) && !(frozen && frozen[v]);
+    }
 };
 
 __global__ void k_tier_keys(TierKey tk, int32_t n, uint32_t *key, int32_t *val, int32_t *counts,
@@ -2047,7 +2051,7 @@ __global__ void k_tier_keys(TierKey tk, int32_t n, uint32_t *key, int32_t *val, 
          v += (int64_t)gridDim.x * blockDim.x) {
         const int32_t d = tk.xadj[v + 1] - tk.xadj[v];
         int t = 0;
-        if (d > 0 && !(tk.active && tk.active[v] < 0) && !(tk.frozen && tk.frozen[v])) {
+        if (tk.listed(v)) {
             t = 1;
             while (t < kTiers - 1 && d > tk.bound[t]) t++;
         }
@@ -2597,6 +2601,13 @@ __global__ __launch_bounds__(kFuseBlock) void k_rounds_settled(LPArgs a, int32_t
         dev->prev_moves = prev;
         dev->done = done;
     }
+}
+
+// Both directions for the vertices of the tier lists, none for the others: the
+// settled rounds take their vertices from these bytes, not from the lists.
+__global__ void k_todo_fill(TierKey tk, int32_t n, uint8_t *todo) {
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
+        todo[v] = tk.listed(v) ? kTodoBoth : 0;
 }
 
 // ---------------------------------------------------------------- active-set rounds
@@ -3358,12 +3369,18 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     // (on small levels, where one launch can then run all later rounds)
     // (between 17 and 64 labels only up to 2048 vertices: above, more than settled_most
     // of them stay active and the try is lost, 50 us of about 900)
-    const bool settled = fuse_rest && dense && (nlabels <= 16 || (nlabels <= 64 && n <= 2048)) && !wide && nbig == 0 &&
+    // (a frozen vertex is only kept out of the lists: its neighbours' moves would mark it)
+    const bool settled = fuse_rest && !frozen && dense && (nlabels <= 16 || (nlabels <= 64 && n <= 2048)) && !wide && nbig == 0 &&
                          g.nnz <= kSettledNnz && (int64_t)nlabels * 4 <= n &&
                          rounds > 2 && !use_round_graphs() && !prof_blocks_replay();
     if (settled || (!fuse_rest && !act && (int64_t)nlabels * 4 <= n)) {
         GP_TRY(sc.alloc(&ac.todo, n));
-        GP_HIP(hipMemsetAsync(ac.todo, kTodoBoth, (size_t)n, s));
+        if (settled) {
+            hipLaunchKernelGGL(k_todo_fill, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, tk, n, ac.todo);
+            GP_LAUNCH_CHECK();
+        } else {
+            GP_HIP(hipMemsetAsync(ac.todo, kTodoBoth, (size_t)n, s));
+        }
     }
 
     // ---- labels with the class of their room, for the tables of the 64-lane,
