@@ -58,7 +58,7 @@ constexpr int kSelBins = 1 << kSelBits;
 
 struct AdmitCtx {
     int32_t n, nlabels;
-    int32_t *prop;  // [n rounded up to kDadmChunk] proposed label, -1: none; all -1 again after the round
+    int32_t *prop;  // [n] proposed label, -1: none; all -1 again after the round
     const int32_t *vwgt;
     int64_t *W;
     int64_t U;
@@ -111,7 +111,14 @@ __device__ __forceinline__ void refuse(const AdmitCtx &c, int32_t v) {
 
 // ---------------------------------------------------------------- up to 256 labels
 
-__device__ __forceinline__ void load16(const int32_t *p, int32_t (&t)[16]) {
+// The proposals of vertices v0 .. v0 + 15, -1 past the last vertex.
+__device__ __forceinline__ void load16(const AdmitCtx &c, int64_t v0, int32_t (&t)[16]) {
+    const int32_t *p = c.prop + v0;
+    if (v0 + 16 > c.n) {
+#pragma unroll
+        for (int i = 0; i < 16; i++) t[i] = v0 + i < c.n ? p[i] : -1;
+        return;
+    }
     const int4 *q = reinterpret_cast<const int4 *>(p);
 #pragma unroll
     for (int i = 0; i < 4; i++) {
@@ -133,7 +140,7 @@ __global__ __launch_bounds__(kDadmBlock) void k_dadm_tally(AdmitCtx c) {
         const int64_t v0 = (int64_t)tile * c.tile + o + threadIdx.x * 16;
         if (v0 >= c.n) break;
         int32_t t[16];
-        load16(c.prop + v0, t);
+        load16(c, v0, t);
 #pragma unroll
         for (int i = 0; i < 16; i++)
             if (t[i] >= 0) atomicAdd(&h[t[i]], (unsigned long long)vweight(c.vwgt, (int32_t)v0 + i));
@@ -193,10 +200,7 @@ __global__ __launch_bounds__(kDadmBlock) void k_dadm_apply(AdmitCtx c) {
             const int64_t v0 = (int64_t)tile * c.tile + o + threadIdx.x * 16;
             if ((int64_t)tile * c.tile + o >= c.n) break;  // uniform
             int32_t t[16];
-            if (v0 < c.n) load16(c.prop + v0, t);
-            else
-#pragma unroll
-                for (int i = 0; i < 16; i++) t[i] = -1;
+            load16(c, v0, t);
             uint32_t adm = 0, mine = 0;  // bit i: vertex v0 + i is admitted; decided here
             if (ordered) {
                 int64_t s = 0;

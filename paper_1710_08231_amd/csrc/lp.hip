@@ -3283,10 +3283,9 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     // ---- per-round buffers
     int32_t *prop = nullptr;
     LPDev *dev = nullptr;
-    const size_t npad = ((size_t)n + kDadmChunk - 1) / kDadmChunk * kDadmChunk;
-    GP_TRY(sc.alloc(&prop, npad));
+    GP_TRY(sc.alloc(&prop, n));
     GP_TRY(sc.alloc(&dev, 1));
-    GP_HIP(hipMemsetAsync(prop, 0xFF, sizeof(int32_t) * npad, s));
+    GP_HIP(hipMemsetAsync(prop, 0xFF, sizeof(int32_t) * (size_t)n, s));
     GP_HIP(hipMemsetAsync(dev, 0, sizeof(LPDev), s));
     GroupState *gstate = nullptr;
     if (group && ngroups > 0) {
@@ -3298,6 +3297,9 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     const int key_bits = bits_for(nlabels > 0 ? nlabels - 1 : 0);
     const int vbits = bits_for(n > 0 ? n - 1 : 0);
     const bool fuse_rest = !group && !active && n <= kFuseMax && nlabels <= kFuseMax && vbits + key_bits <= 32;
+    // Admission by tiles up to 256 labels, unless there are more labels than vertices:
+    // its 24 bytes a label would then be more than all other buffers of the round.
+    const bool tiled = dense && nlabels <= n;
     AdmitCtx ac{};
     if (!fuse_rest) {
         ac.n = n;
@@ -3313,37 +3315,44 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         ac.group = group;
         ac.gs = gstate;
         ac.vbits = vbits;
-        if (dense) {
-            const int64_t chunks = (int64_t)(npad / kDadmChunk);
+        // the tier sort's three other buffers are free by now
+        int32_t *const free0 = tval2, *const free1 = reinterpret_cast<int32_t *>(tkey),
+                *const free2 = reinterpret_cast<int32_t *>(tkey2);
+        int64_t *buf = nullptr;  // the rest in one allocation: 64-bit arrays first
+        if (tiled) {
+            const int64_t chunks = ((int64_t)n + kDadmChunk - 1) / kDadmChunk;
             ac.tile = (int32_t)((chunks + kDadmMaxTiles - 1) / kDadmMaxTiles) * kDadmChunk;
             ac.ntiles = (int32_t)(((int64_t)n + ac.tile - 1) / ac.tile);
             ac.ncol = nlabels + ac.ntiles;
+            const size_t np = (size_t)nlabels * ac.ntiles;
+            GP_TRY(sc.alloc(&buf, np + nlabels + ((size_t)nlabels + ac.ntiles + ac.ncol + 1) / 2));
+            ac.mv = free0;
+            ac.old = free1;
+            ac.part = buf;
+            ac.cutroom = ac.part + np;
+            ac.cut = reinterpret_cast<int32_t *>(ac.cutroom + nlabels);
+            ac.tcnt = ac.cut + nlabels;
+            ac.tmoves = ac.tcnt + ac.ntiles;
         } else {
             ac.tile = kSadmTile;
             ac.ntiles = (int32_t)(((int64_t)n + kSadmTile - 1) / kSadmTile);
             ac.ncol = ac.ntiles;
-        }
-        GP_TRY(sc.alloc(&ac.mv, n));
-        GP_TRY(sc.alloc(&ac.old, n));
-        GP_TRY(sc.alloc(&ac.tcnt, ac.ntiles));
-        GP_TRY(sc.alloc(&ac.tmoves, ac.ncol));
-        if (dense) {
-            GP_TRY(sc.alloc(&ac.part, (size_t)nlabels * ac.ntiles));
-            GP_TRY(sc.alloc(&ac.cut, nlabels));
-            GP_TRY(sc.alloc(&ac.cutroom, nlabels));
-        } else {
-            // the tier sort's three other buffers are free by now
-            ac.cpos = tval2;
-            ac.segv = reinterpret_cast<int32_t *>(tkey);
-            ac.segp = reinterpret_cast<int32_t *>(tkey2);
-            GP_TRY(sc.alloc(&ac.ccnt, nlabels));
             // a contested target has at least two proposers (each alone fits)
-            GP_TRY(sc.alloc(&ac.ct, n / 2));
-            GP_TRY(sc.alloc(&ac.ctW, n / 2));
-            GP_TRY(sc.alloc(&ac.ctS, n / 2));
-            GP_TRY(sc.alloc(&ac.nct, 2));
-            GP_HIP(hipMemsetAsync(ac.ccnt, 0, sizeof(int32_t) * (size_t)nlabels, s));
-            GP_HIP(hipMemsetAsync(ac.nct, 0, sizeof(int32_t) * 2, s));
+            const size_t nc = (size_t)n / 2;
+            GP_TRY(sc.alloc(&ac.mv, n));
+            GP_TRY(sc.alloc(&ac.old, n));
+            GP_TRY(sc.alloc(&buf, nc + (2 * nc + 2 * (size_t)ac.ntiles + 2 + nlabels + 1) / 2));
+            ac.cpos = free0;
+            ac.segv = free1;
+            ac.segp = free2;
+            ac.ctW = buf;
+            ac.ct = reinterpret_cast<int32_t *>(ac.ctW + nc);
+            ac.ctS = ac.ct + nc;
+            ac.tcnt = ac.ctS + nc;
+            ac.tmoves = ac.tcnt + ac.ntiles;
+            ac.nct = ac.tmoves + ac.ntiles;
+            ac.ccnt = ac.nct + 2;
+            GP_HIP(hipMemsetAsync(ac.nct, 0, sizeof(int32_t) * (2 + (size_t)nlabels), s));
         }
     }
     // active-set rounds: every vertex starts owing one evaluation per direction
@@ -3526,7 +3535,7 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
             GP_LAUNCH_CHECK();
             return GP_OK;
         }
-        if (dense) {
+        if (tiled) {
             hipLaunchKernelGGL(k_dadm_tally, dim3(ac.ntiles), dim3(kDadmBlock), 0, s, ac);
             hipLaunchKernelGGL(k_dadm_cut, dim3(nlabels), dim3(256), 0, s, ac);
             hipLaunchKernelGGL(k_dadm_apply, dim3(ac.ncol), dim3(kDadmBlock), 0, s, ac);
@@ -3559,7 +3568,7 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
                                    : rows_update<256, int32_t>(rt, ac, g.xadj, g.adjncy, g.adjwgt, g.nnz, s)));
         }
         if (group) hipLaunchKernelGGL(k_round_end_groups, dim3(grid_for(ngroups, 256, 1024)), dim3(256), 0, s, gstate, ngroups);
-        if (dense) hipLaunchKernelGGL(k_dadm_end, dim3(nlabels), dim3(256), 0, s, ac);
+        if (tiled) hipLaunchKernelGGL(k_dadm_end, dim3(nlabels), dim3(256), 0, s, ac);
         else hipLaunchKernelGGL(k_sadm_end, dim3(1), dim3(256), 0, s, ac);
         GP_LAUNCH_CHECK();
     #undef RT_TRY
