@@ -586,19 +586,26 @@ __global__ __launch_bounds__(kMB) void k_edge_loss(int32_t n, int32_t k, int32_t
     if (threadIdx.x == 0 && lsum != 0.0) atomicAdd(loss, lsum);
 }
 
-// Q[c] = sum_v c(v) S[v][c] (binary64 accumulation)
-__global__ __launch_bounds__(kMB) void k_colsum(int32_t n, int32_t k, const float *__restrict__ S,
+// Q[c] = sum_v c(v) S[v][c], products and sums in binary64: the balance term is
+// the difference of Q / C and 1 / k, so what is lost here grows by the ratio of
+// the two (binary32 sums per workgroup, added up in the order in which lanes came,
+// moved the balance loss by up to 2e-5 from call to call at k = 2). `kp` lanes (a
+// power of two >= k) per vertex.
+__global__ __launch_bounds__(kMB) void k_colsum(int32_t n, int32_t k, int32_t kp, const float *__restrict__ S,
                                                 const int32_t *__restrict__ vwgt, double *__restrict__ Q) {
-    __shared__ float part[kMpMaxK];
-    for (int32_t t = threadIdx.x; t < k; t += kMB) part[t] = 0.0f;
+    __shared__ double part[kMB];
+    const int32_t c = threadIdx.x % kp, grp = threadIdx.x / kp, vpb = kMB / kp;
+    double s = 0.0;
+    if (c < k)
+        for (int64_t v = (int64_t)blockIdx.x * vpb + grp; v < n; v += (int64_t)gridDim.x * vpb)
+            s += (double)S[v * k + c] * (vwgt ? (double)vwgt[v] : 1.0);
+    part[threadIdx.x] = s;
     __syncthreads();
-    const int64_t N = (int64_t)n * k;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t v = (int32_t)(i / k);
-        atomicAdd(&part[i % k], S[i] * (vwgt ? (float)vwgt[v] : 1.0f));
+    for (int32_t h = vpb / 2; h > 0; h >>= 1) {  // vpb is a power of two
+        if (grp < h) part[threadIdx.x] += part[threadIdx.x + h * kp];
+        __syncthreads();
     }
-    __syncthreads();
-    for (int32_t t = threadIdx.x; t < k; t += kMB) atomicAdd(&Q[t], (double)part[t]);
+    if ((int32_t)threadIdx.x < k) atomicAdd(&Q[threadIdx.x], part[threadIdx.x]);
 }
 
 // dZ = S * (g - <S, g>) with g = gS + balance term 2 lam k (Q_c/C - 1/k) c(v)/C;
@@ -972,7 +979,7 @@ int mpnn_backward(const DevGraph &g, int32_t k, const float *params, uint64_t se
     hipLaunchKernelGGL(k_edge_loss, dim3(grid_for(n, 1, 1024)), dim3(kMB), 0, s, n, k, kp, g.xadj, g.adjncy,
                        g.adjwgt, target, S, tot, gS, acc);
     GP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_colsum, dim3(grid_for((int64_t)n * k, 256, 1024)), dim3(kMB), 0, s, n, k, S, g.vwgt,
+    hipLaunchKernelGGL(k_colsum, dim3(grid_for(n, (kMB / kp) * 8, 256)), dim3(kMB), 0, s, n, k, kp, S, g.vwgt,
                        acc + 1);
     GP_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_softmax_back, dim3(gk), dim3(kMB), 0, s, n, k, kp, S, gS, acc + 1, tot + 1, lam, g.vwgt, dZ);
