@@ -1925,7 +1925,7 @@ struct RowTables {
     int32_t nt = 0;
     int32_t nsmall = 0;  // rows filled per vertex; the rest (chunked big vertices) by chunks
     int64_t entries = 0;  // edges of the table vertices
-    int32_t parts = 8;          // workgroups of the update per tile of movers
+    int32_t parts = 0;          // workgroups of the update per tile of movers
     int64_t *pushed = nullptr;  // [tiles * parts] edges of the admitted movers pushed into rows
     double sel_bytes = 0;
 };
@@ -2641,19 +2641,22 @@ __global__ __launch_bounds__(256) void k_act_step(const int32_t *xadj, int32_t n
 }
 
 // After the admission: every neighbour of an admitted mover owes `renew`
-// evaluations. One workgroup per tile of the movers, 16 lanes per mover; a mover above kMarkSplit neighbours is
-// queued instead as chunks of kMarkChunk entries (list `big`, count `nbig`),
-// which k_act_mark_big spreads over whole workgroups.
+// evaluations. `parts` workgroups per tile of the movers, 16 lanes per mover; a
+// mover above kMarkSplit neighbours is queued instead as chunks of kMarkChunk
+// entries (list `big`, count `nbig`), which k_act_mark_big spreads over whole
+// workgroups. With one workgroup per tile the waves in flight were too few: rgg of
+// 300,000 vertices, 257 blocks, 41 us a round, 11 so (sorted movers: 6).
 constexpr int kMarkSplit = 256;
 constexpr int kMarkChunk = 4096;
 __global__ __launch_bounds__(256) void k_act_mark(AdmitCtx c, const int32_t *xadj, const int32_t *adjncy,
-                                                  uint8_t renew, int2 *big, int32_t *nbig) {
-    constexpr int GL = 16;
+                                                  uint8_t renew, int2 *big, int32_t *nbig, int32_t parts) {
+    constexpr int GL = 16, NG = 256 / GL;
     if (c.dev->done) return;
-    const int32_t n = c.tcnt[blockIdx.x];
-    const int32_t *mv = c.mv + (int64_t)blockIdx.x * c.tile, *old = c.old + (int64_t)blockIdx.x * c.tile;
+    const int32_t tile = blockIdx.x / parts, part = blockIdx.x % parts;
+    const int32_t n = c.tcnt[tile];
+    const int32_t *mv = c.mv + (int64_t)tile * c.tile, *old = c.old + (int64_t)tile * c.tile;
     const int gl = threadIdx.x % GL;
-    for (int32_t p = threadIdx.x / GL; p < n; p += 256 / GL) {
+    for (int32_t p = part * NG + threadIdx.x / GL; p < n; p += parts * NG) {
         if (old[p] < 0) continue;
         const int32_t v = mv[p];
         const int32_t e0 = xadj[v], e1 = xadj[v + 1];
@@ -2670,15 +2673,17 @@ __global__ __launch_bounds__(256) void k_act_mark(AdmitCtx c, const int32_t *xad
 }
 
 // The neighbours of an admitted mover, and the mover, are not settled any
-// more. kMarkParts workgroups share a tile's movers: each takes every
-// kMarkParts-th one, 16 lanes per mover, and its share of the entries of the
-// movers above kMarkSplit neighbours.
-constexpr int kMarkParts = 4;
-__global__ __launch_bounds__(256) void k_todo_mark(AdmitCtx c, const int32_t *xadj, const int32_t *adjncy) {
+// more. `parts` workgroups share a tile's movers: each takes every parts-th one,
+// 16 lanes per mover, and its share of the entries of the movers above kMarkSplit
+// neighbours, which it finds by their lanes' bits (R-MAT-18, 257 blocks: 39 us a
+// round with four parts and a walk over all 256 movers at hand, 14 so).
+__global__ __launch_bounds__(256) void k_todo_mark(AdmitCtx c, const int32_t *xadj, const int32_t *adjncy,
+                                                   int32_t parts) {
     constexpr int GL = 16, NG = 256 / GL;
     __shared__ int32_t beg[256], end[256];
+    __shared__ uint64_t big[256 / kWave];  // the movers above kMarkSplit neighbours
     if (c.dev->done) return;
-    const int32_t tile = blockIdx.x / kMarkParts, part = blockIdx.x % kMarkParts;
+    const int32_t tile = blockIdx.x / parts, part = blockIdx.x % parts;
     const int32_t n = c.tcnt[tile];
     const int32_t *mv = c.mv + (int64_t)tile * c.tile, *old = c.old + (int64_t)tile * c.tile;
     const int gl = threadIdx.x % GL, grp = threadIdx.x / GL;
@@ -2689,15 +2694,18 @@ __global__ __launch_bounds__(256) void k_todo_mark(AdmitCtx c, const int32_t *xa
         beg[threadIdx.x] = b;
         end[threadIdx.x] = e;
         if (v >= 0 && part == 0) c.todo[v] = kTodoBoth;
-        const bool anybig = __syncthreads_or(e - b > kMarkSplit);
-        for (int32_t i = part + kMarkParts * grp; i < 256; i += kMarkParts * NG)
+        const uint64_t bm = __ballot(e - b > kMarkSplit);
+        if (lane_id() == 0) big[threadIdx.x / kWave] = bm;
+        __syncthreads();
+        for (int32_t i = part + parts * grp; i < 256; i += parts * NG)
             if (end[i] - beg[i] <= kMarkSplit)
                 for (int32_t x = beg[i] + gl; x < end[i]; x += GL) c.todo[adjncy[x]] = kTodoBoth;
-        if (anybig)
-            for (int32_t i = 0; i < 256; i++)
-                if (end[i] - beg[i] > kMarkSplit)
-                    for (int32_t x = beg[i] + part * 256 + threadIdx.x; x < end[i]; x += kMarkParts * 256)
-                        c.todo[adjncy[x]] = kTodoBoth;
+        for (int w = 0; w < 256 / kWave; w++)
+            for (uint64_t m = big[w]; m; m &= m - 1) {
+                const int32_t i = w * kWave + __ffsll((unsigned long long)m) - 1;
+                for (int32_t x = beg[i] + part * 256 + threadIdx.x; x < end[i]; x += parts * 256)
+                    c.todo[adjncy[x]] = kTodoBoth;
+            }
         __syncthreads();
     }
 }
@@ -3355,6 +3363,11 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
             GP_HIP(hipMemsetAsync(ac.nct, 0, sizeof(int32_t) * (2 + (size_t)nlabels), s));
         }
     }
+    // workgroups per tile of the kernels that walk the movers' rows: one per 256
+    // vertices (32 per tile where they share the wide rows), fewer on large graphs,
+    // whose tiles are enough and mostly hold few movers
+    const int32_t mark_parts = std::clamp(8192 / std::max(ac.ntiles, 1), 4, std::max(ac.tile / 256, 4));
+    const int32_t todo_parts = std::clamp(4096 / std::max(ac.ntiles, 1), 4, 32);
     // active-set rounds: every vertex starts owing one evaluation per direction
     const uint8_t renew = dir_alternate ? 2 : 1;
     uint8_t *act = nullptr;
@@ -3421,6 +3434,7 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         const double rb = (double)nt * KTd * (wide ? 8.0 : 4.0);
         if (nt > 0 && rb <= kRowsMaxBytes) {
             rt.tfirst = tT;
+            rt.parts = std::max(mark_parts, 8);
             rt.nt = (int32_t)nt;
             rt.nsmall = (int32_t)(tstart[6] - tstart[tT]);
             for (int t = tT; t < kTiers; t++) rt.entries += (int64_t)hedge[t];
@@ -3548,13 +3562,15 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         }
         GP_LAUNCH_CHECK();
         if (act) {
-            hipLaunchKernelGGL(k_act_mark, dim3(ac.ntiles), dim3(256), 0, s, ac, g.xadj, g.adjncy, renew, mbig, nmbig);
+            hipLaunchKernelGGL(k_act_mark, dim3(ac.ntiles * mark_parts), dim3(256), 0, s, ac, g.xadj, g.adjncy, renew, mbig,
+                               nmbig, mark_parts);
             hipLaunchKernelGGL(k_act_mark_big, dim3(grid_for(g.nnz / kMarkChunk + 1, 1, 4096)), dim3(256), 0, s, mbig,
                                nmbig, g.xadj, g.adjncy, act, renew);
             GP_LAUNCH_CHECK();
         }
         if (ac.todo && !rt.rows) {  // (the rows' update marks what it visits)
-            hipLaunchKernelGGL(k_todo_mark, dim3(ac.ntiles * kMarkParts), dim3(256), 0, s, ac, g.xadj, g.adjncy);
+            hipLaunchKernelGGL(k_todo_mark, dim3(ac.ntiles * todo_parts), dim3(256), 0, s, ac, g.xadj, g.adjncy,
+                               todo_parts);
             GP_LAUNCH_CHECK();
         }
         if (rt.rows) {
