@@ -6,14 +6,15 @@
 // round start. Weights are >= 1, so the admitted proposers of a target are
 // exactly those below one vertex id; nothing has to be sorted to find it.
 //
-// Up to 256 labels (k_dadm_*): per tile of consecutive vertices the proposed
-// weight per target, a prefix over the tiles per target, and with it the one
-// tile in which the target's room ends. Every tile before that admits, every
-// tile after it refuses, and one workgroup per target takes that tile in order.
+// Few labels against the vertices (k_dadm_*, up to 16,384 labels): per tile of
+// consecutive vertices the proposed weight per target, a prefix over the tiles per
+// target, and with it the one tile in which the target's room ends. Every tile
+// before that admits, every tile after it refuses, and one workgroup per target
+// takes that tile in order.
 //
-// More labels (k_sadm_*): the proposed weights are added to W at once. A
-// target still within its bound admits everything. The proposers of the others
-// (contested targets, usually few) are gathered per target, and one wave or
+// More labels (k_sadm_*), as in clustering: the proposed weights are added to W at
+// once. A target still within its bound admits everything. The proposers of the
+// others (contested targets, usually few) are gathered per target, and one wave or
 // workgroup per contested target finds the id where its room ends: by counting
 // smaller ids for up to 64 proposers, else by a radix selection over the ids
 // with weight histograms.
@@ -25,7 +26,10 @@
 //
 // Atomics on one cache line from many workgroups take about 11 ns each here
 // (they cross the XCDs), so counts and weight changes go through one store per
-// workgroup and a sum in the last kernel, or through an LDS hash first.
+// workgroup and a sum in the last kernel, or through an LDS hash first. (By
+// targets that is what a few hundred or thousand labels cost: nearly every
+// proposer adds to a target that all tiles propose to. R-MAT-20, 3000 blocks: 226 us
+// a round in its tally, apply and select.)
 #pragma once
 #include "lp.hpp"
 
@@ -45,6 +49,7 @@ __device__ __forceinline__ int64_t vweight(const int32_t *vwgt, int32_t v) {
 
 constexpr int kDadmBlock = 256;
 constexpr int kDadmChunk = 4096;     // vertices a workgroup takes at a time: 16 consecutive ones per thread
+constexpr int kDenseAdm = 256, kDadmSome = 2048, kDadmLabels = 16384;  // labels of the tiled form's variants
 constexpr int kDadmMaxTiles = 2048;  // tiles of a round (larger graphs take more chunks per tile)
 constexpr int kSadmBlock = 512;
 constexpr int kSadmPer = 4;
@@ -76,12 +81,12 @@ struct AdmitCtx {
     int32_t *old;     // its label before the move, -1: refused
     int32_t *tcnt;    // [ntiles]
     int32_t *tmoves;  // [ncol] admitted movers per workgroup
-    // up to 256 labels
+    // few labels: by tiles
     int32_t ncol;        // workgroups of the apply kernel: one per label, then one per tile
     int64_t *part;       // [nlabels * ntiles] proposed weight of a tile, then the tile's weight change
     int32_t *cut;        // [nlabels] tile in which the label's room ends (ntiles: none)
     int64_t *cutroom;    // [nlabels] room left before that tile
-    // more labels
+    // more labels: by targets
     int32_t *cpos, *segv, *segp;  // [n] position among the target's proposers; their vertices and list entries
     int32_t *ccnt;                // [nlabels] proposers of a contested target, then their first slot; 0 between rounds
     int32_t *ct, *ctS;            // contested targets, their proposers
@@ -109,7 +114,7 @@ __device__ __forceinline__ void refuse(const AdmitCtx &c, int32_t v) {
     if (c.act && c.act[v] == 0) c.act[v] = 1;  // refused by capacity: evaluated again
 }
 
-// ---------------------------------------------------------------- up to 256 labels
+// ---------------------------------------------------------------- few labels: by tiles
 
 // The proposals of vertices v0 .. v0 + 15, -1 past the last vertex.
 __device__ __forceinline__ void load16(const AdmitCtx &c, int64_t v0, int32_t (&t)[16]) {
@@ -130,10 +135,11 @@ __device__ __forceinline__ void load16(const AdmitCtx &c, int64_t v0, int32_t (&
     }
 }
 
+template <int LMAX>
 __global__ __launch_bounds__(kDadmBlock) void k_dadm_tally(AdmitCtx c) {
     if (c.dev->done) return;
-    __shared__ unsigned long long h[256];
-    h[threadIdx.x] = 0;
+    __shared__ unsigned long long h[LMAX];
+    for (int32_t i = threadIdx.x; i < c.nlabels; i += kDadmBlock) h[i] = 0;
     __syncthreads();
     const int32_t tile = blockIdx.x;
     for (int32_t o = 0; o < c.tile; o += kDadmChunk) {
@@ -146,7 +152,7 @@ __global__ __launch_bounds__(kDadmBlock) void k_dadm_tally(AdmitCtx c) {
             if (t[i] >= 0) atomicAdd(&h[t[i]], (unsigned long long)vweight(c.vwgt, (int32_t)v0 + i));
     }
     __syncthreads();
-    if ((int)threadIdx.x < c.nlabels) c.part[(int64_t)threadIdx.x * c.ntiles + tile] = (int64_t)h[threadIdx.x];
+    for (int32_t i = threadIdx.x; i < c.nlabels; i += kDadmBlock) c.part[(int64_t)i * c.ntiles + tile] = (int64_t)h[i];
     if (threadIdx.x == 0) c.tcnt[tile] = 0;
 }
 
@@ -179,19 +185,32 @@ __global__ __launch_bounds__(256) void k_dadm_cut(AdmitCtx c) {
     if (threadIdx.x == 0 && first == INT_MAX) c.cut[t] = c.ntiles;
 }
 
+// The tiles' workgroups (one per tile) and the labels' (one per label, for the
+// tile in which its room ends). Up to kDadmSome labels in one launch, with the
+// weight changes of both in LDS. With more labels in a launch each: a label's
+// workgroup has few movers then and adds their weights to W itself, without the
+// LDS, whose clearing alone would be most of the launch (rgg of 16,385 vertices,
+// 5000 blocks, 25 rounds: 2811 us with it, 1444 by targets).
+template <int LMAX, bool TILES, bool LABELS>
 __global__ __launch_bounds__(kDadmBlock) void k_dadm_apply(AdmitCtx c) {
     if (c.dev->done) return;
-    __shared__ unsigned long long dw[256];
-    __shared__ int32_t scut[256];
+    constexpr bool LDS = TILES, CUTS = LDS && LMAX <= kDadmSome;
+    __shared__ unsigned long long dw[LDS ? LMAX : 1];
+    __shared__ int32_t scut[CUTS ? LMAX : 1];
     __shared__ int64_t t64[kDadmBlock / kWave + 1];
     __shared__ int32_t t32[kDadmBlock / kWave + 1];
     __shared__ int32_t sbase;
-    const int32_t col = blockIdx.x;
-    const bool ordered = col < c.nlabels;  // the workgroup of label `col` takes the label's last tile in order
+    const int32_t col = blockIdx.x + (LABELS ? 0 : c.nlabels);
+    const bool ordered = LABELS && (!TILES || col < c.nlabels);  // takes the label's last tile in order
     const int32_t tile = ordered ? c.cut[col] : col - c.nlabels;
-    dw[threadIdx.x] = 0;
-    if (!ordered && (int)threadIdx.x < c.nlabels) scut[threadIdx.x] = c.cut[threadIdx.x];
-    __syncthreads();
+    if constexpr (LDS) {
+        for (int32_t i = threadIdx.x; i < c.nlabels; i += kDadmBlock) {
+            dw[i] = 0;
+            if (CUTS && !ordered) scut[i] = c.cut[i];
+        }
+        __syncthreads();
+    }
+    int64_t gain = 0;  // without LDS: the weight this thread's movers bring to the label
     int32_t moves = 0;
     if (tile < c.ntiles) {
         const int64_t room = ordered ? c.cutroom[col] : 0;
@@ -219,11 +238,13 @@ __global__ __launch_bounds__(kDadmBlock) void k_dadm_apply(AdmitCtx c) {
                     }
             } else {
 #pragma unroll
-                for (int i = 0; i < 16; i++)
-                    if (t[i] >= 0 && tile != scut[t[i]]) {
+                for (int i = 0; i < 16; i++) {
+                    const int32_t cut = t[i] < 0 ? tile : CUTS ? scut[t[i]] : c.cut[t[i]];
+                    if (tile != cut) {
                         mine |= 1u << i;
-                        if (tile < scut[t[i]]) adm |= 1u << i;
+                        if (tile < cut) adm |= 1u << i;
                     }
+                }
             }
             const int32_t cnt = __popc(adm);
             int32_t tot;
@@ -247,12 +268,17 @@ __global__ __launch_bounds__(kDadmBlock) void k_dadm_apply(AdmitCtx c) {
                 const int32_t from = c.labels[v];
                 const unsigned long long w = (unsigned long long)vweight(c.vwgt, v);
                 c.labels[v] = t[i];
-                c.lab8[v] = (uint8_t)t[i];
+                if (c.lab8) c.lab8[v] = (uint8_t)t[i];
                 c.mv[at] = v;
                 c.old[at] = from;
                 at++;
-                atomicAdd(&dw[t[i]], w);
-                atomicAdd(&dw[from], (unsigned long long)(-(long long)w));
+                if constexpr (LDS) {
+                    atomicAdd(&dw[t[i]], w);
+                    atomicAdd(&dw[from], (unsigned long long)(-(long long)w));
+                } else {
+                    gain += (int64_t)w;
+                    atomicAdd((unsigned long long *)&c.W[from], (unsigned long long)(-(long long)w));
+                }
             }
             if (c.group)
                 for (int i = 0; i < 16; i++) count_group(c, (int32_t)v0 + i, (adm >> i) & 1);
@@ -260,11 +286,36 @@ __global__ __launch_bounds__(kDadmBlock) void k_dadm_apply(AdmitCtx c) {
     }
     moves = block_sum<kDadmBlock>(moves, t32);
     if (threadIdx.x == 0) c.tmoves[col] = moves;
-    __syncthreads();
-    if ((int)threadIdx.x >= c.nlabels) return;
-    const unsigned long long x = dw[threadIdx.x];
-    if (!ordered) c.part[(int64_t)threadIdx.x * c.ntiles + tile] = (int64_t)x;
-    else if (x) atomicAdd((unsigned long long *)&c.W[threadIdx.x], x);
+    if constexpr (LDS) {
+        __syncthreads();
+        for (int32_t i = threadIdx.x; i < c.nlabels; i += kDadmBlock) {
+            const unsigned long long x = dw[i];
+            if (!ordered) c.part[(int64_t)i * c.ntiles + tile] = (int64_t)x;
+            else if (x) atomicAdd((unsigned long long *)&c.W[i], x);
+        }
+    } else {
+        gain = block_sum<kDadmBlock>(gain, t64);
+        if (threadIdx.x == 0 && gain) atomicAdd((unsigned long long *)&c.W[col], (unsigned long long)gain);
+    }
+}
+
+template <int LMAX>
+inline void launch_tiled_as(const AdmitCtx &c, hipStream_t s) {
+    const dim3 tiles(c.ntiles), labels(c.nlabels), all(c.ncol), block(kDadmBlock);
+    hipLaunchKernelGGL(k_dadm_tally<LMAX>, tiles, block, 0, s, c);
+    hipLaunchKernelGGL(k_dadm_cut, labels, dim3(256), 0, s, c);
+    if constexpr (LMAX <= kDadmSome) {
+        hipLaunchKernelGGL((k_dadm_apply<LMAX, true, true>), all, block, 0, s, c);
+    } else {
+        hipLaunchKernelGGL((k_dadm_apply<LMAX, true, false>), tiles, block, 0, s, c);
+        hipLaunchKernelGGL((k_dadm_apply<1, false, true>), labels, block, 0, s, c);
+    }
+}
+inline void launch_tiled(const AdmitCtx &c, hipStream_t s) {
+    if (c.nlabels <= kDenseAdm) launch_tiled_as<kDenseAdm>(c, s);
+    else if (c.nlabels <= kDadmSome) launch_tiled_as<kDadmSome>(c, s);
+    else if (c.nlabels <= kDadmLabels / 2) launch_tiled_as<kDadmLabels / 2>(c, s);
+    else launch_tiled_as<kDadmLabels>(c, s);
 }
 
 // ---------------------------------------------------------------- round end
@@ -303,7 +354,7 @@ __global__ __launch_bounds__(256) void k_dadm_end(AdmitCtx c) {
     if (t == 0) round_end(c, 0, c.dev->done ? 0 : c.ncol, t32);
 }
 
-// ---------------------------------------------------------------- more than 256 labels
+// ---------------------------------------------------------------- more labels: by targets
 
 // Slot of label t in an LDS table of keys (-1: empty), inserting it.
 __device__ __forceinline__ uint32_t adm_slot(int32_t *key, int32_t t) {

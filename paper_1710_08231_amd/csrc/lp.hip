@@ -3305,9 +3305,14 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     const int key_bits = bits_for(nlabels > 0 ? nlabels - 1 : 0);
     const int vbits = bits_for(n > 0 ? n - 1 : 0);
     const bool fuse_rest = !group && !active && n <= kFuseMax && nlabels <= kFuseMax && vbits + key_bits <= 32;
-    // Admission by tiles up to 256 labels, unless there are more labels than vertices:
-    // its 24 bytes a label would then be more than all other buffers of the round.
-    const bool tiled = dense && nlabels <= n;
+    // Admission by tiles while its label sums (24 bytes a label and 8 a label and
+    // tile) are small against the graph; by targets otherwise. 25 rounds from a
+    // scattered partition, us, targets and tiles: R-MAT-18 with 257 blocks 6278 and
+    // 4035, with 2000 5972 (sorted movers) and 4619; R-MAT-20 with 3000 15130 and
+    // 10025, rgg of 60,000 with 3000 (20 vertices a block) 2294 and 2698.
+    const bool tiled = nlabels <= kDenseAdm ? nlabels <= n
+                       : nlabels <= kDadmSome ? nlabels <= n / 2
+                                              : nlabels <= kDadmLabels && nlabels <= n / 64;
     AdmitCtx ac{};
     if (!fuse_rest) {
         ac.n = n;
@@ -3550,9 +3555,7 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
             return GP_OK;
         }
         if (tiled) {
-            hipLaunchKernelGGL(k_dadm_tally, dim3(ac.ntiles), dim3(kDadmBlock), 0, s, ac);
-            hipLaunchKernelGGL(k_dadm_cut, dim3(nlabels), dim3(256), 0, s, ac);
-            hipLaunchKernelGGL(k_dadm_apply, dim3(ac.ncol), dim3(kDadmBlock), 0, s, ac);
+            launch_tiled(ac, s);
         } else {
             hipLaunchKernelGGL(k_sadm_tally, dim3(ac.ntiles), dim3(kSadmBlock), 0, s, ac);
             hipLaunchKernelGGL(k_sadm_apply, dim3(ac.ntiles), dim3(kSadmBlock), 0, s, ac);
