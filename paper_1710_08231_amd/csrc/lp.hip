@@ -3309,8 +3309,10 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     // tile) are small against the graph; by targets otherwise. 25 rounds from a
     // scattered partition, us, targets and tiles: R-MAT-18 with 257 blocks 6278 and
     // 4035, with 2000 5972 (sorted movers) and 4619; R-MAT-20 with 3000 15130 and
-    // 10025, rgg of 60,000 with 3000 (20 vertices a block) 2294 and 2698.
+    // 10025, rgg of 60,000 with 3000 (20 vertices a block) 2294 and 2698. A batch's
+    // tiles propose to their own graphs' blocks only: 512 graphs 198 and 204 ms.
     const bool tiled = nlabels <= kDenseAdm ? nlabels <= n
+                       : group              ? false
                        : nlabels <= kDadmSome ? nlabels <= n / 2
                                               : nlabels <= kDadmLabels && nlabels <= n / 64;
     AdmitCtx ac{};
@@ -3390,17 +3392,22 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         GP_LAUNCH_CHECK();
     }
 
-    // settled vertices are skipped in refinement (labels are blocks of at least
-    // four vertices on average) where the round tail leaves lists of the movers;
-    // in clustering most vertices neighbour a mover in every round
-    // (on small levels, where one launch can then run all later rounds)
+    // Settled vertices are skipped in refinement where the round tail leaves lists of
+    // the movers; in clustering most vertices neighbour a mover in every round. That is
+    // refinement up to 256 labels. With more, one graph's small blocks keep most vertices
+    // at a border, and marking costs more than it saves (R-MAT-18, 12,000 blocks, 25 rounds:
+    // 6017 us with it, 4733 without; partitions, R-MAT-20 into 1000 448.1 and 432.2 ms)
+    // unless the blocks are large; the graphs of a batch settle one after the other
+    // (512 graphs 198 ms with it, 207 without).
+    // On small levels one launch can then run all later rounds
     // (between 17 and 64 labels only up to 2048 vertices: above, more than settled_most
     // of them stay active and the try is lost, 50 us of about 900)
     // (a frozen vertex is only kept out of the lists: its neighbours' moves would mark it)
     const bool settled = fuse_rest && !frozen && dense && (nlabels <= 16 || (nlabels <= 64 && n <= 2048)) && !wide && nbig == 0 &&
                          g.nnz <= kSettledNnz && (int64_t)nlabels * 4 <= n &&
                          rounds > 2 && !use_round_graphs() && !prof_blocks_replay();
-    if (settled || (!fuse_rest && !act && (int64_t)nlabels * 4 <= n)) {
+    const int64_t per_label = dense || group ? 4 : 128;
+    if (settled || (!fuse_rest && !act && nlabels * per_label <= n)) {
         GP_TRY(sc.alloc(&ac.todo, n));
         if (settled) {
             hipLaunchKernelGGL(k_todo_fill, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, tk, n, ac.todo);
