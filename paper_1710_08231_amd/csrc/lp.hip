@@ -2408,9 +2408,9 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32
 // bits and block weights in LDS: it collects the vertices to evaluate in
 // ascending order, evaluates each with 16 lanes (a dense table of KT sums per
 // lane group, labels from LDS), admits the movers in order and marks their
-// neighbours. The host does not launch it for graphs of more than kSettledNnz
-// entries or with vertices above the 64-lane tier (a hub's row would keep 16
-// lanes busy for long: 1.4 ms a run on R-MAT's coarse levels), and it returns as
+// neighbours. The host does not launch it for graphs of more than kSettledDeg
+// entries a vertex or with vertices above the 64-lane tier (a hub's row would keep
+// 16 lanes busy for long: 1.4 ms a run on R-MAT's coarse levels), and it returns as
 // soon as more than settled_most vertices are to be evaluated at once (the rounds
 // go on with the launched kernels then).
 constexpr int kSettledGroups = kFuseBlock / 16;
@@ -2421,7 +2421,12 @@ constexpr int kSettledMost = 2048;
 // took 1.6 ms (1.2 with launches only, 0.87 with 512 and 0.92 with 1024); above 64
 // labels the launches won (12 x 14 x 11 grid, k = 256: 0.82 against 1.28 ms).
 constexpr int settled_most(int KT) { return KT == 16 ? kSettledMost : 1024; }
-constexpr int64_t kSettledNnz = 1 << 19;
+// A vertex's row takes 16 lanes, 16 entries a step, so rows have to be short (300
+// vertices with 180 neighbours each, k = 17: 1048 us a call with this form, 752 with
+// launches), and a try has to have rounds to save (three rounds of an rgg of 16,384
+// vertices, k = 16: 499 us with a try after the second, 438 without).
+constexpr int64_t kSettledDeg = 32;
+constexpr int kSettledRounds = 8;
 template <int KT>
 __global__ __launch_bounds__(kFuseBlock) void k_rounds_settled(LPArgs a, int32_t n, int32_t nlabels, int32_t rounds,
                                                                int32_t *labels, int64_t *Wg, uint8_t *lab8g,
@@ -2469,7 +2474,10 @@ __global__ __launch_bounds__(kFuseBlock) void k_rounds_settled(LPArgs a, int32_t
         }
         int32_t m = 0;
         int32_t at = fuse_excl_scan<int32_t>(__popc(live), tmpi, &m);
-        if (m > settled_most(KT)) break;  // uniform
+        if (m > settled_most(KT)) {  // uniform
+            if (threadIdx.x == 0) dev->live = m;
+            break;
+        }
         for (int i = 0; i < 16; i++)
             if ((live >> i) & 1) list[at++] = (uint16_t)(threadIdx.x * 16 + i);
         for (int32_t i = threadIdx.x; i < KT; i += kFuseBlock) {
@@ -3404,8 +3412,8 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     // of them stay active and the try is lost, 50 us of about 900)
     // (a frozen vertex is only kept out of the lists: its neighbours' moves would mark it)
     const bool settled = fuse_rest && !frozen && dense && (nlabels <= 16 || (nlabels <= 64 && n <= 2048)) && !wide && nbig == 0 &&
-                         g.nnz <= kSettledNnz && (int64_t)nlabels * 4 <= n &&
-                         rounds > 2 && !use_round_graphs() && !prof_blocks_replay();
+                         g.nnz <= kSettledDeg * (n - tstart[1]) && (int64_t)nlabels * 4 <= n &&
+                         rounds >= kSettledRounds && !use_round_graphs() && !prof_blocks_replay();
     const int64_t per_label = dense || group ? 4 : 128;
     if (settled || (!fuse_rest && !act && nlabels * per_label <= n)) {
         GP_TRY(sc.alloc(&ac.todo, n));
@@ -3618,7 +3626,9 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         // It stops before the end where too many vertices are to be evaluated:
         // then some launched rounds, another try, more of them, and the last one
         // (a try that stops at once costs 50 us: only with 16 labels, where most pay;
-        // 20 x 24 x 21 grid, k = 3: 663 -> 472 us).
+        // 20 x 24 x 21 grid, k = 3: 663 -> 472 us). With more than twice too many, no
+        // other try and no marks any more (rgg of 16,384, k = 16, a seventh of the
+        // vertices scattered: 1506 us with three tries, 1387 so, 1323 before there were any).
         const ProfSuspend quiet(prof_first_round_only());
         for (int32_t more = 2;; more *= 2) {
             if (KTd == 16)
@@ -3630,7 +3640,9 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
             GP_HIP(hipMemcpyAsync(&h, dev, sizeof(LPDev), hipMemcpyDeviceToHost, s));
             GP_HIP(hipStreamSynchronize(s));
             const int32_t left = h.done ? 0 : rounds - h.round;
-            const bool last = KTd != 16 || more > 4 || left <= more;
+            const bool far = h.live > 2 * settled_most(KTd);
+            const bool last = KTd != 16 || more > 4 || left <= more || far;
+            if (last) ac.todo = nullptr;  // evaluate all, mark nothing
             for (int32_t r = 0; r < (last ? left : more); r++) GP_TRY(emit_round(s));
             if (last) break;
         }
