@@ -2085,14 +2085,17 @@ __global__ void k_hub_caps(const int32_t *xadj, const int32_t *hubs, int32_t nh,
 // Everything of a round after the proposals, in one workgroup, for graphs of
 // at most kFuseMax vertices (single graphs without active sets): the weight
 // proposed to each target is summed in LDS, and the proposers of targets that
-// stay within their bound move. Only the proposers of the others go on:
+// stay within their bound move (not after a round that refused some: then all are
+// taken as contested). Only the proposers of the others go on:
 // compaction in ascending vertex order, the stable sort by target, the segmented
 // prefix of their weights per target and admission against the weights of the
 // round start; then the label and weight updates, the todo marks and the round
 // bookkeeping. A contested mover is packed as
-// (target << vbits) | vertex in LDS. Bound: one workgroup's latency
-// chain (loads, LDS sums, barriers); with all movers in the sort it took 10 to
-// 24 us a round.
+// (target << vbits) | vertex in LDS. ROWS: vertices per thread, so small graphs
+// keep few registers. Bound: one workgroup's latency chain (loads, LDS sums,
+// barriers). 300 dense vertices, k = 64: 12.4 us a round with all movers sorted,
+// 14.9 with sums first and 16 vertices a thread, 9.9 so; rgg of 16,384, k = 16,
+// scattered: 24.7, 34.5 and 23.4.
 constexpr int kFuseBlock = 1024;
 constexpr int kFuseWaves = kFuseBlock / kWave;
 constexpr int kFuseRows = 16;
@@ -2119,6 +2122,7 @@ __device__ __forceinline__ T fuse_excl_scan(T x, T *tmp, T *total) {
     return before + inc - x;
 }
 
+template <int ROWS>
 __global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32_t n, int vbits,
                                                             int key_bits, const int32_t *vwgt, int64_t *W,
                                                             int64_t U, const int64_t *capv, int32_t nlabels,
@@ -2126,9 +2130,10 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32
                                                             uint8_t *todo, const int32_t *xadj,
                                                             const int32_t *adjncy) {
     constexpr int NW = kFuseWaves;
-    __shared__ __align__(16) uint32_t buf[2 * kFuseMax];
-    uint32_t *const bufA = buf, *const bufB = buf + kFuseMax;
-    __shared__ uint32_t wc[NW * 256];  // per (wave, digit) counters, then placement offsets
+    constexpr int MAXV = ROWS * kFuseBlock;
+    __shared__ __align__(16) uint32_t buf[2 * MAXV];
+    uint32_t *const bufA = buf, *const bufB = buf + MAXV;
+    __shared__ __align__(16) uint32_t wc[NW * 256];  // per (wave, digit) counters, then placement offsets
     __shared__ long long Wl[kFuseLdsLabels];
     __shared__ int32_t tmpi[NW];
     __shared__ uint32_t tmpu[NW];
@@ -2140,6 +2145,7 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32
     const bool wlds = nlabels <= kFuseLdsLabels;
     // everything the round reads from its start state is requested at once
     const int32_t done = dev->done;
+    const bool presum = !dev->contest;  // the round before refused nobody
     int32_t round = 0, prev_moves = 0;
     if (threadIdx.x == 0) {
         round = dev->round;
@@ -2148,74 +2154,103 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32
     }
     // vertex r * kFuseBlock + thread: a small level occupies the first rows only
     const int vrows = (n + kFuseBlock - 1) / kFuseBlock;
-    int32_t t_of[kFuseRows];
-    bool mine = false;
+    int32_t t_of[ROWS];
+    uint32_t asked = 0;  // bit r: row r's vertex proposes
 #pragma unroll
-    for (int r = 0; r < kFuseRows; r++) {
+    for (int r = 0; r < ROWS; r++) {
         const int32_t v = r * kFuseBlock + (int32_t)threadIdx.x;
         t_of[r] = v < n && !done ? prop[v] : -1;
-        mine |= t_of[r] >= 0;
+        asked |= t_of[r] >= 0 ? 1u << r : 0u;
     }
     if (wlds)
         for (int i = threadIdx.x; i < nlabels; i += kFuseBlock) Wl[i] = W[i];
-    // ---- weight proposed to each target; nlabels <= kFuseMax 64-bit sums fill the two buffers
+    // ---- weight proposed to each target; nlabels <= MAXV 64-bit sums fill the two buffers
     unsigned long long *const inflow = reinterpret_cast<unsigned long long *>(buf);
-    for (int i = threadIdx.x; i < nlabels; i += kFuseBlock) inflow[i] = 0;
-    const bool any = __syncthreads_or(mine);
+    for (int i = threadIdx.x; presum && i < nlabels; i += kFuseBlock) inflow[i] = 0;
+    const bool any = __syncthreads_or(asked != 0);
     uint32_t go = 0;  // bit r: row r's vertex moves (its target stays within its bound)
     int32_t moves = 0;
     int32_t m = 0;  // contested movers
-    uint32_t item[kFuseRows];
-    int32_t rank[kFuseRows];
-    if (any) {
+    const auto weight = [&](int32_t t) { return (unsigned long long *)(wlds ? &Wl[t] : (long long *)&W[t]); };
+    // the proposers of targets that stay within their bound move
+    const auto move_all = [&](const int32_t (&to)[ROWS]) {
+        int32_t old[ROWS];
 #pragma unroll
-        for (int r = 0; r < kFuseRows; r++) {
-            if (r >= vrows) break;
+        for (int r = 0; r < ROWS; r++)
+            old[r] = (go >> r) & 1 ? labels[r * kFuseBlock + (int32_t)threadIdx.x] : 0;
+#pragma unroll
+        for (int r = 0; r < ROWS; r++) {
+            if (r >= vrows) continue;  // uniform
+            const bool x = (go >> r) & 1;
             const int32_t v = r * kFuseBlock + (int32_t)threadIdx.x;
-            if (t_of[r] < 0) continue;
-            prop[v] = -1;  // a settled vertex writes none next time
-            atomicAdd(&inflow[t_of[r]], (unsigned long long)vweight(vwgt, v));
+            const unsigned long long c = x ? (unsigned long long)vweight(vwgt, v) : 0ull;
+            if (x) {
+                labels[v] = to[r];
+                if (lab8) lab8[v] = (uint8_t)to[r];
+                atomicAdd(weight(old[r]), 0ull - c);
+                moves++;
+            }
+            wave_add_keyed(wlds ? reinterpret_cast<unsigned long long *>(Wl) : reinterpret_cast<unsigned long long *>(W),
+                           to[r], c, x);
+        }
+    };
+    uint32_t went = 0;  // bit r: the contested mover of row r is admitted
+    uint32_t item[ROWS];
+    int32_t rank[ROWS];
+    bool contested = false;
+    if (any && presum) {
+#pragma unroll
+        for (int r = 0; r < ROWS; r++) {
+            if (r >= vrows) continue;
+            const int32_t v = r * kFuseBlock + (int32_t)threadIdx.x;
+            const bool x = t_of[r] >= 0;
+            // (a hub's leaves all propose its block)
+            wave_add_keyed(inflow, t_of[r], x ? (unsigned long long)vweight(vwgt, v) : 0ull, x);
         }
         __syncthreads();
-        long long room[kFuseRows];
+        long long room[ROWS];
 #pragma unroll
-        for (int r = 0; r < kFuseRows; r++) {
+        for (int r = 0; r < ROWS; r++) {
             room[r] = 0;
-            if (r >= vrows) break;
+            if (r >= vrows) continue;
             const int32_t t = t_of[r];
             if (t >= 0) room[r] = (capv ? capv[t] : U) - (wlds ? Wl[t] : W[t]);
         }
         bool con = false;
 #pragma unroll
-        for (int r = 0; r < kFuseRows; r++) {
-            if (r >= vrows) break;
-            if (t_of[r] < 0) continue;
+        for (int r = 0; r < ROWS; r++) {
+            if (r >= vrows || t_of[r] < 0) continue;
             if ((long long)inflow[t_of[r]] <= room[r]) go |= 1u << r;
             else con = true;
         }
-        const bool contested = __syncthreads_or(con);
-        if (contested) {
-            // ---- compaction: contested movers in ascending vertex order, counts per (row, wave)
+        contested = __syncthreads_or(con);
+        if (!contested) move_all(t_of);
+    } else {
+        contested = any;
+    }
+    if (contested) {
+        // ---- compaction: contested movers in ascending vertex order, counts per (row, wave)
 #pragma unroll
-            for (int r = 0; r < kFuseRows; r++) {
-                const bool x = t_of[r] >= 0 && !((go >> r) & 1);
-                const uint64_t mb = __ballot(x);
-                item[r] = ((uint32_t)t_of[r] << vbits) | (uint32_t)(r * kFuseBlock + (int32_t)threadIdx.x);
-                rank[r] = x ? (int32_t)__popcll(mb & lt) : -1;
-                if (lane == 0) wc[r * NW + w] = (uint32_t)__popcll(mb);
-            }
-            __syncthreads();
-            uint32_t tot = 0;
-            const uint32_t c0 = threadIdx.x < kFuseRows * NW ? wc[threadIdx.x] : 0u;
-            const uint32_t ex = fuse_excl_scan<uint32_t>(c0, tmpu, &tot);
-            if (threadIdx.x < kFuseRows * NW) wc[threadIdx.x] = ex;
-            __syncthreads();
-            m = (int32_t)tot;
-#pragma unroll
-            for (int r = 0; r < kFuseRows; r++)
-                if (rank[r] >= 0) bufA[wc[r * NW + w] + (uint32_t)rank[r]] = item[r];
-            __syncthreads();
+        for (int r = 0; r < ROWS; r++) {
+            const bool x = t_of[r] >= 0 && !((go >> r) & 1);
+            const uint64_t mb = __ballot(x);
+            item[r] = ((uint32_t)t_of[r] << vbits) | (uint32_t)(r * kFuseBlock + (int32_t)threadIdx.x);
+            rank[r] = x ? (int32_t)__popcll(mb & lt) : -1;
+            if (lane == 0) wc[r * NW + w] = (uint32_t)__popcll(mb);
         }
+        __syncthreads();
+        // every wave scans the ROWS * NW counts itself, four to a lane
+        const uint4 c4 = lane < ROWS * NW / 4 ? reinterpret_cast<const uint4 *>(wc)[lane] : make_uint4(0, 0, 0, 0);
+        const uint32_t own = c4.x + c4.y + c4.z + c4.w, inc = wave_incl_scan(own);
+        const int k4 = w & 3;
+        const uint32_t at = inc - own + (k4 > 0 ? c4.x : 0u) + (k4 > 1 ? c4.y : 0u) + (k4 > 2 ? c4.z : 0u);
+        m = (int32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+#pragma unroll
+        for (int r = 0; r < ROWS; r++) {
+            const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)at, (r * NW + __builtin_amdgcn_readfirstlane(w)) >> 2);
+            if (rank[r] >= 0) bufA[base + (uint32_t)rank[r]] = item[r];
+        }
+        __syncthreads();
     }
     // position p of the contested movers belongs to wave p / (rows * kWave), row
     // (p / kWave) % rows, lane p % kWave: few movers take one row of many waves
@@ -2228,9 +2263,9 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32
         const uint32_t mask = (1u << nb) - 1u;
         for (int d = threadIdx.x; d < NW * 256; d += kFuseBlock) wc[d] = 0;
         __syncthreads();
-        uint32_t dg[kFuseRows];
+        uint32_t dg[ROWS];
 #pragma unroll
-        for (int r = 0; r < kFuseRows; r++) {
+        for (int r = 0; r < ROWS; r++) {
             const int32_t p = wbase + r * kWave + lane;
             rank[r] = -1;
             dg[r] = 0;
@@ -2271,7 +2306,7 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32
         }
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < kFuseRows; r++)
+        for (int r = 0; r < ROWS; r++)
             if (rank[r] >= 0) oth[wc[w * 256 + dg[r]] + (uint32_t)rank[r]] = item[r];
         __syncthreads();
         uint32_t *tq = cur;
@@ -2280,82 +2315,63 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32
     }
     // ---- segmented prefix of mover weights per target, in position order
     const uint32_t vmask = (1u << vbits) - 1u;
-    long long pre[kFuseRows];
-    bool seen[kFuseRows];
-    bool cf = false;  // a segment head at or before the row's end within this wave
-    long long cv = 0;
-#pragma unroll
-    for (int r = 0; r < kFuseRows; r++) {
-        const int32_t p = wbase + r * kWave + lane;
-        pre[r] = 0;
-        seen[r] = false;
-        if (r >= rows || wbase + r * kWave >= m) continue;  // wave-uniform
-        const bool valid = p < m;
-        const uint32_t it = valid ? cur[p] : 0u;
-        item[r] = it;
-        const long long c = valid ? (long long)vweight(vwgt, (int32_t)(it & vmask)) : 0;
-        const bool hd = valid && (p == 0 || (cur[p - 1] >> vbits) != (it >> vbits));
-        bool f = hd;
-        long long v = c;
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-            const int fo = __shfl_up((int)f, d, kWave);
-            const long long vo = __shfl_up(v, d, kWave);
-            if (lane >= d) {
-                v = f ? v : vo + v;
-                f = f || fo;
-            }
-        }
-        if (!f) v += cv;
-        f = f || cf;
-        pre[r] = v;
-        seen[r] = f;
-        cf = __shfl(f, kWave - 1, kWave);
-        cv = __shfl(v, kWave - 1, kWave);
-    }
-    if (lane == 0) {
-        wf[w] = cf;
-        wv[w] = cv;
-    }
-    __syncthreads();
-    long long carry = 0;  // the open segment's sum before this wave
-    for (int i = 0; i < w; i++) carry = wf[i] ? wv[i] : carry + wv[i];
-    // ---- admission against the weights of the round start
+    long long pre[ROWS];
+    bool seen[ROWS];
     uint8_t *adm = reinterpret_cast<uint8_t *>(oth);
+    if (m > 0) {  // uniform
+        bool cf = false;  // a segment head at or before the row's end within this wave
+        long long cv = 0;
 #pragma unroll
-    for (int r = 0; r < kFuseRows; r++) {
-        const int32_t p = wbase + r * kWave + lane;
-        if (r >= rows || p >= m) continue;
-        if (!seen[r]) pre[r] += carry;
-        const uint32_t t = item[r] >> vbits;
-        const long long wt = wlds ? Wl[t] : W[t];
-        adm[p] = (wt + pre[r] <= (capv ? capv[t] : U)) ? 1 : 0;
+        for (int r = 0; r < ROWS; r++) {
+            const int32_t p = wbase + r * kWave + lane;
+            pre[r] = 0;
+            seen[r] = false;
+            if (r >= rows || wbase + r * kWave >= m) continue;  // wave-uniform
+            const bool valid = p < m;
+            const uint32_t it = valid ? cur[p] : 0u;
+            item[r] = it;
+            const long long c = valid ? (long long)vweight(vwgt, (int32_t)(it & vmask)) : 0;
+            const bool hd = valid && (p == 0 || (cur[p - 1] >> vbits) != (it >> vbits));
+            bool f = hd;
+            long long v = c;
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) {
+                const int fo = __shfl_up((int)f, d, kWave);
+                const long long vo = __shfl_up(v, d, kWave);
+                if (lane >= d) {
+                    v = f ? v : vo + v;
+                    f = f || fo;
+                }
+            }
+            if (!f) v += cv;
+            f = f || cf;
+            pre[r] = v;
+            seen[r] = f;
+            cf = __shfl(f, kWave - 1, kWave);
+            cv = __shfl(v, kWave - 1, kWave);
+        }
+        if (lane == 0) {
+            wf[w] = cf;
+            wv[w] = cv;
+        }
+        __syncthreads();
+        long long carry = 0;  // the open segment's sum before this wave
+        for (int i = 0; i < w; i++) carry = wf[i] ? wv[i] : carry + wv[i];
+        // ---- admission against the weights of the round start
+#pragma unroll
+        for (int r = 0; r < ROWS; r++) {
+            const int32_t p = wbase + r * kWave + lane;
+            if (r >= rows || p >= m) continue;
+            if (!seen[r]) pre[r] += carry;
+            const uint32_t t = item[r] >> vbits;
+            const long long wt = wlds ? Wl[t] : W[t];
+            adm[p] = (wt + pre[r] <= (capv ? capv[t] : U)) ? 1 : 0;
+        }
+        __syncthreads();
     }
-    __syncthreads();
     // ---- labels and weights (every decision read the weights of the round start before the barrier)
-    const auto weight = [&](int32_t t) { return (unsigned long long *)(wlds ? &Wl[t] : (long long *)&W[t]); };
-    uint32_t went = 0;  // bit r: the contested mover of row r is admitted
-    int32_t old[kFuseRows];
 #pragma unroll
-    for (int r = 0; r < kFuseRows; r++) {
-        old[r] = 0;
-        if (r >= vrows) break;
-        if ((go >> r) & 1) old[r] = labels[r * kFuseBlock + (int32_t)threadIdx.x];
-    }
-#pragma unroll
-    for (int r = 0; r < kFuseRows; r++) {
-        if (r >= vrows) break;
-        if (!((go >> r) & 1)) continue;
-        const int32_t v = r * kFuseBlock + (int32_t)threadIdx.x, t = t_of[r];
-        const unsigned long long c = (unsigned long long)vweight(vwgt, v);
-        labels[v] = t;
-        if (lab8) lab8[v] = (uint8_t)t;
-        atomicAdd(weight(old[r]), 0ull - c);
-        atomicAdd(weight(t), c);
-        moves++;
-    }
-#pragma unroll
-    for (int r = 0; r < kFuseRows; r++) {
+    for (int r = 0; r < ROWS; r++) {
         const int32_t p = wbase + r * kWave + lane;
         if (r >= rows || p >= m || !adm[p]) continue;
         const uint32_t t = item[r] >> vbits;
@@ -2370,13 +2386,23 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32
         moves++;
         went |= 1u << r;
     }
+    if (contested && presum) {
+        // the others' targets are read again: kept through the sort they would not fit the registers
+        int32_t to[ROWS];
+#pragma unroll
+        for (int r = 0; r < ROWS; r++) to[r] = (go >> r) & 1 ? prop[r * kFuseBlock + (int32_t)threadIdx.x] : -1;
+        move_all(to);
+    }
+#pragma unroll
+    for (int r = 0; r < ROWS; r++)  // a settled vertex writes none next time
+        if ((asked >> r) & 1) prop[r * kFuseBlock + (int32_t)threadIdx.x] = -1;
     int32_t total = 0;
     (void)fuse_excl_scan<int32_t>(moves, tmpi, &total);  // ends with a barrier
     if (wlds)  // this workgroup is the only writer of W in this launch
         for (int i = threadIdx.x; i < nlabels; i += kFuseBlock) W[i] = Wl[i];
     if (todo && total) {  // uniform: the admitted movers, in any order, then 16 lanes each mark the neighbours
 #pragma unroll
-        for (int r = 0; r < kFuseRows; r++) {
+        for (int r = 0; r < ROWS; r++) {
             if ((go >> r) & 1) buf[atomicAdd(&nlist, 1)] = (uint32_t)(r * kFuseBlock + (int32_t)threadIdx.x);
             if ((went >> r) & 1) buf[atomicAdd(&nlist, 1)] = item[r] & vmask;
         }
@@ -2396,6 +2422,7 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32
             if (round >= 1 && total == 0 && prev_moves == 0) dev->done = 1;
             dev->prev_moves = total;
             dev->round_moves = 0;
+            dev->contest = presum ? contested : total < m;
         }
     }
 }
@@ -3564,8 +3591,9 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
             GP_LAUNCH_CHECK();
         }
         if (fuse_rest) {  // small level: the rest of the round in one launch
-            hipLaunchKernelGGL(k_round_small, dim3(1), dim3(kFuseBlock), 0, s, prop, (int32_t)n, vbits, key_bits,
-                               g.vwgt, W, U, capv, (int32_t)nlabels, labels, lab8, dev, ac.todo, g.xadj, g.adjncy);
+            const auto tail = n <= 4 * kFuseBlock && nlabels <= 4 * kFuseBlock ? k_round_small<4> : k_round_small<kFuseRows>;
+            hipLaunchKernelGGL(tail, dim3(1), dim3(kFuseBlock), 0, s, prop, (int32_t)n, vbits, key_bits, g.vwgt, W, U,
+                               capv, (int32_t)nlabels, labels, lab8, dev, ac.todo, g.xadj, g.adjncy);
             GP_LAUNCH_CHECK();
             return GP_OK;
         }
@@ -3628,7 +3656,7 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
         // (a try that stops at once costs 50 us: only with 16 labels, where most pay;
         // 20 x 24 x 21 grid, k = 3: 663 -> 472 us). With more than twice too many, no
         // other try and no marks any more (rgg of 16,384, k = 16, a seventh of the
-        // vertices scattered: 1506 us with three tries, 1387 so, 1323 before there were any).
+        // vertices scattered: 1506 us with three tries, 1387 with one).
         const ProfSuspend quiet(prof_first_round_only());
         for (int32_t more = 2;; more *= 2) {
             if (KTd == 16)

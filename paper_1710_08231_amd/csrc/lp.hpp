@@ -21,6 +21,7 @@ struct LPDev {
     int32_t round_moves;
     int64_t total_moves;
     int64_t visits;  // active-set rounds: edges of the evaluated vertices
+    int32_t contest;  // one-workgroup rounds: the last one refused a proposal (or had a target to sort for)
     int32_t live;    // settled rounds: vertices to evaluate where they gave up, else 0
 };
 
