@@ -147,6 +147,12 @@ constexpr int kRowClasses = 6;      // 16 lanes, 32 lanes, a wave, two workgroup
 constexpr int kRowWaveMax = 128;    // D_i <= 128: one wave per row
 constexpr int kRowSmallMax = 512;   // D_i <= 512: one small workgroup per row
 constexpr int kRowBlockMax = 2048;  // D_i <= 2048: one workgroup per row
+// Graphs of few entries use the wave, the large workgroup and the chunk class only
+// and a wave per row in the last copy: each of the other classes is a launch with
+// its own latency, which small graphs do not earn back (R-MAT-13, 204,000 entries,
+// pairs: 553 us with all classes, 503 so; R-MAT-14, 426,000: 627 and 544; rgg of
+// 60,000, 624,000: 362 and 343; from there on no difference).
+constexpr int32_t kFewEntries = 1 << 20;
 constexpr int kRowChunk = 2048;     // larger rows: flattened entries per aggregating workgroup
 static_assert(kRowWaveMax % kWave == 0, "wave rows: whole entries per lane");
 
@@ -674,8 +680,9 @@ __global__ void k_members(const int32_t *f2c, const int32_t *xadj, int32_t n, co
     }
 }
 
-__global__ void k_row_class(const int32_t *mstart, const int32_t *flat, int32_t nc, uint32_t *key, int32_t *val,
-                            int32_t *ccount) {
+// few: only the classes of a wave, of the large workgroup and of chunks
+__global__ void k_row_class(const int32_t *mstart, const int32_t *flat, int32_t nc, bool few, uint32_t *key,
+                            int32_t *val, int32_t *ccount) {
     __shared__ int32_t h[kRowClasses];
     if (threadIdx.x < kRowClasses) h[threadIdx.x] = 0;
     __syncthreads();
@@ -685,7 +692,8 @@ __global__ void k_row_class(const int32_t *mstart, const int32_t *flat, int32_t 
         const int32_t D = flat[mstart[i + 1]] - flat[mstart[i]];
         const int32_t M = mstart[i + 1] - mstart[i];
         const int32_t sz = D > M ? D : M;
-        const uint32_t k = sz <= 16 ? 0u : sz <= 32 ? 1u : sz <= kRowWaveMax ? 2u : sz <= kRowSmallMax ? 3u : sz <= kRowBlockMax ? 4u : 5u;
+        uint32_t k = sz <= 16 ? 0u : sz <= 32 ? 1u : sz <= kRowWaveMax ? 2u : sz <= kRowSmallMax ? 3u : sz <= kRowBlockMax ? 4u : 5u;
+        if (few) k = k <= 2u ? 2u : k == 3u ? 4u : k;
         key[i] = k;
         val[i] = (int32_t)i;
         atomicAdd(&h[k], 1);
@@ -882,8 +890,8 @@ int contract(const DevGraph &g, const int32_t *labels, bool skip_isolated, Coars
         GP_TRY(sc.alloc(&cv2, nc));
         GP_TRY(sc.alloc(&ccount, kRowClasses));
         GP_HIP(hipMemsetAsync(ccount, 0, sizeof(int32_t) * kRowClasses, s));
-        hipLaunchKernelGGL(k_row_class, dim3(grid_for(nc, 256, 4096)), dim3(256), 0, s, mstart, flat, nc, ck, cv,
-                           ccount);
+        hipLaunchKernelGGL(k_row_class, dim3(grid_for(nc, 256, 4096)), dim3(256), 0, s, mstart, flat, nc,
+                           g.nnz <= kFewEntries, ck, cv, ccount);
         GP_LAUNCH_CHECK();
         GP_TRY((radix_sort<uint32_t, int32_t>(&ck, &cv, &ck2, &cv2, nc, nullptr, 3, sc)));
         int32_t hc[kRowClasses];
@@ -994,7 +1002,7 @@ int contract(const DevGraph &g, const int32_t *labels, bool skip_isolated, Coars
         int32_t *const d_nnzc = flags + 1;
         GP_TRY((scan<int32_t>(CountIn{rcnt}, CountOut{out.xadj}, nc, nullptr, d_nnzc, sc)));
         GP_HIP(hipMemcpyAsync(out.xadj + nc, d_nnzc, sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-        if (g.nnz / nc >= 128)
+        if (g.nnz <= kFewEntries || g.nnz / nc >= 128)
             hipLaunchKernelGGL(k_copy_rows<64>, dim3(grid_for((int64_t)nc * 64, 256, 65536)), dim3(256), 0, s, c,
                                out.xadj, nc, out.adjncy, out.adjwgt, flags);
         else
