@@ -175,21 +175,25 @@ __global__ __launch_bounds__(kAB) void k_begin_local(Window wd, Ctl *c) {
 // all u is the first seed whose neighbourhood meets an earlier one's.
 // A seed at or behind a clash already found need not claim: it could only offer
 // indices behind it.
-__device__ __forceinline__ void claim(const MG &g, int32_t i, int32_t s, int32_t b, int32_t e, Ctl *c,
-                                      unsigned long long *first, int tid, int nt) {
+// Returns the smallest index that this lane has to offer (INT_MAX: none).
+__device__ __forceinline__ int32_t claim(const MG &g, int32_t i, int32_t s, int32_t b, int32_t e, const Ctl *c,
+                                         unsigned long long *first, int tid, int nt) {
     const uint32_t tag = ~c->epoch;
+    int32_t offer = INT_MAX;
     for (int32_t t = b - 1 + tid; t < e; t += nt) {
         const int32_t u = t < b ? s : g.adjncy[t];
         const unsigned long long old = atomicMin(&first[u], ((unsigned long long)tag << 32) | (uint32_t)i);
-        if ((uint32_t)(old >> 32) == tag) atomicMin(&c->clash, max((int32_t)(uint32_t)old, i));
+        if ((uint32_t)(old >> 32) == tag) offer = min(offer, max((int32_t)(uint32_t)old, i));
     }
+    return offer;
 }
 
 __global__ __launch_bounds__(256) void k_claim(MG g, const int32_t *sel, Ctl *c, unsigned long long *first) {
     const int32_t i = blockIdx.x;
     if (i >= c->nsel) return;
     const int32_t s = sel[i];
-    claim(g, i, s, g.xadj[s], g.xadj[s + 1], c, first, threadIdx.x, 256);
+    const int32_t offer = wave_min(claim(g, i, s, g.xadj[s], g.xadj[s + 1], c, first, threadIdx.x, 256));
+    if (lane_id() == 0 && offer != INT_MAX) atomicMin(&c->clash, offer);
 }
 
 struct SearchArgs {
@@ -592,12 +596,18 @@ __global__ __launch_bounds__(kWave) void k_search_rows(SearchArgs a) {
     __shared__ RowsLds<KT> L;
     const int lane = lane_id();
     const int32_t j = blockIdx.x;
-    if (j >= a.c->nsel || j >= clash_now(a)) return;
+    if (j >= a.c->nsel) return;
     const int32_t s = a.sel[j];
     const int32_t sb = a.g.xadj[s], se = a.g.xadj[s + 1];
-    claim(a.g, j, s, sb, se, a.c, a.first, lane, kWave);
-    // the clash only falls while the claims come in: a search behind it is not wanted
-    if (j >= clash_now(a)) return;
+    if (se - sb > kWave && j >= clash_now(a)) return;
+    const int32_t offer = wave_min(claim(a.g, j, s, sb, se, a.c, a.first, lane, kWave));
+    // The clash only falls while the claims come in: a search behind it is not wanted.
+    // All searches start at once and the clash is one word (11 ns an access), so it is
+    // touched once by each: by its offer, or by a look where it has none (a star of
+    // 5000, batches of 1024: 26 us a batch with a look before and after, 14 so).
+    int32_t now = 0;
+    if (lane == 0) now = offer != INT_MAX ? min(offer, atomicMin(&a.c->clash, offer)) : ld_l2(&a.c->clash);
+    if (j >= __builtin_amdgcn_readfirstlane(now)) return;
     for (int i = lane; i < kHT; i += kWave) L.h[i].x = -1;
     for (int b = 0; b < KT; b++) L.conn[b][lane] = 0;
     for (int b = lane; b < KT; b += kWave) L.room[b] = b < a.k ? a.lmax - a.B[b] : LLONG_MIN;
