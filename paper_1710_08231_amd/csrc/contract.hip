@@ -32,11 +32,6 @@ __global__ void k_row_marks(const int32_t *xadj, int32_t n, int32_t *mark) {
         if (xadj[v + 1] > xadj[v]) mark[xadj[v]] = (int32_t)v;
 }
 
-struct MaxScanIn {
-    const int32_t *mark;
-    __device__ int32_t operator()(int64_t i) const { return mark[i]; }
-};
-
 // inclusive max-scan is done with a dedicated tile kernel pair (max is not "+")
 constexpr int kMB = 256, kMI = 8, kMT = kMB * kMI;
 
@@ -369,8 +364,8 @@ __global__ __launch_bounds__(256) void k_crow_wave(RowCtx c, const int32_t *rows
 }
 
 // One workgroup of CB threads per row of at most MAXD entries. Two classes: up to
-// kRowSmallMax entries 128 threads with 13 KB of LDS (twelve workgroups per CU),
-// above that kCB threads with 80 KB (two per CU, so the workgroup is wide to
+// kRowSmallMax entries 128 threads with 15 KB of LDS (ten workgroups per CU),
+// above that kCB threads with 61 KB (two per CU, so the workgroup is wide to
 // keep enough waves in flight for the gathers). Bound: the latency of a row's
 // dependent gathers and its barriers, hence rows in flight: with one class the
 // rows of 129 to 512 entries left most of 512 threads idle (512 graphs: 14.0 ms
@@ -389,7 +384,7 @@ __global__ __launch_bounds__(CB) void k_crow_block(RowCtx c, const int32_t *rows
     // sF (member prefix) is only read while gathering and lj (the distinct
     // columns) only written after that, so they share one array; li holds
     // each column's table slot, whose weight is read at the output. This
-    // keeps the large class's workgroup under 80 KB: two per CU.
+    // keeps the large class's workgroup at 61 KB: two per CU.
     __shared__ __align__(16) int32_t sFlj[MAXD + 4];
     __shared__ uint16_t li[MAXD];
     __shared__ int32_t s_r;

@@ -11,8 +11,10 @@
 //   2. admit (admit.hpp): the proposers to a target in ascending vertex id
 //      while W[t] + (their weight so far) <= U; labels, W and the move count
 //      are updated and the device stop flag set.
-// No host synchronisation happens between rounds; after the stop flag is set
-// every later kernel of the call returns immediately.
+// Between launched rounds the host does not wait; after the stop flag is set every
+// later kernel of the call returns at once. Refinement of small levels reads the
+// bookkeeping back after each try to run all later rounds in one launch
+// (k_rounds_settled; one to three tries a call).
 #include <algorithm>
 #include <climits>
 #include <cstdlib>
@@ -1574,7 +1576,6 @@ __global__ __launch_bounds__(256) void k_dense_chunk(LPArgs a, DenseBig db) {
 template <int KT, typename AccT>
 __global__ __launch_bounds__(256) void k_dense_finish(LPArgs a, DenseBig db, int32_t nlabels) {
     if (*a.done) return;
-    const int32_t dmode = cur_dirmode(a);
     const int w = threadIdx.x / kWave, lane = lane_id();
     const int32_t b = blockIdx.x * (256 / kWave) + w;
     if (b >= db.nbig) return;
@@ -2102,26 +2103,6 @@ constexpr int kFuseRows = 16;
 constexpr int kFuseMax = kFuseBlock * kFuseRows;
 constexpr int kFuseLdsLabels = 1024;  // label weights held in LDS for the whole round
 
-// Exclusive prefix of x over the workgroup in thread order; *total gets the
-// sum. Every thread adds up the wave totals before its own wave.
-template <typename T>
-__device__ __forceinline__ T fuse_excl_scan(T x, T *tmp, T *total) {
-    const int lane = lane_id(), w = threadIdx.x / kWave;
-    const T inc = wave_incl_scan(x);
-    if (lane == kWave - 1) tmp[w] = inc;
-    __syncthreads();
-    T before = 0, all = 0;
-#pragma unroll
-    for (int i = 0; i < kFuseWaves; i++) {
-        const T t = tmp[i];
-        before += i < w ? t : T(0);
-        all += t;
-    }
-    *total = all;
-    __syncthreads();
-    return before + inc - x;
-}
-
 template <int ROWS>
 __global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32_t n, int vbits,
                                                             int key_bits, const int32_t *vwgt, int64_t *W,
@@ -2297,7 +2278,7 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32
                 sum += c[j];
             }
             uint32_t tot = 0;
-            uint32_t off = fuse_excl_scan<uint32_t>(sum, tmpu, &tot);
+            uint32_t off = block_excl_scan<kFuseBlock, uint32_t>(sum, tmpu, &tot);
 #pragma unroll
             for (int j = 0; j < 4; j++) {
                 wc[(q0 + j) * 256 + d] = off;
@@ -2397,7 +2378,7 @@ __global__ __launch_bounds__(kFuseBlock) void k_round_small(int32_t *prop, int32
     for (int r = 0; r < ROWS; r++)  // a settled vertex writes none next time
         if ((asked >> r) & 1) prop[r * kFuseBlock + (int32_t)threadIdx.x] = -1;
     int32_t total = 0;
-    (void)fuse_excl_scan<int32_t>(moves, tmpi, &total);  // ends with a barrier
+    (void)block_excl_scan<kFuseBlock, int32_t>(moves, tmpi, &total);  // ends with a barrier
     if (wlds)  // this workgroup is the only writer of W in this launch
         for (int i = threadIdx.x; i < nlabels; i += kFuseBlock) W[i] = Wl[i];
     if (todo && total) {  // uniform: the admitted movers, in any order, then 16 lanes each mark the neighbours
@@ -2457,7 +2438,7 @@ constexpr int kSettledRounds = 8;
 template <int KT>
 __global__ __launch_bounds__(kFuseBlock) void k_rounds_settled(LPArgs a, int32_t n, int32_t nlabels, int32_t rounds,
                                                                int32_t *labels, int64_t *Wg, uint8_t *lab8g,
-                                                               LPDev *dev, const uint8_t *todog) {
+                                                               LPDev *dev, uint8_t *todog) {
     __shared__ __align__(16) uint8_t lab[kFuseMax];
     __shared__ __align__(16) uint8_t todo[kFuseMax];
     __shared__ int32_t tab[kSettledGroups * (KT + 1)];
@@ -2500,7 +2481,7 @@ __global__ __launch_bounds__(kFuseBlock) void k_rounds_settled(LPArgs a, int32_t
             }
         }
         int32_t m = 0;
-        int32_t at = fuse_excl_scan<int32_t>(__popc(live), tmpi, &m);
+        int32_t at = block_excl_scan<kFuseBlock, int32_t>(__popc(live), tmpi, &m);
         if (m > settled_most(KT)) {  // uniform
             if (threadIdx.x == 0) dev->live = m;
             break;
@@ -2571,7 +2552,7 @@ __global__ __launch_bounds__(kFuseBlock) void k_rounds_settled(LPArgs a, int32_t
             const int32_t v = go ? list[i] : 0;
             const uint8_t t = go ? tgt[i] : 0;
             int32_t tot = 0;
-            const int32_t ex = fuse_excl_scan<int32_t>(go, tmpi, &tot);
+            const int32_t ex = block_excl_scan<kFuseBlock, int32_t>(go, tmpi, &tot);
             if (go) {
                 list[mm + ex] = (uint16_t)v;
                 tgt[mm + ex] = t;
@@ -2617,7 +2598,7 @@ __global__ __launch_bounds__(kFuseBlock) void k_rounds_settled(LPArgs a, int32_t
         }
         for (int32_t i = threadIdx.x; i < KT; i += kFuseBlock) W[i] += delta[i];
         int32_t total = 0;
-        (void)fuse_excl_scan<int32_t>(moves, tmpi, &total);  // ends with a barrier
+        (void)block_excl_scan<kFuseBlock, int32_t>(moves, tmpi, &total);  // ends with a barrier
         all_moves += total;
         done = round >= 1 && total == 0 && prev == 0;
         prev = total;
@@ -2627,7 +2608,7 @@ __global__ __launch_bounds__(kFuseBlock) void k_rounds_settled(LPArgs a, int32_t
     for (int32_t i = threadIdx.x; i < nlabels; i += kFuseBlock) Wg[i] = W[i];
     for (int32_t i = threadIdx.x; i < n; i += kFuseBlock) {
         lab8g[i] = lab[i];
-        const_cast<uint8_t *>(todog)[i] = todo[i];
+        todog[i] = todo[i];
     }
     if (threadIdx.x == 0) {
         dev->round = round;
