@@ -6,7 +6,7 @@
 // round start. Weights are >= 1, so the admitted proposers of a target are
 // exactly those below one vertex id; nothing has to be sorted to find it.
 //
-// Few labels against the vertices (k_dadm_*, up to 16,384 labels): per tile of
+// Few labels against the vertices (k_dadm_*, up to 12,288 labels): per tile of
 // consecutive vertices the proposed weight per target, a prefix over the tiles per
 // target, and with it the one tile in which the target's room ends. Every tile
 // before that admits, every tile after it refuses, and one workgroup per target
@@ -49,7 +49,9 @@ __device__ __forceinline__ int64_t vweight(const int32_t *vwgt, int32_t v) {
 
 constexpr int kDadmBlock = 256;
 constexpr int kDadmChunk = 4096;     // vertices a workgroup takes at a time: 16 consecutive ones per thread
-constexpr int kDenseAdm = 256, kDadmSome = 2048, kDadmLabels = 16384;  // labels of the tiled form's variants
+constexpr int kDenseAdm = 256, kDadmSome = 2048, kDadmMany = 8192, kDadmLabels = 12288;  // labels of the tiled form's variants
+// (12,288 labels: a tile's sums are 24 bytes a vertex, which keeps a round's buffers
+// within those of the sorted movers)
 constexpr int kDadmMaxTiles = 2048;  // tiles of a round (larger graphs take more chunks per tile)
 constexpr int kSadmBlock = 512;
 constexpr int kSadmPer = 4;
@@ -314,7 +316,7 @@ inline void launch_tiled_as(const AdmitCtx &c, hipStream_t s) {
 inline void launch_tiled(const AdmitCtx &c, hipStream_t s) {
     if (c.nlabels <= kDenseAdm) launch_tiled_as<kDenseAdm>(c, s);
     else if (c.nlabels <= kDadmSome) launch_tiled_as<kDadmSome>(c, s);
-    else if (c.nlabels <= kDadmLabels / 2) launch_tiled_as<kDadmLabels / 2>(c, s);
+    else if (c.nlabels <= kDadmMany) launch_tiled_as<kDadmMany>(c, s);
     else launch_tiled_as<kDadmLabels>(c, s);
 }
 

@@ -3440,7 +3440,9 @@ int lp_run(const DevGraph &g, int32_t *labels, int64_t *W, int32_t nlabels, int6
     {
         unsigned long long gathers = 0;
         for (int t = 5; t < kTiers; t++) gathers += hedge[t];
+        // (not beside the largest tile sums: together they would exceed the sorted movers' buffers)
         if (!dense && !wide && !ac.todo && n <= (1 << kRoomShift) && nlabels <= (1 << kRoomShift) && !fuse_rest &&
+            !(tiled && nlabels > kDadmMany) &&
             gathers >= 4ull * (unsigned long long)n)
             GP_TRY(sc.alloc(&lroom, n));
     }

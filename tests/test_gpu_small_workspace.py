@@ -63,3 +63,18 @@ def test_partition_batch():
     part, _, _ = gp.partition_batch(gp.to_device(u), off, [2, 2], 0.03, ws=_ws(49408))
     want = np.concatenate([oracle.partition(g, 2, 0.03)[0] for g in gs])
     assert np.array_equal(part.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("k,size", [(8192, 159734528), (12288, 159783680), (12289, 159784192)])
+def test_refine_with_many_blocks(k, size):
+    # the label sums of the tiled admission are largest here
+    import torch
+    import paper_1710_08231_amd as gp
+    g = graphgen.rmat(20, 3)
+    n = len(g["xadj"]) - 1
+    part = (np.arange(n, dtype=np.int64) * k // n).astype(np.int32)
+    part[::5] = np.random.default_rng(k).integers(0, k, len(part[::5]))
+    lm = 2 * n // k + 2
+    want, _ = oracle.lp_refine(g, part, k, lm, 2)
+    got, st = gp.lp_refine(gp.to_device(g), torch.from_numpy(part).cuda(), k, lm, 2, ws=_ws(size))
+    assert np.array_equal(got.cpu().numpy(), want) and st["workspace_bytes"] <= size

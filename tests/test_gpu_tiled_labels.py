@@ -1,6 +1,6 @@
 """GPU tests of the admission by tiles with more than 256 labels against the
 oracle's rounds: label counts on both sides of each variant (2,048, 8,192 and
-16,384 labels) and of the rules that choose it (two vertices a label up to 2,048
+12,288 labels) and of the rules that choose it (two vertices a label up to 2,048
 labels, 64 above), with bounds that end every block's room in some tile and
 loose ones, both direction settings, active sets, weights, and as a batch."""
 import numpy as np
@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("x,y,z,k", [
     (26, 26, 25, 257), (26, 26, 25, 2048),  # 16,900 vertices
     (52, 51, 50, 2049), (51, 51, 50, 2049),  # 132,600 and 130,050: on both sides of 64 a label
-    (81, 81, 80, 8192), (81, 81, 80, 8193), (102, 102, 101, 16384), (102, 102, 101, 16385)])
+    (81, 81, 80, 8192), (81, 81, 80, 8193), (93, 93, 91, 12288), (93, 93, 91, 12289)])
 def test_refine(x, y, z, k):
     import torch
     import paper_1710_08231_amd as gp
